@@ -65,11 +65,12 @@ smoe_ws_layout smoe_ws_plan(const smoe_config& c) {
     w.hist = off;    off = align_up(off + (size_t)smoe_sort_blocks(c.max_tokens) * c.K * 4, 256);
     w.hist32 = off;  off = align_up(off + (size_t)((c.max_tokens + 31) / 32) * c.K * 4, 256);
     // hidden activations: every segment is re-based to a multiple of 32 rows
-    w.hidden = off;  off = align_up(off + ((size_t)c.max_tokens + 32 * (size_t)c.K) * c.d_ff * smoe_elem_size(c.dtype), 256);
+    const size_t rows = std::max((size_t)c.max_tokens + 32 * (size_t)c.K, smoe_small_batch_rows(c));
+    w.hidden = off;  off = align_up(off + rows * c.d_ff * smoe_elem_size(c.dtype), 256);
     w.partial = off; off = align_up(off, 256);
-    // bf16 path: three bf16 pieces of every router weight, experts padded to a multiple of 32
+    // bf16 path: the router's weights in matrix-operand order, experts padded to a multiple of 32
     w.rsplit = off;
-    if (c.dtype == SMOE_BF16) off = align_up(off + (size_t)((c.E + 31) / 32 * 32) * c.d_model * 2 * 3, 256);
+    if (c.dtype == SMOE_BF16) off = align_up(off + (size_t)((c.E + 31) / 32 * 32) * c.d_model * 4, 256);
     w.norm = off;    off = align_up(off + (size_t)c.E * 64 * 4, 256);      // smoe_expert_norm partial sums
     // asynchronous loads from a host bank land here (copy engine) before they are packed into a slot
     w.stage = off;   off = align_up(off + (size_t)c.spare_slots * 2 * c.d_model * c.d_ff * smoe_elem_size(c.dtype), 256);

@@ -1,0 +1,518 @@
+// smoe_forward on a small batch (bf16, at most SMALL_T tokens whose rows fit the LDS of a compute
+// unit together): the whole layer in two launches.
+//
+// With few tokens the layer is bound by reading the slots' weights once, so nothing that stands
+// between the kernel's start and its weight stream is tolerated: no sort (every slot's workgroups
+// multiply the batch in token order, an MFMA column depends on its own token only, so the bits are
+// those of the sorted path), and no wait for the router.
+//
+//   first launch   one workgroup per 32 tokens is the router; all the others compute the first
+//                  product of EVERY slot on EVERY token: h[slot][feature / 8][token].  The price is
+//                  the first matrices of slots nobody was routed to, what it buys is the router's
+//                  whole time.
+//   second launch  one workgroup ranks the tokens and adds the importance sums (it needs only what
+//                  the router left); the others compute the second product of the slots that got
+//                  tokens, for those tokens, with the gate and the residual.
+
+#include <algorithm>
+#include <type_traits>
+
+#include "route_mfma.h"
+
+namespace {
+
+constexpr int SMALL_T = SMOE_SMALL_T;                      // the token lists below are two 64-lane ballots long
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int LDS_LIMIT = 160 * 1024 - 2048;               // dynamic LDS; the rest covers the static tables
+
+// ---------------------------------------------------------------------------
+// First product for every slot and every token.  fbw waves of the workgroup own one 32-feature
+// block each (all 8 waves stage the tokens); the token operands come from LDS (row pitch d_model + 8
+// elements: conflict-free 16-byte reads), so the vector-memory pipe carries nothing but 1-KiB weight
+// loads, 16 of them in flight per wave.  NBF: 32-token blocks the instance holds accumulators for.
+// STREAM: the weight loads are marked non-temporal (see smoe_weights_outgrow_cache).
+template <int NBF, bool STREAM>
+__device__ __forceinline__ void dense_first_all(const uint16_t* __restrict__ x, const uint4* __restrict__ Wp, int T,
+                                                uint16_t* __restrict__ h, int R, int N, const int32_t* __restrict__ phys,
+                                                int block, int fbw, uint16_t* xs) {
+    constexpr int G = 8;
+    const int nfb = N >> 5, nrb = R >> 4, ldx = R + 8, nb = (T + 31) >> 5;
+    const int ftiles = (nfb + fbw - 1) / fbw;
+    const int slot = block / ftiles, ftile = block - slot * ftiles;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int fb = ftile * fbw + wave;
+    const bool streams = wave < fbw && fb < nfb;           // the other waves help with the staging only
+    const uint4* wp = Wp + ((size_t)(phys ? phys[slot] : slot) * nfb + min(fb, nfb - 1)) * nrb * 64 + lane;
+    uint4 wA[G], wB[G];
+    auto fetch_w = [&](uint4 (&w)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {                      // past the end: reloaded, not used
+            const uint4* src = wp + (size_t)min(g0 + i, nrb - 1) * 64;
+            w[i] = STREAM ? smoe_load_stream(src) : *src;
+        }
+    };
+    // The tokens are staged one chunk of 2 G reduction steps ahead of their use.  A wave's loads
+    // complete in order, so each chunk of x is asked for before the weights that follow it: waiting
+    // for the chunk then leaves two groups of weight loads in flight.
+    constexpr int CC = 2 * G * 16, CPR = CC / 8;           // columns and 16-byte pieces per row of a chunk
+    constexpr int XPT = NBF * 32 * CPR / 512;              // pieces per thread
+    u32x4 xr[XPT];
+    auto fetch_x = [&](u32x4 (&v)[XPT], int k0) {
+#pragma unroll
+        for (int q = 0; q < XPT; ++q) {
+            const int idx = tid + q * 512, r = min(idx / CPR, T - 1), c = min(k0 + (idx % CPR) * 8, R - 8);
+            v[q] = *(const u32x4*)(x + (size_t)r * R + c); // pieces outside the batch: read again, not stored
+        }
+    };
+    auto stage_x = [&](u32x4 (&v)[XPT], int k0) {
+#pragma unroll
+        for (int q = 0; q < XPT; ++q) {
+            const int idx = tid + q * 512, r = idx / CPR, c = k0 + (idx % CPR) * 8;
+            if (r < T && c < R) *(u32x4*)&xs[r * ldx + c] = v[q];
+        }
+    };
+    fetch_x(xr, 0);
+    if (!streams) {                                        // a wave that only helps with the staging
+        for (int g0 = 0; g0 < nrb; g0 += 2 * G) {
+            stage_x(xr, g0 * 16);
+            fetch_x(xr, g0 * 16 + CC);
+            __syncthreads();
+        }
+        return;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_w(wA, 0);
+    const uint16_t* xrow[NBF];                             // columns past the batch repeat its last row, unstored
+#pragma unroll
+    for (int b = 0; b < NBF; ++b) xrow[b] = xs + min(b * 32 + (lane & 31), T - 1) * ldx + (lane >> 5) * 8;
+    smoe_f32x16 acc[NBF];
+#pragma unroll
+    for (int b = 0; b < NBF; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+    auto consume = [&](uint4 (&w)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const bool in = g0 + i < nrb;                  // steps past the end multiply by a zero operand
+#pragma unroll
+            for (int b = 0; b < NBF; ++b) {
+                uint4 xv = *(const uint4*)(xrow[b] + min(g0 + i, nrb - 1) * 16);
+                if (!in) xv = make_uint4(0, 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(smoe_frag(w[i]), smoe_frag(xv), acc[b], 0, 0, 0);
+            }
+        }
+    };
+    int g0 = 0;
+    for (; nrb - g0 > 2 * G; g0 += 2 * G) {
+        fetch_w(wB, g0 + G);
+        stage_x(xr, g0 * 16);
+        fetch_x(xr, g0 * 16 + CC);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wA, g0);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_w(wA, g0 + 2 * G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    fetch_w(wB, g0 + G);
+    stage_x(xr, g0 * 16);
+    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    consume(wA, g0);
+    if (nrb - g0 > G) consume(wB, g0 + G);
+    // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, token l%32
+    const int pitch = nb * 32;
+#pragma unroll
+    for (int b = 0; b < NBF; ++b) {
+        const int tok = b * 32 + (lane & 31);
+        if (tok >= T) continue;
+        uint16_t* ydst = h + (((size_t)slot * (N >> 3) + fb * 4) * pitch + tok) * 8 + (lane >> 5) * 4;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float v0 = fmaxf(acc[b][4 * g], 0.f), v1 = fmaxf(acc[b][4 * g + 1], 0.f), v2 = fmaxf(acc[b][4 * g + 2], 0.f),
+                        v3 = fmaxf(acc[b][4 * g + 3], 0.f);
+            uint2 o;
+            o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
+            o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+            *(uint2*)(ydst + (size_t)g * pitch * 8) = o;
+        }
+    }
+}
+
+// The router's workgroups come first: they are the launch's critical path.
+template <int NEB, int NBF, bool STREAM>
+__device__ __forceinline__ void decode_first_body(const smoe_route_args& ra, const uint4* W1, uint16_t* h, int d_ff,
+                                                  const int32_t* phys, int fbw) {
+    extern __shared__ __align__(16) float smem[];
+    const int routers = (ra.T + SMOE_RT - 1) / SMOE_RT;
+    if ((int)blockIdx.x < routers) smoe_route_mfma_body<NEB, 1>(blockIdx.x, ra, smem);
+    else dense_first_all<NBF, STREAM>(ra.x, W1, ra.T, h, ra.d, d_ff, phys, blockIdx.x - routers, fbw, (uint16_t*)smem);
+}
+
+// Two kernels with one body: the second streams its weights past the caches.
+template <int NEB, int NBF>
+__global__ __launch_bounds__(512) void decode_first_kernel(const smoe_route_args ra, const uint4* __restrict__ W1, uint16_t* __restrict__ h,
+                                                           int d_ff, const int32_t* __restrict__ phys, int fbw) {
+    decode_first_body<NEB, NBF, false>(ra, W1, h, d_ff, phys, fbw);
+}
+
+template <int NEB, int NBF>
+__global__ __launch_bounds__(512) void decode_first_stream_kernel(const smoe_route_args ra, const uint4* __restrict__ W1,
+                                                                  uint16_t* __restrict__ h, int d_ff, const int32_t* __restrict__ phys,
+                                                                  int fbw) {
+    decode_first_body<NEB, NBF, true>(ra, W1, h, d_ff, phys, fbw);
+}
+
+// ---------------------------------------------------------------------------
+// Ranking (the index part of smoe_permute) and importance sums (Eq. 1) of at most SMALL_T tokens
+// by one workgroup of 256 threads, from what the router left in memory.
+__device__ __forceinline__ void finish_small(const smoe_step_tail& t, const int32_t* __restrict__ slot, int T, int E, int K) {
+    __shared__ __align__(16) int32_t s_slot[SMALL_T];
+    __shared__ int32_t s_oe[SMALL_T], s_cnt[256];
+    __shared__ float s_og[SMALL_T], s_r[SMALL_T], s_gsum[256], s_rsum[256];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int c0 = 0;
+    float g0 = 0.f, r0 = 0.f, en = 0.f;
+    if (tid < E) {                                         // asked for before anything else
+        en = t.expert_norm[tid];
+        if (t.accumulate) { c0 = t.count[tid]; g0 = t.gsum[tid]; r0 = t.score[tid]; }
+    }
+    if (tid < SMALL_T) {
+        s_slot[tid] = tid < T ? slot[tid] : 0x7fffffff;    // past the batch: behind every slot, no expert's token
+        s_oe[tid] = tid < T ? t.orig_expert[tid] : -1;
+        const float og = tid < T ? t.orig_gate[tid] : 0.f;
+        s_og[tid] = og;
+        s_r[tid] = tid < T ? t.xnorm[tid] * og : 0.f;
+    }
+    __syncthreads();
+    // stable position = tokens of lower slots + earlier tokens of the same slot
+    const int nq = (T + 3) >> 2;
+    if (tid < T) {
+        const int my = s_slot[tid];
+        int pos = 0;
+        for (int q = 0; q < nq; ++q) {
+            const int4 s = *(const int4*)&s_slot[4 * q];
+            const int u = 4 * q;
+            pos += (s.x < my) | ((s.x == my) & (u < tid));
+            pos += (s.y < my) | ((s.y == my) & (u + 1 < tid));
+            pos += (s.z < my) | ((s.z == my) & (u + 2 < tid));
+            pos += (s.w < my) | ((s.w == my) & (u + 3 < tid));
+        }
+        t.perm[pos] = tid;
+        t.inv_perm[tid] = pos;
+    }
+    for (int k = tid; k <= K; k += 256) {
+        int before = 0;
+        for (int q = 0; q < nq; ++q) {
+            const int4 s = *(const int4*)&s_slot[4 * q];
+            before += (s.x < k) + (s.y < k) + (s.z < k) + (s.w < k);
+        }
+        t.offsets[k] = before;
+    }
+    // importance: one wave per expert.  The tokens sit in leaves 0 .. 127 of the separate call's
+    // 256-leaf summation tree and its other leaves are zero; token t + 64 first, then strides 32 .. 1,
+    // are that tree's levels, so the sums have the same bits.
+    const int oe0 = s_oe[lane], oe1 = s_oe[lane + 64];
+    const float og0 = s_og[lane], og1 = s_og[lane + 64], rr0 = s_r[lane], rr1 = s_r[lane + 64];
+    for (int e = wave; e < E; e += 4) {
+        const bool h0 = oe0 == e, h1 = oe1 == e;
+        const unsigned long long m0 = __ballot(h0), m1 = __ballot(h1);
+        float g = 0.f, r = 0.f;
+        if (m0 | m1) {
+            g = (h0 ? og0 : 0.f) + (h1 ? og1 : 0.f);
+            r = (h0 ? rr0 : 0.f) + (h1 ? rr1 : 0.f);
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) { g += __shfl_xor(g, w); r += __shfl_xor(r, w); }
+        }
+        if (lane == 0) { s_cnt[e] = __popcll(m0) + __popcll(m1); s_gsum[e] = g; s_rsum[e] = r; }
+    }
+    __syncthreads();
+    if (tid < E) {
+        const float sc = en * s_rsum[tid];
+        t.count[tid] = c0 + s_cnt[tid];
+        t.gsum[tid] = t.accumulate ? g0 + s_gsum[tid] : s_gsum[tid];
+        t.score[tid] = t.accumulate ? r0 + sc : sc;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Second product.  Workgroup (slot, feature block): 4 waves split the reduction four ways and meet
+// in LDS (added in wave order: reproducible).  The first group of weight loads is issued before the
+// slot ids have arrived, so the latency of the two overlaps; the workgroups of a slot nobody was
+// routed to then simply leave.  The slot's own tokens are packed into the columns of as few 32-token
+// blocks as they need, at most MAXNB of them at a time.
+struct second_args {
+    const uint16_t* h;            // [slot][d_ff / 8][pitch tokens] units of 8 features
+    const uint4* W2;
+    const int32_t* slot;
+    int T, E, K, R, N;
+    const int32_t* phys;
+    const float* gate;
+    const uint16_t* residual;
+    uint16_t* out;
+    smoe_step_tail tail;
+};
+
+template <int MAXNB, bool STREAM>
+__device__ __forceinline__ void decode_second_body(const second_args& a) {
+    constexpr int KSPLIT = 4;
+    __shared__ __align__(16) float red[(KSPLIT - 1) * MAXNB * 16 * 64];
+    __shared__ int32_t s_tok[KSPLIT][SMALL_T];
+    if (blockIdx.x == 0) {
+        finish_small(a.tail, a.slot, a.T, a.E, a.K);
+        return;
+    }
+    const int nfb = a.N >> 5, nrb = a.R >> 4;
+    const int slot = (blockIdx.x - 1) / nfb, fb = (blockIdx.x - 1) % nfb;
+    // wave index as a scalar: MFMA loop bounds must be wave-uniform for the compiler too
+    const int tid = threadIdx.x, part = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int per = (nrb + KSPLIT - 1) / KSPLIT;
+    const int kb_lo = min(part * per, nrb), kb_hi = min(kb_lo + per, nrb);
+    const uint4* wp = a.W2 + ((size_t)(a.phys ? a.phys[slot] : slot) * nfb + fb) * nrb * 64 + lane;
+    auto fetch_w = [&](auto& w, int g0) {
+        constexpr int G = sizeof(w) / sizeof(uint4);
+#pragma unroll
+        for (int i = 0; i < G; ++i) {                      // past the end: reloaded, not used
+            const uint4* src = wp + (size_t)max(min(g0 + i, kb_hi - 1), 0) * 64;
+            w[i] = STREAM ? smoe_load_stream(src) : *src;
+        }
+    };
+    // A wave's loads complete in order: the slot ids are asked for first, so that waiting for them
+    // does not wait for the weights, and the weights' first group right after, before anything is known.
+    constexpr int G1 = 8;                                  // reduction steps fetched together
+    const int id0 = a.slot[min(lane, a.T - 1)], id1 = MAXNB > 1 ? a.slot[min(lane + 64, a.T - 1)] : 0;
+    __builtin_amdgcn_sched_barrier(0);
+    uint4 w0[G1];
+    fetch_w(w0, kb_lo);
+    __builtin_amdgcn_sched_barrier(0);
+    const bool own0 = lane < a.T && id0 == slot, own1 = MAXNB > 1 && lane + 64 < a.T && id1 == slot;
+    const unsigned long long m0 = __ballot(own0), m1 = MAXNB > 1 ? __ballot(own1) : 0ull;
+    const int n0 = __popcll(m0), n = n0 + __popcll(m1);
+    if (n == 0) return;                                    // nothing routed to this slot (uniform over the workgroup)
+    const unsigned long long below = (1ull << lane) - 1ull;
+    if (own0) s_tok[part][__popcll(m0 & below)] = lane;
+    if (own1) s_tok[part][n0 + __popcll(m1 & below)] = lane + 64;
+    const int pitch = (a.T + 31) & ~31;
+    const size_t xstep = 2 * (size_t)pitch;                // 16-byte units per reduction step
+    const uint4* hs = (const uint4*)a.h + ((size_t)slot * (a.R >> 3) + (lane >> 5)) * pitch;
+
+    auto blocks = [&](auto nbc, auto& wA, int c0) {        // token columns c0 .. of the slot's list
+        constexpr int NB = decltype(nbc)::value;
+        constexpr int G = sizeof(wA) / sizeof(uint4);
+        uint4 wB[G], xA[NB][G], xB[NB][G];
+        int tok[NB];
+        bool live[NB];
+        const uint4* xp[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int c = c0 + b * 32 + (lane & 31);
+            live[b] = c < n;
+            tok[b] = s_tok[part][min(c, n - 1)];           // columns past the list repeat its last token
+            xp[b] = hs + tok[b];
+        }
+        auto fetch_x = [&](uint4 (&xv)[NB][G], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) xv[b][i] = xp[b][(size_t)max(min(g0 + i, kb_hi - 1), 0) * xstep];
+        };
+        fetch_x(xA, kb_lo);
+        float gmul[NB];
+        uint2 rres[NB][4];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {                     // asked for now, used after the loop
+            gmul[b] = 1.f;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) rres[b][g] = make_uint2(0, 0);
+            if (live[b] && part == 0) {
+                gmul[b] = a.gate[tok[b]];
+                if (a.residual) {
+                    const uint16_t* rp = a.residual + (size_t)tok[b] * a.N + fb * 32 + (lane >> 5) * 4;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) rres[b][g] = *(const uint2*)(rp + g * 8);
+                }
+            }
+        }
+        smoe_f32x16 acc[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+        auto consume = [&](auto& w, uint4 (&xv)[NB][G], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {             // steps past the end multiply by a zero operand
+                    const uint4 xz = g0 + i < kb_hi ? xv[b][i] : make_uint4(0, 0, 0, 0);
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(smoe_frag(w[i]), smoe_frag(xz), acc[b], 0, 0, 0);
+                }
+        };
+        int g0 = kb_lo;
+        for (; kb_hi - g0 > 2 * G; g0 += 2 * G) {
+            fetch_w(wB, g0 + G);
+            fetch_x(xB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wA, xA, g0);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_w(wA, g0 + 2 * G);
+            fetch_x(xA, g0 + 2 * G);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wB, xB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        fetch_w(wB, g0 + G);
+        fetch_x(xB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wA, xA, g0);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wB, xB, g0 + G);
+        if (part > 0) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) red[(((part - 1) * MAXNB + b) * 16 + i) * 64 + lane] = acc[b][i];
+        }
+        __syncthreads();
+        if (part == 0) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                for (int w2 = 0; w2 < KSPLIT - 1; ++w2)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[b][i] += red[((w2 * MAXNB + b) * 16 + i) * 64 + lane];
+                if (!live[b]) continue;
+                // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, column l%32
+                uint16_t* ydst = a.out + (size_t)tok[b] * a.N + fb * 32 + (lane >> 5) * 4;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    float v0 = acc[b][4 * g], v1 = acc[b][4 * g + 1], v2 = acc[b][4 * g + 2], v3 = acc[b][4 * g + 3];
+                    smoe_apply_gate(v0, v1, v2, v3, gmul[b], rres[b][g], a.residual != nullptr);
+                    uint2 o;
+                    o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
+                    o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+                    *(uint2*)(ydst + g * 8) = o;
+                }
+            }
+        }
+    };
+    __syncthreads();                                       // the token lists are complete
+    if (MAXNB == 1 || n <= 32) {
+        blocks(std::integral_constant<int, 1>{}, w0, 0);
+    } else if constexpr (MAXNB > 1) {
+        for (int c0 = 0; c0 < n; c0 += 64) {
+            if (c0) __syncthreads();                       // the previous sums have been read
+            uint4 w[4];
+            fetch_w(w, kb_lo);
+            blocks(std::integral_constant<int, 2>{}, w, c0);
+        }
+    }
+}
+
+template <int MAXNB>
+__global__ __launch_bounds__(256, 2) void decode_second_kernel(const second_args a) { decode_second_body<MAXNB, false>(a); }
+
+template <int MAXNB>
+__global__ __launch_bounds__(256, 2) void decode_second_stream_kernel(const second_args a) { decode_second_body<MAXNB, true>(a); }
+
+// 32-expert blocks rounded up to an instance of the router
+int router_instance(int E) { return E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8; }
+
+size_t first_lds(const smoe_config& c, int T) {
+    const int neb = router_instance(c.E), d = c.d_model;
+    const size_t router = neb == 1   ? smoe_route_shape<1, 1>::lds_bytes(d)
+                          : neb == 2 ? smoe_route_shape<2, 1>::lds_bytes(d)
+                          : neb == 4 ? smoe_route_shape<4, 1>::lds_bytes(d)
+                                     : smoe_route_shape<8, 1>::lds_bytes(d);
+    return std::max(router, (size_t)T * (d + 8) * 2);
+}
+
+// Feature blocks per workgroup of the first product: as many of the 8 waves as leave at least
+// three workgroups per four compute units.
+int first_fbw(const smoe_config& c) {
+    const int nfb = c.d_ff >> 5;
+    int fbw = 8;
+    while (fbw > 1 && c.K * ((nfb + fbw - 1) / fbw) < 192) fbw >>= 1;
+    return fbw;
+}
+
+template <int NEB, int NBF>
+int launch_first(const smoe_layer* L, const smoe_route_args& ra, bool stream, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const smoe_config& c = L->cfg;
+    const size_t lds = first_lds(c, ra.T);
+    const int fbw = first_fbw(c), ftiles = ((c.d_ff >> 5) + fbw - 1) / fbw;
+    const dim3 grid(c.K * ftiles + (ra.T + SMOE_RT - 1) / SMOE_RT);
+    const int32_t* phys = c.spare_slots > 0 ? L->d_phys : nullptr;
+    auto kern = stream ? decode_first_stream_kernel<NEB, NBF> : decode_first_kernel<NEB, NBF>;
+    static smoe_lds_raised raised[2];                      // per kernel: devices whose dynamic-LDS limit is up
+    if (int rc = raised[stream].ensure((const void*)kern, lds, LDS_LIMIT)) return rc;
+    if (e0 && e1)
+        hipExtLaunchKernelGGL(kern, grid, dim3(512), lds, s, e0, e1, 0, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden, c.d_ff,
+                              phys, fbw);
+    else
+        hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden, c.d_ff, phys, fbw);
+    return smoe_check_hip(hipGetLastError(), "smoe_forward: decode launch");
+}
+
+template <int NEB>
+int launch_first_nbf(const smoe_layer* L, const smoe_route_args& ra, bool stream, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (ra.T <= 32) return launch_first<NEB, 1>(L, ra, stream, s, e0, e1);
+    if (ra.T <= 64) return launch_first<NEB, 2>(L, ra, stream, s, e0, e1);
+    return launch_first<NEB, 4>(L, ra, stream, s, e0, e1);
+}
+
+}  // namespace
+
+int smoe_lds_raised::ensure(const void* kern, size_t lds, int limit) {
+    if (lds <= 48 * 1024) return SMOE_OK;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (dev < 0 || dev >= 64) return smoe_fail(SMOE_EINVAL, "device index %d outside [0,64)", dev);
+    const unsigned long long bit = 1ull << dev;
+    if (mask.load(std::memory_order_acquire) & bit) return SMOE_OK;
+    int rc = smoe_check_hip(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, limit), "LDS size");
+    if (!rc) mask.fetch_or(bit, std::memory_order_release);
+    return rc;
+}
+
+bool smoe_decode_first_applies(const smoe_layer* L, int T) {
+    return L->cfg.dtype == SMOE_BF16 && T >= 1 && T <= SMALL_T && first_lds(L->cfg, T) <= (size_t)LDS_LIMIT;
+}
+
+int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t* orig_expert, float* orig_gate,
+                             int32_t* slot, float* gate, float* xnorm, int32_t* count, float* gsum, float* score,
+                             int accumulate, int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s,
+                             hipEvent_t e0, hipEvent_t e1) {
+    if (!smoe_decode_first_applies(L, T)) return smoe_fail(SMOE_EINVAL, "smoe_forward: the fused decode launch does not apply");
+    const smoe_config& c = L->cfg;
+    L->tail = smoe_step_tail{L->expert_norm, orig_expert, orig_gate, xnorm, count, gsum, score, accumulate, perm, inv_perm, offsets};
+    const smoe_route_args ra{(const uint16_t*)x, (const uint4*)L->d_router_split, L->d_expert_to_slot, T, c.d_model, c.E, c.gate_mode,
+                             orig_expert, orig_gate, slot, gate, xnorm, nullptr, c.K};
+    const bool stream = smoe_weights_outgrow_cache();
+    switch (router_instance(c.E)) {
+        case 1: return launch_first_nbf<1>(L, ra, stream, s, e0, e1);
+        case 2: return launch_first_nbf<2>(L, ra, stream, s, e0, e1);
+        case 4: return launch_first_nbf<4>(L, ra, stream, s, e0, e1);
+        default: return launch_first_nbf<8>(L, ra, stream, s, e0, e1);
+    }
+}
+
+int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_of, const float* gate,
+                                      const uint16_t* residual, int T, uint16_t* out, hipStream_t s) {
+    const smoe_config& c = L->cfg;
+    const second_args a{(const uint16_t*)L->d_hidden, (const uint4*)L->slot_w2, slot_of, T, c.E, c.K, c.d_ff, c.d_model,
+                        c.spare_slots > 0 ? L->d_phys : nullptr, gate, residual, out, L->tail};
+    const dim3 grid(c.K * (c.d_model >> 5) + 1);
+    const bool stream = smoe_weights_outgrow_cache();
+    auto kern = T <= 32 ? (stream ? decode_second_stream_kernel<1> : decode_second_kernel<1>)
+                        : (stream ? decode_second_stream_kernel<2> : decode_second_kernel<2>);
+    smoe_launch_timed(kern, grid, dim3(256), s, L->prof_ev[2], L->prof_ev[3], a);
+    return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");
+}
+
+std::string smoe_describe_decode(const smoe_layer* L, int T, bool first) {
+    const std::string st = smoe_weights_outgrow_cache() ? "_stream" : "";
+    if (!first) return "decode_second" + st + "_kernel<" + (T <= 32 ? "1>" : "2>");
+    return "decode_first" + st + "_kernel<" + std::to_string(router_instance(L->cfg.E)) + ", " + (T <= 32 ? "1>" : T <= 64 ? "2>" : "4>");
+}

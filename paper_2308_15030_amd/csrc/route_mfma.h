@@ -1,0 +1,301 @@
+// The router for bf16 activations: product, softmax, original top-1, masked top-1 and |x|,
+// as a device function shared by smoe_route's kernel and the small batch's first launch.
+//
+// x is exactly bf16, and an fp32 router weight is exactly the sum of three bf16 numbers
+// (8 + 8 + 8 significand bits): w = hi + mid + lo, each the upper half of what the one before left.
+// Every product x * {hi, mid, lo} is exact in fp32, so three bf16 MFMA passes with fp32 accumulation
+// give the fp32-weight logits up to accumulation rounding -- the same error class as an fp32 FMA
+// chain, at matrix-core speed.  The workspace holds the fp32 weights in MFMA operand order (made on
+// the first smoe_route after smoe_bind); they are cut in registers, eleven vector instructions a
+// pair, because what bounds the kernel is the bytes a compute unit can take in (one workgroup needs
+// the whole router): four per weight instead of the six of three stored pieces.
+//
+// One workgroup = 8 waves = TB blocks of 32 tokens x all experts.  The tokens are staged in LDS
+// (read straight into operand order, an instruction would touch 32 rows with 32 bytes each: twice
+// the cache accesses of the weights per byte).  The reduction (d_model) is cut into NS slices (8 up
+// to 32 experts, 4 above) and, above 32 experts, the expert blocks into two groups: wave = (slice,
+// group).  The partial logits meet in LDS, token by token with the experts side by side, and are
+// added in slice order (fixed, so results are reproducible).
+//
+// Epilogue: 16 lanes per token, so a wave finishes four tokens at once; the maximum, the masked
+// maximum, their lowest indexes and the softmax sums are rotations within the 16 lanes, without a
+// barrier.
+#pragma once
+
+#include "smoe_internal.h"
+#include "wave_ops.h"
+
+typedef __bf16 smoe_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float smoe_f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ smoe_bf16x8 smoe_frag(uint4 v) {
+    union { uint4 u; smoe_bf16x8 b; } c;
+    c.u = v;
+    return c.b;
+}
+
+constexpr int SMOE_RT = 32;       // tokens per token block (one MFMA operand)
+
+struct smoe_route_args {
+    const uint16_t* x;
+    const uint4* wr;              // fp32 [expert block][reduction step][2 halves][lane][4]
+    const int32_t* e2s;
+    int T, d, E, gate_mode;
+    int32_t* orig_expert;
+    float* orig_gate;
+    int32_t* slot;
+    float* gate;
+    float* xnorm;
+    int32_t* hist32;              // tokens per slot of every 32-token block, or NULL
+    int K;
+};
+
+constexpr int SMOE_ROUTE_KC = 1024;   // columns of x staged together
+
+// NEB: 32-expert blocks the instance is compiled for (1, 2, 4 or 8; surplus blocks are skipped).
+template <int NEB, int TB>
+struct smoe_route_shape {
+    static constexpr int NS = NEB == 1 ? 8 : 4;            // slices of the reduction
+    static constexpr int NEBH = NEB * NS / 8;              // expert blocks per group
+    static constexpr int EP = NEB * 32;
+    static constexpr int LDP = EP + 4;                     // padded token row of partial logits: 16-byte stores hit all banks
+    static constexpr int NTOK = TB * SMOE_RT;
+    // the staged tokens, and after them the partial logits and sums of squares, in the same place
+    static size_t lds_bytes(int d) {
+        const size_t part = (size_t)(NS * NTOK * LDP + NS * 2 * NTOK) * 4;
+        const size_t xs = (size_t)NTOK * ((d < SMOE_ROUTE_KC ? d : SMOE_ROUTE_KC) + 8) * 2;
+        return part > xs ? part : xs;
+    }
+};
+
+template <int NEB, int TB>
+__device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe_route_args& a, float* smem) {
+    using S = smoe_route_shape<NEB, TB>;
+    constexpr int NS = S::NS, NEBH = S::NEBH, EP = S::EP, LDP = S::LDP, RT = SMOE_RT, NTOK = S::NTOK;
+    constexpr int KC = SMOE_ROUTE_KC;
+    // reduction steps whose weights are fetched together; two such groups are in flight
+    constexpr int G = NEBH == 1 ? 4 : NEBH == 2 ? 3 : 2;
+    uint16_t* xs = (uint16_t*)smem;                        // [NTOK][ldx] columns of x
+    float* part = smem;                                    // [NS][NTOK][LDP] partial logits, once the tokens are used up
+    float* sqp = smem + NS * NTOK * LDP;                   // [NS][2 halves][NTOK] partial sums of squares
+    __shared__ int32_t s_hist[TB * 256];                   // tokens per block and slot
+
+    // wave index as a scalar: loop bounds that guard MFMAs must be wave-uniform for the
+    // compiler as well (an MFMA under a lane mask still runs for every lane)
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int slice = wave % NS, group = wave / NS;
+    const int tw0 = block * NTOK;                          // first token of the workgroup
+    const int neb = (a.E + 31) >> 5, nkb = a.d >> 4;
+    const uint4* wp[NEBH];
+#pragma unroll
+    for (int b = 0; b < NEBH; ++b) wp[b] = a.wr + (size_t)min(group * NEBH + b, neb - 1) * nkb * 2 * 64 + lane;
+
+    smoe_f32x16 acc[NEBH][TB];
+    float sq[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+        sq[tb] = 0.f;
+#pragma unroll
+        for (int b = 0; b < NEBH; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[b][tb][i] = 0.f;
+    }
+    if (a.hist32)
+        for (int i = tid; i < TB * 256; i += 512) s_hist[i] = 0;
+    constexpr int EC = (EP + 63) / 64;                     // chunks of 64 experts; a lane of the epilogue has 4 of each
+    const int sub = lane & 15;                             // the 16 lanes of a token
+    int sl[EC][4];                                         // slots of this lane's experts, -1 if not resident
+#pragma unroll
+    for (int c = 0; c < EC; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = 64 * c + 4 * sub + j;
+            sl[c][j] = e < a.E ? a.e2s[e] : -1;
+        }
+
+    const int ldx = min(a.d, KC) + 8;                      // conflict-free 16-byte operand reads
+    for (int k0 = 0; k0 < a.d; k0 += KC) {                 // (one pass up to d_model = 1024)
+        const int kc = min(KC, a.d - k0), steps = kc >> 4;
+        const int per = (steps + NS - 1) / NS;
+        const int lo = min(slice * per, steps), hi = min(lo + per, steps);   // this wave's steps of the chunk
+        const int n = hi - lo;
+        const uint4* w0[NEBH];
+#pragma unroll
+        for (int b = 0; b < NEBH; ++b) w0[b] = wp[b] + (size_t)((k0 >> 4) + lo) * 2 * 64;
+        uint4 wA[G][NEBH][2], wB[G][NEBH][2];
+        auto fetch = [&](uint4 (&w)[G][NEBH][2], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i)                    // past the end: reloaded, not used
+#pragma unroll
+                for (int b = 0; b < NEBH; ++b)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) w[i][b][h] = w0[b][(size_t)(max(min(g0 + i, n - 1), 0) * 2 + h) * 64];
+        };
+        fetch(wA, 0);                                      // on their way while the tokens are staged
+        if (k0) __syncthreads();                           // the previous chunk has been used up
+        const int cpr = kc >> 3;                           // 16-byte pieces per row
+        constexpr int PPT = 8;                             // pieces fetched together
+        for (int i0 = tid; i0 < NTOK * cpr; i0 += 512 * PPT) {
+            uint4 v[PPT];
+#pragma unroll
+            for (int q = 0; q < PPT; ++q) {
+                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
+                v[q] = *(const uint4*)(a.x + (size_t)min(tw0 + r, a.T - 1) * a.d + k0 + c * 8);
+            }
+#pragma unroll
+            for (int q = 0; q < PPT; ++q) {                // pieces past the end repeat the last one
+                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
+                *(uint4*)&xs[r * ldx + c * 8] = v[q];
+            }
+        }
+        __syncthreads();
+        const uint16_t* xrow = xs + (lane & 31) * ldx + (lane >> 5) * 8 + lo * 16;
+        auto consume = [&](uint4 (&w)[G][NEBH][2], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                smoe_bf16x8 xf[TB];
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) {
+                    uint4 xv = *(const uint4*)(xrow + tb * RT * ldx + max(min(g0 + i, n - 1), 0) * 16);
+                    if (g0 + i >= n) xv = make_uint4(0, 0, 0, 0);   // steps past the end multiply by a zero operand
+                    xf[tb] = smoe_frag(xv);
+                    if (group == 0) {                      // the groups read the same tokens: one of them adds the squares
+                        const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float l = __uint_as_float(xw[q] << 16), h = __uint_as_float(xw[q] & 0xFFFF0000u);
+                            sq[tb] = fmaf(l, l, sq[tb]);
+                            sq[tb] = fmaf(h, h, sq[tb]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < NEBH; ++b) {
+                    const uint32_t f[8] = {w[i][b][0].x, w[i][b][0].y, w[i][b][0].z, w[i][b][0].w,
+                                           w[i][b][1].x, w[i][b][1].y, w[i][b][1].z, w[i][b][1].w};
+                    uint32_t pc[3][4];                     // hi, mid, lo of four pairs
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float u = __uint_as_float(f[2 * q]), v = __uint_as_float(f[2 * q + 1]);
+#pragma unroll
+                        for (int s3 = 0; s3 < 3; ++s3) {   // upper halves packed; the remainders are exact
+                            pc[s3][q] = __builtin_amdgcn_perm(__float_as_uint(v), __float_as_uint(u), 0x07060302u);
+                            u -= __uint_as_float(__float_as_uint(u) & 0xFFFF0000u);
+                            v -= __uint_as_float(__float_as_uint(v) & 0xFFFF0000u);
+                        }
+                    }
+                    // smallest terms first, so they are not absorbed by the large partial sums
+#pragma unroll
+                    for (int s3 = 2; s3 >= 0; --s3)
+#pragma unroll
+                        for (int tb = 0; tb < TB; ++tb)
+                            acc[b][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                smoe_frag(make_uint4(pc[s3][0], pc[s3][1], pc[s3][2], pc[s3][3])), xf[tb], acc[b][tb], 0, 0, 0);
+                }
+            }
+        };
+        int g0 = 0;
+        for (; n - g0 > 2 * G; g0 += 2 * G) {
+            fetch(wB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);             // the next group's loads are issued first
+            consume(wA, g0);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(wA, g0 + 2 * G);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (n - g0 > G) {
+            fetch(wB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wA, g0);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wB, g0 + G);
+        } else {
+            consume(wA, g0);
+        }
+    }
+    __syncthreads();                                       // the partial logits take the tokens' place
+    // accumulator register i of lane l: expert 8*(i/4) + 4*(l/32) + i%4 (+32 per block), token l%32
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+        float* row = part + (slice * NTOK + tb * RT + (lane & 31)) * LDP + 4 * (lane >> 5);
+#pragma unroll
+        for (int b = 0; b < NEBH; ++b) {
+            if (group * NEBH + b >= neb) continue;         // a surplus block
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *(float4*)(row + (group * NEBH + b) * 32 + 8 * q) =
+                    make_float4(acc[b][tb][4 * q], acc[b][tb][4 * q + 1], acc[b][tb][4 * q + 2], acc[b][tb][4 * q + 3]);
+        }
+        if (group == 0) sqp[(slice * 2 + (lane >> 5)) * NTOK + tb * RT + (lane & 31)] = sq[tb];
+    }
+    __syncthreads();
+
+    // epilogue: lanes 16q .. 16q + 15 of wave w own token 4w + q of every 32-token block
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+        const int t = tb * RT + wave * 4 + (lane >> 4), tok = tw0 + t;
+        float v[EC][4];
+#pragma unroll
+        for (int c = 0; c < EC; ++c) {
+            const int e = 64 * c + 4 * sub;
+            const float* col = part + t * LDP + min(e, EP - 4);
+            float4 s = *(const float4*)col;
+#pragma unroll
+            for (int q = 1; q < NS; ++q) {                 // fixed order
+                const float4 o = *(const float4*)(col + q * NTOK * LDP);
+                s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+            }
+            v[c][0] = s.x; v[c][1] = s.y; v[c][2] = s.z; v[c][3] = s.w;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[c][j] = e + j < a.E ? v[c][j] : -INFINITY;   // past E: never wins, adds exp(-inf) = 0
+        }
+        float best = -INFINITY, rbest = -INFINITY;
+#pragma unroll
+        for (int c = 0; c < EC; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                best = fmaxf(best, v[c][j]);
+                rbest = fmaxf(rbest, sl[c][j] >= 0 ? v[c][j] : -INFINITY);
+            }
+        best = smoe_row_max(best);
+        rbest = smoe_row_max(rbest);
+        int bi = 0x7fffffff, rb = 0x7fffffff;              // lowest expert id that holds the maximum; (id, slot) of the masked one
+        float z = 0.f, zr = 0.f;
+#pragma unroll
+        for (int c = EC - 1; c >= 0; --c)
+#pragma unroll
+            for (int j = 3; j >= 0; --j) {
+                const int e = 64 * c + 4 * sub + j;
+                bi = v[c][j] == best ? e : bi;
+                rb = sl[c][j] >= 0 && v[c][j] == rbest ? (e << 8 | sl[c][j]) : rb;
+                const float p = expf(v[c][j] - best);
+                z += p;
+                zr += sl[c][j] >= 0 ? p : 0.f;
+            }
+        bi = smoe_row_min(bi);
+        rb = smoe_row_min(rb);
+        z = smoe_row_sum(z);
+        if (a.gate_mode == SMOE_GATE_RENORM) zr = smoe_row_sum(zr);
+        if (sub == 0 && tok < a.T) {
+            float ss = 0.f;
+#pragma unroll
+            for (int q = 0; q < 2 * NS; ++q) ss += sqp[q * NTOK + t];
+            const int sv = rb & 255;
+            a.orig_expert[tok] = bi;
+            a.orig_gate[tok] = 1.0f / z;
+            a.slot[tok] = sv;
+            a.gate[tok] = expf(rbest - best) / (a.gate_mode == SMOE_GATE_RENORM ? zr : z);
+            a.xnorm[tok] = sqrtf(ss);
+            if (a.hist32) atomicAdd(&s_hist[tb * 256 + sv], 1);   // integer: order cannot matter
+        }
+    }
+    if (a.hist32) {                                        // tokens per slot in each block, for the ranking that follows
+        __syncthreads();
+        for (int i = tid; i < TB * a.K; i += 512) {
+            const int tb = i / a.K, k = i - tb * a.K;
+            if (tw0 + tb * RT < a.T) a.hist32[((size_t)block * TB + tb) * a.K + k] = s_hist[tb * 256 + k];
+        }
+    }
+}

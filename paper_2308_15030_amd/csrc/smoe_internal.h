@@ -6,6 +6,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <atomic>
+#include <string>
 #include <vector>
 
 #include "swapmoe.h"
@@ -14,8 +16,24 @@
 constexpr int SMOE_SORT_BLOCK = 1024;
 // Upper bound on d_ff tiles / token tiles is derived from the config at bind time.
 
+// What the second launch of a small batch finishes: ranking and importance sums.
+struct smoe_step_tail {
+    const float* expert_norm;
+    const int32_t* orig_expert;
+    const float* orig_gate;
+    const float* xnorm;
+    int32_t* count;
+    float* gsum;
+    float* score;
+    int accumulate;
+    int32_t* perm;
+    int32_t* inv_perm;
+    int32_t* offsets;
+};
+
 struct smoe_layer {
     smoe_config cfg;
+    mutable smoe_step_tail tail{};           // left by a small batch's first launch for its second
     bool bound = false;
     int slots_set = 0;                       // number of slots that hold an expert
     std::vector<int32_t> slot_to_expert;     // host copies of the maps
@@ -61,7 +79,7 @@ struct smoe_layer {
     bool maps_stale = false;
     hipStream_t maps_stream = nullptr;
     const void* dev_update_seen[3] = {nullptr, nullptr, nullptr};   // pointers smoe_update_on_device has checked
-    void* d_router_split = nullptr;          // bf16 path: router weights split in three, MFMA order
+    void* d_router_split = nullptr;          // bf16 path: router weights in matrix-operand order
     bool router_split_done = false;          // made by the first smoe_route after a bind
 
     hipEvent_t prof_ev[4] = {nullptr, nullptr, nullptr, nullptr};   // one-shot FFN profiling events
@@ -82,6 +100,13 @@ int smoe_fail(int code, const char* fmt, ...);
 int smoe_check_hip(hipError_t e, const char* what);
 
 inline size_t smoe_elem_size(int dtype) { return dtype == SMOE_BF16 ? 2 : 4; }
+// smoe_forward takes at most this many tokens through its two-launch path (decode.hip), which keeps the
+// hidden activations of every slot for every token of the batch
+constexpr int SMOE_SMALL_T = 128;
+inline size_t smoe_small_batch_rows(const smoe_config& c) {
+    const int t = c.max_tokens < SMOE_SMALL_T ? c.max_tokens : SMOE_SMALL_T;
+    return c.dtype == SMOE_BF16 ? (size_t)c.K * ((t + 31) / 32 * 32) : 0;
+}
 inline int smoe_sort_blocks(int T) { return (T + SMOE_SORT_BLOCK - 1) / SMOE_SORT_BLOCK; }
 
 // Kernel launchers, one per translation unit.  All validate nothing: the ABI
@@ -94,12 +119,13 @@ int smoe_launch_route_rank_small(const smoe_layer* L, const void* x, int T, int3
                                  float* orig_gate, int32_t* slot, float* gate, float* xnorm, int32_t* count,
                                  float* gsum, float* score, int accumulate, int32_t* perm, int32_t* inv_perm,
                                  int32_t* offsets, hipStream_t s);
+// smoe_forward on a small batch, two launches (decode.hip): when it applies, the launches, and the names of its kernel instances
 bool smoe_decode_first_applies(const smoe_layer* L, int T);
+std::string smoe_describe_decode(const smoe_layer* L, int T, bool first);
 int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t* orig_expert, float* orig_gate,
                              int32_t* slot, float* gate, float* xnorm, int32_t* count, float* gsum, float* score,
                              int accumulate, int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s,
                              hipEvent_t e0, hipEvent_t e1);
-// true when the FFN of a T-token batch takes the one-tile-per-slot kernels (no sorted tiles)
 // True when the expert slots of all layers alive in this process (both matrices, spare slots
 // included) exceed what the 256 MB Infinity Cache can hold between two steps: the decode
 // kernels then mark their weight loads non-temporal.  Measured with 16 slots of 768 x 3072:
@@ -108,6 +134,7 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
 bool smoe_weights_outgrow_cache();
 // plain read of the first K slots of slot_w1 (which = 0) or slot_w2 (1): see smoe_profile_stream_read
 int smoe_launch_stream_read(const smoe_layer* L, int which, hipStream_t s);
+// true when the tile override, if any, leaves a T-token batch to the small-batch path
 bool smoe_ffn_dense_path(const smoe_layer* L, int T);
 int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_of, const float* gate,
                                       const uint16_t* residual, int T, uint16_t* out, hipStream_t s);
@@ -158,6 +185,12 @@ inline void smoe_launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t s, hi
     else hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
 }
 
+// Raises a kernel's dynamic-LDS limit once per device, not on every launch (one object per kernel).
+struct smoe_lds_raised {
+    std::atomic<unsigned long long> mask{0};
+    int ensure(const void* kern, size_t lds, int limit);
+};
+
 // bf16 <-> fp32 on the device.  Widening is exact; narrowing rounds to
 // nearest, ties to even (inputs are finite by contract).
 // 16-byte load of data that is read once per launch (the decode path's weight streams): marked
@@ -175,4 +208,18 @@ __device__ __forceinline__ uint16_t smoe_f32_to_bf16(float f) {
     uint32_t u = __float_as_uint(f);
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
+}
+
+// Combine on 4 consecutive outputs of one token.  The product is first rounded to bf16 exactly as the
+// separate calls store y_perm, so both give the same bits; then out = gate * y (+ residual) in fp32
+// with one final rounding.
+__device__ __forceinline__ void smoe_apply_gate(float& v0, float& v1, float& v2, float& v3, float g, uint2 r, bool has_res) {
+    v0 = smoe_bf16_to_f32(smoe_f32_to_bf16(v0)); v1 = smoe_bf16_to_f32(smoe_f32_to_bf16(v1));
+    v2 = smoe_bf16_to_f32(smoe_f32_to_bf16(v2)); v3 = smoe_bf16_to_f32(smoe_f32_to_bf16(v3));
+    if (has_res) {
+        v0 = fmaf(g, v0, __uint_as_float(r.x << 16)); v1 = fmaf(g, v1, __uint_as_float(r.x & 0xFFFF0000u));
+        v2 = fmaf(g, v2, __uint_as_float(r.y << 16)); v3 = fmaf(g, v3, __uint_as_float(r.y & 0xFFFF0000u));
+    } else {
+        v0 *= g; v1 *= g; v2 *= g; v3 *= g;
+    }
 }
