@@ -78,15 +78,22 @@ smoe_ws_layout smoe_ws_plan(const smoe_config& c) {
     return w;
 }
 
-// slot bytes of every live layer (see smoe_weights_outgrow_cache)
-static std::atomic<long long> g_live_slot_bytes{0};
-static long long layer_slot_bytes(const smoe_config& c) {
-    return 2ll * (c.K + c.spare_slots) * c.d_model * c.d_ff * (long long)smoe_elem_size(c.dtype);
+// Slot bytes that passed through the GPU's memory in this process so far: every layer's own at its
+// creation and at each pass over its slots (see smoe_weights_outgrow_cache).
+static std::atomic<uint64_t> g_slot_traffic{0};
+static uint64_t layer_slot_bytes(const smoe_config& c) {
+    return 2ull * (c.K + c.spare_slots) * c.d_model * c.d_ff * smoe_elem_size(c.dtype);
 }
 
-bool smoe_weights_outgrow_cache() {
-    constexpr long long kCacheable = 192ll << 20;          // three quarters of the 256 MB Infinity Cache
-    return g_live_slot_bytes.load(std::memory_order_relaxed) > kCacheable;
+static void note_slot_pass(smoe_layer* L) {
+    const uint64_t own = layer_slot_bytes(L->cfg);
+    L->slot_traffic_seen = g_slot_traffic.fetch_add(own, std::memory_order_relaxed) + own;
+}
+
+bool smoe_weights_outgrow_cache(const smoe_layer* L) {
+    constexpr uint64_t kCacheable = 192ull << 20;          // three quarters of the 256 MB Infinity Cache
+    const uint64_t since = g_slot_traffic.load(std::memory_order_relaxed) - L->slot_traffic_seen;
+    return since + layer_slot_bytes(L->cfg) > kCacheable;
 }
 
 int smoe_refresh_maps(smoe_layer* L) {
@@ -143,14 +150,13 @@ int smoe_create(const smoe_config* cfg, smoe_layer_t** out) {
         int a = -1, b = -1;
         if (sscanf(env, "%d,%d", &a, &b) == 2 && a >= 0 && b >= 0) { L->ffn_variant[0] = a; L->ffn_variant[1] = b; }
     }
-    g_live_slot_bytes += layer_slot_bytes(c);
+    note_slot_pass(L);
     *out = L;
     return SMOE_OK;
 }
 
 int smoe_destroy(smoe_layer_t* layer) {
     if (!layer) return smoe_fail(SMOE_EINVAL, "smoe_destroy: null handle");
-    g_live_slot_bytes -= layer_slot_bytes(layer->cfg);
     for (auto& st : layer->staged) if (st.done) (void)hipEventDestroy(st.done);
     for (hipEvent_t e : layer->event_pool) (void)hipEventDestroy(e);
     for (hipEvent_t e : layer->released) if (e) (void)hipEventDestroy(e);
@@ -581,6 +587,7 @@ int smoe_expert_ffn(smoe_layer_t* L, const void* x_perm, const int32_t* offsets,
         rc = smoe_launch_ffn_f32(L, (const float*)x_perm, offsets, T, (float*)y_perm, as_stream(stream));
     else
         rc = smoe_launch_ffn_bf16(L, (const uint16_t*)x_perm, offsets, T, (uint16_t*)y_perm, as_stream(stream));
+    note_slot_pass(L);
     L->prof_ev[0] = L->prof_ev[1] = L->prof_ev[2] = L->prof_ev[3] = nullptr;
     return rc;
 }
@@ -611,6 +618,7 @@ int smoe_forward(smoe_layer_t* L, const void* x, int T, const void* residual, vo
         return smoe_fail(SMOE_EINVAL, "smoe_forward: x, residual and out must be 16-byte aligned");
     if (x == out) return smoe_fail(SMOE_EINVAL, "smoe_forward: out must not alias x");
     hipStream_t s = as_stream(stream);
+    struct Noted { smoe_layer* L; ~Noted() { note_slot_pass(L); } } noted{L};   // after the launches, which ask what came before
     if (!L->router_split_done) {
         rc = smoe_launch_split_router(L, s);
         if (rc) return rc;

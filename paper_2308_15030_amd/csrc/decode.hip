@@ -489,7 +489,7 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
     L->tail = smoe_step_tail{L->expert_norm, orig_expert, orig_gate, xnorm, count, gsum, score, accumulate, perm, inv_perm, offsets};
     const smoe_route_args ra{(const uint16_t*)x, (const uint4*)L->d_router_split, L->d_expert_to_slot, T, c.d_model, c.E, c.gate_mode,
                              orig_expert, orig_gate, slot, gate, xnorm, nullptr, c.K};
-    const bool stream = smoe_weights_outgrow_cache();
+    const bool stream = smoe_weights_outgrow_cache(L);
     switch (router_instance(c.E)) {
         case 1: return launch_first_nbf<1>(L, ra, stream, s, e0, e1);
         case 2: return launch_first_nbf<2>(L, ra, stream, s, e0, e1);
@@ -504,7 +504,7 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
     const second_args a{(const uint16_t*)L->d_hidden, (const uint4*)L->slot_w2, slot_of, T, c.E, c.K, c.d_ff, c.d_model,
                         c.spare_slots > 0 ? L->d_phys : nullptr, gate, residual, out, L->tail};
     const dim3 grid(c.K * (c.d_model >> 5) + 1);
-    const bool stream = smoe_weights_outgrow_cache();
+    const bool stream = smoe_weights_outgrow_cache(L);
     auto kern = T <= 32 ? (stream ? decode_second_stream_kernel<1> : decode_second_kernel<1>)
                         : (stream ? decode_second_stream_kernel<2> : decode_second_kernel<2>);
     smoe_launch_timed(kern, grid, dim3(256), s, L->prof_ev[2], L->prof_ev[3], a);
@@ -512,7 +512,7 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
 }
 
 std::string smoe_describe_decode(const smoe_layer* L, int T, bool first) {
-    const std::string st = smoe_weights_outgrow_cache() ? "_stream" : "";
+    const std::string st = smoe_weights_outgrow_cache(L) ? "_stream" : "";
     if (!first) return "decode_second" + st + "_kernel<" + (T <= 32 ? "1>" : "2>");
     return "decode_first" + st + "_kernel<" + std::to_string(router_instance(L->cfg.E)) + ", " + (T <= 32 ? "1>" : T <= 64 ? "2>" : "4>");
 }
