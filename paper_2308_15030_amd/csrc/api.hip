@@ -67,7 +67,6 @@ smoe_ws_layout smoe_ws_plan(const smoe_config& c) {
     // hidden activations: every segment is re-based to a multiple of 32 rows
     const size_t rows = std::max((size_t)c.max_tokens + 32 * (size_t)c.K, smoe_small_batch_rows(c));
     w.hidden = off;  off = align_up(off + rows * c.d_ff * smoe_elem_size(c.dtype), 256);
-    w.partial = off; off = align_up(off, 256);
     // bf16 path: the router's weights in matrix-operand order, experts padded to a multiple of 32
     w.rsplit = off;
     if (c.dtype == SMOE_BF16) off = align_up(off + (size_t)((c.E + 31) / 32 * 32) * c.d_model * 4, 256);
@@ -201,7 +200,6 @@ int smoe_bind(smoe_layer_t* L, const float* router_w, void* slot_w1, void* slot_
     L->d_sort_hist = (int32_t*)(L->workspace + w.hist);
     L->d_hist32 = (int32_t*)(L->workspace + w.hist32);
     L->d_hidden = L->workspace + w.hidden;
-    L->d_partial = (float*)(L->workspace + w.partial);
     L->d_router_split = L->workspace + w.rsplit;
     L->router_split_done = false;
     L->ws_ready = false;

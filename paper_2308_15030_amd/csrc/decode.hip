@@ -148,7 +148,7 @@ __device__ __forceinline__ void decode_first_body(const smoe_route_args& ra, con
     extern __shared__ __align__(16) float smem[];
     const int routers = (ra.T + SMOE_RT - 1) / SMOE_RT;
     if ((int)blockIdx.x < routers) smoe_route_mfma_body<NEB, 1>(blockIdx.x, ra, smem);
-    else dense_first_all<NBF, STREAM>(ra.x, W1, ra.T, h, ra.d, d_ff, phys, blockIdx.x - routers, fbw, (uint16_t*)smem);
+    else dense_first_all<NBF, STREAM>((const uint16_t*)ra.x, W1, ra.T, h, ra.d, d_ff, phys, blockIdx.x - routers, fbw, (uint16_t*)smem);
 }
 
 // Two kernels with one body: the second streams its weights past the caches.
@@ -487,7 +487,7 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
     if (!smoe_decode_first_applies(L, T)) return smoe_fail(SMOE_EINVAL, "smoe_forward: the fused decode launch does not apply");
     const smoe_config& c = L->cfg;
     L->tail = smoe_step_tail{L->expert_norm, orig_expert, orig_gate, xnorm, count, gsum, score, accumulate, perm, inv_perm, offsets};
-    const smoe_route_args ra{(const uint16_t*)x, (const uint4*)L->d_router_split, L->d_expert_to_slot, T, c.d_model, c.E, c.gate_mode,
+    const smoe_route_args ra{x, (const uint4*)L->d_router_split, L->router_w, L->d_expert_to_slot, T, c.d_model, c.E, c.gate_mode,
                              orig_expert, orig_gate, slot, gate, xnorm, nullptr, c.K};
     const bool stream = smoe_weights_outgrow_cache(L);
     switch (router_instance(c.E)) {

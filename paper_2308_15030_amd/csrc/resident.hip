@@ -9,7 +9,8 @@
 //     ((n/32 * R/16 + r/16) * 64 + lane) * 8 + r%8,   lane = n%32 + 32*((r%16)/8)
 // i.e. one 1-KiB block per (32 features x 16 reduction steps): exactly one
 // operand of the 32x32x16 bf16 MFMA, lane-major, and all blocks of one feature
-// group contiguous along the reduction.  fp32 slots keep the bank layout.
+// group contiguous along the reduction.  fp32 slots hold panels of 64 features (the last one narrower),
+// each [R / 4][panel width][4] (see ffn_f32.hip).
 
 #include "smoe_internal.h"
 
@@ -159,10 +160,32 @@ __global__ __launch_bounds__(256) void pack_planned_kernel(const uint16_t* __res
     }
 }
 
-__global__ __launch_bounds__(256) void copy16_kernel(const uint4* __restrict__ src, size_t n16,
-                                                     uint4* __restrict__ dst) {
-    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n16) dst[i] = src[i];
+// fp32: both matrices of one expert into their panels; a thread turns 4 rows x 4 features in registers
+// (16-byte reads and writes); blocks [0, nblk1) take W1.  With map_slot >= 0 the first thread also
+// switches the maps.
+__global__ __launch_bounds__(256) void pack_f32_kernel(const float4* __restrict__ w1, const float4* __restrict__ w2, int d_model,
+                                                       int d_ff, float4* __restrict__ dst1, float4* __restrict__ dst2, int nblk1,
+                                                       int32_t* e2s, int32_t* s2e, int32_t* phys, int map_slot, int expert,
+                                                       int old_expert, int p) {
+    const bool first = (int)blockIdx.x < nblk1;
+    const int i = (first ? blockIdx.x : blockIdx.x - nblk1) * 256 + threadIdx.x;
+    const int R4 = (first ? d_model : d_ff) >> 2, n4 = (first ? d_ff : d_model) >> 2;         // units of 4 rows, pieces of 4 features
+    if (i < R4 * n4) {
+        const int u = i / n4, c = i - u * n4, c0 = c & ~15, w = min(16, n4 - c0);             // first piece and width of the panel
+        const float4* src = (first ? w1 : w2) + (size_t)(4 * u) * n4 + c;
+        const float4 a = src[0], b = src[n4], e = src[2 * n4], g = src[3 * n4];
+        float4* dst = (first ? dst1 : dst2) + (size_t)c0 * 4 * R4 + ((size_t)u * w + (c - c0)) * 4;
+        dst[0] = make_float4(a.x, b.x, e.x, g.x);
+        dst[1] = make_float4(a.y, b.y, e.y, g.y);
+        dst[2] = make_float4(a.z, b.z, e.z, g.z);
+        dst[3] = make_float4(a.w, b.w, e.w, g.w);
+    }
+    if (map_slot >= 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+        if (old_expert >= 0) e2s[old_expert] = -1;
+        e2s[expert] = map_slot;
+        s2e[map_slot] = expert;
+        phys[map_slot] = p;
+    }
 }
 
 // |E_i|^2 partial sums: grid (chunks, experts); a fixed tree per block and a
@@ -219,8 +242,7 @@ int smoe_launch_clear_maps(const smoe_layer* L, hipStream_t s) {
     return smoe_check_hip(hipGetLastError(), "smoe_set_resident: map reset");
 }
 
-// map_slot >= 0: the launch that loads the weights also switches the maps (bf16 layers; fp32
-// layers take the separate map launch).  Returns 1 in *map_done when it did.
+// map_slot >= 0: the launch that loads the weights also switches the maps and *map_done becomes 1.
 int smoe_launch_pack_slot(const smoe_layer* L, int slot, const void* w1_src, const void* w2_src, hipStream_t s,
                           int map_slot, int expert, int old_expert, int* map_done) {
     const smoe_config& c = L->cfg;
@@ -234,15 +256,13 @@ int smoe_launch_pack_slot(const smoe_layer* L, int slot, const void* w1_src, con
         hipLaunchKernelGGL(pack_bf16_kernel, dim3(nblk1 + nblk2), dim3(256), 0, s, (const uint16_t*)w1_src,
                            (const uint16_t*)w2_src, c.d_model, c.d_ff, d1, d2, nblk1, L->d_expert_to_slot,
                            L->d_slot_to_expert, L->d_phys, map_slot, expert, old_expert, slot);
-        if (map_done && map_slot >= 0) *map_done = 1;
     } else {
-        size_t n16 = per * 4 / 16;
-        dim3 grid((unsigned)((n16 + 255) / 256));
-        hipLaunchKernelGGL(copy16_kernel, grid, dim3(256), 0, s, (const uint4*)w1_src, n16,
-                           (uint4*)((float*)L->slot_w1 + (size_t)slot * per));
-        hipLaunchKernelGGL(copy16_kernel, grid, dim3(256), 0, s, (const uint4*)w2_src, n16,
-                           (uint4*)((float*)L->slot_w2 + (size_t)slot * per));
+        const int nblk = (int)((per / 16 + 255) / 256);
+        hipLaunchKernelGGL(pack_f32_kernel, dim3(2 * nblk), dim3(256), 0, s, (const float4*)w1_src, (const float4*)w2_src, c.d_model,
+                           c.d_ff, (float4*)((float*)L->slot_w1 + (size_t)slot * per), (float4*)((float*)L->slot_w2 + (size_t)slot * per),
+                           nblk, L->d_expert_to_slot, L->d_slot_to_expert, L->d_phys, map_slot, expert, old_expert, slot);
     }
+    if (map_done && map_slot >= 0) *map_done = 1;
     return smoe_check_hip(hipGetLastError(), "expert load launch");
 }
 

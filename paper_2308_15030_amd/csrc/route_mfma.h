@@ -37,8 +37,9 @@ __device__ __forceinline__ smoe_bf16x8 smoe_frag(uint4 v) {
 constexpr int SMOE_RT = 32;       // tokens per token block (one MFMA operand)
 
 struct smoe_route_args {
-    const uint16_t* x;
-    const uint4* wr;              // fp32 [expert block][reduction step][2 halves][lane][4]
+    const void* x;                // bf16 or fp32 [T, d]
+    const uint4* wr;              // bf16 layers: fp32 [expert block][reduction step][2 halves][lane][4]
+    const float* wrow;            // fp32 layers: the caller's [E, d]
     const int32_t* e2s;
     int T, d, E, gate_mode;
     int32_t* orig_expert;
@@ -68,38 +69,19 @@ struct smoe_route_shape {
     }
 };
 
+// The partial logits of the 8 waves meet in LDS and every token's results are written.
 template <int NEB, int TB>
-__device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe_route_args& a, float* smem) {
+__device__ __forceinline__ void smoe_route_finish(const int block, const smoe_route_args& a,
+                                                  smoe_f32x16 (&acc)[smoe_route_shape<NEB, TB>::NEBH][TB], float (&sq)[TB],
+                                                  float* smem) {
     using S = smoe_route_shape<NEB, TB>;
     constexpr int NS = S::NS, NEBH = S::NEBH, EP = S::EP, LDP = S::LDP, RT = SMOE_RT, NTOK = S::NTOK;
-    constexpr int KC = SMOE_ROUTE_KC;
-    // reduction steps whose weights are fetched together; two such groups are in flight
-    constexpr int G = NEBH == 1 ? 4 : NEBH == 2 ? 3 : 2;
-    uint16_t* xs = (uint16_t*)smem;                        // [NTOK][ldx] columns of x
-    float* part = smem;                                    // [NS][NTOK][LDP] partial logits, once the tokens are used up
+    float* part = smem;                                    // [NS][NTOK][LDP] partial logits
     float* sqp = smem + NS * NTOK * LDP;                   // [NS][2 halves][NTOK] partial sums of squares
     __shared__ int32_t s_hist[TB * 256];                   // tokens per block and slot
-
-    // wave index as a scalar: loop bounds that guard MFMAs must be wave-uniform for the
-    // compiler as well (an MFMA under a lane mask still runs for every lane)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int slice = wave % NS, group = wave / NS;
-    const int tw0 = block * NTOK;                          // first token of the workgroup
-    const int neb = (a.E + 31) >> 5, nkb = a.d >> 4;
-    const uint4* wp[NEBH];
-#pragma unroll
-    for (int b = 0; b < NEBH; ++b) wp[b] = a.wr + (size_t)min(group * NEBH + b, neb - 1) * nkb * 2 * 64 + lane;
-
-    smoe_f32x16 acc[NEBH][TB];
-    float sq[TB];
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        sq[tb] = 0.f;
-#pragma unroll
-        for (int b = 0; b < NEBH; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[b][tb][i] = 0.f;
-    }
+    const int tw0 = block * NTOK, neb = (a.E + 31) >> 5;
     if (a.hist32)
         for (int i = tid; i < TB * 256; i += 512) s_hist[i] = 0;
     constexpr int EC = (EP + 63) / 64;                     // chunks of 64 experts; a lane of the epilogue has 4 of each
@@ -113,109 +95,7 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
             sl[c][j] = e < a.E ? a.e2s[e] : -1;
         }
 
-    const int ldx = min(a.d, KC) + 8;                      // conflict-free 16-byte operand reads
-    for (int k0 = 0; k0 < a.d; k0 += KC) {                 // (one pass up to d_model = 1024)
-        const int kc = min(KC, a.d - k0), steps = kc >> 4;
-        const int per = (steps + NS - 1) / NS;
-        const int lo = min(slice * per, steps), hi = min(lo + per, steps);   // this wave's steps of the chunk
-        const int n = hi - lo;
-        const uint4* w0[NEBH];
-#pragma unroll
-        for (int b = 0; b < NEBH; ++b) w0[b] = wp[b] + (size_t)((k0 >> 4) + lo) * 2 * 64;
-        uint4 wA[G][NEBH][2], wB[G][NEBH][2];
-        auto fetch = [&](uint4 (&w)[G][NEBH][2], int g0) {
-#pragma unroll
-            for (int i = 0; i < G; ++i)                    // past the end: reloaded, not used
-#pragma unroll
-                for (int b = 0; b < NEBH; ++b)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) w[i][b][h] = w0[b][(size_t)(max(min(g0 + i, n - 1), 0) * 2 + h) * 64];
-        };
-        fetch(wA, 0);                                      // on their way while the tokens are staged
-        if (k0) __syncthreads();                           // the previous chunk has been used up
-        const int cpr = kc >> 3;                           // 16-byte pieces per row
-        constexpr int PPT = 8;                             // pieces fetched together
-        for (int i0 = tid; i0 < NTOK * cpr; i0 += 512 * PPT) {
-            uint4 v[PPT];
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
-                v[q] = *(const uint4*)(a.x + (size_t)min(tw0 + r, a.T - 1) * a.d + k0 + c * 8);
-            }
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {                // pieces past the end repeat the last one
-                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
-                *(uint4*)&xs[r * ldx + c * 8] = v[q];
-            }
-        }
-        __syncthreads();
-        const uint16_t* xrow = xs + (lane & 31) * ldx + (lane >> 5) * 8 + lo * 16;
-        auto consume = [&](uint4 (&w)[G][NEBH][2], int g0) {
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                smoe_bf16x8 xf[TB];
-#pragma unroll
-                for (int tb = 0; tb < TB; ++tb) {
-                    uint4 xv = *(const uint4*)(xrow + tb * RT * ldx + max(min(g0 + i, n - 1), 0) * 16);
-                    if (g0 + i >= n) xv = make_uint4(0, 0, 0, 0);   // steps past the end multiply by a zero operand
-                    xf[tb] = smoe_frag(xv);
-                    if (group == 0) {                      // the groups read the same tokens: one of them adds the squares
-                        const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float l = __uint_as_float(xw[q] << 16), h = __uint_as_float(xw[q] & 0xFFFF0000u);
-                            sq[tb] = fmaf(l, l, sq[tb]);
-                            sq[tb] = fmaf(h, h, sq[tb]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < NEBH; ++b) {
-                    const uint32_t f[8] = {w[i][b][0].x, w[i][b][0].y, w[i][b][0].z, w[i][b][0].w,
-                                           w[i][b][1].x, w[i][b][1].y, w[i][b][1].z, w[i][b][1].w};
-                    uint32_t pc[3][4];                     // hi, mid, lo of four pairs
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float u = __uint_as_float(f[2 * q]), v = __uint_as_float(f[2 * q + 1]);
-#pragma unroll
-                        for (int s3 = 0; s3 < 3; ++s3) {   // upper halves packed; the remainders are exact
-                            pc[s3][q] = __builtin_amdgcn_perm(__float_as_uint(v), __float_as_uint(u), 0x07060302u);
-                            u -= __uint_as_float(__float_as_uint(u) & 0xFFFF0000u);
-                            v -= __uint_as_float(__float_as_uint(v) & 0xFFFF0000u);
-                        }
-                    }
-                    // smallest terms first, so they are not absorbed by the large partial sums
-#pragma unroll
-                    for (int s3 = 2; s3 >= 0; --s3)
-#pragma unroll
-                        for (int tb = 0; tb < TB; ++tb)
-                            acc[b][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                smoe_frag(make_uint4(pc[s3][0], pc[s3][1], pc[s3][2], pc[s3][3])), xf[tb], acc[b][tb], 0, 0, 0);
-                }
-            }
-        };
-        int g0 = 0;
-        for (; n - g0 > 2 * G; g0 += 2 * G) {
-            fetch(wB, g0 + G);
-            __builtin_amdgcn_sched_barrier(0);             // the next group's loads are issued first
-            consume(wA, g0);
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(wA, g0 + 2 * G);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(wB, g0 + G);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (n - g0 > G) {
-            fetch(wB, g0 + G);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(wA, g0);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(wB, g0 + G);
-        } else {
-            consume(wA, g0);
-        }
-    }
-    __syncthreads();                                       // the partial logits take the tokens' place
+    __syncthreads();                                       // the partial logits take the staged tokens' place
     // accumulator register i of lane l: expert 8*(i/4) + 4*(l/32) + i%4 (+32 per block), token l%32
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
@@ -298,4 +178,217 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
             if (tw0 + tb * RT < a.T) a.hist32[((size_t)block * TB + tb) * a.K + k] = s_hist[tb * 256 + k];
         }
     }
+}
+
+template <int NEB, int TB>
+__device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe_route_args& a, float* smem) {
+    using S = smoe_route_shape<NEB, TB>;
+    constexpr int NS = S::NS, NEBH = S::NEBH, RT = SMOE_RT, NTOK = S::NTOK;
+    constexpr int KC = SMOE_ROUTE_KC;
+    // reduction steps whose weights are fetched together; two such groups are in flight
+    constexpr int G = NEBH == 1 ? 4 : NEBH == 2 ? 3 : 2;
+    uint16_t* xs = (uint16_t*)smem;                        // [NTOK][ldx] columns of x
+
+    // wave index as a scalar: loop bounds that guard MFMAs must be wave-uniform for the
+    // compiler as well (an MFMA under a lane mask still runs for every lane)
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int slice = wave % NS, group = wave / NS;
+    const int tw0 = block * NTOK;                          // first token of the workgroup
+    const int neb = (a.E + 31) >> 5, nkb = a.d >> 4;
+    const uint4* wp[NEBH];
+#pragma unroll
+    for (int b = 0; b < NEBH; ++b) wp[b] = a.wr + (size_t)min(group * NEBH + b, neb - 1) * nkb * 2 * 64 + lane;
+
+    smoe_f32x16 acc[NEBH][TB];
+    float sq[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+        sq[tb] = 0.f;
+#pragma unroll
+        for (int b = 0; b < NEBH; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[b][tb][i] = 0.f;
+    }
+    const int ldx = min(a.d, KC) + 8;                      // conflict-free 16-byte operand reads
+    for (int k0 = 0; k0 < a.d; k0 += KC) {                 // (one pass up to d_model = 1024)
+        const int kc = min(KC, a.d - k0), steps = kc >> 4;
+        const int per = (steps + NS - 1) / NS;
+        const int lo = min(slice * per, steps), hi = min(lo + per, steps);   // this wave's steps of the chunk
+        const int n = hi - lo;
+        const uint4* w0[NEBH];
+#pragma unroll
+        for (int b = 0; b < NEBH; ++b) w0[b] = wp[b] + (size_t)((k0 >> 4) + lo) * 2 * 64;
+        uint4 wA[G][NEBH][2], wB[G][NEBH][2];
+        auto fetch = [&](uint4 (&w)[G][NEBH][2], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i)                    // past the end: reloaded, not used
+#pragma unroll
+                for (int b = 0; b < NEBH; ++b)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) w[i][b][h] = w0[b][(size_t)(max(min(g0 + i, n - 1), 0) * 2 + h) * 64];
+        };
+        fetch(wA, 0);                                      // on their way while the tokens are staged
+        if (k0) __syncthreads();                           // the previous chunk has been used up
+        const int cpr = kc >> 3;                           // 16-byte pieces per row
+        constexpr int PPT = 8;                             // pieces fetched together
+        for (int i0 = tid; i0 < NTOK * cpr; i0 += 512 * PPT) {
+            uint4 v[PPT];
+#pragma unroll
+            for (int q = 0; q < PPT; ++q) {
+                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
+                v[q] = *(const uint4*)((const uint16_t*)a.x + (size_t)min(tw0 + r, a.T - 1) * a.d + k0 + c * 8);
+            }
+#pragma unroll
+            for (int q = 0; q < PPT; ++q) {                // pieces past the end repeat the last one
+                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
+                *(uint4*)&xs[r * ldx + c * 8] = v[q];
+            }
+        }
+        __syncthreads();
+        const uint16_t* xrow = xs + (lane & 31) * ldx + (lane >> 5) * 8 + lo * 16;
+        auto consume = [&](uint4 (&w)[G][NEBH][2], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                smoe_bf16x8 xf[TB];
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) {
+                    uint4 xv = *(const uint4*)(xrow + tb * RT * ldx + max(min(g0 + i, n - 1), 0) * 16);
+                    if (g0 + i >= n) xv = make_uint4(0, 0, 0, 0);   // steps past the end multiply by a zero operand
+                    xf[tb] = smoe_frag(xv);
+                    if (group == 0) {                      // the groups read the same tokens: one of them adds the squares
+                        const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float l = __uint_as_float(xw[q] << 16), h = __uint_as_float(xw[q] & 0xFFFF0000u);
+                            sq[tb] = fmaf(l, l, sq[tb]);
+                            sq[tb] = fmaf(h, h, sq[tb]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < NEBH; ++b) {
+                    const uint32_t f[8] = {w[i][b][0].x, w[i][b][0].y, w[i][b][0].z, w[i][b][0].w,
+                                           w[i][b][1].x, w[i][b][1].y, w[i][b][1].z, w[i][b][1].w};
+                    uint32_t pc[3][4];                     // hi, mid, lo of four pairs
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float u = __uint_as_float(f[2 * q]), v = __uint_as_float(f[2 * q + 1]);
+#pragma unroll
+                        for (int s3 = 0; s3 < 3; ++s3) {   // upper halves packed; the remainders are exact
+                            pc[s3][q] = __builtin_amdgcn_perm(__float_as_uint(v), __float_as_uint(u), 0x07060302u);
+                            u -= __uint_as_float(__float_as_uint(u) & 0xFFFF0000u);
+                            v -= __uint_as_float(__float_as_uint(v) & 0xFFFF0000u);
+                        }
+                    }
+                    // smallest terms first, so they are not absorbed by the large partial sums
+#pragma unroll
+                    for (int s3 = 2; s3 >= 0; --s3)
+#pragma unroll
+                        for (int tb = 0; tb < TB; ++tb)
+                            acc[b][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                smoe_frag(make_uint4(pc[s3][0], pc[s3][1], pc[s3][2], pc[s3][3])), xf[tb], acc[b][tb], 0, 0, 0);
+                }
+            }
+        };
+        int g0 = 0;
+        for (; n - g0 > 2 * G; g0 += 2 * G) {
+            fetch(wB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);             // the next group's loads are issued first
+            consume(wA, g0);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(wA, g0 + 2 * G);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (n - g0 > G) {
+            fetch(wB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wA, g0);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wB, g0 + G);
+        } else {
+            consume(wA, g0);
+        }
+    }
+    smoe_route_finish<NEB, TB>(block, a, acc, sq, smem);
+}
+
+// fp32 activations: the same split of the work with fp32 matrix products (v_mfma_f32_32x32x2_f32).
+// A lane holds four consecutive reduction elements of its row, the two halves of the wave eight: one
+// 16-byte load per operand feeds four MFMAs.  A product of 32 x 32 x 2 takes 64 cycles, so the operands
+// come straight from memory.
+template <int NEB>
+__device__ __forceinline__ void smoe_route_f32_body(const int block, const smoe_route_args& a, float* smem) {
+    using S = smoe_route_shape<NEB, 1>;
+    constexpr int NS = S::NS, NEBH = S::NEBH;
+    constexpr int G = NEBH == 1 ? 6 : NEBH == 2 ? 4 : 2;   // steps of 8 reduction elements fetched together
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int slice = wave % NS, group = wave / NS, half4 = (lane >> 5) * 4;
+    const int steps = (a.d + 7) >> 3, per = (steps + NS - 1) / NS;
+    const int lo = min(slice * per, steps), n = min(lo + per, steps) - lo;
+    const float* xp = (const float*)a.x + (size_t)min(block * SMOE_RT + (lane & 31), a.T - 1) * a.d;
+    const float* wp[NEBH];
+    smoe_f32x16 acc[NEBH][1];
+#pragma unroll
+    for (int b = 0; b < NEBH; ++b) {
+        wp[b] = a.wrow + (size_t)min((group * NEBH + b) * 32 + (lane & 31), a.E - 1) * a.d;   // experts past E: computed, not used
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[b][0][i] = 0.f;
+    }
+    float sq[1] = {0.f};
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    f32x4 xA[G], wA[G][NEBH], xB[G], wB[G][NEBH];
+    auto fetch = [&](f32x4 (&xv)[G], f32x4 (&w)[G][NEBH], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {                      // past the end: read again, not used
+            const int k = min((lo + max(min(g0 + i, n - 1), 0)) * 8 + half4, a.d - 4);
+            xv[i] = *(const f32x4*)(xp + k);
+#pragma unroll
+            for (int b = 0; b < NEBH; ++b) w[i][b] = *(const f32x4*)(wp[b] + k);
+        }
+    };
+    auto step = [&](f32x4& xv, f32x4 (&w)[NEBH], int k) {
+        const bool in = k + half4 < a.d;                   // d_model may end in the middle of a step
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float xj = in ? xv[j] : 0.f;
+            sq[0] = fmaf(xj, xj, sq[0]);
+#pragma unroll
+            for (int b = 0; b < NEBH; ++b) acc[b][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[b][j], xj, acc[b][0], 0, 0, 0);
+        }
+    };
+    auto consume = [&](f32x4 (&xv)[G], f32x4 (&w)[G][NEBH], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) step(xv[i], w[i], (lo + g0 + i) * 8);
+    };
+    auto consume_tail = [&](f32x4 (&xv)[G], f32x4 (&w)[G][NEBH], int g0) {   // nothing is fetched after this
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            if (g0 + i >= n) break;                        // uniform
+            step(xv[i], w[i], (lo + g0 + i) * 8);
+        }
+    };
+    fetch(xA, wA, 0);
+    int g0 = 0;
+    for (; n - g0 > 2 * G; g0 += 2 * G) {
+        fetch(xB, wB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(xA, wA, g0);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(xA, wA, g0 + 2 * G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(xB, wB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (n - g0 > G) {
+        fetch(xB, wB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(xA, wA, g0);
+        __builtin_amdgcn_sched_barrier(0);
+        consume_tail(xB, wB, g0 + G);
+    } else {
+        consume_tail(xA, wA, g0);
+    }
+    smoe_route_finish<NEB, 1>(block, a, acc, sq, smem);
 }

@@ -71,7 +71,6 @@ struct smoe_layer {
     int32_t* d_sort_hist = nullptr;          // [sort blocks, K]
     int32_t* d_hist32 = nullptr;             // fused path: [ceil(max_tokens/32), K] from the router
     void* d_hidden = nullptr;                // [max_tokens, d_ff] activations of the FFN
-    float* d_partial = nullptr;              // small-T FFN: split partial sums
     float* d_norm_partial = nullptr;         // smoe_expert_norm: [E][64] partial sums of squares
     bool ws_ready = false;                   // device maps and counters initialised since the bind
     // smoe_update_on_device changes the device maps without the host: the host copies are then
@@ -94,7 +93,7 @@ struct smoe_layer {
 };
 
 struct smoe_ws_layout {
-    size_t e2s, s2e, phys, dplan, hist, hist32, hidden, partial, rsplit, norm, stage, total;
+    size_t e2s, s2e, phys, dplan, hist, hist32, hidden, rsplit, norm, stage, total;
 };
 smoe_ws_layout smoe_ws_plan(const smoe_config& c);
 
