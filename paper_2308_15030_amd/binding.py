@@ -96,14 +96,23 @@ def _ptr(t):
     """Device (or host) address of a tensor / numpy array; None -> NULL."""
     if t is None:
         return None
-    if isinstance(t, torch.Tensor):
+    try:
         return t.data_ptr()
-    return t.ctypes.data
+    except AttributeError:
+        return t.ctypes.data
+
+
+# The handle of the current stream without building a torch.cuda.Stream object for it: 0.2 us instead
+# of 2.7 us, on calls whose whole host side is 2 us.
+_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def smoe_create(E, K, d_model, d_ff, max_tokens, dtype, gate_mode=SMOE_GATE_FULL, spare_slots=0):
