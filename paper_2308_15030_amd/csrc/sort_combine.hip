@@ -4,16 +4,18 @@
 //  * importance (SwapMoE Eq. 1): one workgroup per expert walks all T tokens
 //    and keeps those whose original choice is that expert; a fixed-shape LDS
 //    tree gives the three sums, so the result is bit-reproducible (no atomics).
-//  * permute: stable counting sort by slot in three launches -- per-block
-//    histograms, a ranking pass that turns them into exact positions with
-//    wavefront ballots (no atomics on positions, hence one unique, stable
-//    order), and a row gather spread over the whole chip.
+//  * permute: stable counting sort by slot -- per-block histograms, a ranking pass that
+//    turns them into exact positions with wavefront ballots (no atomics on
+//    positions, hence one unique, stable order), and the move of the rows; one to
+//    three launches, by batch size.
 //  * combine: out[t] = gate[t] * y_perm[inv_perm[t]] (+ residual); top-1 means
 //    one source row per token, so this is a gather with 16-byte accesses.
 
+#include <algorithm>
 #include <mutex>
 
 #include "smoe_internal.h"
+#include "wave_ops.h"
 
 namespace {
 
@@ -103,8 +105,6 @@ __global__ __launch_bounds__(SB) void sort_hist_kernel(const int32_t* __restrict
 
 // Position of token t = offsets[slot] + (tokens of that slot in earlier blocks)
 //                     + (in earlier waves of this block) + (in lower lanes of this wave).
-// With a single block (T <= 1024) the histogram pass is skipped (hist == nullptr)
-// and the block's own wave counts give the totals.
 __global__ __launch_bounds__(SB) void sort_rank_kernel(const int32_t* __restrict__ slot, int T, int K,
                                                        int nblk, const int32_t* __restrict__ hist,
                                                        int32_t* __restrict__ perm,
@@ -141,14 +141,11 @@ __global__ __launch_bounds__(SB) void sort_rank_kernel(const int32_t* __restrict
             s_wave[w * K + k] = run;
             run += c;
         }
-        int before = 0, total = run;
-        if (hist) {
-            total = 0;
-            for (int b = 0; b < nblk; ++b) {
-                int h = hist[(size_t)b * K + k];
-                if (b < blk) before += h;
-                total += h;
-            }
+        int before = 0, total = 0;
+        for (int b = 0; b < nblk; ++b) {
+            int h = hist[(size_t)b * K + k];
+            if (b < blk) before += h;
+            total += h;
         }
         s_base[k] = before;
         s_total[k] = total;
@@ -281,6 +278,116 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restric
     x_perm[idx] = x[(size_t)src * chunks_per_row + c];
 }
 
+// smoe_permute without a launch for the ranking and one for the rows: workgroup (b, part) ranks the 64
+// tokens of block b and moves 16 of them.  Counting is by ballots: the lanes of a wave that hold the
+// same slot find each other, the lowest of them adds their number to the wave's own table, so nothing is
+// contended, and the position of a token -- slot offset + tokens of its slot in front of it -- is that
+// of the sorting kernels above.
+//   T <= PERM_ONE_MAX    every workgroup looks at all the slot ids (hist == nullptr): one launch
+//   T <= PERM_TWO_MAX    at those of its 1024-token sort block, and takes the rest from the blocks'
+//                        histograms: two launches
+// and beyond, where adding up the histograms in every workgroup costs more than it saves, the three
+// launches above.  Measured (K = 16, rows of 1.5 KB): T = 64 7.2 -> 4.4 us, T = 2048 10.1 -> 7.9 us.
+constexpr int PERM_ONE_MAX = 2048, PERM_TWO_MAX = 65536;
+
+__global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ slot, int T, int K,
+                                                          int chunks_per_row, uint4* __restrict__ x_perm, int32_t* __restrict__ perm,
+                                                          int32_t* __restrict__ inv_perm, int32_t* __restrict__ offsets,
+                                                          const int32_t* __restrict__ hist, int nblk) {
+    __shared__ int32_t s_total[4][256], s_before[4][256];  // per wave: tokens of each slot, and those in front of the block
+    __shared__ int32_t s_pos[64];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int blk = blockIdx.x >> 2, part = blockIdx.x & 3, t0 = blk * 64;
+    const int first = hist ? t0 / SB * SB : 0, end = hist ? t0 + 64 : T;   // the slot ids looked at
+    {
+        int total = 0, before = 0;                         // from the other sort blocks
+        if (hist && tid < K)
+            for (int b = 0; b < nblk; ++b) {
+                const int h = hist[(size_t)b * K + tid];
+                total += h;
+                if (b < t0 / SB) before += h;
+            }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { s_total[w][tid] = w ? 0 : total; s_before[w][tid] = w ? 0 : before; }
+    }
+    __syncthreads();
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int my = -1, my_rank = 0;                              // of this block's token `lane`, in the wave that meets it
+    constexpr int U = 4;                                   // ids fetched together
+    for (int c0 = first + wave * 64; c0 < end; c0 += 256 * U) {
+        int id[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = c0 + u * 256 + lane;
+            id[u] = t < T ? slot[t] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int base = c0 + u * 256;
+            if (base >= end) break;                        // uniform
+            const bool live = (unsigned)id[u] < (unsigned)K;   // out-of-contract slot values are skipped
+            const int v = live ? id[u] : 0;
+            unsigned long long peers = __ballot(live);
+            for (int bit = 0; (1 << bit) < K; ++bit) {
+                const unsigned long long b = __ballot(live && ((v >> bit) & 1));
+                peers &= ((v >> bit) & 1) ? b : ~b;
+            }
+            const int rank = __popcll(peers & below);
+            if (base == t0) { my = live ? v : -1; my_rank = rank; }
+            if (live && rank == 0) {
+                const int n = __popcll(peers);
+                if (!hist) s_total[wave][v] += n;
+                if (base < t0) s_before[wave][v] += n;
+            }
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {                                       // exclusive scan over the slots, 64 at a time
+        int run = 0;
+        for (int base = 0; base < K; base += 64) {
+            const int k = base + lane;
+            int n = 0, b = 0;
+            if (k < K)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) { n += s_total[w][k]; b += s_before[w][k]; }
+            const int incl = run + smoe_wave_incl_scan(n, lane);
+            if (k < K) {
+                s_before[0][k] = incl - n + b;             // first position of the block's tokens of slot k
+                if (blockIdx.x == 0) offsets[k] = incl - n;
+            }
+            run = __builtin_amdgcn_readlane(incl, 63);
+        }
+        if (blockIdx.x == 0 && lane == 0) offsets[K] = run;
+    }
+    __syncthreads();
+    if (wave == ((t0 >> 6) & 3)) {                         // the wave that met this block's tokens
+        const int pos = my >= 0 ? s_before[0][my] + my_rank : -1;
+        s_pos[lane] = pos;
+        if (pos >= 0 && (lane >> 4) == part) {
+            perm[pos] = t0 + lane;
+            inv_perm[t0 + lane] = pos;
+        }
+    }
+    __syncthreads();
+    const int r0 = part * 16, rows = min(16, T - t0 - r0);
+    for (int idx = tid; idx < rows * chunks_per_row; idx += 256) {
+        const int r = idx / chunks_per_row, c = idx - r * chunks_per_row, pos = s_pos[r0 + r];
+        if (pos >= 0) x_perm[(size_t)pos * chunks_per_row + c] = x[(size_t)(t0 + r0 + r) * chunks_per_row + c];
+    }
+}
+
+// hist: [blocks of SB tokens][K], needed above PERM_ONE_MAX tokens.
+int launch_permute_fused(const smoe_config& c, const void* x, const int32_t* slot, int T, void* x_perm, int32_t* perm,
+                         int32_t* inv_perm, int32_t* offsets, int32_t* hist, hipStream_t s, const char* what) {
+    const int cpr = (int)((size_t)c.d_model * smoe_elem_size(c.dtype) / 16), nblk = smoe_sort_blocks(T);
+    if (T <= PERM_ONE_MAX) hist = nullptr;
+    else hipLaunchKernelGGL(sort_hist_kernel, dim3(nblk), dim3(SB), c.K * sizeof(int32_t), s, slot, T, c.K, hist);
+    const int blocks = std::max(1, (T + 63) / 64);         // T = 0 still writes offsets = 0
+    hipLaunchKernelGGL(permute_rows_kernel, dim3(4 * blocks), dim3(256), 0, s, (const uint4*)x, slot, T, c.K, cpr, (uint4*)x_perm, perm,
+                       inv_perm, offsets, hist, nblk);
+    return smoe_check_hip(hipGetLastError(), what);
+}
+
 // ------------------------------------------------------------- combine
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ y_perm,
@@ -333,19 +440,16 @@ int smoe_launch_importance(const smoe_layer* L, const int32_t* orig_expert, cons
 
 int smoe_launch_permute(const smoe_layer* L, const void* x, const int32_t* slot, int T, void* x_perm,
                         int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s) {
-    const int K = L->cfg.K;
-    const int nblk = T > 0 ? smoe_sort_blocks(T) : 1;       // T = 0 still writes offsets = 0
-    if (nblk > 1)
-        hipLaunchKernelGGL(sort_hist_kernel, dim3(nblk), dim3(SB), K * sizeof(int32_t), s, slot, T, K,
-                           L->d_sort_hist);
+    if (T <= PERM_TWO_MAX)
+        return launch_permute_fused(L->cfg, x, slot, T, x_perm, perm, inv_perm, offsets, L->d_sort_hist, s, "smoe_permute launch");
+    const int K = L->cfg.K, nblk = smoe_sort_blocks(T);
+    hipLaunchKernelGGL(sort_hist_kernel, dim3(nblk), dim3(SB), K * sizeof(int32_t), s, slot, T, K, L->d_sort_hist);
     hipLaunchKernelGGL(sort_rank_kernel, dim3(nblk), dim3(SB), (2 + SB_WAVES) * K * sizeof(int32_t), s,
-                       slot, T, K, nblk, nblk > 1 ? L->d_sort_hist : nullptr, perm, inv_perm, offsets);
-    if (T > 0) {
-        int cpr = (int)((size_t)L->cfg.d_model * smoe_elem_size(L->cfg.dtype) / 16);
-        size_t total = (size_t)T * cpr;
-        hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                           (const uint4*)x, perm, T, cpr, (uint4*)x_perm);
-    }
+                       slot, T, K, nblk, L->d_sort_hist, perm, inv_perm, offsets);
+    const int cpr = (int)((size_t)L->cfg.d_model * smoe_elem_size(L->cfg.dtype) / 16);
+    const size_t total = (size_t)T * cpr;
+    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
+                       (const uint4*)x, perm, T, cpr, (uint4*)x_perm);
     return smoe_check_hip(hipGetLastError(), "smoe_permute launch");
 }
 
@@ -388,28 +492,16 @@ static int static_scratch(int32_t** out) {
 
 int smoe_static_max_tokens() { return STATIC_MAX_TOKENS; }
 
-// Same three launches as smoe_launch_permute; only the histogram buffer differs.  Nothing in
-// the array has to start at zero: the histogram launch overwrites every entry the ranking
-// launch reads ([blocks of this call][K]), so a smaller call after a larger one is safe.
+// The launches of smoe_launch_permute; only the histogram buffer differs.  Nothing in the array has to
+// start at zero: the histogram launch overwrites every entry the ranking reads ([blocks of this
+// call][K]), so a smaller call after a larger one is safe.
 int smoe_launch_permute_static(const smoe_config& c, const void* x, const int32_t* slot, int T, void* x_perm,
                                int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s) {
-    const int K = c.K;
-    const int nblk = T > 0 ? smoe_sort_blocks(T) : 1;
+    static_assert(STATIC_MAX_TOKENS <= PERM_TWO_MAX, "the fixed array serves the fused launches only");
     int32_t* hist = nullptr;
-    if (nblk > 1) {
-        int rc = static_scratch(&hist);
-        if (rc) return rc;
-        hipLaunchKernelGGL(sort_hist_kernel, dim3(nblk), dim3(SB), K * sizeof(int32_t), s, slot, T, K, hist);
-    }
-    hipLaunchKernelGGL(sort_rank_kernel, dim3(nblk), dim3(SB), (2 + SB_WAVES) * K * sizeof(int32_t), s,
-                       slot, T, K, nblk, hist, perm, inv_perm, offsets);
-    if (T > 0) {
-        int cpr = (int)((size_t)c.d_model * smoe_elem_size(c.dtype) / 16);
-        size_t total = (size_t)T * cpr;
-        hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                           (const uint4*)x, perm, T, cpr, (uint4*)x_perm);
-    }
-    return smoe_check_hip(hipGetLastError(), "smoe_permute_static launch");
+    if (T > PERM_ONE_MAX)
+        if (int rc = static_scratch(&hist)) return rc;
+    return launch_permute_fused(c, x, slot, T, x_perm, perm, inv_perm, offsets, hist, s, "smoe_permute_static launch");
 }
 
 int smoe_launch_rank_importance(const smoe_layer* L, const int32_t* orig_expert, const float* orig_gate,
