@@ -508,6 +508,7 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
     auto kern = T <= 32 ? (stream ? decode_second_stream_kernel<1> : decode_second_kernel<1>)
                         : (stream ? decode_second_stream_kernel<2> : decode_second_kernel<2>);
     smoe_launch_timed(kern, grid, dim3(256), s, L->prof_ev[2], L->prof_ev[3], a);
+    L->tail = smoe_step_tail{};                            // the caller's pointers are not kept
     return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");
 }
 
