@@ -274,15 +274,18 @@ int smoe_set_resident(smoe_layer_t* L, int slot, int expert, const void* w1_src,
         if (st.slot == slot || st.expert == expert)
             return smoe_fail(SMOE_ESTATE, "smoe_set_resident: slot %d / expert %d has an asynchronous load in flight",
                              st.slot, st.expert);
-    int rc0 = check_gpu_readable(w1_src, "smoe_set_resident", "w1_src");
-    if (!rc0) rc0 = check_gpu_readable(w2_src, "smoe_set_resident", "w2_src");
+    bool h1 = false, h2 = false;
+    int rc0 = check_gpu_readable(w1_src, "smoe_set_resident", "w1_src", &h1);
+    if (!rc0) rc0 = check_gpu_readable(w2_src, "smoe_set_resident", "w2_src", &h2);
     if (rc0) return rc0;
     hipStream_t s = as_stream(stream);
     rc0 = ensure_workspace(L, s);
     if (rc0) return rc0;
     int old = L->slot_to_expert[slot];
     int map_done = 0;
+    L->load_from_host = h1 || h2;
     int rc = smoe_launch_pack_slot(L, L->phys[slot], w1_src, w2_src, s, slot, expert, old, &map_done);
+    L->load_from_host = false;
     if (rc) return rc;
     if (!map_done) {
         rc = smoe_launch_set_map(L, slot, expert, old, L->phys[slot], s);
@@ -348,10 +351,12 @@ int smoe_update_on_device(smoe_layer_t* L, const float* score, const void* bank_
         return smoe_fail(SMOE_ESTATE, "smoe_update_on_device: an asynchronous update is pending");
     // score and banks are read by kernels: checked once per triple of pointers
     if (score != L->dev_update_seen[0] || bank_w1 != L->dev_update_seen[1] || bank_w2 != L->dev_update_seen[2]) {
+        bool h1 = false, h2 = false;
         int rc = check_gpu_readable(score, "smoe_update_on_device", "score");
-        if (!rc) rc = check_gpu_readable(bank_w1, "smoe_update_on_device", "bank_w1");
-        if (!rc) rc = check_gpu_readable(bank_w2, "smoe_update_on_device", "bank_w2");
+        if (!rc) rc = check_gpu_readable(bank_w1, "smoe_update_on_device", "bank_w1", &h1);
+        if (!rc) rc = check_gpu_readable(bank_w2, "smoe_update_on_device", "bank_w2", &h2);
         if (rc) return rc;
+        L->dev_update_host = h1 || h2;
         L->dev_update_seen[0] = score; L->dev_update_seen[1] = bank_w1; L->dev_update_seen[2] = bank_w2;
     }
     hipStream_t s = as_stream(stream);
@@ -359,7 +364,9 @@ int smoe_update_on_device(smoe_layer_t* L, const float* score, const void* bank_
     if (rc) return rc;
     // The host copies must be current before the device changes the maps again only if somebody
     // reads them; they are marked stale and fetched on demand.
+    L->load_from_host = L->dev_update_host;
     rc = smoe_launch_update_on_device(L, score, bank_w1, bank_w2, s);
+    L->load_from_host = false;
     if (rc) return rc;
     L->maps_stale = true;
     L->maps_stream = s;

@@ -39,6 +39,16 @@ __global__ void set_map_kernel(int32_t* e2s, int32_t* s2e, int32_t* phys, int sl
 constexpr int PACK_COLS = 128;
 constexpr int PACK_LD = PACK_COLS + 8;       // LDS row pitch in elements (16-byte aligned rows)
 
+// Workgroups of a load whose source is pinned host memory (WALK instances: workgroup b takes every
+// gridDim.x-th tile from b on).  The host link bounds it, and reads past what the link needs in flight
+// (about 100 KB) queue up and slow one another: one expert of 768 x 3072 (9.4 MB) takes 208 us with a
+// workgroup per tile (2304 of them, 45 GB/s), 198 with 1024, 176 with 512, 172.5 with 256 and 128, 169 with
+// 64 and with 32 (55.7 GB/s; the copy engine's copy alone takes 174.5 us).  Sources in GPU memory keep a
+// workgroup per tile, for the launch is bound by memory that wants all of them, and instances without the
+// loop, which cost 3 % there (swap of 2 experts and a decode step, twice: 44.2 -> 45.8 us with it).
+constexpr int PACK_HOST_WGS = 64;
+inline unsigned pack_grid(int tiles, bool host) { return (unsigned)(host && tiles > PACK_HOST_WGS ? PACK_HOST_WGS : tiles); }
+
 __device__ __forceinline__ void pack_tile(const uint16_t* __restrict__ src, int R, int N,
                                           uint4* __restrict__ dst, int tile, uint16_t* lds) {
     const int ctiles = (N + PACK_COLS - 1) / PACK_COLS;
@@ -63,18 +73,23 @@ __device__ __forceinline__ void pack_tile(const uint16_t* __restrict__ src, int 
     }
 }
 
-// Loads one expert into a physical slot in a single launch: blocks [0, nblk1) re-lay
-// W1 [d_model, d_ff], the rest W2 [d_ff, d_model]; with map_slot >= 0 the first thread
-// also switches the maps.  The maps are read only by later launches of the stream, which
-// start after this whole launch (weights included) has completed.
+// Loads one expert into a physical slot in a single launch: tiles [0, nblk1) re-lay
+// W1 [d_model, d_ff], those up to nblk W2 [d_ff, d_model]; with map_slot >= 0 the first thread also switches the maps.  The maps are read only by
+// later launches of the stream, which start after this whole launch (weights included) has completed.
+template <bool WALK>
 __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint16_t* __restrict__ w1, const uint16_t* __restrict__ w2,
                                                         int d_model, int d_ff, uint4* __restrict__ dst1,
-                                                        uint4* __restrict__ dst2, int nblk1, int32_t* e2s,
+                                                        uint4* __restrict__ dst2, int nblk1, int nblk, int32_t* e2s,
                                                         int32_t* s2e, int32_t* phys, int map_slot, int expert,
                                                         int old_expert, int p) {
     __shared__ __align__(16) uint16_t lds[16 * PACK_LD];
-    if ((int)blockIdx.x < nblk1) pack_tile(w1, d_model, d_ff, dst1, blockIdx.x, lds);
-    else pack_tile(w2, d_ff, d_model, dst2, blockIdx.x - nblk1, lds);
+    int t = blockIdx.x;                                    // the grid has no more workgroups than there are tiles
+    do {
+        if (t < nblk1) pack_tile(w1, d_model, d_ff, dst1, t, lds);
+        else pack_tile(w2, d_ff, d_model, dst2, t - nblk1, lds);
+        if (WALK) __syncthreads();                         // the tile buffer is reused
+        t += gridDim.x;
+    } while (WALK && t < nblk);
     if (map_slot >= 0 && blockIdx.x == 0 && threadIdx.x == 0) {
         if (old_expert >= 0) e2s[old_expert] = -1;
         e2s[expert] = map_slot;
@@ -142,44 +157,54 @@ __global__ __launch_bounds__(256) void plan_update_kernel(const float* __restric
 }
 
 // The planned loads from a bank [E][d_model][d_ff] / [E][d_ff][d_model] in GPU-readable memory:
-// workgroup b re-lays tile b of every planned expert in turn (the plan is short; most updates
-// change a few slots).
+// workgroup b re-lays tile b (WALK: and every gridDim.x-th one after it) of every planned expert
+// in turn (the plan is short; most updates change a few slots).
+template <bool WALK>
 __global__ __launch_bounds__(256) void pack_planned_kernel(const uint16_t* __restrict__ bank1, const uint16_t* __restrict__ bank2,
                                                            int d_model, int d_ff, uint4* __restrict__ slot1,
-                                                           uint4* __restrict__ slot2, int nblk1, const int32_t* __restrict__ plan,
-                                                           int K, const int32_t* __restrict__ phys) {
+                                                           uint4* __restrict__ slot2, int nblk1, int nblk,
+                                                           const int32_t* __restrict__ plan, int K, const int32_t* __restrict__ phys) {
     __shared__ __align__(16) uint16_t lds[16 * PACK_LD];
     const int n = plan[0];
     const size_t per = (size_t)d_model * d_ff;             // elements per matrix
     for (int j = 0; j < n; ++j) {
         const int slot = plan[1 + j], expert = plan[1 + K + j];
         const size_t dst = (size_t)phys[slot] * (per / 8);   // 16-byte units
-        if ((int)blockIdx.x < nblk1) pack_tile(bank1 + (size_t)expert * per, d_model, d_ff, slot1 + dst, blockIdx.x, lds);
-        else pack_tile(bank2 + (size_t)expert * per, d_ff, d_model, slot2 + dst, blockIdx.x - nblk1, lds);
-        __syncthreads();                                   // the tile buffer is reused by the next expert
+        int t = blockIdx.x;                                // the grid has no more workgroups than there are tiles
+        do {
+            if (t < nblk1) pack_tile(bank1 + (size_t)expert * per, d_model, d_ff, slot1 + dst, t, lds);
+            else pack_tile(bank2 + (size_t)expert * per, d_ff, d_model, slot2 + dst, t - nblk1, lds);
+            __syncthreads();                               // the tile buffer is reused by the next tile or expert
+            t += gridDim.x;
+        } while (WALK && t < nblk);
     }
 }
 
 // fp32: both matrices of one expert into their panels; a thread turns 4 rows x 4 features in registers
-// (16-byte reads and writes); blocks [0, nblk1) take W1.  With map_slot >= 0 the first thread also
-// switches the maps.
+// (16-byte reads and writes); blocks [0, nblk1) of nblk take W1.  With map_slot >= 0 the first
+// thread also switches the maps.
+template <bool WALK>
 __global__ __launch_bounds__(256) void pack_f32_kernel(const float4* __restrict__ w1, const float4* __restrict__ w2, int d_model,
                                                        int d_ff, float4* __restrict__ dst1, float4* __restrict__ dst2, int nblk1,
-                                                       int32_t* e2s, int32_t* s2e, int32_t* phys, int map_slot, int expert,
+                                                       int nblk, int32_t* e2s, int32_t* s2e, int32_t* phys, int map_slot, int expert,
                                                        int old_expert, int p) {
-    const bool first = (int)blockIdx.x < nblk1;
-    const int i = (first ? blockIdx.x : blockIdx.x - nblk1) * 256 + threadIdx.x;
-    const int R4 = (first ? d_model : d_ff) >> 2, n4 = (first ? d_ff : d_model) >> 2;         // units of 4 rows, pieces of 4 features
-    if (i < R4 * n4) {
-        const int u = i / n4, c = i - u * n4, c0 = c & ~15, w = min(16, n4 - c0);             // first piece and width of the panel
-        const float4* src = (first ? w1 : w2) + (size_t)(4 * u) * n4 + c;
-        const float4 a = src[0], b = src[n4], e = src[2 * n4], g = src[3 * n4];
-        float4* dst = (first ? dst1 : dst2) + (size_t)c0 * 4 * R4 + ((size_t)u * w + (c - c0)) * 4;
-        dst[0] = make_float4(a.x, b.x, e.x, g.x);
-        dst[1] = make_float4(a.y, b.y, e.y, g.y);
-        dst[2] = make_float4(a.z, b.z, e.z, g.z);
-        dst[3] = make_float4(a.w, b.w, e.w, g.w);
-    }
+    int blk = blockIdx.x;                                  // the grid has no more workgroups than there are blocks
+    do {
+        const bool first = blk < nblk1;
+        const int i = (first ? blk : blk - nblk1) * 256 + threadIdx.x;
+        const int R4 = (first ? d_model : d_ff) >> 2, n4 = (first ? d_ff : d_model) >> 2;     // units of 4 rows, pieces of 4 features
+        if (i < R4 * n4) {
+            const int u = i / n4, c = i - u * n4, c0 = c & ~15, w = min(16, n4 - c0);         // first piece and width of the panel
+            const float4* src = (first ? w1 : w2) + (size_t)(4 * u) * n4 + c;
+            const float4 a = src[0], b = src[n4], e = src[2 * n4], g = src[3 * n4];
+            float4* dst = (first ? dst1 : dst2) + (size_t)c0 * 4 * R4 + ((size_t)u * w + (c - c0)) * 4;
+            dst[0] = make_float4(a.x, b.x, e.x, g.x);
+            dst[1] = make_float4(a.y, b.y, e.y, g.y);
+            dst[2] = make_float4(a.z, b.z, e.z, g.z);
+            dst[3] = make_float4(a.w, b.w, e.w, g.w);
+        }
+        blk += gridDim.x;
+    } while (WALK && blk < nblk);
     if (map_slot >= 0 && blockIdx.x == 0 && threadIdx.x == 0) {
         if (old_expert >= 0) e2s[old_expert] = -1;
         e2s[expert] = map_slot;
@@ -253,14 +278,16 @@ int smoe_launch_pack_slot(const smoe_layer* L, int slot, const void* w1_src, con
         const int nblk2 = (c.d_ff / 16) * ((c.d_model + PACK_COLS - 1) / PACK_COLS);
         uint4* d1 = (uint4*)((uint16_t*)L->slot_w1 + (size_t)slot * per);
         uint4* d2 = (uint4*)((uint16_t*)L->slot_w2 + (size_t)slot * per);
-        hipLaunchKernelGGL(pack_bf16_kernel, dim3(nblk1 + nblk2), dim3(256), 0, s, (const uint16_t*)w1_src,
-                           (const uint16_t*)w2_src, c.d_model, c.d_ff, d1, d2, nblk1, L->d_expert_to_slot,
-                           L->d_slot_to_expert, L->d_phys, map_slot, expert, old_expert, slot);
+        hipLaunchKernelGGL(L->load_from_host ? pack_bf16_kernel<true> : pack_bf16_kernel<false>,
+                           dim3(pack_grid(nblk1 + nblk2, L->load_from_host)), dim3(256), 0, s,
+                           (const uint16_t*)w1_src, (const uint16_t*)w2_src, c.d_model, c.d_ff, d1, d2, nblk1, nblk1 + nblk2,
+                           L->d_expert_to_slot, L->d_slot_to_expert, L->d_phys, map_slot, expert, old_expert, slot);
     } else {
         const int nblk = (int)((per / 16 + 255) / 256);
-        hipLaunchKernelGGL(pack_f32_kernel, dim3(2 * nblk), dim3(256), 0, s, (const float4*)w1_src, (const float4*)w2_src, c.d_model,
-                           c.d_ff, (float4*)((float*)L->slot_w1 + (size_t)slot * per), (float4*)((float*)L->slot_w2 + (size_t)slot * per),
-                           nblk, L->d_expert_to_slot, L->d_slot_to_expert, L->d_phys, map_slot, expert, old_expert, slot);
+        hipLaunchKernelGGL(L->load_from_host ? pack_f32_kernel<true> : pack_f32_kernel<false>,
+                           dim3(pack_grid(2 * nblk, L->load_from_host)), dim3(256), 0, s,
+                           (const float4*)w1_src, (const float4*)w2_src, c.d_model, c.d_ff,
+                           (float4*)((float*)L->slot_w1 + (size_t)slot * per), (float4*)((float*)L->slot_w2 + (size_t)slot * per), nblk, 2 * nblk, L->d_expert_to_slot, L->d_slot_to_expert, L->d_phys, map_slot, expert, old_expert, slot);
     }
     if (map_done && map_slot >= 0) *map_done = 1;
     return smoe_check_hip(hipGetLastError(), "expert load launch");
@@ -331,8 +358,9 @@ int smoe_launch_update_on_device(const smoe_layer* L, const float* score, const 
                        L->d_slot_to_expert, L->d_plan);
     const int nblk1 = (c.d_model / 16) * ((c.d_ff + PACK_COLS - 1) / PACK_COLS);
     const int nblk2 = (c.d_ff / 16) * ((c.d_model + PACK_COLS - 1) / PACK_COLS);
-    hipLaunchKernelGGL(pack_planned_kernel, dim3(nblk1 + nblk2), dim3(256), 0, s, (const uint16_t*)bank_w1,
-                       (const uint16_t*)bank_w2, c.d_model, c.d_ff, (uint4*)L->slot_w1, (uint4*)L->slot_w2, nblk1,
-                       L->d_plan, c.K, L->d_phys);
+    hipLaunchKernelGGL(L->load_from_host ? pack_planned_kernel<true> : pack_planned_kernel<false>,
+                       dim3(pack_grid(nblk1 + nblk2, L->load_from_host)), dim3(256), 0, s,
+                       (const uint16_t*)bank_w1, (const uint16_t*)bank_w2, c.d_model, c.d_ff, (uint4*)L->slot_w1,
+                       (uint4*)L->slot_w2, nblk1, nblk1 + nblk2, L->d_plan, c.K, L->d_phys);
     return smoe_check_hip(hipGetLastError(), "smoe_update_on_device launch");
 }

@@ -78,6 +78,8 @@ struct smoe_layer {
     bool maps_stale = false;
     hipStream_t maps_stream = nullptr;
     const void* dev_update_seen[3] = {nullptr, nullptr, nullptr};   // pointers smoe_update_on_device has checked
+    bool dev_update_host = false;            // ... and whether a bank among them is pinned host memory
+    bool load_from_host = false;             // set around a load's launch: its source is pinned host memory
     void* d_router_split = nullptr;          // bf16 path: router weights in matrix-operand order
     bool router_split_done = false;          // made by the first smoe_route after a bind
 
