@@ -227,7 +227,9 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
 #pragma unroll
                     for (int h = 0; h < 2; ++h) w[i][b][h] = w0[b][(size_t)(max(min(g0 + i, n - 1), 0) * 2 + h) * 64];
         };
-        fetch(wA, 0);                                      // on their way while the tokens are staged
+        // A slice may have no step of this chunk (n = 0): its w0 is then one step past the expert block, so
+        // nothing is fetched and nothing multiplied (whatever lies there times a zero operand need not be zero).
+        if (n > 0) fetch(wA, 0);                           // on their way while the tokens are staged
         if (k0) __syncthreads();                           // the previous chunk has been used up
         const int cpr = kc >> 3;                           // 16-byte pieces per row
         constexpr int PPT = 8;                             // pieces fetched together
@@ -307,7 +309,7 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
             consume(wA, g0);
             __builtin_amdgcn_sched_barrier(0);
             consume(wB, g0 + G);
-        } else {
+        } else if (n > 0) {
             consume(wA, g0);
         }
     }
