@@ -162,7 +162,7 @@ __device__ __forceinline__ void smoe_route_finish(const int block, const smoe_ro
             float ss = 0.f;
 #pragma unroll
             for (int q = 0; q < 2 * NS; ++q) ss += sqp[q * NTOK + t];
-            const int sv = rb & 255;
+            const int sv = rb == 0x7fffffff ? 0 : rb & 255;   // a token whose logits are all NaN: slot 0, a NaN gate
             a.orig_expert[tok] = bi;
             a.orig_gate[tok] = 1.0f / z;
             a.slot[tok] = sv;
