@@ -103,14 +103,15 @@ def _ptr(t):
 
 
 # The handle of the current stream without building a torch.cuda.Stream object for it: 0.2 us instead
-# of 2.7 us, on calls whose whole host side is 2 us.
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# of 2.7 us, on calls whose whole host side is 2 us.  A torch built without GPU support lacks both names:
+# the module still imports there, for the host-only calls.
+_raw_stream, _device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
 
 
 def _stream(stream=None):
     if stream is not None:
         return stream.cuda_stream
-    if not torch.cuda.is_initialized():
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_device())
 

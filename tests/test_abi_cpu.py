@@ -196,3 +196,16 @@ def test_profile_bookkeeping_on_host():
     us = C.c_float()
     assert b._lib.smoe_profile_end(h, None, C.byref(us)) == b.SMOE_ESTATE
     b.smoe_destroy(h)
+
+
+def test_binding_imports_without_gpu_support_in_torch():
+    """A torch without the private stream names still imports the binding and serves the host-only calls."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    delattr(torch._C, n) if hasattr(torch._C, n) else None\n"
+            "from paper_2308_15030_amd import binding as b\n"
+            "assert b.smoe_profile_memory(8, 2, 64, 256, 32, b.SMOE_F32)['expert_bytes'] == 2 * 64 * 256 * 4\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
