@@ -77,8 +77,8 @@ smoe_ws_layout smoe_ws_plan(const smoe_config& c) {
     return w;
 }
 
-// Slot bytes that passed through the GPU's memory in this process so far: every layer's own at its
-// creation and at each pass over its slots (see smoe_weights_outgrow_cache).
+// Slot bytes that passed through the GPU's memory in this process so far: every expert loaded by the
+// host's calls, and a layer's own at each pass over its slots (see smoe_weights_outgrow_cache).
 static std::atomic<uint64_t> g_slot_traffic{0};
 static uint64_t layer_slot_bytes(const smoe_config& c) {
     return 2ull * (c.K + c.spare_slots) * c.d_model * c.d_ff * smoe_elem_size(c.dtype);
@@ -87,6 +87,13 @@ static uint64_t layer_slot_bytes(const smoe_config& c) {
 static void note_slot_pass(smoe_layer* L) {
     const uint64_t own = layer_slot_bytes(L->cfg);
     L->slot_traffic_seen = g_slot_traffic.fetch_add(own, std::memory_order_relaxed) + own;
+}
+
+// An expert written to one of L's slots: traffic for the other layers, L's own bytes are counted as such.
+static void note_slot_load(smoe_layer* L) {
+    const uint64_t one = 2ull * L->cfg.d_model * L->cfg.d_ff * smoe_elem_size(L->cfg.dtype);
+    g_slot_traffic.fetch_add(one, std::memory_order_relaxed);
+    L->slot_traffic_seen += one;
 }
 
 bool smoe_weights_outgrow_cache(const smoe_layer* L) {
@@ -149,7 +156,7 @@ int smoe_create(const smoe_config* cfg, smoe_layer_t** out) {
         int a = -1, b = -1;
         if (sscanf(env, "%d,%d", &a, &b) == 2 && a >= 0 && b >= 0) { L->ffn_variant[0] = a; L->ffn_variant[1] = b; }
     }
-    note_slot_pass(L);
+    L->slot_traffic_seen = g_slot_traffic.load(std::memory_order_relaxed);   // no byte has moved yet
     *out = L;
     return SMOE_OK;
 }
@@ -287,6 +294,7 @@ int smoe_set_resident(smoe_layer_t* L, int slot, int expert, const void* w1_src,
     int rc = smoe_launch_pack_slot(L, L->phys[slot], w1_src, w2_src, s, slot, expert, old, &map_done);
     L->load_from_host = false;
     if (rc) return rc;
+    note_slot_load(L);
     if (!map_done) {
         rc = smoe_launch_set_map(L, slot, expert, old, L->phys[slot], s);
         if (rc) return rc;
@@ -496,6 +504,7 @@ int smoe_update_tick(smoe_layer_t* L, const void* bank_w1, const void* bank_w2, 
             src2 = s1 + per;
         }
         if (!rc) rc = smoe_launch_pack_slot(L, st.phys, src1, src2, ls);
+        if (!rc) note_slot_load(L);
         if (!rc) rc = smoe_check_hip(hipEventRecord(st.done, ls), "smoe_update_tick: load event");
         if (rc) {
             L->event_pool.push_back(st.done);

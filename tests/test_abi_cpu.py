@@ -209,3 +209,14 @@ def test_binding_imports_without_gpu_support_in_torch():
             "assert b.smoe_profile_memory(8, 2, 64, 256, 32, b.SMOE_F32)['expert_bytes'] == 2 * 64 * 256 * 4\n")
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+def test_size_queries_do_not_count_as_slot_traffic():
+    """A layer whose slots fit the cache keeps its plain weight loads when other layers are only created or sized."""
+    h = b.smoe_create(64, 16, 768, 3072, 32, b.SMOE_BF16)
+    plain = b.smoe_describe_ffn(h, 8)
+    assert "_stream" not in plain
+    b.smoe_profile_memory(128, 128, 1024, 4096, 32, b.SMOE_BF16)       # 2 GiB of slots, none of them touched
+    other = b.smoe_create(128, 128, 1024, 4096, 32, b.SMOE_BF16)
+    assert b.smoe_describe_ffn(h, 8) == plain
+    b.smoe_destroy(other); b.smoe_destroy(h)
