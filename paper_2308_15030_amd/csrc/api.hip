@@ -77,28 +77,48 @@ smoe_ws_layout smoe_ws_plan(const smoe_config& c) {
     return w;
 }
 
-// Slot bytes that passed through the GPU's memory in this process so far: every expert loaded by the
-// host's calls, and a layer's own at each pass over its slots (see smoe_weights_outgrow_cache).
-static std::atomic<uint64_t> g_slot_traffic{0};
+// Slot bytes that passed through each GPU's memory in this process so far: every expert loaded by the
+// host's calls, and a layer's own at each pass over its slots (see smoe_weights_outgrow_cache).  Each GPU
+// has a cache of its own, so the traffic of the others does not count; a layer's calls are made with its
+// GPU as the current device.
+constexpr int TRAFFIC_DEVICES = 64;
+static std::atomic<uint64_t> g_slot_traffic[TRAFFIC_DEVICES];
 static uint64_t layer_slot_bytes(const smoe_config& c) {
     return 2ull * (c.K + c.spare_slots) * c.d_model * c.d_ff * smoe_elem_size(c.dtype);
 }
 
+static int traffic_device() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return dev % TRAFFIC_DEVICES;
+}
+
 static void note_slot_pass(smoe_layer* L) {
     const uint64_t own = layer_slot_bytes(L->cfg);
-    L->slot_traffic_seen = g_slot_traffic.fetch_add(own, std::memory_order_relaxed) + own;
+    L->slot_device = traffic_device();
+    L->slot_traffic_seen = g_slot_traffic[L->slot_device].fetch_add(own, std::memory_order_relaxed) + own;
 }
 
 // An expert written to one of L's slots: traffic for the other layers, L's own bytes are counted as such.
 static void note_slot_load(smoe_layer* L) {
     const uint64_t one = 2ull * L->cfg.d_model * L->cfg.d_ff * smoe_elem_size(L->cfg.dtype);
-    g_slot_traffic.fetch_add(one, std::memory_order_relaxed);
-    L->slot_traffic_seen += one;
+    const int dev = traffic_device();
+    const uint64_t now = g_slot_traffic[dev].fetch_add(one, std::memory_order_relaxed) + one;
+    if (L->slot_device == dev) {
+        L->slot_traffic_seen += one;
+    } else {                                               // the layer's first load on this GPU
+        L->slot_device = dev;
+        L->slot_traffic_seen = now;
+    }
 }
 
 bool smoe_weights_outgrow_cache(const smoe_layer* L) {
     constexpr uint64_t kCacheable = 192ull << 20;          // three quarters of the 256 MB Infinity Cache
-    const uint64_t since = g_slot_traffic.load(std::memory_order_relaxed) - L->slot_traffic_seen;
+    const int dev = L->slot_device;                        // -1: nothing of the layer has been loaded yet
+    const uint64_t since = dev < 0 ? 0 : g_slot_traffic[dev].load(std::memory_order_relaxed) - L->slot_traffic_seen;
     return since + layer_slot_bytes(L->cfg) > kCacheable;
 }
 
@@ -156,7 +176,6 @@ int smoe_create(const smoe_config* cfg, smoe_layer_t** out) {
         int a = -1, b = -1;
         if (sscanf(env, "%d,%d", &a, &b) == 2 && a >= 0 && b >= 0) { L->ffn_variant[0] = a; L->ffn_variant[1] = b; }
     }
-    L->slot_traffic_seen = g_slot_traffic.load(std::memory_order_relaxed);   // no byte has moved yet
     *out = L;
     return SMOE_OK;
 }

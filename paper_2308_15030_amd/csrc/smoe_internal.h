@@ -87,7 +87,8 @@ struct smoe_layer {
     hipEvent_t bracket[2] = {nullptr, nullptr};                     // smoe_profile_begin / _end
     bool bracket_open = false;
 
-    uint64_t slot_traffic_seen = 0;          // process-wide slot traffic after this layer's last pass or load (or at its creation)
+    int slot_device = -1;                    // GPU of the layer's last load or pass, -1 before the first
+    uint64_t slot_traffic_seen = 0;          // that GPU's slot traffic after the last pass, the layer's own loads since added
 
     // load-on-miss baseline: when each slot's expert was last some token's own choice
     std::vector<int64_t> last_use;
@@ -130,10 +131,11 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
                              int accumulate, int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s,
                              hipEvent_t e0, hipEvent_t e1);
 // True when the layer's expert slots (both matrices, spare slots included) and the slots of the other
-// layers that were loaded or passed over since its own last pass are more than the 256 MB Infinity
-// Cache can hold: its weights come from HBM then, and the small batch's kernels mark their loads
-// non-temporal.  Measured with 16 slots of 768 x 3072: one layer stepped alone (151 MB, stays cached
-// from step to step) is 15 % slower with such loads, six layers in turn (906 MB) are 7 % faster.
+// layers on its GPU that were loaded or passed over since its own last pass are more than the 256 MB
+// Infinity Cache can hold: its weights come from HBM then, and the small batch's kernels mark their loads
+// non-temporal.  Measured with 16 slots of 768 x 3072: one layer stepped alone (151 MB, stays cached from
+// step to step) is 15 % slower with such loads, six layers in turn (906 MB) are 7 % faster.  A captured
+// graph keeps the choice of its capture; the results are the same bits either way.
 bool smoe_weights_outgrow_cache(const smoe_layer* L);
 // plain read of the first K slots of slot_w1 (which = 0) or slot_w2 (1): see smoe_profile_stream_read
 int smoe_launch_stream_read(const smoe_layer* L, int which, hipStream_t s);
