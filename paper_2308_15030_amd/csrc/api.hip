@@ -77,10 +77,10 @@ smoe_ws_layout smoe_ws_plan(const smoe_config& c) {
     return w;
 }
 
-// Slot bytes that passed through each GPU's memory in this process so far: every expert loaded by the
-// host's calls, and a layer's own at each pass over its slots (see smoe_weights_outgrow_cache).  Each GPU
-// has a cache of its own, so the traffic of the others does not count; a layer's calls are made with its
-// GPU as the current device.
+// Slot bytes that passed through each GPU's memory in this process so far: a layer's own when it is bound
+// there and at each pass over its slots, and every expert that replaces another (see
+// smoe_weights_outgrow_cache).  Each GPU has a cache of its own, so the traffic of the others does not
+// count; a layer's calls are made with its GPU as the current device.
 constexpr int TRAFFIC_DEVICES = 64;
 static std::atomic<uint64_t> g_slot_traffic[TRAFFIC_DEVICES];
 static uint64_t layer_slot_bytes(const smoe_config& c) {
@@ -102,22 +102,17 @@ static void note_slot_pass(smoe_layer* L) {
     L->slot_traffic_seen = g_slot_traffic[L->slot_device].fetch_add(own, std::memory_order_relaxed) + own;
 }
 
-// An expert written to one of L's slots: traffic for the other layers, L's own bytes are counted as such.
+// A slot of L changes hands: traffic for the other layers, L's own bytes are counted as such.
 static void note_slot_load(smoe_layer* L) {
     const uint64_t one = 2ull * L->cfg.d_model * L->cfg.d_ff * smoe_elem_size(L->cfg.dtype);
     const int dev = traffic_device();
-    const uint64_t now = g_slot_traffic[dev].fetch_add(one, std::memory_order_relaxed) + one;
-    if (L->slot_device == dev) {
-        L->slot_traffic_seen += one;
-    } else {                                               // the layer's first load on this GPU
-        L->slot_device = dev;
-        L->slot_traffic_seen = now;
-    }
+    g_slot_traffic[dev].fetch_add(one, std::memory_order_relaxed);
+    if (L->slot_device == dev) L->slot_traffic_seen += one;
 }
 
 bool smoe_weights_outgrow_cache(const smoe_layer* L) {
     constexpr uint64_t kCacheable = 192ull << 20;          // three quarters of the 256 MB Infinity Cache
-    const int dev = L->slot_device;                        // -1: nothing of the layer has been loaded yet
+    const int dev = L->slot_device;                        // -1: not bound yet
     const uint64_t since = dev < 0 ? 0 : g_slot_traffic[dev].load(std::memory_order_relaxed) - L->slot_traffic_seen;
     return since + layer_slot_bytes(L->cfg) > kCacheable;
 }
@@ -246,6 +241,7 @@ int smoe_bind(smoe_layer_t* L, const float* router_w, void* slot_w1, void* slot_
     L->staged.clear();
     L->slots_set = 0;
     L->bound = true;
+    if (L->slot_device != traffic_device()) note_slot_pass(L);   // binding again where it was moves nothing
     return SMOE_OK;
 }
 
@@ -313,7 +309,7 @@ int smoe_set_resident(smoe_layer_t* L, int slot, int expert, const void* w1_src,
     int rc = smoe_launch_pack_slot(L, L->phys[slot], w1_src, w2_src, s, slot, expert, old, &map_done);
     L->load_from_host = false;
     if (rc) return rc;
-    note_slot_load(L);
+    if (old >= 0) note_slot_load(L);
     if (!map_done) {
         rc = smoe_launch_set_map(L, slot, expert, old, L->phys[slot], s);
         if (rc) return rc;
