@@ -1,5 +1,5 @@
 // smoe_forward on a small batch (bf16, at most SMALL_T tokens whose rows fit the LDS of a compute
-// unit together): the whole layer in two launches.
+// unit together): the whole layer in two launches, or three where most slots stay empty.
 //
 // With few tokens the layer is bound by reading the slots' weights once, so nothing that stands
 // between the kernel's start and its weight stream is tolerated: no sort (every slot's workgroups
@@ -13,8 +13,12 @@
 //   second launch  one workgroup ranks the tokens and adds the importance sums (it needs only what
 //                  the router left); the others compute the second product of the slots that got
 //                  tokens, for those tokens, with the gate and the residual.
+//
+// Where the empty slots' first matrices cost more than the router (see sparse), the router is launched first
+// and neither product reads a weight of a slot without a token.
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "route_mfma.h"
@@ -31,15 +35,20 @@ constexpr int LDS_LIMIT = 160 * 1024 - 2048;               // dynamic LDS; the r
 // elements: conflict-free 16-byte reads), so the vector-memory pipe carries nothing but 1-KiB weight
 // loads, 16 of them in flight per wave.  NBF: 32-token blocks the instance holds accumulators for.
 // STREAM: the weight loads are marked non-temporal (see smoe_weights_outgrow_cache).
+// served: the tokens' slots if the router has run already (then only slots with a token are computed), else NULL.
 template <int NBF, bool STREAM>
 __device__ __forceinline__ void dense_first_all(const uint16_t* __restrict__ x, const uint4* __restrict__ Wp, int T,
                                                 uint16_t* __restrict__ h, int R, int N, const int32_t* __restrict__ phys,
-                                                int block, int fbw, uint16_t* xs) {
+                                                const int32_t* __restrict__ served, int block, int fbw, uint16_t* xs) {
     constexpr int G = 8;
     const int nfb = N >> 5, nrb = R >> 4, ldx = R + 8, nb = (T + 31) >> 5;
     const int ftiles = (nfb + fbw - 1) / fbw;
     const int slot = block / ftiles, ftile = block - slot * ftiles;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    if (served) {
+        const bool own = served[min(lane, T - 1)] == slot || (NBF > 2 && served[min(lane + 64, T - 1)] == slot);
+        if (!__ballot(own)) return;                        // uniform over the workgroup
+    }
     const int fb = ftile * fbw + wave;
     const bool streams = wave < fbw && fb < nfb;           // the other waves help with the staging only
     const uint4* wp = Wp + ((size_t)(phys ? phys[slot] : slot) * nfb + min(fb, nfb - 1)) * nrb * 64 + lane;
@@ -148,7 +157,7 @@ __device__ __forceinline__ void decode_first_body(const smoe_route_args& ra, con
     extern __shared__ __align__(16) float smem[];
     const int routers = (ra.T + SMOE_RT - 1) / SMOE_RT;
     if ((int)blockIdx.x < routers) smoe_route_mfma_body<NEB, 1>(blockIdx.x, ra, smem);
-    else dense_first_all<NBF, STREAM>((const uint16_t*)ra.x, W1, ra.T, h, ra.d, d_ff, phys, blockIdx.x - routers, fbw, (uint16_t*)smem);
+    else dense_first_all<NBF, STREAM>((const uint16_t*)ra.x, W1, ra.T, h, ra.d, d_ff, phys, nullptr, blockIdx.x - routers, fbw, (uint16_t*)smem);
 }
 
 // Two kernels with one body: the second streams its weights past the caches.
@@ -163,6 +172,15 @@ __global__ __launch_bounds__(512) void decode_first_stream_kernel(const smoe_rou
                                                                   uint16_t* __restrict__ h, int d_ff, const int32_t* __restrict__ phys,
                                                                   int fbw) {
     decode_first_body<NEB, NBF, true>(ra, W1, h, d_ff, phys, fbw);
+}
+
+// The same product behind a router launch of its own, for the slots that got tokens.
+template <int NBF, bool STREAM>
+__global__ __launch_bounds__(512) void dense_first_kernel(const uint16_t* __restrict__ x, const uint4* __restrict__ W1, int T,
+                                                          uint16_t* __restrict__ h, int d, int d_ff, const int32_t* __restrict__ phys,
+                                                          const int32_t* __restrict__ slot, int fbw) {
+    extern __shared__ __align__(16) float smem[];
+    dense_first_all<NBF, STREAM>(x, W1, T, h, d, d_ff, phys, slot, blockIdx.x, fbw, (uint16_t*)smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -255,7 +273,9 @@ struct second_args {
     smoe_step_tail tail;
 };
 
-template <int MAXNB, bool STREAM>
+// SPARSE: no weights are asked for before the slot ids are there (an instance of its own: with a branch around
+// the early loads the wait for the ids becomes a wait for everything, 0.8 us per layer).
+template <int MAXNB, bool STREAM, bool SPARSE>
 __device__ __forceinline__ void decode_second_body(const second_args& a) {
     constexpr int KSPLIT = 4;
     __shared__ __align__(16) float red[(KSPLIT - 1) * MAXNB * 16 * 64];
@@ -285,12 +305,13 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
     const int id0 = a.slot[min(lane, a.T - 1)], id1 = MAXNB > 1 ? a.slot[min(lane + 64, a.T - 1)] : 0;
     __builtin_amdgcn_sched_barrier(0);
     uint4 w0[G1];
-    fetch_w(w0, kb_lo);
+    if (!SPARSE) fetch_w(w0, kb_lo);
     __builtin_amdgcn_sched_barrier(0);
     const bool own0 = lane < a.T && id0 == slot, own1 = MAXNB > 1 && lane + 64 < a.T && id1 == slot;
     const unsigned long long m0 = __ballot(own0), m1 = MAXNB > 1 ? __ballot(own1) : 0ull;
     const int n0 = __popcll(m0), n = n0 + __popcll(m1);
     if (n == 0) return;                                    // nothing routed to this slot (uniform over the workgroup)
+    if (SPARSE) fetch_w(w0, kb_lo);
     const unsigned long long below = (1ull << lane) - 1ull;
     if (own0) s_tok[part][__popcll(m0 & below)] = lane;
     if (own1) s_tok[part][n0 + __popcll(m1 & below)] = lane + 64;
@@ -411,10 +432,13 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
 }
 
 template <int MAXNB>
-__global__ __launch_bounds__(256, 2) void decode_second_kernel(const second_args a) { decode_second_body<MAXNB, false>(a); }
+__global__ __launch_bounds__(256, 2) void decode_second_kernel(const second_args a) { decode_second_body<MAXNB, false, false>(a); }
 
 template <int MAXNB>
-__global__ __launch_bounds__(256, 2) void decode_second_stream_kernel(const second_args a) { decode_second_body<MAXNB, true>(a); }
+__global__ __launch_bounds__(256, 2) void decode_second_stream_kernel(const second_args a) { decode_second_body<MAXNB, true, false>(a); }
+
+template <int MAXNB, bool STREAM>
+__global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<MAXNB, STREAM, true>(a); }
 
 // 32-expert blocks rounded up to an instance of the router
 int router_instance(int E) { return E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8; }
@@ -428,20 +452,39 @@ size_t first_lds(const smoe_config& c, int T) {
     return std::max(router, (size_t)T * (d + 8) * 2);
 }
 
+// Slots with a token, if T tokens are spread evenly.
+double served_slots(const smoe_config& c, int T) { return c.K * (1.0 - std::pow(1.0 - 1.0 / c.K, T)); }
+
 // Feature blocks per workgroup of the first product: as many of the 8 waves as leave at least
-// three workgroups per four compute units.
-int first_fbw(const smoe_config& c) {
+// three workgroups with work per four compute units.
+int first_fbw(const smoe_config& c, double slots) {
     const int nfb = c.d_ff >> 5;
     int fbw = 8;
-    while (fbw > 1 && c.K * ((nfb + fbw - 1) / fbw) < 192) fbw >>= 1;
+    while (fbw > 1 && slots * ((nfb + fbw - 1) / fbw) < 192) fbw >>= 1;
     return fbw;
+}
+
+// True when the router gets a launch of its own in front of the first product, which then reads the weights
+// of the slots with a token only.  Beside the router every slot's first matrix is read, so what that costs is
+// the matrices of the slots that stay empty, at the 6 TB/s they stream with; what it saves is the router's
+// launch, 8 us up to 64 experts and 12 us above.  The line lies where the two meet, at 48 and 72 MB.  Measured
+// per layer in stacks of 0.7 GB and more (beside the router / launch of its own, MB for nothing):
+//   768 x 3072, E = 64    K = 16 T = 1 24 / 20 us (71 MB), T = 16 29 / 34 us (27 MB); K = 64 T = 1 61 / 23 us
+//                         (297 MB), T = 33 88 / 66 us (180 MB); K = 32 T = 32 48 / 48 us (55 MB)
+//   768 x 3072, E = 128   K = 32 T = 16 44 / 40 us (91 MB), T = 32 51 / 55 us (55 MB); K = 128 T = 1 114 / 31 us
+//                         (599 MB), T = 96 200 / 163 us (284 MB)
+//   1024 x 4096, E = 128  K = 32 T = 1 62 / 29 us (260 MB), T = 64 108 / 108 us (35 MB)
+//   512 x 2048, E = 200   K = 100 T = 64 74 / 64 us (110 MB); at 256 x 1024 T = 1 21 / 23 us (52 MB)
+bool sparse(const smoe_config& c, int T) {
+    const double unused = (c.K - served_slots(c, T)) * 2.0 * c.d_model * c.d_ff;
+    return unused > (c.E <= 64 ? 48e6 : 72e6);
 }
 
 template <int NEB, int NBF>
 int launch_first(const smoe_layer* L, const smoe_route_args& ra, bool stream, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const smoe_config& c = L->cfg;
     const size_t lds = first_lds(c, ra.T);
-    const int fbw = first_fbw(c), ftiles = ((c.d_ff >> 5) + fbw - 1) / fbw;
+    const int fbw = first_fbw(c, c.K), ftiles = ((c.d_ff >> 5) + fbw - 1) / fbw;
     const dim3 grid(c.K * ftiles + (ra.T + SMOE_RT - 1) / SMOE_RT);
     const int32_t* phys = c.spare_slots > 0 ? L->d_phys : nullptr;
     auto kern = stream ? decode_first_stream_kernel<NEB, NBF> : decode_first_kernel<NEB, NBF>;
@@ -460,6 +503,26 @@ int launch_first_nbf(const smoe_layer* L, const smoe_route_args& ra, bool stream
     if (ra.T <= 32) return launch_first<NEB, 1>(L, ra, stream, s, e0, e1);
     if (ra.T <= 64) return launch_first<NEB, 2>(L, ra, stream, s, e0, e1);
     return launch_first<NEB, 4>(L, ra, stream, s, e0, e1);
+}
+
+// The first product by itself (see dense_first_kernel).
+template <int NBF>
+int launch_first_served(const smoe_layer* L, const smoe_route_args& ra, bool stream, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const smoe_config& c = L->cfg;
+    const size_t lds = (size_t)ra.T * (c.d_model + 8) * 2;
+    const int fbw = first_fbw(c, served_slots(c, ra.T)), ftiles = ((c.d_ff >> 5) + fbw - 1) / fbw;
+    const dim3 grid(c.K * ftiles);
+    const int32_t* phys = c.spare_slots > 0 ? L->d_phys : nullptr;
+    auto kern = stream ? dense_first_kernel<NBF, true> : dense_first_kernel<NBF, false>;
+    static smoe_lds_raised raised[2];
+    if (int rc = raised[stream].ensure((const void*)kern, lds, LDS_LIMIT)) return rc;
+    if (e0 && e1)
+        hipExtLaunchKernelGGL(kern, grid, dim3(512), lds, s, e0, e1, 0, (const uint16_t*)ra.x, (const uint4*)L->slot_w1, ra.T,
+                              (uint16_t*)L->d_hidden, c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
+    else
+        hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, (const uint16_t*)ra.x, (const uint4*)L->slot_w1, ra.T, (uint16_t*)L->d_hidden,
+                           c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
+    return smoe_check_hip(hipGetLastError(), "smoe_forward: first product launch");
 }
 
 }  // namespace
@@ -490,6 +553,12 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
     const smoe_route_args ra{x, (const uint4*)L->d_router_split, L->router_w, L->d_expert_to_slot, T, c.d_model, c.E, c.gate_mode,
                              orig_expert, orig_gate, slot, gate, xnorm, nullptr, c.K};
     const bool stream = smoe_weights_outgrow_cache(L);
+    if (sparse(c, T)) {
+        if (int rc = smoe_launch_route(L, x, T, orig_expert, orig_gate, slot, gate, xnorm, nullptr, s)) return rc;
+        if (T <= 32) return launch_first_served<1>(L, ra, stream, s, e0, e1);
+        if (T <= 64) return launch_first_served<2>(L, ra, stream, s, e0, e1);
+        return launch_first_served<4>(L, ra, stream, s, e0, e1);
+    }
     switch (router_instance(c.E)) {
         case 1: return launch_first_nbf<1>(L, ra, stream, s, e0, e1);
         case 2: return launch_first_nbf<2>(L, ra, stream, s, e0, e1);
@@ -507,6 +576,9 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
     const bool stream = smoe_weights_outgrow_cache(L);
     auto kern = T <= 32 ? (stream ? decode_second_stream_kernel<1> : decode_second_kernel<1>)
                         : (stream ? decode_second_stream_kernel<2> : decode_second_kernel<2>);
+    if (sparse(c, T))
+        kern = T <= 32 ? (stream ? dense_second_kernel<1, true> : dense_second_kernel<1, false>)
+                       : (stream ? dense_second_kernel<2, true> : dense_second_kernel<2, false>);
     smoe_launch_timed(kern, grid, dim3(256), s, L->prof_ev[2], L->prof_ev[3], a);
     L->tail = smoe_step_tail{};                            // the caller's pointers are not kept
     return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");
@@ -514,6 +586,9 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
 
 std::string smoe_describe_decode(const smoe_layer* L, int T, bool first) {
     const std::string st = smoe_weights_outgrow_cache(L) ? "_stream" : "";
+    if (sparse(L->cfg, T))
+        return std::string(first ? "dense_first_kernel<" : "dense_second_kernel<") +
+               (T <= 32 ? "1, " : !first || T <= 64 ? "2, " : "4, ") + (st.empty() ? "false>" : "true>");
     if (!first) return "decode_second" + st + "_kernel<" + (T <= 32 ? "1>" : "2>");
     return "decode_first" + st + "_kernel<" + std::to_string(router_instance(L->cfg.E)) + ", " + (T <= 32 ? "1>" : T <= 64 ? "2>" : "4>");
 }
