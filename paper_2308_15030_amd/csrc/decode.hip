@@ -27,7 +27,7 @@ namespace {
 
 constexpr int SMALL_T = SMOE_SMALL_T;                      // the token lists below are two 64-lane ballots long
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-constexpr int LDS_LIMIT = 160 * 1024 - 2048;               // dynamic LDS; the rest covers the static tables
+constexpr int LDS_LIMIT = SMOE_SMALL_LDS;
 
 // ---------------------------------------------------------------------------
 // First product for every slot and every token.  fbw waves of the workgroup own one 32-feature

@@ -70,7 +70,7 @@ struct smoe_layer {
     int32_t* d_plan = nullptr;               // [1 + 2K] smoe_update_on_device: number of loads, their slots, their experts
     int32_t* d_sort_hist = nullptr;          // [sort blocks, K]
     int32_t* d_hist32 = nullptr;             // fused path: [ceil(max_tokens/32), K] from the router
-    void* d_hidden = nullptr;                // [max_tokens, d_ff] activations of the FFN
+    void* d_hidden = nullptr;                // activations of the FFN: [rows, d_ff], rows as in smoe_ws_plan
     float* d_norm_partial = nullptr;         // smoe_expert_norm: [E][64] partial sums of squares
     bool ws_ready = false;                   // device maps and counters initialised since the bind
     // smoe_update_on_device changes the device maps without the host: the host copies are then
@@ -104,12 +104,15 @@ int smoe_fail(int code, const char* fmt, ...);
 int smoe_check_hip(hipError_t e, const char* what);
 
 inline size_t smoe_elem_size(int dtype) { return dtype == SMOE_BF16 ? 2 : 4; }
-// smoe_forward takes at most this many tokens through its two-launch path (decode.hip), which keeps the
-// hidden activations of every slot for every token of the batch
+// smoe_forward takes at most this many tokens through its small-batch path (decode.hip), and at most those
+// whose rows (8 elements of padding each) fit the dynamic LDS of a compute unit; the path keeps the hidden
+// activations of every slot for every token of the batch, in blocks of 32 tokens.
 constexpr int SMOE_SMALL_T = 128;
+constexpr int SMOE_SMALL_LDS = 160 * 1024 - 2048;          // the rest covers the static tables
 inline size_t smoe_small_batch_rows(const smoe_config& c) {
+    const int fit = SMOE_SMALL_LDS / (2 * (c.d_model + 8));
     const int t = c.max_tokens < SMOE_SMALL_T ? c.max_tokens : SMOE_SMALL_T;
-    return c.dtype == SMOE_BF16 ? (size_t)c.K * ((t + 31) / 32 * 32) : 0;
+    return c.dtype == SMOE_BF16 ? (size_t)c.K * (((t < fit ? t : fit) + 31) / 32 * 32) : 0;
 }
 inline int smoe_sort_blocks(int T) { return (T + SMOE_SORT_BLOCK - 1) / SMOE_SORT_BLOCK; }
 

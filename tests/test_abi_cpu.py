@@ -220,3 +220,14 @@ def test_size_queries_do_not_count_as_slot_traffic():
     other = b.smoe_create(128, 128, 1024, 4096, 32, b.SMOE_BF16)
     assert b.smoe_describe_ffn(h, 8) == plain
     b.smoe_destroy(other); b.smoe_destroy(h)
+
+
+@pytest.mark.parametrize("d", [256, 1024, 2560, 4096])
+def test_workspace_holds_no_rows_the_small_batch_path_cannot_take(d):
+    """Hidden activations: K slots times the tokens (in blocks of 32) whose rows fit 158 KiB of LDS, or the sorted path's rows."""
+    K, f, T = 64, 1024, 128
+    fit = min(T, 158 * 1024 // (2 * (d + 8)))
+    rows = max(T + 32 * K, K * ((fit + 31) // 32 * 32))
+    got = b.smoe_profile_memory(128, K, d, f, T, b.SMOE_BF16)["workspace_bytes"]
+    rest = 128 * d * 4 + 128 * 64 * 4                                 # packed router, norm partial sums
+    assert rows * f * 2 + rest <= got <= rows * f * 2 + rest + 64 * 1024
