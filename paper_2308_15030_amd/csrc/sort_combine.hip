@@ -296,25 +296,32 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restric
 }
 
 // smoe_permute without a launch for the ranking and one for the rows: workgroup (b, part) ranks the 64
-// tokens of block b and moves 16 of them.  Counting is by ballots: the lanes of a wave that hold the
+// tokens of block b and moves its share of them.  Counting is by ballots: the lanes of a wave that hold the
 // same slot find each other, the lowest of them adds their number to the wave's own table, so nothing is
 // contended, and the position of a token -- slot offset + tokens of its slot in front of it -- is that
 // of the sorting kernels above.
 //   T <= PERM_ONE_MAX    every workgroup looks at all the slot ids (hist == nullptr): one launch
-//   T <= PERM_TWO_MAX    at those of its 1024-token sort block, and takes the rest from the blocks'
+//   beyond               at those of its 1024-token sort block, and takes the rest from the blocks'
 //                        histograms: two launches
-// and beyond, where adding up the histograms in every workgroup costs more than it saves, the three
-// launches above.  Measured (K = 16, rows of 1.5 KB): T = 64 7.2 -> 4.4 us, T = 2048 10.1 -> 7.9 us.
-constexpr int PERM_ONE_MAX = 2048, PERM_TWO_MAX = 65536;
+// Past PERM_TWO_MAX tokens or PERM_TWO_BYTES of rows, where adding up the histograms in every workgroup or
+// moving rows with so few waves costs more than a launch, the three launches above.  Measured with K = 4, 128
+// and 32 (fused / three launches, us): 65536 rows of 512 bytes 28, 45, 45 / 23, 39, 36; 32768 of 2 KB 29, 36,
+// 34 / 29, 41, 37; 32768 of 4 KB 54, 61, 60 / 47, 60, 55; 16384 of 8 KB 51, 55, 54 / 46, 56, 52; 8192 of 8 KB
+// 27, 30, 29 / 27, 36, 30.
+// A block's rows are moved by four workgroups, rows of 4 KB and more by sixteen up to PERM_WIDE_MAX tokens,
+// while that fills the chip (T = 2000 of 8 KB 19.0 -> 9.9 us, T = 8192 of 4 KB 17.8 -> 16.6, T = 16384 of 4 KB
+// 27.7 -> 28.4).  K = 16, rows of 1.5 KB: T = 64 7.2 -> 4.4 us, T = 2048 10.1 -> 7.9 us against three launches.
+constexpr int PERM_ONE_MAX = 2048, PERM_TWO_MAX = 32768, PERM_WIDE_MAX = 8192;
+constexpr size_t PERM_TWO_BYTES = (size_t)64 << 20;
 
 __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ slot, int T, int K,
                                                           int chunks_per_row, uint4* __restrict__ x_perm, int32_t* __restrict__ perm,
                                                           int32_t* __restrict__ inv_perm, int32_t* __restrict__ offsets,
-                                                          const int32_t* __restrict__ hist, int nblk) {
+                                                          const int32_t* __restrict__ hist, int nblk, int parts) {
     __shared__ int32_t s_total[4][256], s_before[4][256];  // per wave: tokens of each slot, and those in front of the block
     __shared__ int32_t s_pos[64];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int blk = blockIdx.x >> 2, part = blockIdx.x & 3, t0 = blk * 64;
+    const int blk = blockIdx.x / parts, part = blockIdx.x - blk * parts, per = 64 / parts, t0 = blk * 64;
     const int first = hist ? t0 / SB * SB : 0, end = hist ? t0 + 64 : T;   // the slot ids looked at
     {
         int total = 0, before = 0;                         // from the other sort blocks
@@ -380,28 +387,41 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restri
     if (wave == ((t0 >> 6) & 3)) {                         // the wave that met this block's tokens
         const int pos = my >= 0 ? s_before[0][my] + my_rank : -1;
         s_pos[lane] = pos;
-        if (pos >= 0 && (lane >> 4) == part) {
+        if (pos >= 0 && lane / per == part) {
             perm[pos] = t0 + lane;
             inv_perm[t0 + lane] = pos;
         }
     }
     __syncthreads();
-    const int r0 = part * 16, rows = min(16, T - t0 - r0);
+    const int r0 = part * per, rows = min(per, T - t0 - r0);
     for (int idx = tid; idx < rows * chunks_per_row; idx += 256) {
         const int r = idx / chunks_per_row, c = idx - r * chunks_per_row, pos = s_pos[r0 + r];
         if (pos >= 0) x_perm[(size_t)pos * chunks_per_row + c] = x[(size_t)(t0 + r0 + r) * chunks_per_row + c];
     }
 }
 
+bool permute_fused(const smoe_config& c, int T) {
+    return T <= PERM_ONE_MAX || (T <= PERM_TWO_MAX && (size_t)T * c.d_model * smoe_elem_size(c.dtype) <= PERM_TWO_BYTES);
+}
+
 // hist: [blocks of SB tokens][K], needed above PERM_ONE_MAX tokens.
-int launch_permute_fused(const smoe_config& c, const void* x, const int32_t* slot, int T, void* x_perm, int32_t* perm,
-                         int32_t* inv_perm, int32_t* offsets, int32_t* hist, hipStream_t s, const char* what) {
-    const int cpr = (int)((size_t)c.d_model * smoe_elem_size(c.dtype) / 16), nblk = smoe_sort_blocks(T);
+int launch_permute(const smoe_config& c, const void* x, const int32_t* slot, int T, void* x_perm, int32_t* perm, int32_t* inv_perm,
+                   int32_t* offsets, int32_t* hist, hipStream_t s, const char* what) {
+    const int K = c.K, cpr = (int)((size_t)c.d_model * smoe_elem_size(c.dtype) / 16), nblk = smoe_sort_blocks(T);
     if (T <= PERM_ONE_MAX) hist = nullptr;
-    else hipLaunchKernelGGL(sort_hist_kernel, dim3(nblk), dim3(SB), c.K * sizeof(int32_t), s, slot, T, c.K, hist);
-    const int blocks = std::max(1, (T + 63) / 64);         // T = 0 still writes offsets = 0
-    hipLaunchKernelGGL(permute_rows_kernel, dim3(4 * blocks), dim3(256), 0, s, (const uint4*)x, slot, T, c.K, cpr, (uint4*)x_perm, perm,
-                       inv_perm, offsets, hist, nblk);
+    else hipLaunchKernelGGL(sort_hist_kernel, dim3(nblk), dim3(SB), K * sizeof(int32_t), s, slot, T, K, hist);
+    if (permute_fused(c, T)) {
+        const int parts = cpr >= 256 && T <= PERM_WIDE_MAX ? 16 : 4;
+        const int blocks = std::max(1, (T + 63) / 64);     // T = 0 still writes offsets = 0
+        hipLaunchKernelGGL(permute_rows_kernel, dim3(parts * blocks), dim3(256), 0, s, (const uint4*)x, slot, T, K, cpr, (uint4*)x_perm,
+                           perm, inv_perm, offsets, hist, nblk, parts);
+    } else {
+        hipLaunchKernelGGL(sort_rank_kernel, dim3(nblk), dim3(SB), (2 + SB_WAVES) * K * sizeof(int32_t), s, slot, T, K, nblk, hist, perm,
+                           inv_perm, offsets);
+        const size_t total = (size_t)T * cpr;
+        hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (const uint4*)x, perm, T, cpr,
+                           (uint4*)x_perm);
+    }
     return smoe_check_hip(hipGetLastError(), what);
 }
 
@@ -457,17 +477,7 @@ int smoe_launch_importance(const smoe_layer* L, const int32_t* orig_expert, cons
 
 int smoe_launch_permute(const smoe_layer* L, const void* x, const int32_t* slot, int T, void* x_perm,
                         int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s) {
-    if (T <= PERM_TWO_MAX)
-        return launch_permute_fused(L->cfg, x, slot, T, x_perm, perm, inv_perm, offsets, L->d_sort_hist, s, "smoe_permute launch");
-    const int K = L->cfg.K, nblk = smoe_sort_blocks(T);
-    hipLaunchKernelGGL(sort_hist_kernel, dim3(nblk), dim3(SB), K * sizeof(int32_t), s, slot, T, K, L->d_sort_hist);
-    hipLaunchKernelGGL(sort_rank_kernel, dim3(nblk), dim3(SB), (2 + SB_WAVES) * K * sizeof(int32_t), s,
-                       slot, T, K, nblk, L->d_sort_hist, perm, inv_perm, offsets);
-    const int cpr = (int)((size_t)L->cfg.d_model * smoe_elem_size(L->cfg.dtype) / 16);
-    const size_t total = (size_t)T * cpr;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                       (const uint4*)x, perm, T, cpr, (uint4*)x_perm);
-    return smoe_check_hip(hipGetLastError(), "smoe_permute launch");
+    return launch_permute(L->cfg, x, slot, T, x_perm, perm, inv_perm, offsets, L->d_sort_hist, s, "smoe_permute launch");
 }
 
 // ---------------------------------------------------------------------------
@@ -514,11 +524,10 @@ int smoe_static_max_tokens() { return STATIC_MAX_TOKENS; }
 // call][K]), so a smaller call after a larger one is safe.
 int smoe_launch_permute_static(const smoe_config& c, const void* x, const int32_t* slot, int T, void* x_perm,
                                int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s) {
-    static_assert(STATIC_MAX_TOKENS <= PERM_TWO_MAX, "the fixed array serves the fused launches only");
     int32_t* hist = nullptr;
     if (T > PERM_ONE_MAX)
         if (int rc = static_scratch(&hist)) return rc;
-    return launch_permute_fused(c, x, slot, T, x_perm, perm, inv_perm, offsets, hist, s, "smoe_permute_static launch");
+    return launch_permute(c, x, slot, T, x_perm, perm, inv_perm, offsets, hist, s, "smoe_permute_static launch");
 }
 
 int smoe_launch_rank_importance(const smoe_layer* L, const int32_t* orig_expert, const float* orig_gate,
