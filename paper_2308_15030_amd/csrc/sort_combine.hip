@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "smoe_internal.h"
 #include "wave_ops.h"
@@ -31,19 +32,24 @@ constexpr int IMP_THREADS = 256;
 // sequential, so the result does not depend on U.  What bounds it is the number
 // of trips to the L2, one per group: 16 tokens a thread make one trip of a batch
 // of 4096, 4 are enough up to 1024.  (rank_importance_kernel with this and the
-// ranking's sums in registers: T = 16384, E = 128 11.7 -> 7.2 us.)
-template <int U>
+// ranking's sums in registers: T = 16384, E = 128 11.7 -> 7.2 us.)  LONG: whole groups
+// go without the checks against the end of the batch, which the adds of a long
+// batch would feel (smoe_importance, T = 65536: 16.0 us with them, 11.3 without);
+// not in rank_importance_kernel, whose workgroups are four times as large and get
+// slower by the registers it takes (T = 4096, E = 256: 0.9 us).
+template <int U, bool LONG>
 __device__ __forceinline__ void importance_groups(const int32_t* __restrict__ orig_expert,
                                                   const float* __restrict__ orig_gate,
                                                   const float* __restrict__ xnorm, int T, int e, int tid,
                                                   int& c, float& g, float& r) {
     c = 0; g = 0.f; r = 0.f;
-    for (int t = tid; t < T; t += U * IMP_THREADS) {
+    int t = tid;
+    auto group = [&](auto full) {
         int ev[U];
         float gv[U], xv[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {                      // past the batch: read again, not added
-            const int u = min(t + i * IMP_THREADS, T - 1);
+            const int u = full ? t + i * IMP_THREADS : min(t + i * IMP_THREADS, T - 1);
             ev[i] = orig_expert[u];
             gv[i] = orig_gate[u];
             xv[i] = xnorm[u];
@@ -51,20 +57,25 @@ __device__ __forceinline__ void importance_groups(const int32_t* __restrict__ or
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const bool mine = ev[i] == e && t + i * IMP_THREADS < T;
+            const bool mine = ev[i] == e && (full || t + i * IMP_THREADS < T);
             c += mine;
             g += mine ? gv[i] : 0.f;
             r += mine ? xv[i] * gv[i] : 0.f;
         }
-    }
+    };
+    if (LONG)
+        for (; t - tid + U * IMP_THREADS <= T; t += U * IMP_THREADS) group(std::true_type{});
+    for (; t < T; t += U * IMP_THREADS) group(std::false_type{});
 }
 
+template <bool LONG>
 __device__ __forceinline__ void importance_share(const int32_t* __restrict__ orig_expert,
                                                  const float* __restrict__ orig_gate,
                                                  const float* __restrict__ xnorm, int T, int e, int tid,
                                                  int& c, float& g, float& r) {
-    if (T <= 4 * IMP_THREADS) importance_groups<4>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
-    else importance_groups<16>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    if (T <= 4 * IMP_THREADS) importance_groups<4, false>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    else if (!LONG || T <= 16 * IMP_THREADS) importance_groups<16, false>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    else importance_groups<16, true>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
 }
 
 __global__ __launch_bounds__(IMP_THREADS) void importance_kernel(
@@ -76,7 +87,7 @@ __global__ __launch_bounds__(IMP_THREADS) void importance_kernel(
     const int e = blockIdx.x, tid = threadIdx.x;
     int c;
     float g, r;
-    importance_share(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    importance_share<true>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
     s_c[tid] = c; s_g[tid] = g; s_r[tid] = r;
     __syncthreads();
     for (int w = IMP_THREADS / 2; w > 0; w >>= 1) {
@@ -198,7 +209,7 @@ __global__ __launch_bounds__(SB) void rank_importance_kernel(
         if (tid < IMP_THREADS) {
             int c;
             float g, r;
-            importance_share(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+            importance_share<false>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
             s_c[tid] = c; s_g[tid] = g; s_r[tid] = r;
         }
         __syncthreads();

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 NAMES = ("orig_expert", "orig_gate", "slot", "gate", "xnorm", "count", "gsum", "score", "perm", "inv_perm", "offsets")
 
 
-@pytest.mark.parametrize("T", [129, 1024, 1025, 4096, 4097, 8225])
+@pytest.mark.parametrize("T", [129, 1024, 1025, 4096, 4097, 8192, 8225])
 @pytest.mark.parametrize("E,K", [(256, 200), (100, 65), (8, 3), (33, 1)])
 def test_rank_importance_edges(T, E, K):
     cfg = wl.MoEConfig("rank", E=E, K=K, d_model=32, d_ff=32, T=T, dtype=wl.BF16, seed=T + E)
