@@ -156,7 +156,7 @@ __device__ __forceinline__ void decode_first_body(const smoe_route_args& ra, con
                                                   const int32_t* phys, int fbw) {
     extern __shared__ __align__(16) float smem[];
     const int routers = (ra.T + SMOE_RT - 1) / SMOE_RT;
-    if ((int)blockIdx.x < routers) smoe_route_mfma_body<NEB, 1>(blockIdx.x, ra, smem);
+    if ((int)blockIdx.x < routers) smoe_route_mfma_body<NEB, 1, false>(blockIdx.x, ra, smem);
     else dense_first_all<NBF, STREAM>((const uint16_t*)ra.x, W1, ra.T, h, ra.d, d_ff, phys, nullptr, blockIdx.x - routers, fbw, (uint16_t*)smem);
 }
 

@@ -25,21 +25,31 @@ __global__ __launch_bounds__(256) void pack_router_kernel(const float* __restric
     out[unit] = e < E ? *(const float4*)&Wr[(size_t)e * d + k0] : make_float4(0, 0, 0, 0);
 }
 
-template <int NEB, int TB>
+template <int NEB, int TB, bool MULTI>
 __global__ __launch_bounds__(512) void route_mfma_kernel(const smoe_route_args a) {
     extern __shared__ __align__(16) float smem[];
-    smoe_route_mfma_body<NEB, TB>(blockIdx.x, a, smem);
+    smoe_route_mfma_body<NEB, TB, MULTI>(blockIdx.x, a, smem);
+}
+
+template <int NEB, int TB, bool MULTI>
+int launch_mfma_multi(const smoe_route_args& a, hipStream_t s) {
+    using S = smoe_route_shape<NEB, TB>;
+    const size_t lds = S::lds_bytes(a.d);
+    static smoe_lds_raised raised;
+    if (int rc = raised.ensure((const void*)route_mfma_kernel<NEB, TB, MULTI>, lds, (int)S::lds_bytes(SMOE_ROUTE_KC))) return rc;
+    constexpr int NTOK = SMOE_RT * TB;
+    hipLaunchKernelGGL((route_mfma_kernel<NEB, TB, MULTI>), dim3((a.T + NTOK - 1) / NTOK), dim3(512), lds, s, a);
+    return smoe_check_hip(hipGetLastError(), "smoe_route launch");
 }
 
 template <int NEB, int TB>
 int launch_mfma_tb(const smoe_route_args& a, hipStream_t s) {
-    using S = smoe_route_shape<NEB, TB>;
-    const size_t lds = S::lds_bytes(a.d);
-    static smoe_lds_raised raised;
-    if (int rc = raised.ensure((const void*)route_mfma_kernel<NEB, TB>, lds, (int)S::lds_bytes(SMOE_ROUTE_KC))) return rc;
-    constexpr int NTOK = SMOE_RT * TB;
-    hipLaunchKernelGGL((route_mfma_kernel<NEB, TB>), dim3((a.T + NTOK - 1) / NTOK), dim3(512), lds, s, a);
-    return smoe_check_hip(hipGetLastError(), "smoe_route launch");
+    // the prefetch across chunks pays for two token blocks, whose staging takes two rounds, and takes registers
+    // that more than 64 experts do not leave
+    if constexpr (TB == 2 && NEB <= 2) {
+        if (a.d > SMOE_ROUTE_KC) return launch_mfma_multi<NEB, TB, true>(a, s);
+    }
+    return launch_mfma_multi<NEB, TB, false>(a, s);
 }
 
 template <int NEB>

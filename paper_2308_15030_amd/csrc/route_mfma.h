@@ -180,7 +180,9 @@ __device__ __forceinline__ void smoe_route_finish(const int block, const smoe_ro
     }
 }
 
-template <int NEB, int TB>
+// MULTI: d_model takes more than one chunk; the first round of the next chunk's loads is then in flight
+// while this one is multiplied.
+template <int NEB, int TB, bool MULTI>
 __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe_route_args& a, float* smem) {
     using S = smoe_route_shape<NEB, TB>;
     constexpr int NS = S::NS, NEBH = S::NEBH, RT = SMOE_RT, NTOK = S::NTOK;
@@ -210,6 +212,18 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
             for (int i = 0; i < 16; ++i) acc[b][tb][i] = 0.f;
     }
     const int ldx = min(a.d, KC) + 8;                      // conflict-free 16-byte operand reads
+    constexpr int PPT = 8;                                 // 16-byte pieces of x a thread fetches together
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // (an array of uint4 would live in scratch memory across chunks)
+    u32x4 v[PPT];
+    const int rows = min(NTOK, a.T - tw0);                 // rows past the batch stay as they are: their logits are not used
+    auto fetch_x = [&](int k0, int i0) {                   // pieces past the end repeat the last one
+        const int cpr = min(KC, a.d - k0) >> 3;            // pieces per row
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) {
+            const int idx = min(i0 + q * 512, rows * cpr - 1), r = idx / cpr, c = idx - r * cpr;
+            v[q] = *(const u32x4*)((const uint16_t*)a.x + (size_t)(tw0 + r) * a.d + k0 + c * 8);
+        }
+    };
     for (int k0 = 0; k0 < a.d; k0 += KC) {                 // (one pass up to d_model = 1024)
         const int kc = min(KC, a.d - k0), steps = kc >> 4;
         const int per = (steps + NS - 1) / NS;
@@ -232,21 +246,16 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
         if (n > 0) fetch(wA, 0);                           // on their way while the tokens are staged
         if (k0) __syncthreads();                           // the previous chunk has been used up
         const int cpr = kc >> 3;                           // 16-byte pieces per row
-        constexpr int PPT = 8;                             // pieces fetched together
-        for (int i0 = tid; i0 < NTOK * cpr; i0 += 512 * PPT) {
-            uint4 v[PPT];
+        for (int i0 = tid; i0 < rows * cpr; i0 += 512 * PPT) {
+            if (!MULTI || !k0 || i0 != tid) fetch_x(k0, i0);
 #pragma unroll
             for (int q = 0; q < PPT; ++q) {
-                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
-                v[q] = *(const uint4*)((const uint16_t*)a.x + (size_t)min(tw0 + r, a.T - 1) * a.d + k0 + c * 8);
-            }
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {                // pieces past the end repeat the last one
-                const int idx = min(i0 + q * 512, NTOK * cpr - 1), r = idx / cpr, c = idx - r * cpr;
-                *(uint4*)&xs[r * ldx + c * 8] = v[q];
+                const int idx = min(i0 + q * 512, rows * cpr - 1), r = idx / cpr, c = idx - r * cpr;
+                *(u32x4*)&xs[r * ldx + c * 8] = v[q];
             }
         }
         __syncthreads();
+        if (MULTI && k0 + KC < a.d) fetch_x(k0 + KC, tid);
         const uint16_t* xrow = xs + (lane & 31) * ldx + (lane >> 5) * 8 + lo * 16;
         auto consume = [&](uint4 (&w)[G][NEBH][2], int g0) {
 #pragma unroll

@@ -50,3 +50,30 @@ def test_empty_slices(E, d, T):
         np.testing.assert_allclose(to_host(L.xnorm), ref["xnorm"], rtol=1e-5)
     assert max_abs_rel(values(to_host(L.out), cfg.dtype)[ok], values(ref["out"], cfg.dtype)[ok]) <= 2e-2
     L.close()
+
+
+@pytest.mark.parametrize("E,d,T", [(8, 1056, 8193), (8, 2080, 8225), (64, 1056, 8225), (100, 2080, 8193)])
+def test_chunks_of_two_token_blocks(E, d, T):
+    """More than one staged chunk of x with two token blocks per workgroup (more than 8192 tokens), a last workgroup
+    with one token or 33: the router against the oracle."""
+    K = min(E, 7)
+    cfg = wl.MoEConfig("chunks", E=E, K=K, d_model=d, d_ff=32, T=T, dtype=wl.BF16, seed=E + d)
+    print(f"[E={E} d={d} T={T}]", flush=True)
+    Wr = (wl.router_weights(cfg, 0) * np.float32(160.0 / d ** 0.5)).astype(np.float32)
+    x = wl.hidden_states(cfg, 0)
+    e2s = np.full(E, -1, np.int32)
+    e2s[:K] = np.arange(K, dtype=np.int32)
+    L = b.Layer(E, K, d, 32, T, b.SMOE_BF16, router_w=torch.from_numpy(Wr))
+    w1, w2 = (torch.zeros(n, dtype=torch.int16, device="cuda:0") for n in (d * 32, d * 32))
+    for s in range(K):
+        L.set_resident(s, s, w1, w2)
+    ref = oracle.route(x, Wr, e2s, 0)
+    ok = ~ref["ambiguous"]
+    L.route(to_dev(x), T)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(L.orig_expert)[ok], ref["orig_expert"][ok])
+    assert np.array_equal(to_host(L.slot)[ok], ref["slot"][ok])
+    np.testing.assert_allclose(to_host(L.orig_gate)[ok], ref["orig_gate"][ok], rtol=1e-5)
+    np.testing.assert_allclose(to_host(L.gate)[ok], ref["gate"][ok], rtol=1e-5)
+    np.testing.assert_allclose(to_host(L.xnorm), ref["xnorm"], rtol=1e-5)
+    L.close()
