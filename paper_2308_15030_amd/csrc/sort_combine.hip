@@ -13,7 +13,6 @@
 
 #include <algorithm>
 #include <mutex>
-#include <type_traits>
 
 #include "smoe_internal.h"
 #include "wave_ops.h"
@@ -32,24 +31,18 @@ constexpr int IMP_THREADS = 256;
 // sequential, so the result does not depend on U.  What bounds it is the number
 // of trips to the L2, one per group: 16 tokens a thread make one trip of a batch
 // of 4096, 4 are enough up to 1024.  (rank_importance_kernel with this and the
-// ranking's sums in registers: T = 16384, E = 128 11.7 -> 7.2 us.)  LONG: whole groups
-// go without the checks against the end of the batch, which the adds of a long
-// batch would feel (smoe_importance, T = 65536: 16.0 us with them, 11.3 without);
-// not in rank_importance_kernel, whose workgroups are four times as large and get
-// slower by the registers it takes (T = 4096, E = 256: 0.9 us).
-template <int U, bool LONG>
+// ranking's sums in registers: T = 16384, E = 128 11.7 -> 7.2 us.)
+template <int U>
 __device__ __forceinline__ void importance_groups(const int32_t* __restrict__ orig_expert,
                                                   const float* __restrict__ orig_gate,
                                                   const float* __restrict__ xnorm, int T, int e, int tid,
                                                   int& c, float& g, float& r) {
-    c = 0; g = 0.f; r = 0.f;
-    int t = tid;
-    auto group = [&](auto full) {
+    for (int t = tid; t < T; t += U * IMP_THREADS) {
         int ev[U];
         float gv[U], xv[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {                      // past the batch: read again, not added
-            const int u = full ? t + i * IMP_THREADS : min(t + i * IMP_THREADS, T - 1);
+            const int u = min(t + i * IMP_THREADS, T - 1);
             ev[i] = orig_expert[u];
             gv[i] = orig_gate[u];
             xv[i] = xnorm[u];
@@ -57,27 +50,63 @@ __device__ __forceinline__ void importance_groups(const int32_t* __restrict__ or
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const bool mine = ev[i] == e && (full || t + i * IMP_THREADS < T);
+            const bool mine = ev[i] == e && t + i * IMP_THREADS < T;
             c += mine;
             g += mine ? gv[i] : 0.f;
             r += mine ? xv[i] * gv[i] : 0.f;
         }
-    };
-    if (LONG)
-        for (; t - tid + U * IMP_THREADS <= T; t += U * IMP_THREADS) group(std::true_type{});
-    for (; t < T; t += U * IMP_THREADS) group(std::false_type{});
+    }
 }
 
+// The whole groups of 16 of a long batch without the checks against its end, which the adds would feel
+// (smoe_importance, T = 65536: 16.0 us with them, 11.9 without); returns the tokens they cover.
+__device__ __forceinline__ int importance_whole_groups(const int32_t* __restrict__ orig_expert,
+                                                       const float* __restrict__ orig_gate,
+                                                       const float* __restrict__ xnorm, int T, int e, int tid,
+                                                       int& c, float& g, float& r) {
+    constexpr int U = 16;
+    int t0 = 0;
+    for (; t0 + U * IMP_THREADS <= T; t0 += U * IMP_THREADS) {
+        int ev[U];
+        float gv[U], xv[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int u = t0 + tid + i * IMP_THREADS;
+            ev[i] = orig_expert[u];
+            gv[i] = orig_gate[u];
+            xv[i] = xnorm[u];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const bool mine = ev[i] == e;
+            c += mine;
+            g += mine ? gv[i] : 0.f;
+            r += mine ? xv[i] * gv[i] : 0.f;
+        }
+    }
+    return t0;
+}
+
+// LONG: more than 4096 tokens.  An instance of its own: short batches (T = 4096) take 1 us more beside its
+// code, and so does rank_importance_kernel.
 template <bool LONG>
 __device__ __forceinline__ void importance_share(const int32_t* __restrict__ orig_expert,
                                                  const float* __restrict__ orig_gate,
                                                  const float* __restrict__ xnorm, int T, int e, int tid,
                                                  int& c, float& g, float& r) {
-    if (T <= 4 * IMP_THREADS) importance_groups<4, false>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
-    else if (!LONG || T <= 16 * IMP_THREADS) importance_groups<16, false>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
-    else importance_groups<16, true>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    c = 0; g = 0.f; r = 0.f;
+    if (LONG) {
+        const int t0 = importance_whole_groups(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+        importance_groups<16>(orig_expert + t0, orig_gate + t0, xnorm + t0, T - t0, e, tid, c, g, r);
+    } else if (T <= 4 * IMP_THREADS) {
+        importance_groups<4>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    } else {
+        importance_groups<16>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    }
 }
 
+template <bool LONG>
 __global__ __launch_bounds__(IMP_THREADS) void importance_kernel(
     const int32_t* __restrict__ orig_expert, const float* __restrict__ orig_gate,
     const float* __restrict__ xnorm, const float* __restrict__ expert_norm, int T,
@@ -87,7 +116,7 @@ __global__ __launch_bounds__(IMP_THREADS) void importance_kernel(
     const int e = blockIdx.x, tid = threadIdx.x;
     int c;
     float g, r;
-    importance_share<true>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
+    importance_share<LONG>(orig_expert, orig_gate, xnorm, T, e, tid, c, g, r);
     s_c[tid] = c; s_g[tid] = g; s_r[tid] = r;
     __syncthreads();
     for (int w = IMP_THREADS / 2; w > 0; w >>= 1) {
@@ -325,14 +354,16 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restric
 constexpr int PERM_ONE_MAX = 2048, PERM_TWO_MAX = 32768, PERM_WIDE_MAX = 8192;
 constexpr size_t PERM_TWO_BYTES = (size_t)64 << 20;
 
+template <int PARTS>
 __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ slot, int T, int K,
                                                           int chunks_per_row, uint4* __restrict__ x_perm, int32_t* __restrict__ perm,
                                                           int32_t* __restrict__ inv_perm, int32_t* __restrict__ offsets,
-                                                          const int32_t* __restrict__ hist, int nblk, int parts) {
+                                                          const int32_t* __restrict__ hist, int nblk) {
     __shared__ int32_t s_total[4][256], s_before[4][256];  // per wave: tokens of each slot, and those in front of the block
     __shared__ int32_t s_pos[64];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int blk = blockIdx.x / parts, part = blockIdx.x - blk * parts, per = 64 / parts, t0 = blk * 64;
+    constexpr int PER = 64 / PARTS;                        // rows to move
+    const int blk = blockIdx.x / PARTS, part = blockIdx.x % PARTS, t0 = blk * 64;
     const int first = hist ? t0 / SB * SB : 0, end = hist ? t0 + 64 : T;   // the slot ids looked at
     {
         int total = 0, before = 0;                         // from the other sort blocks
@@ -398,13 +429,13 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restri
     if (wave == ((t0 >> 6) & 3)) {                         // the wave that met this block's tokens
         const int pos = my >= 0 ? s_before[0][my] + my_rank : -1;
         s_pos[lane] = pos;
-        if (pos >= 0 && lane / per == part) {
+        if (pos >= 0 && lane / PER == part) {
             perm[pos] = t0 + lane;
             inv_perm[t0 + lane] = pos;
         }
     }
     __syncthreads();
-    const int r0 = part * per, rows = min(per, T - t0 - r0);
+    const int r0 = part * PER, rows = min(PER, T - t0 - r0);
     for (int idx = tid; idx < rows * chunks_per_row; idx += 256) {
         const int r = idx / chunks_per_row, c = idx - r * chunks_per_row, pos = s_pos[r0 + r];
         if (pos >= 0) x_perm[(size_t)pos * chunks_per_row + c] = x[(size_t)(t0 + r0 + r) * chunks_per_row + c];
@@ -424,8 +455,8 @@ int launch_permute(const smoe_config& c, const void* x, const int32_t* slot, int
     if (permute_fused(c, T)) {
         const int parts = cpr >= 256 && T <= PERM_WIDE_MAX ? 16 : 4;
         const int blocks = std::max(1, (T + 63) / 64);     // T = 0 still writes offsets = 0
-        hipLaunchKernelGGL(permute_rows_kernel, dim3(parts * blocks), dim3(256), 0, s, (const uint4*)x, slot, T, K, cpr, (uint4*)x_perm,
-                           perm, inv_perm, offsets, hist, nblk, parts);
+        hipLaunchKernelGGL(parts == 16 ? permute_rows_kernel<16> : permute_rows_kernel<4>, dim3(parts * blocks), dim3(256), 0, s,
+                           (const uint4*)x, slot, T, K, cpr, (uint4*)x_perm, perm, inv_perm, offsets, hist, nblk);
     } else {
         hipLaunchKernelGGL(sort_rank_kernel, dim3(nblk), dim3(SB), (2 + SB_WAVES) * K * sizeof(int32_t), s, slot, T, K, nblk, hist, perm,
                            inv_perm, offsets);
@@ -481,7 +512,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
 int smoe_launch_importance(const smoe_layer* L, const int32_t* orig_expert, const float* orig_gate,
                            const float* xnorm, int T, int32_t* count, float* gsum, float* score,
                            int accumulate, hipStream_t s) {
-    hipLaunchKernelGGL(importance_kernel, dim3(L->cfg.E), dim3(IMP_THREADS), 0, s, orig_expert,
+    hipLaunchKernelGGL(T > 16 * IMP_THREADS ? importance_kernel<true> : importance_kernel<false>, dim3(L->cfg.E), dim3(IMP_THREADS), 0, s, orig_expert,
                        orig_gate, xnorm, L->expert_norm, T, count, gsum, score, accumulate);
     return smoe_check_hip(hipGetLastError(), "smoe_importance launch");
 }
