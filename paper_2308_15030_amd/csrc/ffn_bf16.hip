@@ -873,9 +873,8 @@ bool smoe_ffn_dense_path(const smoe_layer* L, int T) {
 
 // Fused form used by smoe_forward: the first product gathers its rows from x
 // through perm, the second scatters gate * y (+ residual) to out in token order.
-int smoe_launch_ffn_bf16_fused(const smoe_layer* L, const uint16_t* x, const int32_t* slot_of,
-                               const int32_t* perm, const int32_t* offsets, const float* gate,
-                               const uint16_t* residual, int T, uint16_t* out, hipStream_t s) {
+int smoe_launch_ffn_bf16_fused(const smoe_layer* L, const uint16_t* x, const int32_t* perm, const int32_t* offsets,
+                               const float* gate, const uint16_t* residual, int T, uint16_t* out, hipStream_t s) {
     const smoe_config& c = L->cfg;
     int v1, v2;
     pick_variants(L, T, v1, v2);

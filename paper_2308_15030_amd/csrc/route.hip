@@ -100,15 +100,3 @@ int smoe_launch_route(const smoe_layer* L, const void* x, int T, int32_t* orig_e
     if (c.E <= 128) return f32 ? launch_f32<4>(a, s) : launch_mfma<4>(a, s);
     return f32 ? launch_f32<8>(a, s) : launch_mfma<8>(a, s);
 }
-
-// A batch of at most 32 tokens that the two-launch path cannot take (its rows do not fit the LDS):
-// router and ranking as for a larger one.
-int smoe_launch_route_rank_small(const smoe_layer* L, const void* x, int T, int32_t* orig_expert,
-                                 float* orig_gate, int32_t* slot, float* gate, float* xnorm, int32_t* count,
-                                 float* gsum, float* score, int accumulate, int32_t* perm, int32_t* inv_perm,
-                                 int32_t* offsets, hipStream_t s) {
-    int rc = smoe_launch_route(L, x, T, orig_expert, orig_gate, slot, gate, xnorm, L->d_hist32, s);
-    if (rc) return rc;
-    return smoe_launch_rank_importance(L, orig_expert, orig_gate, xnorm, slot, T, count, gsum, score, accumulate, perm,
-                                       inv_perm, offsets, s);
-}

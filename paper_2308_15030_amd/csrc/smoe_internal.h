@@ -122,11 +122,8 @@ inline int smoe_sort_blocks(int T) { return (T + SMOE_SORT_BLOCK - 1) / SMOE_SOR
 int smoe_launch_route(const smoe_layer* L, const void* x, int T, int32_t* orig_expert,
                       float* orig_gate, int32_t* slot, float* gate, float* xnorm, int32_t* hist32,
                       hipStream_t s);
-int smoe_launch_route_rank_small(const smoe_layer* L, const void* x, int T, int32_t* orig_expert,
-                                 float* orig_gate, int32_t* slot, float* gate, float* xnorm, int32_t* count,
-                                 float* gsum, float* score, int accumulate, int32_t* perm, int32_t* inv_perm,
-                                 int32_t* offsets, hipStream_t s);
-// smoe_forward on a small batch, two launches (decode.hip): when it applies, the launches, and the names of its kernel instances
+// smoe_forward on a small batch, two or three launches (decode.hip): when it applies, the launches, and the names of its
+// kernel instances
 bool smoe_decode_first_applies(const smoe_layer* L, int T);
 std::string smoe_describe_decode(const smoe_layer* L, int T, bool first);
 int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t* orig_expert, float* orig_gate,
@@ -150,9 +147,8 @@ int smoe_launch_rank_importance(const smoe_layer* L, const int32_t* orig_expert,
                                 const float* xnorm, const int32_t* slot, int T, int32_t* count, float* gsum,
                                 float* score, int accumulate, int32_t* perm, int32_t* inv_perm,
                                 int32_t* offsets, hipStream_t s);
-int smoe_launch_ffn_bf16_fused(const smoe_layer* L, const uint16_t* x, const int32_t* slot_of,
-                               const int32_t* perm, const int32_t* offsets, const float* gate,
-                               const uint16_t* residual, int T, uint16_t* out, hipStream_t s);
+int smoe_launch_ffn_bf16_fused(const smoe_layer* L, const uint16_t* x, const int32_t* perm, const int32_t* offsets,
+                               const float* gate, const uint16_t* residual, int T, uint16_t* out, hipStream_t s);
 int smoe_launch_importance(const smoe_layer* L, const int32_t* orig_expert, const float* orig_gate,
                            const float* xnorm, int T, int32_t* count, float* gsum, float* score,
                            int accumulate, hipStream_t s);
