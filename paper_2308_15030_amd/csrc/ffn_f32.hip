@@ -22,6 +22,7 @@
 // 280 -> 77 us (63 TFLOP/s), T = 32 23 us, T = 4 16 us (75 MB of weights: 4.7 TB/s).
 
 #include <algorithm>
+#include <cstdio>
 #include <type_traits>
 
 #include "smoe_internal.h"
@@ -219,15 +220,20 @@ __global__ __launch_bounds__(PK_WAVES * 64) void panel_gemm_f32(
     });
 }
 
+// 16-feature blocks of an item: the widest range that still gives three items per four compute units.
+int feature_blocks(const smoe_config& c, int T, int N) {
+    const int tiles = T / 32 + (std::min(c.K, T) + 1) / 2;                              // expected row tiles
+    int nc = 4;
+    while (nc > 1 && tiles * ((N + 16 * nc - 1) / (16 * nc)) < 192) nc >>= 1;
+    return nc;
+}
+
 // As many workgroups as the chip keeps resident (one of 8 waves on each of 32 compute units of a die),
-// fewer if the items run out.  The feature range is the widest that still gives three items per four
-// compute units.
+// fewer if the items run out.
 template <bool FIRST>
 void launch(const smoe_layer* L, const float* X, const void* W, const int32_t* offsets, int T, float* Y, int R, int N, hipStream_t s,
             hipEvent_t e0, hipEvent_t e1) {
-    const int K = L->cfg.K, tiles = T / 32 + (std::min(K, T) + 1) / 2;                  // expected row tiles
-    int nc = 4;
-    while (nc > 1 && tiles * ((N + 16 * nc - 1) / (16 * nc)) < 192) nc >>= 1;
+    const int K = L->cfg.K, nc = feature_blocks(L->cfg, T, N);
     const long long items = (long long)((N + 16 * nc - 1) / (16 * nc)) * (T / 32 + std::min(K, T));   // upper bound
     const dim3 grid(XCDS * (unsigned)std::min<long long>((items + XCDS - 1) / XCDS, 32));
     auto kern = nc == 4 ? panel_gemm_f32<FIRST, 4> : nc == 2 ? panel_gemm_f32<FIRST, 2> : panel_gemm_f32<FIRST, 1>;
@@ -243,4 +249,11 @@ int smoe_launch_ffn_f32(const smoe_layer* L, const float* x_perm, const int32_t*
     launch<true>(L, x_perm, L->slot_w1, offsets, T, h, c.d_model, c.d_ff, s, L->prof_ev[0], L->prof_ev[1]);
     launch<false>(L, h, L->slot_w2, offsets, T, y_perm, c.d_ff, c.d_model, s, L->prof_ev[2], L->prof_ev[3]);
     return smoe_check_hip(hipGetLastError(), "smoe_expert_ffn launch");
+}
+
+// Names of the two kernel instances of a T-token batch, as a profiler prints them.
+int smoe_describe_ffn_f32(const smoe_layer* L, int T, char* out, size_t n) {
+    const smoe_config& c = L->cfg;
+    snprintf(out, n, "panel_gemm_f32<true, %d> | panel_gemm_f32<false, %d>", feature_blocks(c, T, c.d_ff), feature_blocks(c, T, c.d_model));
+    return SMOE_OK;
 }

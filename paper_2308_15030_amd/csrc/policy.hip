@@ -109,7 +109,7 @@ int smoe_profile_end(smoe_layer_t* L, void* stream, float* elapsed_us) {
 int smoe_describe_ffn(const smoe_layer_t* L, int T, int fused, char* out, size_t n) {
     if (!L || !out || n == 0) return smoe_fail(SMOE_EINVAL, "smoe_describe_ffn: null argument");
     if (T < 1 || T > L->cfg.max_tokens) return smoe_fail(SMOE_EINVAL, "smoe_describe_ffn: T=%d outside [1,%d]", T, L->cfg.max_tokens);
-    if (L->cfg.dtype != SMOE_BF16) { snprintf(out, n, "ffn_f32_kernel | ffn_f32_kernel"); return SMOE_OK; }
+    if (L->cfg.dtype != SMOE_BF16) return smoe_describe_ffn_f32(L, T, out, n);
     return smoe_describe_ffn_bf16(L, T, fused, out, n);
 }
 

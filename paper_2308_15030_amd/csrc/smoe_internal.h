@@ -162,6 +162,7 @@ int smoe_launch_ffn_f32(const smoe_layer* L, const float* x_perm, const int32_t*
                         float* y_perm, hipStream_t s);
 int smoe_launch_ffn_bf16(const smoe_layer* L, const uint16_t* x_perm, const int32_t* offsets, int T,
                          uint16_t* y_perm, hipStream_t s);
+int smoe_describe_ffn_f32(const smoe_layer* L, int T, char* out, size_t n);
 int smoe_describe_ffn_bf16(const smoe_layer* L, int T, int fused, char* out, size_t n);
 int smoe_launch_combine(const smoe_layer* L, const void* y_perm, const int32_t* inv_perm,
                         const float* gate, const void* residual, int T, void* out, hipStream_t s);

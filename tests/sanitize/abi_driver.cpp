@@ -28,6 +28,7 @@ int smoe_launch_permute_static(const smoe_config&, const void*, const int32_t*, 
                                hipStream_t) { return 0; }
 int smoe_launch_ffn_f32(const smoe_layer*, const float*, const int32_t*, int, float*, hipStream_t) { return 0; }
 int smoe_launch_ffn_bf16(const smoe_layer*, const uint16_t*, const int32_t*, int, uint16_t*, hipStream_t) { return 0; }
+int smoe_describe_ffn_f32(const smoe_layer*, int, char* out, size_t n) { snprintf(out, n, "stub | stub"); return 0; }
 int smoe_describe_ffn_bf16(const smoe_layer*, int, int, char* out, size_t n) { snprintf(out, n, "stub | stub"); return 0; }
 int smoe_launch_combine(const smoe_layer*, const void*, const int32_t*, const float*, const void*, int, void*, hipStream_t) { return 0; }
 int smoe_launch_pack_slot(const smoe_layer*, int, const void*, const void*, hipStream_t, int, int, int, int*) { return 0; }

@@ -231,3 +231,13 @@ def test_workspace_holds_no_rows_the_small_batch_path_cannot_take(d):
     got = b.smoe_profile_memory(128, K, d, f, T, b.SMOE_BF16)["workspace_bytes"]
     rest = 128 * d * 4 + 128 * 64 * 4                                 # packed router, norm partial sums
     assert rows * f * 2 + rest <= got <= rows * f * 2 + rest + 64 * 1024
+
+
+@pytest.mark.parametrize("T,first,second", [(1, 1, 1), (512, 4, 4), (192, 4, 2)])
+def test_describe_ffn_names_the_fp32_kernels(T, first, second):
+    """The names are those of kernels the library holds (panel_gemm_f32 and its feature blocks per item)."""
+    h = b.smoe_create(8, 4, 768, 3072, 512, b.SMOE_F32)
+    assert b.smoe_describe_ffn(h, T, False) == f"panel_gemm_f32<true, {first}> | panel_gemm_f32<false, {second}>"
+    b.smoe_destroy(h)
+    with open(b.LIB_PATH, "rb") as f:
+        assert b"panel_gemm_f32" in f.read()
