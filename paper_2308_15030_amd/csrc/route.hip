@@ -44,8 +44,9 @@ int launch_mfma_multi(const smoe_route_args& a, hipStream_t s) {
 
 template <int NEB, int TB>
 int launch_mfma_tb(const smoe_route_args& a, hipStream_t s) {
-    // the prefetch across chunks pays for two token blocks, whose staging takes two rounds, and takes registers
-    // that more than 64 experts do not leave
+    // The prefetch across chunks pays for two token blocks, whose staging takes two rounds (E = 8, T = 16384: d_model =
+    // 2048 26.1 -> 22.7 us, 4096 46.6 -> 38.1), not for one (d_model = 2048, T = 32 10.0 -> 10.5), and takes registers that
+    // more than 64 experts do not leave (E = 128, d_model = 1056, T = 16384 27.8 us without, 33.1 with)
     if constexpr (TB == 2 && NEB <= 2) {
         if (a.d > SMOE_ROUTE_KC) return launch_mfma_multi<NEB, TB, true>(a, s);
     }
