@@ -33,12 +33,11 @@
 #include <string>
 #include <type_traits>
 
-#include "smoe_internal.h"
+#include "ffn_bf16.h"
 #include "wave_ops.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int KPAD = 8;   // row-major token tile: LDS pitch (BKT+8)*2 B keeps b128 reads conflict-free
@@ -120,18 +119,6 @@ __device__ __forceinline__ bf16x8 as_frag(uint4 v) {
     c.u = v;
     return c.b;
 }
-
-// Optional fusion of the permute and combine steps into the two products
-// (perm == nullptr: plain products on x_perm / y_perm).
-//   first product:  row r of the sorted order is read from x[perm[r]] (no x_perm);
-//   second product: row r is written to out[perm[r]] = gate[perm[r]] * y (+ residual[perm[r]]),
-//                   i.e. y = G(x)_i E_i(x) lands in token order (no y_perm).
-struct FuseArgs {
-    const int32_t* phys;      // virtual slot -> physical weight slot, [nslots]; NULL = identity (no spare slots)
-    const int32_t* perm;
-    const float* gate;
-    const uint16_t* residual;
-};
 
 __device__ __forceinline__ void apply_gate_v(float& v0, float& v1, float& v2, float& v3, float g, uint2 r,
                                              bool has_res, bool fused) {
@@ -765,17 +752,26 @@ void launch_gemm(const uint16_t* X, const void* Wp, const int32_t* offsets, int 
                           (const uint4*)Wp, offsets, nslots, T, Y, R, N, fz);
 }
 
-// The tile shapes launch_variant knows (every one of them is chosen somewhere by pick_variants,
-// except the 256 x 256 tile as the second product: 139 KB of LDS for the output turn and 85
-// spilled registers make it slow, and it is there for the override only).
+// The tile shapes launch_variant knows; every one of them is chosen somewhere by pick_variants.
 constexpr bool is_variant(int v) {
-    return v == 1 || v == 3 || v == 4 || v == 5 || v == 6 || v == 8 || v == 10;
+    return v == 1 || v == 3 || v == 4 || v == 5 || v == 6 || v == 8 || v == 9 || v == 10;
+}
+
+// What stands in where the ring kernel (9, 10) does not apply.
+int ring_or_tiled(int v, bool first, int R, int T) {
+    if (v < 9 || smoe_ring_applies(first, R, T)) return v;
+    return v == 9 ? 1 : 8;
 }
 
 template <bool FIRST>
 void launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots,
                     uint16_t* Y, int R, int N, int T, const FuseArgs& fz, hipStream_t s, hipEvent_t e0,
                     hipEvent_t e1) {
+    v = ring_or_tiled(v, FIRST, R, T);
+    if (v >= 9) {
+        (void)smoe_launch_ring(v == 9 ? 4 : 8, FIRST, X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die(), s, e0, e1);
+        return;
+    }
     if (R % 64 != 0 && v != 5 && v != 6) {   // d_model / d_ff are multiples of 32 by contract: 32-deep slices always fit
         launch_gemm<1, 4, 4, 32, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);
         return;
@@ -785,30 +781,54 @@ void launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* off
         case 3: launch_gemm<1, 2, 4, 64, 1, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  64 x 128
         case 4: launch_gemm<1, 1, 4, 64, 3, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  32 x 128
         case 8: launch_gemm<1, 4, 8, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  // 128 x 256, 8 waves
-        case 10: launch_gemm<1, 8, 8, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  // 256 x 256, 8 waves
         case 5: launch_small<4, 1, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;   // 32 x 128, streaming
         case 6: launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;   // 32 x 32, reduction split 4 ways
         default: launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;
     }
 }
 
+// Which tile of the ring kernel (9: at most 128 x 128, 10: at most 256 x 256) takes a product, or 0.
+// Two reasons to take it, by what the two products of a layer measured (us, tiled -> ring):
+//  * The reduction is no multiple of 128: the tiled kernel then has no weight prefetch.  16 slots of 992 x 3296,
+//    T = 800 33.0 -> 29.8 and 77.0 -> 42.6, T = 8000 107 -> 72 and 134 -> 70; 11 of 416 x 1696, T = 800 12.5 -> 10.7
+//    and 31.6 -> 18.0.  Where the streaming kernel splits a second product (v = 6) it stays ahead (T = 200: 15.8, 17.8),
+//    and so do 32-row tiles (v = 4) of 64-deep slices (6 slots of 448 x 1280, T = 140 8.1, 9.2).
+//  * There are large tiles for the chip.  First product, 300 and more tokens per slot (16 slots of 768 x 2048, T = 8000
+//    53.1 -> 43.4; of 1024 x 4096, T = 16384 160 -> 149) and where its tiles of 128 rows would take two rounds, those
+//    of 256 one (768 x 3072, T = 2000 30.8 -> 27.5; T = 4096 37.7 tiled, 39.0 ring).  Second product: its tiles are
+//    few and deep, and below a hundred full ones 128 x 128 tiles of two workgroups per compute unit keep up
+//    (768 x 3072, T = 8000 58.8, 59.4; 768 x 2048 40.8, 43.0; but T = 16384 104.7 -> 80.7 and 73 -> 62; 32 slots of
+//    1024 x 4096, T = 8000 119 -> 102), from four feature tiles on half as many do (1024 x 4096, T = 3000 99 -> 83,
+//    16 slots, T = 4096 73.4 -> 68.9; T = 1213 43.1, 58.8).
+// The small tiles serve where fewer than a hundred large ones exist (608 x 2912, T = 8000 second: 44.5, 49.0 with
+// large ones; 992 x 3296 70 with large ones, 96).
+int ring_tile(bool first, int R, int N, int T, int per_slot, int tiled) {
+    const double tiles = (double)T * N / 65536;            // full 256 x 256 tiles
+    if (R % (tiled == 4 ? 64 : 128) != 0) return tiled == 6 ? 0 : tiles >= 100 ? 10 : 9;
+    if (first) return tiles >= 80 && (per_slot >= 300 || (per_slot >= 120 && per_slot < 184)) ? 10 : 0;
+    return tiles >= 100 || (N >= 1024 && tiles >= 45) ? 10 : 0;
+}
+
 // Tile shapes for the two GEMMs.  A pair fixed at smoe_create (SMOE_FFN_VARIANT="v1,v2", a
 // tuning aid; the indices are those of launch_variant) overrides the built-in choice.
 void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
     // Thresholds measured on the Switch-base-64 shape (K = 16, 768 x 3072) over T = 48 .. 8192.
-    // What decides in the middle range is whether the first product's tiles fit the chip in one
-    // round (256-row tiles at 120-183 tokens per slot: one tile per slot and feature tile).
-    int per_slot = T / L->cfg.K;
-    if (per_slot >= 384) { v1 = 10; v2 = 1; }
-    else if (per_slot >= 184) { v1 = 8; v2 = 1; }
-    else if (per_slot >= 120) { v1 = 10; v2 = 3; }
+    const int per_slot = T / L->cfg.K;
+    if (per_slot >= 184) { v1 = 8; v2 = 1; }
     else if (per_slot >= 60) { v1 = 8; v2 = 3; }
     else if (per_slot >= 28) { v1 = 3; v2 = 4; }
     else if (per_slot >= 6) { v1 = 4; v2 = 6; }
     else { v1 = 5; v2 = 6; }             // decode: a few tokens per slot, weight streaming
-    // the small-batch path of smoe_forward splits the second product's reduction four ways: the
-    // separate call does the same, so that both give the same bits
-    if (smoe_decode_first_applies(L, T)) v2 = 6;
+    // the small-batch path of smoe_forward splits the second product's reduction four ways and multiplies 16
+    // reduction elements at a time: the separate call does the same, so that both give the same bits
+    if (smoe_decode_first_applies(L, T)) {
+        v2 = 6;
+    } else {
+        const int d = L->cfg.d_model, f = L->cfg.d_ff;
+        const int r1 = ring_tile(true, d, f, T, per_slot, v1), r2 = ring_tile(false, f, d, T, per_slot, v2);
+        if (r1 && smoe_ring_applies(true, d, T)) v1 = r1;
+        if (r2 && smoe_ring_applies(false, f, T)) v2 = r2;
+    }
     if (is_variant(L->ffn_variant[0]) && is_variant(L->ffn_variant[1])) {
         v1 = L->ffn_variant[0];
         v2 = L->ffn_variant[1];
@@ -827,17 +847,18 @@ int smoe_describe_ffn_bf16(const smoe_layer* L, int T, int fused, char* out, siz
     for (int i = 0; i < 2; ++i) {
         const bool first = i == 0;
         const int R = first ? L->cfg.d_model : L->cfg.d_ff;
+        v[i] = ring_or_tiled(v[i], first, R, T);
         const char* shape = nullptr;                       // AF, MAXB, NW, BKT, PD, OCC of launch_variant
         std::string name;
         if (fused && smoe_decode_first_applies(L, T) && v[1] == 6) name = smoe_describe_decode(L, T, first);
         else if (v[i] == 5) name = std::string("small_gemm_bf16<4, 1, ") + (first ? "true>" : "false>");
         else if (v[i] == 6) name = std::string("small_gemm_bf16<4, 4, ") + (first ? "true>" : "false>");
+        else if (v[i] >= 9) name = std::string("ring_gemm_bf16<") + (v[i] == 9 ? "2, " : "4, ") + (first ? "true>" : "false>");
         else if (R % 64 != 0) shape = "1, 4, 4, 32, ";
         else if (v[i] == 1) shape = "1, 4, 4, 64, ";
         else if (v[i] == 3) shape = "1, 2, 4, 64, ";
         else if (v[i] == 4) shape = "1, 1, 4, 64, ";
         else if (v[i] == 8) shape = "1, 4, 8, 64, ";
-        else if (v[i] == 10) shape = "1, 8, 8, 64, ";
         if (shape) {
             const int bkt = R % 64 != 0 ? 32 : 64, pd = (R % 64 == 0 && v[i] == 4) ? 3 : 1;
             const int occ = (R % 64 == 0 && (v[i] == 3 || v[i] == 4)) ? 4 : 2;

@@ -184,10 +184,15 @@ int smoe_launch_split_router(const smoe_layer* L, hipStream_t s);
 // Kernel launch that, when a pair of events is given, attaches them to the
 // dispatch itself (start and end of the kernel's execution).
 template <typename K, typename... Args>
+inline void smoe_launch_timed_lds(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, hipEvent_t e0, hipEvent_t e1,
+                                  Args... args) {
+    if (e0 && e1) hipExtLaunchKernelGGL(kernel, grid, block, lds, s, e0, e1, 0, args...);
+    else hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
+}
+template <typename K, typename... Args>
 inline void smoe_launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t s, hipEvent_t e0, hipEvent_t e1,
                               Args... args) {
-    if (e0 && e1) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, e0, e1, 0, args...);
-    else hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
+    smoe_launch_timed_lds(kernel, grid, block, 0, s, e0, e1, args...);
 }
 
 // Raises a kernel's dynamic-LDS limit once per device, not on every launch (one object per kernel).
