@@ -70,6 +70,12 @@ smoe_ws_layout smoe_ws_plan(const smoe_config& c) {
     // bf16 path: the router's weights in matrix-operand order, experts padded to a multiple of 32
     w.rsplit = off;
     if (c.dtype == SMOE_BF16) off = align_up(off + (size_t)((c.E + 31) / 32 * 32) * c.d_model * 4, 256);
+    // ... and the partial logits of few tokens: 8 slices of 32 experts, or 4 of 64, 128 or 256; sums of squares behind them
+    w.rpart = off;
+    if (c.dtype == SMOE_BF16) {
+        const size_t logits = c.E <= 64 ? 256 : c.E <= 128 ? 512 : 1024;
+        off = align_up(off + SMOE_FEW_T * (logits + 8 * 2) * 4, 256);
+    }
     w.norm = off;    off = align_up(off + (size_t)c.E * 64 * 4, 256);      // smoe_expert_norm partial sums
     // asynchronous loads from a host bank land here (copy engine) before they are packed into a slot
     w.stage = off;   off = align_up(off + (size_t)c.spare_slots * 2 * c.d_model * c.d_ff * smoe_elem_size(c.dtype), 256);
@@ -222,6 +228,7 @@ int smoe_bind(smoe_layer_t* L, const float* router_w, void* slot_w1, void* slot_
     L->d_hist32 = (int32_t*)(L->workspace + w.hist32);
     L->d_hidden = L->workspace + w.hidden;
     L->d_router_split = L->workspace + w.rsplit;
+    L->d_route_part = L->workspace + w.rpart;
     L->router_split_done = false;
     L->ws_ready = false;
     L->d_norm_partial = (float*)(L->workspace + w.norm);

@@ -15,7 +15,8 @@
 //                  tokens, for those tokens, with the gate and the residual.
 //
 // Where the empty slots' first matrices cost more than the router (see sparse), the router is launched first
-// and neither product reads a weight of a slot without a token.
+// and neither product reads a weight of a slot without a token; up to 16 tokens in a form of its own (see
+// route_partial_kernel).
 
 #include <algorithm>
 #include <cmath>
@@ -181,6 +182,170 @@ __global__ __launch_bounds__(512) void dense_first_kernel(const uint16_t* __rest
                                                           const int32_t* __restrict__ slot, int fbw) {
     extern __shared__ __align__(16) float smem[];
     dense_first_all<NBF, STREAM>(x, W1, T, h, d, d_ff, phys, slot, blockIdx.x, fbw, (uint16_t*)smem);
+}
+
+// ---------------------------------------------------------------------------
+// At most 16 tokens that reach few of the slots: three launches of short chains.  With one token a product is the
+// 4.7 MB of one matrix, which the whole chip reads in a microsecond; what counts is how many compute units pull it and
+// how many trips to memory follow one another.  So
+//   route_partial_kernel       the partial logits of smoe_route_mfma_body, one wave on its own compute unit per (slice of
+//                              the reduction, 32 experts) where that body's eight waves share one;
+//   dense_first_kernel_served  every workgroup finishes the router for the whole batch by itself (the first one writes
+//                              the results down), takes the served slots in order of their first token, and each wave
+//                              streams 16 features of one with all its loads in flight;
+//   dense_second_kernel_served the same for the second product, the reduction split four ways as in the other forms.
+// Products of 16 x 16 x 32 halve the dependent chain of those of 32 x 32 x 16; the bits are the same.
+// T = 1, 64 experts, 16 slots of 768 x 3072: 19.4 -> 14.5 us per layer (router, first and second launch took 5.8, 6.6
+// and 7.6 us with one compute unit for the router, 96 and 24 with work for the products); 128 slots T = 5 36 -> 19 us.
+constexpr int FEW_T = SMOE_FEW_T;
+
+template <int NEB>
+__global__ __launch_bounds__(64) void route_partial_kernel(const smoe_route_args a, float* __restrict__ part, float* __restrict__ sqp) {
+    using S = smoe_route_shape<NEB, 1>;
+    constexpr int NS = S::NS, EP = S::EP, G = 8;
+    const int lane = threadIdx.x, slice = blockIdx.x % NS, eb = blockIdx.x / NS;
+    const int nkb = a.d >> 4;
+    const uint4* wp = a.wr + (size_t)eb * nkb * 2 * 64 + lane;
+    const uint16_t* xp = (const uint16_t*)a.x + (size_t)min(lane & 31, a.T - 1) * a.d + (lane >> 5) * 8;
+    smoe_f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    float sq = 0.f;
+    for (int k0 = 0; k0 < a.d; k0 += SMOE_ROUTE_KC) {      // the same steps in the same order as smoe_route_mfma_body
+        const int steps = min(SMOE_ROUTE_KC, a.d - k0) >> 4, per = (steps + NS - 1) / NS;
+        const int lo = min(slice * per, steps), n = min(lo + per, steps) - lo, first = (k0 >> 4) + lo;
+        if (n <= 0) continue;
+        uint4 wA[G][2], wB[G][2], xA[G], xB[G];
+        auto fetch = [&](uint4 (&w)[G][2], uint4 (&x)[G], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) {                  // past the end: reloaded, not used
+                const int k = first + min(g0 + i, n - 1);
+                x[i] = *(const uint4*)(xp + k * 16);
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) w[i][hf] = wp[(size_t)(k * 2 + hf) * 64];
+            }
+        };
+        auto consume = [&](uint4 (&w)[G][2], uint4 (&x)[G], int g0) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                if (g0 + i >= n) break;                    // uniform
+                smoe_add_squares(sq, x[i]);
+                uint4 pc[3];
+                smoe_cut_weights(w[i], pc);
+#pragma unroll
+                for (int s3 = 2; s3 >= 0; --s3)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(smoe_frag(pc[s3]), smoe_frag(x[i]), acc, 0, 0, 0);
+            }
+        };
+        fetch(wA, xA, 0);
+        for (int g0 = 0; g0 < n; g0 += 2 * G) {
+            fetch(wB, xB, g0 + G);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(wA, xA, g0);
+            if (g0 + 2 * G < n) fetch(wA, xA, g0 + 2 * G);
+            consume(wB, xB, g0 + G);
+        }
+    }
+    const int t = lane & 31;
+    if (t >= a.T) return;
+    float* row = part + ((size_t)slice * FEW_T + t) * EP + eb * 32 + 4 * (lane >> 5);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *(float4*)(row + 8 * q) = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+    if (eb == 0) sqp[(slice * 2 + (lane >> 5)) * FEW_T + t] = sq;
+}
+
+typedef float smoe_f32x4 __attribute__((ext_vector_type(4)));
+
+// The rank-th distinct slot of the batch in order of its first token, -1 past the last; id = slot of token `lane` (T <= 64).
+__device__ __forceinline__ int nth_served(int id, int T, int rank) {
+    const int lane = threadIdx.x & 63;
+    bool seen = lane >= T;
+    for (int u = 0; u < T; ++u) seen |= u < lane && __builtin_amdgcn_readlane(id, u) == id;
+    const unsigned long long firsts = __ballot(!seen);
+    const unsigned long long at = __ballot(!seen && __popcll(firsts & ((1ull << lane) - 1ull)) == rank);
+    return at ? __builtin_amdgcn_readlane(id, __ffsll(at) - 1) : -1;
+}
+
+// 16-byte units of a 16 x 32 operand out of fragment order (blocks of 16 reduction elements x 32 features):
+// lane's feature n (of 32) and reduction units (lane / 16) of 8 elements each.
+__device__ __forceinline__ int unit_of(int lane, int n) { return (lane >> 5) * 64 + ((lane >> 4) & 1) * 32 + n; }
+
+template <int NEB, bool STREAM>
+__global__ __launch_bounds__(256, 2) void dense_first_kernel_served(const smoe_route_args a, const float* __restrict__ part,
+                                                                    const float* __restrict__ sqp, const uint4* __restrict__ W1,
+                                                                    uint16_t* __restrict__ h, int d_ff, const int32_t* __restrict__ phys,
+                                                                    int fbw) {
+    using S = smoe_route_shape<NEB, 1>;
+    constexpr int NS = S::NS, EP = S::EP, G = 16;
+    extern __shared__ __align__(16) float smem[];
+    __shared__ int32_t s_slot[FEW_T];
+    uint16_t* xs = (uint16_t*)smem;                        // [T][ldx]
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int cpr = a.d >> 3, pieces = a.T * cpr, ldx = a.d + 8;
+    for (int i0 = tid; i0 < pieces; i0 += 4 * 256) {
+        u32x4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = ((const u32x4*)a.x)[min(i0 + q * 256, pieces - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = min(i0 + q * 256, pieces - 1), r = i / cpr, c = i - r * cpr;
+            *(u32x4*)&xs[r * ldx + c * 8] = v[q];
+        }
+    }
+    const int sub = lane & 15;
+    int sl[smoe_route_chunks(NEB)][4];
+    smoe_route_slots<NEB>(sl, a, sub);
+    for (int t0 = wave * 4; t0 < a.T; t0 += 16) {
+        const int t = t0 + (lane >> 4), tc = min(t, a.T - 1);
+        const smoe_choice c = smoe_route_token<NEB, NS>(part + tc * EP, FEW_T * EP, sl, a.E, a.gate_mode, sub);
+        if (sub == 0 && t < a.T) {
+            s_slot[t] = c.slot;
+            if (blockIdx.x == 0) smoe_store_choice<NS>(a, t, c, sqp + t, FEW_T);
+        }
+    }
+    __syncthreads();
+    const int nhb = d_ff >> 4, nst = a.d >> 5, ftiles = (nhb + fbw - 1) / fbw;
+    const int rank = blockIdx.x / ftiles, hb = (blockIdx.x - rank * ftiles) * fbw + wave;   // hb: 16 features
+    const int slot = nth_served(s_slot[min(lane, a.T - 1)], a.T, rank);
+    if (slot < 0 || wave >= fbw || hb >= nhb) return;      // (no barrier follows)
+    const uint4* wp = W1 + ((size_t)(phys ? phys[slot] : slot) * (d_ff >> 5) + (hb >> 1)) * (a.d >> 4) * 64 +
+                      unit_of(lane, (hb & 1) * 16 + (lane & 15));
+    uint4 wA[G], wB[G];
+    auto fetch = [&](uint4 (&w)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {                      // past the end: reloaded, not used
+            const uint4* src = wp + (size_t)min(g0 + i, nst - 1) * 128;
+            w[i] = STREAM ? smoe_load_stream(src) : *src;
+        }
+    };
+    smoe_f32x4 acc;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = 0.f;
+    // columns past the batch repeat its last row, unstored
+    const uint16_t* xrow = xs + min(lane & 15, a.T - 1) * ldx + (lane >> 4) * 8;
+    auto consume = [&](uint4 (&w)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            if (g0 + i >= nst) break;                      // uniform
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(smoe_frag(w[i]), smoe_frag(*(const uint4*)(xrow + (g0 + i) * 32)), acc, 0, 0, 0);
+        }
+    };
+    fetch(wA, 0);
+    for (int g0 = 0; g0 < nst; g0 += 2 * G) {
+        fetch(wB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wA, g0);
+        if (g0 + 2 * G < nst) fetch(wA, g0 + 2 * G);
+        consume(wB, g0 + G);
+    }
+    // accumulator register i of lane l: feature 4*(l/16) + i, token l%16
+    // (h[slot][feature / 8][T tokens] here: a line holds as many reduction units of the batch as fit)
+    const int tok = lane & 15;
+    if (tok >= a.T) return;
+    uint2 o;
+    o.x = (uint32_t)smoe_f32_to_bf16(fmaxf(acc[0], 0.f)) | ((uint32_t)smoe_f32_to_bf16(fmaxf(acc[1], 0.f)) << 16);
+    o.y = (uint32_t)smoe_f32_to_bf16(fmaxf(acc[2], 0.f)) | ((uint32_t)smoe_f32_to_bf16(fmaxf(acc[3], 0.f)) << 16);
+    *(uint2*)(h + (((size_t)slot * (d_ff >> 3) + hb * 2 + (lane >> 5)) * a.T + tok) * 8 + ((lane >> 4) & 1) * 4) = o;
 }
 
 // ---------------------------------------------------------------------------
@@ -440,6 +605,89 @@ __global__ __launch_bounds__(256, 2) void decode_second_stream_kernel(const seco
 template <int MAXNB, bool STREAM>
 __global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<MAXNB, STREAM, true>(a); }
 
+// Few tokens: workgroup (served slot, 16 features, or 8 of them while that leaves compute units idle: the lanes of
+// the other 8 then read the same weights again).  4 waves split the reduction as above, each with 24 loads in flight.
+template <bool STREAM>
+__global__ __launch_bounds__(256, 2) void dense_second_kernel_served(const second_args a, int width) {
+    constexpr int KSPLIT = 4, G = 12;
+    __shared__ __align__(16) float red[(KSPLIT - 1) * 4 * 64];
+    if (blockIdx.x == 0) {
+        finish_small(a.tail, a.slot, a.T, a.E, a.K);
+        return;
+    }
+    const int tid = threadIdx.x, part = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int cols = a.N / width, rank = (blockIdx.x - 1) / cols, f0 = ((blockIdx.x - 1) - rank * cols) * width;
+    const int id = a.slot[min(lane, a.T - 1)];
+    const int slot = nth_served(id, a.T, rank);
+    if (slot < 0) return;                                  // uniform over the workgroup
+    const int nrb = a.R >> 4, per = (nrb + KSPLIT - 1) / KSPLIT;
+    const int kb_lo = min(part * per, nrb), nkb = min(kb_lo + per, nrb) - kb_lo, nst = (nkb + 1) >> 1;   // 16-deep blocks; steps of two
+    const uint4* wp = a.W2 + (((size_t)(a.phys ? a.phys[slot] : slot) * (a.N >> 5) + (f0 >> 5)) * nrb + kb_lo) * 64 +
+                      unit_of(lane, (f0 & 31) + (lane & (width - 1)));
+    // the slot's tokens, packed into columns; columns past the list repeat its last token
+    const unsigned long long mine = __ballot(lane < a.T && id == slot);
+    const int n = __popcll(mine), col = lane & 15;
+    int tok = 0;                                           // the col-th set bit
+    for (int u = 0; u < a.T; ++u) tok = ((mine >> u) & 1) && __popcll(mine & ((1ull << u) - 1ull)) == min(col, n - 1) ? u : tok;
+    const uint4* xp = (const uint4*)a.h + ((size_t)slot * (a.R >> 3) + 2 * kb_lo + (lane >> 4)) * a.T + tok;
+    uint4 wA[G], wB[G], xA[G], xB[G];
+    // A range of an odd number of blocks ends in the middle of a step: the lanes of its upper half then read the lower
+    // half again and multiply zeros.
+    auto fetch = [&](uint4 (&w)[G], uint4 (&x)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {                      // past the end: reloaded, not used
+            const int st = min(g0 + i, nst - 1);
+            const bool half = 2 * st + 1 >= nkb && lane >= 32;
+            const uint4* src = wp + (size_t)st * 128 - (half ? 64 : 0);
+            w[i] = STREAM ? smoe_load_stream(src) : *src;
+            x[i] = xp[(ptrdiff_t)(st * 4 - (half ? 2 : 0)) * a.T];
+        }
+    };
+    smoe_f32x4 acc;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = 0.f;
+    auto consume = [&](uint4 (&w)[G], uint4 (&x)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            if (g0 + i >= nst) break;                      // uniform
+            const bool half = 2 * (g0 + i) + 1 >= nkb && lane >= 32;
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(smoe_frag(w[i]), smoe_frag(half ? make_uint4(0, 0, 0, 0) : x[i]), acc, 0, 0, 0);
+        }
+    };
+    const int f = f0 + 4 * (lane >> 4);                    // this lane's four features
+    const bool store = part == 0 && 4 * (lane >> 4) < width && col < n;
+    if (nst > 0) fetch(wA, xA, 0);
+    float gmul = 1.f;
+    uint2 rres = make_uint2(0, 0);
+    if (store) {                                           // asked for now, used after the loop
+        gmul = a.gate[tok];
+        if (a.residual) rres = *(const uint2*)(a.residual + (size_t)tok * a.N + f);
+    }
+    for (int g0 = 0; g0 < nst; g0 += 2 * G) {
+        fetch(wB, xB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wA, xA, g0);
+        if (g0 + 2 * G < nst) fetch(wA, xA, g0 + 2 * G);
+        consume(wB, xB, g0 + G);
+    }
+    if (part > 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[((part - 1) * 4 + i) * 64 + lane] = acc[i];
+    }
+    __syncthreads();
+    if (!store) return;
+#pragma unroll
+    for (int w2 = 0; w2 < KSPLIT - 1; ++w2)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += red[(w2 * 4 + i) * 64 + lane];
+    float v0 = acc[0], v1 = acc[1], v2 = acc[2], v3 = acc[3];
+    smoe_apply_gate(v0, v1, v2, v3, gmul, rres, a.residual != nullptr);
+    uint2 o;
+    o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
+    o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+    *(uint2*)(a.out + (size_t)tok * a.N + f) = o;
+}
+
 // 32-expert blocks rounded up to an instance of the router
 int router_instance(int E) { return E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8; }
 
@@ -464,19 +712,26 @@ int first_fbw(const smoe_config& c, double slots) {
     return fbw;
 }
 
-// True when the router gets a launch of its own in front of the first product, which then reads the weights
+// True when the router gets a launch (or two) in front of the first product, which then reads the weights
 // of the slots with a token only.  Beside the router every slot's first matrix is read, so what that costs is
-// the matrices of the slots that stay empty, at the 6 TB/s they stream with; what it saves is the router's
-// launch, 8 us up to 64 experts and 12 us above.  The line lies where the two meet, at 48 and 72 MB.  Measured
-// per layer in stacks of 0.7 GB and more (beside the router / launch of its own, MB for nothing):
-//   768 x 3072, E = 64    K = 16 T = 1 24 / 20 us (71 MB), T = 16 29 / 34 us (27 MB); K = 64 T = 1 61 / 23 us
-//                         (297 MB), T = 33 88 / 66 us (180 MB); K = 32 T = 32 48 / 48 us (55 MB)
-//   768 x 3072, E = 128   K = 32 T = 16 44 / 40 us (91 MB), T = 32 51 / 55 us (55 MB); K = 128 T = 1 114 / 31 us
-//                         (599 MB), T = 96 200 / 163 us (284 MB)
-//   1024 x 4096, E = 128  K = 32 T = 1 62 / 29 us (260 MB), T = 64 108 / 108 us (35 MB)
-//   512 x 2048, E = 200   K = 100 T = 64 74 / 64 us (110 MB); at 256 x 1024 T = 1 21 / 23 us (52 MB)
+// the matrices of the slots that stay empty, at the 6 TB/s they stream with.
+// More than 16 tokens: what it saves is the router's launch, 8 us up to 64 experts and 12 us above.  The line lies
+// where the two meet, at 48 and 72 MB.  Measured per layer in stacks of 0.7 GB and more (beside the router / launch of
+// its own, MB for nothing):
+//   768 x 3072, E = 64    K = 64 T = 33 88 / 66 us (180 MB); K = 32 T = 32 48 / 48 us (55 MB)
+//   768 x 3072, E = 128   K = 32 T = 32 51 / 55 us (55 MB); K = 128 T = 96 200 / 163 us (284 MB)
+//   1024 x 4096, E = 128  K = 32 T = 64 108 / 108 us (35 MB)
+//   512 x 2048, E = 200   K = 100 T = 64 74 / 64 us (110 MB)
+// Up to 16 tokens the launches are those of route_partial_kernel, whose workgroups repeat the end of the router and
+// the staging for every slot: the line rises with T, 16 MB + 2 MB a token (beside the router / launches of its own):
+//   768 x 3072, E = 64    K = 16 T = 1 22.5 / 14.6 us (71 MB), T = 10 26.5 / 24.7 us (40 MB), T = 16 28.7 / 30.4 us (27 MB);
+//                         K = 10 T = 4 17.8 / 17.2 us (31 MB), T = 6 18.1 / 20.1 us (25 MB)
+//   768 x 3072, E = 32    K = 8 T = 1 16.3 / 14.1 us (33 MB), T = 6 16.7 / 17.7 us (17 MB); E = 8 K = 4 T = 1 13.7 / 14.0 us (14 MB)
+//   1024 x 4096, E = 64   K = 16 T = 16 45.0 / 42.0 us (48 MB); E = 128 K = 16 T = 16 51.0 / 51.7 us (48 MB)
+//   512 x 2048, E = 64    K = 20 T = 6 18.4 / 16.5 us (31 MB), T = 13 20.0 / 21.9 us (22 MB)
 bool sparse(const smoe_config& c, int T) {
     const double unused = (c.K - served_slots(c, T)) * 2.0 * c.d_model * c.d_ff;
+    if (T <= FEW_T) return unused > 16e6 + 2e6 * T;
     return unused > (c.E <= 64 ? 48e6 : 72e6);
 }
 
@@ -525,6 +780,30 @@ int launch_first_served(const smoe_layer* L, const smoe_route_args& ra, bool str
     return smoe_check_hip(hipGetLastError(), "smoe_forward: first product launch");
 }
 
+// Few tokens on few slots: the three launches of route_partial_kernel's comment.
+template <int NEB>
+int launch_few(const smoe_layer* L, const smoe_route_args& ra, bool stream, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    using S = smoe_route_shape<NEB, 1>;
+    const smoe_config& c = L->cfg;
+    float* part = (float*)L->d_route_part;
+    float* sqp = part + (size_t)S::NS * FEW_T * S::EP;
+    hipLaunchKernelGGL(route_partial_kernel<NEB>, dim3(S::NS * ((c.E + 31) / 32)), dim3(64), 0, s, ra, part, sqp);
+    if (int rc = smoe_check_hip(hipGetLastError(), "smoe_forward: router launch")) return rc;
+    const size_t lds = (size_t)ra.T * (c.d_model + 8) * 2;
+    const int nhb = c.d_ff >> 4, most = std::min(ra.T, c.K);
+    const double slots = std::min<double>(served_slots(c, ra.T), most);
+    int fbw = 4;                                           // waves of a workgroup that stream: fewer while compute units idle
+    while (fbw > 1 && slots * ((nhb + fbw - 1) / fbw) < 192) fbw >>= 1;
+    const dim3 grid(most * ((nhb + fbw - 1) / fbw));
+    const int32_t* phys = c.spare_slots > 0 ? L->d_phys : nullptr;
+    auto kern = stream ? dense_first_kernel_served<NEB, true> : dense_first_kernel_served<NEB, false>;
+    static smoe_lds_raised raised[2];
+    if (int rc = raised[stream].ensure((const void*)kern, lds, LDS_LIMIT)) return rc;
+    smoe_launch_timed_lds(kern, grid, dim3(256), lds, s, e0, e1, ra, (const float*)part, (const float*)sqp, (const uint4*)L->slot_w1,
+                          (uint16_t*)L->d_hidden, c.d_ff, phys, fbw);
+    return smoe_check_hip(hipGetLastError(), "smoe_forward: first product launch");
+}
+
 }  // namespace
 
 int smoe_lds_raised::ensure(const void* kern, size_t lds, int limit) {
@@ -553,6 +832,14 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
     const smoe_route_args ra{x, (const uint4*)L->d_router_split, L->router_w, L->d_expert_to_slot, T, c.d_model, c.E, c.gate_mode,
                              orig_expert, orig_gate, slot, gate, xnorm, nullptr, c.K};
     const bool stream = smoe_weights_outgrow_cache(L);
+    if (sparse(c, T) && T <= FEW_T) {
+        switch (router_instance(c.E)) {
+            case 1: return launch_few<1>(L, ra, stream, s, e0, e1);
+            case 2: return launch_few<2>(L, ra, stream, s, e0, e1);
+            case 4: return launch_few<4>(L, ra, stream, s, e0, e1);
+            default: return launch_few<8>(L, ra, stream, s, e0, e1);
+        }
+    }
     if (sparse(c, T)) {
         if (int rc = smoe_launch_route(L, x, T, orig_expert, orig_gate, slot, gate, xnorm, nullptr, s)) return rc;
         if (T <= 32) return launch_first_served<1>(L, ra, stream, s, e0, e1);
@@ -572,8 +859,16 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
     const smoe_config& c = L->cfg;
     const second_args a{(const uint16_t*)L->d_hidden, (const uint4*)L->slot_w2, slot_of, T, c.E, c.K, c.d_ff, c.d_model,
                         c.spare_slots > 0 ? L->d_phys : nullptr, gate, residual, out, L->tail};
-    const dim3 grid(c.K * (c.d_model >> 5) + 1);
     const bool stream = smoe_weights_outgrow_cache(L);
+    if (sparse(c, T) && T <= FEW_T) {
+        const int most = std::min(T, c.K);
+        const int width = most * (c.d_model >> 3) <= 256 ? 8 : 16;
+        auto few = stream ? dense_second_kernel_served<true> : dense_second_kernel_served<false>;
+        smoe_launch_timed(few, dim3(most * (c.d_model / width) + 1), dim3(256), s, L->prof_ev[2], L->prof_ev[3], a, width);
+        L->tail = smoe_step_tail{};                        // the caller's pointers are not kept
+        return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");
+    }
+    const dim3 grid(c.K * (c.d_model >> 5) + 1);
     auto kern = T <= 32 ? (stream ? decode_second_stream_kernel<1> : decode_second_kernel<1>)
                         : (stream ? decode_second_stream_kernel<2> : decode_second_kernel<2>);
     if (sparse(c, T))
@@ -586,9 +881,11 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
 
 std::string smoe_describe_decode(const smoe_layer* L, int T, bool first) {
     const std::string st = smoe_weights_outgrow_cache(L) ? "_stream" : "";
-    if (sparse(L->cfg, T))
-        return std::string(first ? "dense_first_kernel<" : "dense_second_kernel<") +
-               (T <= 32 ? "1, " : !first || T <= 64 ? "2, " : "4, ") + (st.empty() ? "false>" : "true>");
+    const std::string tf = st.empty() ? "false>" : "true>";
+    if (sparse(L->cfg, T) && T <= FEW_T) {
+        return (first ? "dense_first_kernel_served<" + std::to_string(router_instance(L->cfg.E)) + ", " : std::string("dense_second_kernel_served<")) + tf;
+    }
+    if (sparse(L->cfg, T)) return std::string(first ? "dense_first_kernel<" : "dense_second_kernel<") + (T <= 32 ? "1, " : !first || T <= 64 ? "2, " : "4, ") + tf;
     if (!first) return "decode_second" + st + "_kernel<" + (T <= 32 ? "1>" : "2>");
     return "decode_first" + st + "_kernel<" + std::to_string(router_instance(L->cfg.E)) + ", " + (T <= 32 ? "1>" : T <= 64 ? "2>" : "4>");
 }

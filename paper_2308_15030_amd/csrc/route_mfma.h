@@ -69,13 +69,101 @@ struct smoe_route_shape {
     }
 };
 
+// What the router finds for one token.
+struct smoe_choice {
+    int expert, slot;
+    float orig_gate, gate;
+};
+
+constexpr int smoe_route_chunks(int NEB) { return (NEB * 32 + 63) / 64; }   // chunks of 64 experts; a lane of the epilogue has 4 of each
+
+// Slots of this lane's experts, -1 if not resident; sub = the lane's place among the 16 of its token.
+template <int NEB>
+__device__ __forceinline__ void smoe_route_slots(int (&sl)[smoe_route_chunks(NEB)][4], const smoe_route_args& a, int sub) {
+#pragma unroll
+    for (int c = 0; c < smoe_route_chunks(NEB); ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = 64 * c + 4 * sub + j;
+            sl[c][j] = e < a.E ? a.e2s[e] : -1;
+        }
+}
+
+// Choice of one token by its 16 lanes: row = its partial logits of slice 0, those of the next slice slice_stride further.
+template <int NEB, int NS>
+__device__ __forceinline__ smoe_choice smoe_route_token(const float* row, int slice_stride, const int (&sl)[smoe_route_chunks(NEB)][4],
+                                                        int E, int gate_mode, int sub) {
+    constexpr int EC = smoe_route_chunks(NEB), EP = NEB * 32;
+    float v[EC][4];
+#pragma unroll
+    for (int c = 0; c < EC; ++c) {
+        const int e = 64 * c + 4 * sub;
+        const float* col = row + min(e, EP - 4);
+        float4 s = *(const float4*)col;
+#pragma unroll
+        for (int q = 1; q < NS; ++q) {                     // fixed order
+            const float4 o = *(const float4*)(col + q * slice_stride);
+            s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+        }
+        v[c][0] = s.x; v[c][1] = s.y; v[c][2] = s.z; v[c][3] = s.w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[c][j] = e + j < E ? v[c][j] : -INFINITY;   // past E: never wins, adds exp(-inf) = 0
+    }
+    float best = -INFINITY, rbest = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < EC; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            best = fmaxf(best, v[c][j]);
+            rbest = fmaxf(rbest, sl[c][j] >= 0 ? v[c][j] : -INFINITY);
+        }
+    best = smoe_row_max(best);
+    rbest = smoe_row_max(rbest);
+    int bi = 0x7fffffff, rb = 0x7fffffff;                  // lowest expert id that holds the maximum; (id, slot) of the masked one
+    float z = 0.f, zr = 0.f;
+#pragma unroll
+    for (int c = EC - 1; c >= 0; --c)
+#pragma unroll
+        for (int j = 3; j >= 0; --j) {
+            const int e = 64 * c + 4 * sub + j;
+            bi = v[c][j] == best ? e : bi;
+            rb = sl[c][j] >= 0 && v[c][j] == rbest ? (e << 8 | sl[c][j]) : rb;
+            const float p = expf(v[c][j] - best);
+            z += p;
+            zr += sl[c][j] >= 0 ? p : 0.f;
+        }
+    bi = smoe_row_min(bi);
+    rb = smoe_row_min(rb);
+    z = smoe_row_sum(z);
+    if (gate_mode == SMOE_GATE_RENORM) zr = smoe_row_sum(zr);
+    smoe_choice r;
+    r.expert = bi;
+    r.slot = rb == 0x7fffffff ? 0 : rb & 255;              // a token whose logits are all NaN: slot 0, a NaN gate
+    r.orig_gate = 1.0f / z;
+    r.gate = expf(rbest - best) / (gate_mode == SMOE_GATE_RENORM ? zr : z);
+    return r;
+}
+
+// Writes a token's results; sq = its partial sums of squares, stride apart, two halves of every slice.
+template <int NS>
+__device__ __forceinline__ void smoe_store_choice(const smoe_route_args& a, int tok, const smoe_choice& c, const float* sq, int stride) {
+    float ss = 0.f;
+#pragma unroll
+    for (int q = 0; q < 2 * NS; ++q) ss += sq[q * stride];
+    a.orig_expert[tok] = c.expert;
+    a.orig_gate[tok] = c.orig_gate;
+    a.slot[tok] = c.slot;
+    a.gate[tok] = c.gate;
+    a.xnorm[tok] = sqrtf(ss);
+}
+
 // The partial logits of the 8 waves meet in LDS and every token's results are written.
 template <int NEB, int TB>
 __device__ __forceinline__ void smoe_route_finish(const int block, const smoe_route_args& a,
                                                   smoe_f32x16 (&acc)[smoe_route_shape<NEB, TB>::NEBH][TB], float (&sq)[TB],
                                                   float* smem) {
     using S = smoe_route_shape<NEB, TB>;
-    constexpr int NS = S::NS, NEBH = S::NEBH, EP = S::EP, LDP = S::LDP, RT = SMOE_RT, NTOK = S::NTOK;
+    constexpr int NS = S::NS, NEBH = S::NEBH, LDP = S::LDP, RT = SMOE_RT, NTOK = S::NTOK;
     float* part = smem;                                    // [NS][NTOK][LDP] partial logits
     float* sqp = smem + NS * NTOK * LDP;                   // [NS][2 halves][NTOK] partial sums of squares
     __shared__ int32_t s_hist[TB * 256];                   // tokens per block and slot
@@ -84,16 +172,9 @@ __device__ __forceinline__ void smoe_route_finish(const int block, const smoe_ro
     const int tw0 = block * NTOK, neb = (a.E + 31) >> 5;
     if (a.hist32)
         for (int i = tid; i < TB * 256; i += 512) s_hist[i] = 0;
-    constexpr int EC = (EP + 63) / 64;                     // chunks of 64 experts; a lane of the epilogue has 4 of each
     const int sub = lane & 15;                             // the 16 lanes of a token
-    int sl[EC][4];                                         // slots of this lane's experts, -1 if not resident
-#pragma unroll
-    for (int c = 0; c < EC; ++c)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = 64 * c + 4 * sub + j;
-            sl[c][j] = e < a.E ? a.e2s[e] : -1;
-        }
+    int sl[smoe_route_chunks(NEB)][4];
+    smoe_route_slots<NEB>(sl, a, sub);
 
     __syncthreads();                                       // the partial logits take the staged tokens' place
     // accumulator register i of lane l: expert 8*(i/4) + 4*(l/32) + i%4 (+32 per block), token l%32
@@ -116,59 +197,10 @@ __device__ __forceinline__ void smoe_route_finish(const int block, const smoe_ro
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
         const int t = tb * RT + wave * 4 + (lane >> 4), tok = tw0 + t;
-        float v[EC][4];
-#pragma unroll
-        for (int c = 0; c < EC; ++c) {
-            const int e = 64 * c + 4 * sub;
-            const float* col = part + t * LDP + min(e, EP - 4);
-            float4 s = *(const float4*)col;
-#pragma unroll
-            for (int q = 1; q < NS; ++q) {                 // fixed order
-                const float4 o = *(const float4*)(col + q * NTOK * LDP);
-                s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
-            }
-            v[c][0] = s.x; v[c][1] = s.y; v[c][2] = s.z; v[c][3] = s.w;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[c][j] = e + j < a.E ? v[c][j] : -INFINITY;   // past E: never wins, adds exp(-inf) = 0
-        }
-        float best = -INFINITY, rbest = -INFINITY;
-#pragma unroll
-        for (int c = 0; c < EC; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                best = fmaxf(best, v[c][j]);
-                rbest = fmaxf(rbest, sl[c][j] >= 0 ? v[c][j] : -INFINITY);
-            }
-        best = smoe_row_max(best);
-        rbest = smoe_row_max(rbest);
-        int bi = 0x7fffffff, rb = 0x7fffffff;              // lowest expert id that holds the maximum; (id, slot) of the masked one
-        float z = 0.f, zr = 0.f;
-#pragma unroll
-        for (int c = EC - 1; c >= 0; --c)
-#pragma unroll
-            for (int j = 3; j >= 0; --j) {
-                const int e = 64 * c + 4 * sub + j;
-                bi = v[c][j] == best ? e : bi;
-                rb = sl[c][j] >= 0 && v[c][j] == rbest ? (e << 8 | sl[c][j]) : rb;
-                const float p = expf(v[c][j] - best);
-                z += p;
-                zr += sl[c][j] >= 0 ? p : 0.f;
-            }
-        bi = smoe_row_min(bi);
-        rb = smoe_row_min(rb);
-        z = smoe_row_sum(z);
-        if (a.gate_mode == SMOE_GATE_RENORM) zr = smoe_row_sum(zr);
+        const smoe_choice c = smoe_route_token<NEB, NS>(part + t * LDP, NTOK * LDP, sl, a.E, a.gate_mode, sub);
         if (sub == 0 && tok < a.T) {
-            float ss = 0.f;
-#pragma unroll
-            for (int q = 0; q < 2 * NS; ++q) ss += sqp[q * NTOK + t];
-            const int sv = rb == 0x7fffffff ? 0 : rb & 255;   // a token whose logits are all NaN: slot 0, a NaN gate
-            a.orig_expert[tok] = bi;
-            a.orig_gate[tok] = 1.0f / z;
-            a.slot[tok] = sv;
-            a.gate[tok] = expf(rbest - best) / (a.gate_mode == SMOE_GATE_RENORM ? zr : z);
-            a.xnorm[tok] = sqrtf(ss);
-            if (a.hist32) atomicAdd(&s_hist[tb * 256 + sv], 1);   // integer: order cannot matter
+            smoe_store_choice<NS>(a, tok, c, sqp + t, NTOK);
+            if (a.hist32) atomicAdd(&s_hist[tb * 256 + c.slot], 1);   // integer: order cannot matter
         }
     }
     if (a.hist32) {                                        // tokens per slot in each block, for the ranking that follows
@@ -177,6 +209,35 @@ __device__ __forceinline__ void smoe_route_finish(const int block, const smoe_ro
             const int tb = i / a.K, k = i - tb * a.K;
             if (tw0 + tb * RT < a.T) a.hist32[((size_t)block * TB + tb) * a.K + k] = s_hist[tb * 256 + k];
         }
+    }
+}
+
+// Eight fp32 weights -> their hi, mid and lo pieces as three operands of a bf16 product.
+__device__ __forceinline__ void smoe_cut_weights(const uint4 (&w)[2], uint4 (&pc)[3]) {
+    const uint32_t f[8] = {w[0].x, w[0].y, w[0].z, w[0].w, w[1].x, w[1].y, w[1].z, w[1].w};
+    uint32_t p[3][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float u = __uint_as_float(f[2 * q]), v = __uint_as_float(f[2 * q + 1]);
+#pragma unroll
+        for (int s3 = 0; s3 < 3; ++s3) {                   // upper halves packed; the remainders are exact
+            p[s3][q] = __builtin_amdgcn_perm(__float_as_uint(v), __float_as_uint(u), 0x07060302u);
+            u -= __uint_as_float(__float_as_uint(u) & 0xFFFF0000u);
+            v -= __uint_as_float(__float_as_uint(v) & 0xFFFF0000u);
+        }
+    }
+#pragma unroll
+    for (int s3 = 0; s3 < 3; ++s3) pc[s3] = make_uint4(p[s3][0], p[s3][1], p[s3][2], p[s3][3]);
+}
+
+// Adds the squares of eight bf16 values to sq, in order.
+__device__ __forceinline__ void smoe_add_squares(float& sq, const uint4& xv) {
+    const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float l = __uint_as_float(xw[q] << 16), h = __uint_as_float(xw[q] & 0xFFFF0000u);
+        sq = fmaf(l, l, sq);
+        sq = fmaf(h, h, sq);
     }
 }
 
@@ -266,38 +327,19 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
                     uint4 xv = *(const uint4*)(xrow + tb * RT * ldx + max(min(g0 + i, n - 1), 0) * 16);
                     if (g0 + i >= n) xv = make_uint4(0, 0, 0, 0);   // steps past the end multiply by a zero operand
                     xf[tb] = smoe_frag(xv);
-                    if (group == 0) {                      // the groups read the same tokens: one of them adds the squares
-                        const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float l = __uint_as_float(xw[q] << 16), h = __uint_as_float(xw[q] & 0xFFFF0000u);
-                            sq[tb] = fmaf(l, l, sq[tb]);
-                            sq[tb] = fmaf(h, h, sq[tb]);
-                        }
-                    }
+                    if (group == 0) smoe_add_squares(sq[tb], xv);   // the groups read the same tokens: one of them adds the squares
                 }
 #pragma unroll
                 for (int b = 0; b < NEBH; ++b) {
-                    const uint32_t f[8] = {w[i][b][0].x, w[i][b][0].y, w[i][b][0].z, w[i][b][0].w,
-                                           w[i][b][1].x, w[i][b][1].y, w[i][b][1].z, w[i][b][1].w};
-                    uint32_t pc[3][4];                     // hi, mid, lo of four pairs
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float u = __uint_as_float(f[2 * q]), v = __uint_as_float(f[2 * q + 1]);
-#pragma unroll
-                        for (int s3 = 0; s3 < 3; ++s3) {   // upper halves packed; the remainders are exact
-                            pc[s3][q] = __builtin_amdgcn_perm(__float_as_uint(v), __float_as_uint(u), 0x07060302u);
-                            u -= __uint_as_float(__float_as_uint(u) & 0xFFFF0000u);
-                            v -= __uint_as_float(__float_as_uint(v) & 0xFFFF0000u);
-                        }
-                    }
+                    uint4 pc[3];
+                    smoe_cut_weights(w[i][b], pc);
                     // smallest terms first, so they are not absorbed by the large partial sums
 #pragma unroll
                     for (int s3 = 2; s3 >= 0; --s3)
 #pragma unroll
                         for (int tb = 0; tb < TB; ++tb)
                             acc[b][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                smoe_frag(make_uint4(pc[s3][0], pc[s3][1], pc[s3][2], pc[s3][3])), xf[tb], acc[b][tb], 0, 0, 0);
+                                smoe_frag(pc[s3]), xf[tb], acc[b][tb], 0, 0, 0);
                 }
             }
         };

@@ -81,6 +81,7 @@ struct smoe_layer {
     bool dev_update_host = false;            // ... and whether a bank among them is pinned host memory
     bool load_from_host = false;             // set around a load's launch: its source is pinned host memory
     void* d_router_split = nullptr;          // bf16 path: router weights in matrix-operand order
+    void* d_route_part = nullptr;            // small batches: partial logits and sums of squares of at most SMOE_FEW_T tokens
     bool router_split_done = false;          // made by the first smoe_route after a bind
 
     hipEvent_t prof_ev[4] = {nullptr, nullptr, nullptr, nullptr};   // one-shot FFN profiling events
@@ -96,7 +97,7 @@ struct smoe_layer {
 };
 
 struct smoe_ws_layout {
-    size_t e2s, s2e, phys, dplan, hist, hist32, hidden, rsplit, norm, stage, total;
+    size_t e2s, s2e, phys, dplan, hist, hist32, hidden, rsplit, rpart, norm, stage, total;
 };
 smoe_ws_layout smoe_ws_plan(const smoe_config& c);
 
@@ -108,6 +109,7 @@ inline size_t smoe_elem_size(int dtype) { return dtype == SMOE_BF16 ? 2 : 4; }
 // whose rows (8 elements of padding each) fit the dynamic LDS of a compute unit; the path keeps the hidden
 // activations of every slot for every token of the batch, in blocks of 32 tokens.
 constexpr int SMOE_SMALL_T = 128;
+constexpr int SMOE_FEW_T = 16;                             // ... and at most this many take its launches for few tokens
 constexpr int SMOE_SMALL_LDS = 160 * 1024 - 2048;          // the rest covers the static tables
 inline size_t smoe_small_batch_rows(const smoe_config& c) {
     const int fit = SMOE_SMALL_LDS / (2 * (c.d_model + 8));
