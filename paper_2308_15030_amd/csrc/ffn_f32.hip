@@ -19,7 +19,9 @@
 // 21 us, so the feature range is narrowed until the items fill the chip.
 //
 // Both products, four slots of 768 x 3072 (LDS tiles of 32 x 64 with vector FMAs before): T = 512
-// 280 -> 77 us (63 TFLOP/s), T = 32 23 us, T = 4 16 us (75 MB of weights: 4.7 TB/s).
+// 280 -> 68 us (71 TFLOP/s), T = 32 23 us, T = 4 16 us (75 MB of weights: 4.7 TB/s).  What bounds T = 512 now: an item of
+// the first product takes 295 KB through its compute unit (8.4 us at the 35 GB/s of a mix of cached and missing lines) for
+// 5.1 us of products.  Items of 64 tokens halve that per product and gave nothing (T = 512 35 us, T = 1024 67 and 54 us).
 
 #include <algorithm>
 #include <cstdio>
@@ -159,17 +161,17 @@ __device__ __forceinline__ void panel_tile(const float* const (&wp)[NC], const f
 }
 
 // FIRST: row-major x in, ReLU, hidden activations out; else hidden activations in, row-major y out.
-// NC: 16-feature blocks of an item.
-template <bool FIRST, int NC>
-__global__ __launch_bounds__(PK_WAVES * 64) void panel_gemm_f32(
-    const float* __restrict__ X, const float* __restrict__ W, const int32_t* __restrict__ offsets,
-    const int32_t* __restrict__ phys, int nslots, int T, float* __restrict__ Y, int R, int N) {
-    __shared__ __align__(16) f32x4 red[PK_WAVES][2 * NC][64];
+// NC: 16-feature blocks of an item.  WAVES: 8, one part of the reduction each, or 4, which take two parts each
+// and add them.
+template <bool FIRST, int NC, int WAVES>
+__device__ __forceinline__ void panel_items(const float* __restrict__ X, const float* __restrict__ W, const int32_t* __restrict__ offsets,
+                                            const int32_t* __restrict__ phys, int nslots, int T, float* __restrict__ Y, int R, int N,
+                                            f32x4 (&red)[PK_WAVES][2 * NC][64]) {
+    constexpr int PARTS = PK_WAVES / WAVES;
     for_items(offsets, nslots, T, 32, (N + 16 * NC - 1) / (16 * NC), [&](int range, int slot, int m0, int m_end, int pm0) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, col = lane & 15;
     const int n0 = range * 16 * NC, p0 = n0 & ~(PW - 1), nw = min(PW, N - p0), rows = min(32, m_end - m0);
     const int units = R >> 2, steps = (units + 3) >> 2, per = (steps + PK_WAVES - 1) / PK_WAVES;
-    const int lo = min(wave * per, steps), n = min(lo + per, steps) - lo;
     const float* wp[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) wp[c] = W + ((size_t)phys[slot] * N + p0) * R + min(n0 - p0 + c * 16 + col, nw - 1) * 4;
@@ -184,40 +186,61 @@ __global__ __launch_bounds__(PK_WAVES * 64) void panel_gemm_f32(
     auto run = [&](auto nbc) {
         constexpr int NB = decltype(nbc)::value;
         const float* xq[NB];
-        f32x4 acc[NC][NB];
+        f32x4 sum[NC][NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            xq[b] = xp[b];
+        for (int b = 0; b < NB; ++b) xq[b] = xp[b];
+#pragma unroll 1
+        for (int i = 0; i < PARTS; ++i) {
+            const int lo = min((wave * PARTS + i) * per, steps), n = min(lo + per, steps) - lo;
+            f32x4 acc[NC][NB];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[c][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (n > 0) panel_tile<NB, NC>(wp, xq, nw * 4, xstep, lo * 4, n, units, acc);
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) sum[c][b] = i ? sum[c][b] + acc[c][b] : acc[c][b];
         }
-        if (n > 0) panel_tile<NB, NC>(wp, xq, nw * 4, xstep, lo * 4, n, units, acc);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) red[wave][c * 2 + b][lane] = acc[c][b];
+            for (int b = 0; b < NB; ++b) red[wave][c * 2 + b][lane] = sum[c][b];
     };
     if (two) run(std::integral_constant<int, 2>{});
     else run(std::integral_constant<int, 1>{});
     __syncthreads();
-    // wave w finishes (feature block, token block) w.  Accumulator register i of lane l: feature
-    // 4*(l/16) + i of the block, token l%16
-    const int c = wave >> 1, b = wave & 1;
-    const int r = b * 16 + col, f = n0 + c * 16 + (lane >> 4) * 4;
-    if (c < NC && (b == 0 || two) && r < rows && f < N) {
-        f32x4 v = red[0][wave][lane];
+    // wave w finishes (feature block, token block) w, and w + 4 where there are 4 waves.  Accumulator register i of
+    // lane l: feature 4*(l/16) + i of the block, token l%16
 #pragma unroll
-        for (int w = 1; w < PK_WAVES; ++w) v += red[w][wave][lane];
-        if (FIRST) {
+    for (int q = wave; q < 2 * NC; q += WAVES) {
+        const int c = q >> 1, b = q & 1;
+        const int r = b * 16 + col, f = n0 + c * 16 + (lane >> 4) * 4;
+        if ((b == 0 || two) && r < rows && f < N) {
+            f32x4 v = red[0][q][lane];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q], 0.f);
-            *(f32x4*)&Y[((size_t)(pm0 >> 5) * (N >> 2) + (f >> 2)) * 128 + r * 4] = v;
-        } else {
-            *(f32x4*)&Y[(size_t)(m0 + r) * N + f] = v;
+            for (int w = 1; w < WAVES; ++w) v += red[w][q][lane];
+            if (FIRST) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+                *(f32x4*)&Y[((size_t)(pm0 >> 5) * (N >> 2) + (f >> 2)) * 128 + r * 4] = v;
+            } else {
+                *(f32x4*)&Y[(size_t)(m0 + r) * N + f] = v;
+            }
         }
     }
     __syncthreads();                                       // the sums have been read
     });
+}
+
+template <bool FIRST, int NC>
+__global__ __launch_bounds__(PK_WAVES * 64) void panel_gemm_f32(
+    const float* __restrict__ X, const float* __restrict__ W, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ phys, int nslots, int T, float* __restrict__ Y, int R, int N) {
+    __shared__ __align__(16) f32x4 red[PK_WAVES][2 * NC][64];
+    if (blockDim.x == PK_WAVES * 64) panel_items<FIRST, NC, PK_WAVES>(X, W, offsets, phys, nslots, T, Y, R, N, red);
+    else panel_items<FIRST, NC, PK_WAVES / 2>(X, W, offsets, phys, nslots, T, Y, R, N, red);
 }
 
 // 16-feature blocks of an item: the widest range that still gives three items per four compute units.
@@ -228,16 +251,22 @@ int feature_blocks(const smoe_config& c, int T, int N) {
     return nc;
 }
 
-// As many workgroups as the chip keeps resident (one of 8 waves on each of 32 compute units of a die),
-// fewer if the items run out.
+// As many workgroups as the chip keeps resident, fewer if the items run out: one of 8 waves on each of the 32 compute
+// units of a die, or two of 4 waves where some compute units have two items and slots are filled.  Two that are at
+// different places of their items hide the wait for an item's first operands and the meeting of its parts.  8 -> 4 waves:
+// four slots of 768 x 3072, T = 1024 70 -> 60 and 59.5 -> 57 us, T = 512 first product 41 -> 36 us, T = 256 22.7 -> 21; two of
+// 300 x 1200, T = 256 first product 10.9 -> 9.2 us.  But with 216 items (T = 512 second product) 31.4 -> 33.0, and with few
+// tokens per slot, whose items are short, T = 128 13.4 -> 14.7 and eight slots of 512 x 2048, T = 64 11.4 -> 12.8.
 template <bool FIRST>
 void launch(const smoe_layer* L, const float* X, const void* W, const int32_t* offsets, int T, float* Y, int R, int N, hipStream_t s,
             hipEvent_t e0, hipEvent_t e1) {
-    const int K = L->cfg.K, nc = feature_blocks(L->cfg, T, N);
-    const long long items = (long long)((N + 16 * nc - 1) / (16 * nc)) * (T / 32 + std::min(K, T));   // upper bound
-    const dim3 grid(XCDS * (unsigned)std::min<long long>((items + XCDS - 1) / XCDS, 32));
+    const int K = L->cfg.K, nc = feature_blocks(L->cfg, T, N), ranges = (N + 16 * nc - 1) / (16 * nc);
+    const bool pairs = (long long)ranges * (T / 32 + (std::min(K, T) + 1) / 2) > 256 && T >= 48 * K;   // expected items
+    const long long items = (long long)ranges * (T / 32 + std::min(K, T));              // upper bound
+    const dim3 grid(XCDS * (unsigned)std::min<long long>((items + XCDS - 1) / XCDS, pairs ? 64 : 32));
     auto kern = nc == 4 ? panel_gemm_f32<FIRST, 4> : nc == 2 ? panel_gemm_f32<FIRST, 2> : panel_gemm_f32<FIRST, 1>;
-    smoe_launch_timed(kern, grid, dim3(PK_WAVES * 64), s, e0, e1, X, (const float*)W, offsets, (const int32_t*)L->d_phys, K, T, Y, R, N);
+    smoe_launch_timed(kern, grid, dim3(PK_WAVES * (pairs ? 32 : 64)), s, e0, e1, X, (const float*)W, offsets, (const int32_t*)L->d_phys, K, T, Y, R,
+                      N);
 }
 
 }  // namespace
