@@ -7,7 +7,7 @@
 // those of the sorted path), and no wait for the router.
 //
 //   first launch   one workgroup per 32 tokens is the router; all the others compute the first
-//                  product of EVERY slot on EVERY token: h[slot][feature / 8][token].  The price is
+//                  product of EVERY slot on EVERY token (hidden_layout).  The price is
 //                  the first matrices of slots nobody was routed to, what it buys is the router's
 //                  whole time.
 //   second launch  one workgroup ranks the tokens and adds the importance sums (it needs only what
@@ -30,6 +30,12 @@ constexpr int SMALL_T = SMOE_SMALL_T;                      // the token lists be
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int LDS_LIMIT = SMOE_SMALL_LDS;
 
+// Where the hidden activations of a small batch are: unit u (8 features, 16 bytes) of token t of slot k is unit
+// k * slot + t * token + u * unit.
+struct hidden_strides {
+    int slot, token, unit;
+};
+
 // ---------------------------------------------------------------------------
 // First product for every slot and every token.  fbw waves of the workgroup own one 32-feature
 // block each (all 8 waves stage the tokens); the token operands come from LDS (row pitch d_model + 8
@@ -39,10 +45,10 @@ constexpr int LDS_LIMIT = SMOE_SMALL_LDS;
 // served: the tokens' slots if the router has run already (then only slots with a token are computed), else NULL.
 template <int NBF, bool STREAM>
 __device__ __forceinline__ void dense_first_all(const uint16_t* __restrict__ x, const uint4* __restrict__ Wp, int T,
-                                                uint16_t* __restrict__ h, int R, int N, const int32_t* __restrict__ phys,
+                                                uint16_t* __restrict__ h, const hidden_strides hs, int R, int N, const int32_t* __restrict__ phys,
                                                 const int32_t* __restrict__ served, int block, int fbw, uint16_t* xs) {
     constexpr int G = 8;
-    const int nfb = N >> 5, nrb = R >> 4, ldx = R + 8, nb = (T + 31) >> 5;
+    const int nfb = N >> 5, nrb = R >> 4, ldx = R + 8;
     const int ftiles = (nfb + fbw - 1) / fbw;
     const int slot = block / ftiles, ftile = block - slot * ftiles;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -133,12 +139,11 @@ __device__ __forceinline__ void dense_first_all(const uint16_t* __restrict__ x, 
     consume(wA, g0);
     if (nrb - g0 > G) consume(wB, g0 + G);
     // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, token l%32
-    const int pitch = nb * 32;
 #pragma unroll
     for (int b = 0; b < NBF; ++b) {
         const int tok = b * 32 + (lane & 31);
         if (tok >= T) continue;
-        uint16_t* ydst = h + (((size_t)slot * (N >> 3) + fb * 4) * pitch + tok) * 8 + (lane >> 5) * 4;
+        uint16_t* ydst = h + ((size_t)slot * hs.slot + (size_t)tok * hs.token + (size_t)fb * 4 * hs.unit) * 8 + (lane >> 5) * 4;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const float v0 = fmaxf(acc[b][4 * g], 0.f), v1 = fmaxf(acc[b][4 * g + 1], 0.f), v2 = fmaxf(acc[b][4 * g + 2], 0.f),
@@ -146,42 +151,42 @@ __device__ __forceinline__ void dense_first_all(const uint16_t* __restrict__ x, 
             uint2 o;
             o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
             o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
-            *(uint2*)(ydst + (size_t)g * pitch * 8) = o;
+            *(uint2*)(ydst + (size_t)g * hs.unit * 8) = o;
         }
     }
 }
 
 // The router's workgroups come first: they are the launch's critical path.
 template <int NEB, int NBF, bool STREAM>
-__device__ __forceinline__ void decode_first_body(const smoe_route_args& ra, const uint4* W1, uint16_t* h, int d_ff,
+__device__ __forceinline__ void decode_first_body(const smoe_route_args& ra, const uint4* W1, uint16_t* h, const hidden_strides hs, int d_ff,
                                                   const int32_t* phys, int fbw) {
     extern __shared__ __align__(16) float smem[];
     const int routers = (ra.T + SMOE_RT - 1) / SMOE_RT;
     if ((int)blockIdx.x < routers) smoe_route_mfma_body<NEB, 1, false>(blockIdx.x, ra, smem);
-    else dense_first_all<NBF, STREAM>((const uint16_t*)ra.x, W1, ra.T, h, ra.d, d_ff, phys, nullptr, blockIdx.x - routers, fbw, (uint16_t*)smem);
+    else dense_first_all<NBF, STREAM>((const uint16_t*)ra.x, W1, ra.T, h, hs, ra.d, d_ff, phys, nullptr, blockIdx.x - routers, fbw, (uint16_t*)smem);
 }
 
 // Two kernels with one body: the second streams its weights past the caches.
 template <int NEB, int NBF>
 __global__ __launch_bounds__(512) void decode_first_kernel(const smoe_route_args ra, const uint4* __restrict__ W1, uint16_t* __restrict__ h,
-                                                           int d_ff, const int32_t* __restrict__ phys, int fbw) {
-    decode_first_body<NEB, NBF, false>(ra, W1, h, d_ff, phys, fbw);
+                                                           const hidden_strides hs, int d_ff, const int32_t* __restrict__ phys, int fbw) {
+    decode_first_body<NEB, NBF, false>(ra, W1, h, hs, d_ff, phys, fbw);
 }
 
 template <int NEB, int NBF>
 __global__ __launch_bounds__(512) void decode_first_stream_kernel(const smoe_route_args ra, const uint4* __restrict__ W1,
-                                                                  uint16_t* __restrict__ h, int d_ff, const int32_t* __restrict__ phys,
-                                                                  int fbw) {
-    decode_first_body<NEB, NBF, true>(ra, W1, h, d_ff, phys, fbw);
+                                                                  uint16_t* __restrict__ h, const hidden_strides hs, int d_ff,
+                                                                  const int32_t* __restrict__ phys, int fbw) {
+    decode_first_body<NEB, NBF, true>(ra, W1, h, hs, d_ff, phys, fbw);
 }
 
 // The same product behind a router launch of its own, for the slots that got tokens.
 template <int NBF, bool STREAM>
 __global__ __launch_bounds__(512) void dense_first_kernel(const uint16_t* __restrict__ x, const uint4* __restrict__ W1, int T,
-                                                          uint16_t* __restrict__ h, int d, int d_ff, const int32_t* __restrict__ phys,
-                                                          const int32_t* __restrict__ slot, int fbw) {
+                                                          uint16_t* __restrict__ h, const hidden_strides hs, int d, int d_ff,
+                                                          const int32_t* __restrict__ phys, const int32_t* __restrict__ slot, int fbw) {
     extern __shared__ __align__(16) float smem[];
-    dense_first_all<NBF, STREAM>(x, W1, T, h, d, d_ff, phys, slot, blockIdx.x, fbw, (uint16_t*)smem);
+    dense_first_all<NBF, STREAM>(x, W1, T, h, hs, d, d_ff, phys, slot, blockIdx.x, fbw, (uint16_t*)smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -339,13 +344,12 @@ __global__ __launch_bounds__(256, 2) void dense_first_kernel_served(const smoe_r
         consume(wB, g0 + G);
     }
     // accumulator register i of lane l: feature 4*(l/16) + i, token l%16
-    // (h[slot][feature / 8][T tokens] here: a line holds as many reduction units of the batch as fit)
     const int tok = lane & 15;
     if (tok >= a.T) return;
     uint2 o;
     o.x = (uint32_t)smoe_f32_to_bf16(fmaxf(acc[0], 0.f)) | ((uint32_t)smoe_f32_to_bf16(fmaxf(acc[1], 0.f)) << 16);
     o.y = (uint32_t)smoe_f32_to_bf16(fmaxf(acc[2], 0.f)) | ((uint32_t)smoe_f32_to_bf16(fmaxf(acc[3], 0.f)) << 16);
-    *(uint2*)(h + (((size_t)slot * (d_ff >> 3) + hb * 2 + (lane >> 5)) * a.T + tok) * 8 + ((lane >> 4) & 1) * 4) = o;
+    *(uint2*)(h + ((size_t)slot * a.T + tok) * d_ff + hb * 16 + 4 * (lane >> 4)) = o;
 }
 
 // ---------------------------------------------------------------------------
@@ -424,10 +428,13 @@ __device__ __forceinline__ void finish_small(const smoe_step_tail& t, const int3
 // Second product.  Workgroup (slot, feature block): 4 waves split the reduction four ways and meet
 // in LDS (added in wave order: reproducible).  The first group of weight loads is issued before the
 // slot ids have arrived, so the latency of the two overlaps; the workgroups of a slot nobody was
-// routed to then simply leave.  The slot's own tokens are packed into the columns of as few 32-token
-// blocks as they need, at most MAXNB of them at a time.
+// routed to then simply leave.  The slot's own tokens are packed into columns; a batch of more than 32
+// tokens (WIDE) has a workgroup for every 32 of them, the later ones at the end of the grid, where a slot
+// with many tokens then keeps no workgroup longer than the others (one slot of 768 x 3072, T = 100 27.0 -> 18.3 us per
+// layer with two blocks of columns at a time before).
 struct second_args {
-    const uint16_t* h;            // [slot][d_ff / 8][pitch tokens] units of 8 features
+    const uint16_t* h;
+    hidden_strides hs;
     const uint4* W2;
     const int32_t* slot;
     int T, E, K, R, N;
@@ -440,24 +447,25 @@ struct second_args {
 
 // SPARSE: no weights are asked for before the slot ids are there (an instance of its own: with a branch around
 // the early loads the wait for the ids becomes a wait for everything, 0.8 us per layer).
-template <int MAXNB, bool STREAM, bool SPARSE>
+template <bool WIDE, bool STREAM, bool SPARSE>
 __device__ __forceinline__ void decode_second_body(const second_args& a) {
-    constexpr int KSPLIT = 4;
-    __shared__ __align__(16) float red[(KSPLIT - 1) * MAXNB * 16 * 64];
+    constexpr int KSPLIT = 4, G = 8;                       // G: reduction steps fetched together
+    __shared__ __align__(16) float red[(KSPLIT - 1) * 16 * 64];
     __shared__ int32_t s_tok[KSPLIT][SMALL_T];
     if (blockIdx.x == 0) {
         finish_small(a.tail, a.slot, a.T, a.E, a.K);
         return;
     }
     const int nfb = a.N >> 5, nrb = a.R >> 4;
-    const int slot = (blockIdx.x - 1) / nfb, fb = (blockIdx.x - 1) % nfb;
+    const int pair = WIDE ? (blockIdx.x - 1) % (a.K * nfb) : blockIdx.x - 1;
+    const int c0 = WIDE ? 32 * ((blockIdx.x - 1) / (a.K * nfb)) : 0;   // first of this workgroup's columns of the slot's token list
+    const int slot = pair / nfb, fb = pair % nfb;
     // wave index as a scalar: MFMA loop bounds must be wave-uniform for the compiler too
     const int tid = threadIdx.x, part = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int per = (nrb + KSPLIT - 1) / KSPLIT;
     const int kb_lo = min(part * per, nrb), kb_hi = min(kb_lo + per, nrb);
     const uint4* wp = a.W2 + ((size_t)(a.phys ? a.phys[slot] : slot) * nfb + fb) * nrb * 64 + lane;
-    auto fetch_w = [&](auto& w, int g0) {
-        constexpr int G = sizeof(w) / sizeof(uint4);
+    auto fetch_w = [&](uint4 (&w)[G], int g0) {
 #pragma unroll
         for (int i = 0; i < G; ++i) {                      // past the end: reloaded, not used
             const uint4* src = wp + (size_t)max(min(g0 + i, kb_hi - 1), 0) * 64;
@@ -466,144 +474,106 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
     };
     // A wave's loads complete in order: the slot ids are asked for first, so that waiting for them
     // does not wait for the weights, and the weights' first group right after, before anything is known.
-    constexpr int G1 = 8;                                  // reduction steps fetched together
-    const int id0 = a.slot[min(lane, a.T - 1)], id1 = MAXNB > 1 ? a.slot[min(lane + 64, a.T - 1)] : 0;
+    // (Past the first 32 columns most workgroups have no token: they ask for the ids only.)
+    const int id0 = a.slot[min(lane, a.T - 1)], id1 = WIDE ? a.slot[min(lane + 64, a.T - 1)] : 0;
     __builtin_amdgcn_sched_barrier(0);
-    uint4 w0[G1];
-    if (!SPARSE) fetch_w(w0, kb_lo);
+    uint4 wA[G], wB[G];
+    if (!SPARSE && !WIDE) fetch_w(wA, kb_lo);
     __builtin_amdgcn_sched_barrier(0);
-    const bool own0 = lane < a.T && id0 == slot, own1 = MAXNB > 1 && lane + 64 < a.T && id1 == slot;
-    const unsigned long long m0 = __ballot(own0), m1 = MAXNB > 1 ? __ballot(own1) : 0ull;
+    const bool own0 = lane < a.T && id0 == slot, own1 = WIDE && lane + 64 < a.T && id1 == slot;
+    const unsigned long long m0 = __ballot(own0), m1 = WIDE ? __ballot(own1) : 0ull;
     const int n0 = __popcll(m0), n = n0 + __popcll(m1);
-    if (n == 0) return;                                    // nothing routed to this slot (uniform over the workgroup)
-    if (SPARSE) fetch_w(w0, kb_lo);
+    if (n <= c0) return;                                   // nothing routed to this slot, or no token left (uniform over the workgroup)
+    if (SPARSE || WIDE) fetch_w(wA, kb_lo);
     const unsigned long long below = (1ull << lane) - 1ull;
     if (own0) s_tok[part][__popcll(m0 & below)] = lane;
     if (own1) s_tok[part][n0 + __popcll(m1 & below)] = lane + 64;
-    const int pitch = (a.T + 31) & ~31;
-    const size_t xstep = 2 * (size_t)pitch;                // 16-byte units per reduction step
-    const uint4* hs = (const uint4*)a.h + ((size_t)slot * (a.R >> 3) + (lane >> 5)) * pitch;
-
-    auto blocks = [&](auto nbc, auto& wA, int c0) {        // token columns c0 .. of the slot's list
-        constexpr int NB = decltype(nbc)::value;
-        constexpr int G = sizeof(wA) / sizeof(uint4);
-        uint4 wB[G], xA[NB][G], xB[NB][G];
-        int tok[NB];
-        bool live[NB];
-        const uint4* xp[NB];
+    __syncthreads();                                       // the token lists are complete
+    const int c = c0 + (lane & 31);
+    const bool live = c < n;
+    const int tok = s_tok[part][min(c, n - 1)];            // columns past the list repeat its last token
+    const uint4* xp = (const uint4*)a.h + (size_t)slot * a.hs.slot + (size_t)tok * a.hs.token + (lane >> 5) * a.hs.unit;
+    const int xstep = 2 * a.hs.unit;
+    uint4 xA[G], xB[G];
+    auto fetch_x = [&](uint4 (&xv)[G], int g0) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int c = c0 + b * 32 + (lane & 31);
-            live[b] = c < n;
-            tok[b] = s_tok[part][min(c, n - 1)];           // columns past the list repeat its last token
-            xp[b] = hs + tok[b];
+        for (int i = 0; i < G; ++i) xv[i] = xp[(size_t)max(min(g0 + i, kb_hi - 1), 0) * xstep];
+    };
+    fetch_x(xA, kb_lo);
+    float gmul = 1.f;
+    uint2 rres[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) rres[g] = make_uint2(0, 0);
+    if (live && part == 0) {                               // asked for now, used after the loop
+        gmul = a.gate[tok];
+        if (a.residual) {
+            const uint16_t* rp = a.residual + (size_t)tok * a.N + fb * 32 + (lane >> 5) * 4;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) rres[g] = *(const uint2*)(rp + g * 8);
         }
-        auto fetch_x = [&](uint4 (&xv)[NB][G], int g0) {
+    }
+    smoe_f32x16 acc;
 #pragma unroll
-            for (int i = 0; i < G; ++i)
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    auto consume = [&](uint4 (&w)[G], uint4 (&xv)[G], int g0) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) xv[b][i] = xp[b][(size_t)max(min(g0 + i, kb_hi - 1), 0) * xstep];
-        };
-        fetch_x(xA, kb_lo);
-        float gmul[NB];
-        uint2 rres[NB][4];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {                     // asked for now, used after the loop
-            gmul[b] = 1.f;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) rres[b][g] = make_uint2(0, 0);
-            if (live[b] && part == 0) {
-                gmul[b] = a.gate[tok[b]];
-                if (a.residual) {
-                    const uint16_t* rp = a.residual + (size_t)tok[b] * a.N + fb * 32 + (lane >> 5) * 4;
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) rres[b][g] = *(const uint2*)(rp + g * 8);
-                }
-            }
+        for (int i = 0; i < G; ++i) {                      // steps past the end multiply by a zero operand
+            const uint4 xz = g0 + i < kb_hi ? xv[i] : make_uint4(0, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(smoe_frag(w[i]), smoe_frag(xz), acc, 0, 0, 0);
         }
-        smoe_f32x16 acc[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
-        auto consume = [&](auto& w, uint4 (&xv)[NB][G], int g0) {
-#pragma unroll
-            for (int i = 0; i < G; ++i)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {             // steps past the end multiply by a zero operand
-                    const uint4 xz = g0 + i < kb_hi ? xv[b][i] : make_uint4(0, 0, 0, 0);
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(smoe_frag(w[i]), smoe_frag(xz), acc[b], 0, 0, 0);
-                }
-        };
-        int g0 = kb_lo;
-        for (; kb_hi - g0 > 2 * G; g0 += 2 * G) {
-            fetch_w(wB, g0 + G);
-            fetch_x(xB, g0 + G);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(wA, xA, g0);
-            __builtin_amdgcn_sched_barrier(0);
-            fetch_w(wA, g0 + 2 * G);
-            fetch_x(xA, g0 + 2 * G);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(wB, xB, g0 + G);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    };
+    int g0 = kb_lo;
+    for (; kb_hi - g0 > 2 * G; g0 += 2 * G) {
         fetch_w(wB, g0 + G);
         fetch_x(xB, g0 + G);
         __builtin_amdgcn_sched_barrier(0);
         consume(wA, xA, g0);
         __builtin_amdgcn_sched_barrier(0);
+        fetch_w(wA, g0 + 2 * G);
+        fetch_x(xA, g0 + 2 * G);
+        __builtin_amdgcn_sched_barrier(0);
         consume(wB, xB, g0 + G);
-        if (part > 0) {
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    fetch_w(wB, g0 + G);
+    fetch_x(xB, g0 + G);
+    __builtin_amdgcn_sched_barrier(0);
+    consume(wA, xA, g0);
+    __builtin_amdgcn_sched_barrier(0);
+    consume(wB, xB, g0 + G);
+    if (part > 0) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+        for (int i = 0; i < 16; ++i) red[((part - 1) * 16 + i) * 64 + lane] = acc[i];
+    }
+    __syncthreads();
+    if (part > 0) return;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) red[(((part - 1) * MAXNB + b) * 16 + i) * 64 + lane] = acc[b][i];
-        }
-        __syncthreads();
-        if (part == 0) {
+    for (int w2 = 0; w2 < KSPLIT - 1; ++w2)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
+        for (int i = 0; i < 16; ++i) acc[i] += red[(w2 * 16 + i) * 64 + lane];
+    if (!live) return;
+    // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, column l%32
+    uint16_t* ydst = a.out + (size_t)tok * a.N + fb * 32 + (lane >> 5) * 4;
 #pragma unroll
-                for (int w2 = 0; w2 < KSPLIT - 1; ++w2)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[b][i] += red[((w2 * MAXNB + b) * 16 + i) * 64 + lane];
-                if (!live[b]) continue;
-                // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, column l%32
-                uint16_t* ydst = a.out + (size_t)tok[b] * a.N + fb * 32 + (lane >> 5) * 4;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float v0 = acc[b][4 * g], v1 = acc[b][4 * g + 1], v2 = acc[b][4 * g + 2], v3 = acc[b][4 * g + 3];
-                    smoe_apply_gate(v0, v1, v2, v3, gmul[b], rres[b][g], a.residual != nullptr);
-                    uint2 o;
-                    o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-                    o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
-                    *(uint2*)(ydst + g * 8) = o;
-                }
-            }
-        }
-    };
-    __syncthreads();                                       // the token lists are complete
-    if (MAXNB == 1 || n <= 32) {
-        blocks(std::integral_constant<int, 1>{}, w0, 0);
-    } else if constexpr (MAXNB > 1) {
-        for (int c0 = 0; c0 < n; c0 += 64) {
-            if (c0) __syncthreads();                       // the previous sums have been read
-            uint4 w[4];
-            fetch_w(w, kb_lo);
-            blocks(std::integral_constant<int, 2>{}, w, c0);
-        }
+    for (int g = 0; g < 4; ++g) {
+        float v0 = acc[4 * g], v1 = acc[4 * g + 1], v2 = acc[4 * g + 2], v3 = acc[4 * g + 3];
+        smoe_apply_gate(v0, v1, v2, v3, gmul, rres[g], a.residual != nullptr);
+        uint2 o;
+        o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
+        o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+        *(uint2*)(ydst + g * 8) = o;
     }
 }
 
-template <int MAXNB>
-__global__ __launch_bounds__(256, 2) void decode_second_kernel(const second_args a) { decode_second_body<MAXNB, false, false>(a); }
+// NB = 1: at most 32 tokens, 2: more.
+template <int NB>
+__global__ __launch_bounds__(256, 2) void decode_second_kernel(const second_args a) { decode_second_body<(NB > 1), false, false>(a); }
 
-template <int MAXNB>
-__global__ __launch_bounds__(256, 2) void decode_second_stream_kernel(const second_args a) { decode_second_body<MAXNB, true, false>(a); }
+template <int NB>
+__global__ __launch_bounds__(256, 2) void decode_second_stream_kernel(const second_args a) { decode_second_body<(NB > 1), true, false>(a); }
 
-template <int MAXNB, bool STREAM>
-__global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<MAXNB, STREAM, true>(a); }
+template <int NB, bool STREAM>
+__global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<(NB > 1), STREAM, true>(a); }
 
 // Few tokens: workgroup (served slot, 16 features, or 8 of them while that leaves compute units idle: the lanes of
 // the other 8 then read the same weights again).  4 waves split the reduction as above, each with 24 loads in flight.
@@ -629,7 +599,7 @@ __global__ __launch_bounds__(256, 2) void dense_second_kernel_served(const secon
     const int n = __popcll(mine), col = lane & 15;
     int tok = 0;                                           // the col-th set bit
     for (int u = 0; u < a.T; ++u) tok = ((mine >> u) & 1) && __popcll(mine & ((1ull << u) - 1ull)) == min(col, n - 1) ? u : tok;
-    const uint4* xp = (const uint4*)a.h + ((size_t)slot * (a.R >> 3) + 2 * kb_lo + (lane >> 4)) * a.T + tok;
+    const uint4* xp = (const uint4*)a.h + ((size_t)slot * a.T + tok) * (a.R >> 3) + 2 * kb_lo + (lane >> 4);
     uint4 wA[G], wB[G], xA[G], xB[G];
     // A range of an odd number of blocks ends in the middle of a step: the lanes of its upper half then read the lower
     // half again and multiply zeros.
@@ -640,7 +610,7 @@ __global__ __launch_bounds__(256, 2) void dense_second_kernel_served(const secon
             const bool half = 2 * st + 1 >= nkb && lane >= 32;
             const uint4* src = wp + (size_t)st * 128 - (half ? 64 : 0);
             w[i] = STREAM ? smoe_load_stream(src) : *src;
-            x[i] = xp[(ptrdiff_t)(st * 4 - (half ? 2 : 0)) * a.T];
+            x[i] = xp[st * 4 - (half ? 2 : 0)];
         }
     };
     smoe_f32x4 acc;
@@ -735,6 +705,19 @@ bool sparse(const smoe_config& c, int T) {
     return unused > (c.E <= 64 ? 48e6 : 72e6);
 }
 
+// Layout of the hidden activations between the two launches.  A wave of the second one reads 32 bytes of each of its
+// tokens per step.  Token by token the steps of a token share lines, and only the slot's own tokens are touched: better
+// where slots hold few of the batch's tokens (us per layer, [feature / 8][token] / [token][feature]: 16 slots of
+// 768 x 3072, T = 32 31.4 / 30.0, T = 64 37.1 / 34.6; eight T = 32 19.6 / 18.4; four of 1024 x 4096, T = 13 20.2 / 19.5).  Unit by
+// unit neighbouring tokens share a line: better where slots hold most of them (two slots of 768 x 3072, T = 32 13.5 /
+// 15.2, T = 64 15.1 / 17.3), and for rows of up to 4 KB (20 slots of 512 x 2048, T = 48 24.5 / 25.3; four of 768 x 2048,
+// T = 48 17.0 / 18.0; six of 416 x 1696 alike).
+hidden_strides hidden_layout(const smoe_config& c, int T) {
+    const int units = c.d_ff >> 3, pitch = (T + 31) & ~31;
+    if (c.K >= 4 && c.d_ff > 2048) return hidden_strides{units * T, units, 1};
+    return hidden_strides{units * pitch, 1, pitch};
+}
+
 template <int NEB, int NBF>
 int launch_first(const smoe_layer* L, const smoe_route_args& ra, bool stream, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const smoe_config& c = L->cfg;
@@ -746,10 +729,11 @@ int launch_first(const smoe_layer* L, const smoe_route_args& ra, bool stream, hi
     static smoe_lds_raised raised[2];                      // per kernel: devices whose dynamic-LDS limit is up
     if (int rc = raised[stream].ensure((const void*)kern, lds, LDS_LIMIT)) return rc;
     if (e0 && e1)
-        hipExtLaunchKernelGGL(kern, grid, dim3(512), lds, s, e0, e1, 0, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden, c.d_ff,
-                              phys, fbw);
+        hipExtLaunchKernelGGL(kern, grid, dim3(512), lds, s, e0, e1, 0, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden,
+                              hidden_layout(c, ra.T), c.d_ff, phys, fbw);
     else
-        hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden, c.d_ff, phys, fbw);
+        hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden, hidden_layout(c, ra.T),
+                           c.d_ff, phys, fbw);
     return smoe_check_hip(hipGetLastError(), "smoe_forward: decode launch");
 }
 
@@ -773,10 +757,10 @@ int launch_first_served(const smoe_layer* L, const smoe_route_args& ra, bool str
     if (int rc = raised[stream].ensure((const void*)kern, lds, LDS_LIMIT)) return rc;
     if (e0 && e1)
         hipExtLaunchKernelGGL(kern, grid, dim3(512), lds, s, e0, e1, 0, (const uint16_t*)ra.x, (const uint4*)L->slot_w1, ra.T,
-                              (uint16_t*)L->d_hidden, c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
+                              (uint16_t*)L->d_hidden, hidden_layout(c, ra.T), c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
     else
         hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, (const uint16_t*)ra.x, (const uint4*)L->slot_w1, ra.T, (uint16_t*)L->d_hidden,
-                           c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
+                           hidden_layout(c, ra.T), c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
     return smoe_check_hip(hipGetLastError(), "smoe_forward: first product launch");
 }
 
@@ -857,7 +841,7 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
 int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_of, const float* gate,
                                       const uint16_t* residual, int T, uint16_t* out, hipStream_t s) {
     const smoe_config& c = L->cfg;
-    const second_args a{(const uint16_t*)L->d_hidden, (const uint4*)L->slot_w2, slot_of, T, c.E, c.K, c.d_ff, c.d_model,
+    const second_args a{(const uint16_t*)L->d_hidden, hidden_layout(c, T), (const uint4*)L->slot_w2, slot_of, T, c.E, c.K, c.d_ff, c.d_model,
                         c.spare_slots > 0 ? L->d_phys : nullptr, gate, residual, out, L->tail};
     const bool stream = smoe_weights_outgrow_cache(L);
     if (sparse(c, T) && T <= FEW_T) {
@@ -868,7 +852,7 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
         L->tail = smoe_step_tail{};                        // the caller's pointers are not kept
         return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");
     }
-    const dim3 grid(c.K * (c.d_model >> 5) + 1);
+    const dim3 grid((T + 31) / 32 * c.K * (c.d_model >> 5) + 1);
     auto kern = T <= 32 ? (stream ? decode_second_stream_kernel<1> : decode_second_kernel<1>)
                         : (stream ? decode_second_stream_kernel<2> : decode_second_kernel<2>);
     if (sparse(c, T))
