@@ -29,6 +29,7 @@
 // kernel runs as persistent workgroups that each walk a fixed share of the tiles.
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <string>
 #include <type_traits>
@@ -787,44 +788,79 @@ void launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* off
     }
 }
 
-// Which tile of the ring kernel (9: at most 128 x 128, 10: at most 256 x 256) takes a product, or 0.
-// Two reasons to take it, by what the two products of a layer measured (us, tiled -> ring):
-//  * The reduction is no multiple of 128: the tiled kernel then has no weight prefetch.  16 slots of 992 x 3296,
-//    T = 800 33.0 -> 29.8 and 77.0 -> 42.6, T = 8000 107 -> 72 and 134 -> 70; 11 of 416 x 1696, T = 800 12.5 -> 10.7
+// Tile shape of one product of a prefill batch, chosen by its predicted time: for every round of one item per compute
+// unit the bytes of an item's weights and rows at the rate at which that tile takes them in.  A slot with x tiles' worth
+// of tokens in the mean has about x + 1/2 tiles, and one where x is small.  The rates were fitted to 180 batches (13
+// shapes from 4 slots of 256 x 768 to 32 of 1024 x 4096, T = 140 .. 6000, weights from HBM, every tile measured on each): the
+// pick is 1.3 % (first product) and 0.5 % (second) slower than the best tile of each batch in the mean, where thresholds
+// on the tokens per slot alone were 10 and 13 % slower.  us, those thresholds / this choice, second product: 8 slots of
+// 768 x 3072, T = 1000 27.0 / 23.0, T = 2000 33.4 / 27.1; 16 slots, T = 2500 43.7 / 35.9; 16 of 1024 x 4096, T = 2000 60.4 /
+// 48.7; first: 4 slots of 768 x 3072, T = 600 17.4 / 13.1; 16 of 768 x 2048, T = 4096 35.4 / 27.3.
+int pick_tile(bool first, int R, int N, int T, int K) {
+    struct Rate { int v, rows, features; double first_gbs, second_gbs; };
+    static constexpr Rate rates[] = {{4, 32, 128, 47.4, 71.6}, {3, 64, 128, 56.7, 67.3}, {1, 128, 128, 61.1, 60.0}, {8, 128, 256, 48.4, 47.2}};
+    const double ends = first ? 0.5 : 0.55;
+    // slots of less than two blocks of rows: no wide tiles for the first product (each weight would pass through one compute
+    // unit only, at the rate of cold lines: 16 slots of 1024 x 4096, T = 777 39.5, 31.0 with 128 features), and a count
+    // that is nearer to the truth
+    const bool thin = first && T / K < 60;
+    auto rounds = [&](int rows, int features) {
+        const double x = (double)T / K / rows, tiles = K * (x + ends + (1 - ends) * std::exp(-2 * x));
+        return std::max(1.0, std::ceil(tiles * ((N + features - 1) / features) / 256 - (thin ? 0.06 : 0.03)));
+    };
+    int best = 1;
+    double least = 1e30;
+    for (const Rate& r : rates) {
+        if (thin && r.features > 128) continue;
+        const double us = rounds(r.rows, r.features) * (r.rows + r.features) * 2e-3 * R / (first ? r.first_gbs : r.second_gbs);
+        if (us < least) { least = us; best = r.v; }
+    }
+    if (!thin && smoe_ring_applies(first, R, T))
+        for (int h = 1; h <= 8; ++h) {                     // the ring kernel chooses the height of its tiles
+            const double us = (first ? -0.6 : 1.6) + rounds(32 * h, 256) * (256 + 32 * h) * 2e-3 * R / (first ? 38.4 : 42.0);
+            if (us < least) { least = us; best = 10; }
+        }
+    return best;
+}
+
+// Where the ring kernel takes a product in any case: 9 (at most 128 x 128) or 10 (at most 256 x 256), else 0.
+//  * The reduction is no multiple of 128: the tiled kernel then has no weight prefetch.  us, tiled -> ring: 16 slots of
+//    992 x 3296, T = 800 33.0 -> 29.8 and 77.0 -> 42.6, T = 8000 107 -> 72 and 134 -> 70; 11 of 416 x 1696, T = 800 12.5 -> 10.7
 //    and 31.6 -> 18.0.  Where the streaming kernel splits a second product (v = 6) it stays ahead (T = 200: 15.8, 17.8),
-//    and so do 32-row tiles (v = 4) of 64-deep slices (6 slots of 448 x 1280, T = 140 8.1, 9.2).
-//  * There are large tiles for the chip.  First product, 300 and more tokens per slot (16 slots of 768 x 2048, T = 8000
-//    53.1 -> 43.4; of 1024 x 4096, T = 16384 160 -> 149) and where its tiles of 128 rows would take two rounds, those
-//    of 256 one (768 x 3072, T = 2000 30.8 -> 27.5; T = 4096 37.7 tiled, 39.0 ring).  Second product: its tiles are
-//    few and deep, and below a hundred full ones 128 x 128 tiles of two workgroups per compute unit keep up
-//    (768 x 3072, T = 8000 58.8, 59.4; 768 x 2048 40.8, 43.0; but T = 16384 104.7 -> 80.7 and 73 -> 62; 32 slots of
-//    1024 x 4096, T = 8000 119 -> 102), from four feature tiles on half as many do (1024 x 4096, T = 3000 99 -> 83,
-//    16 slots, T = 4096 73.4 -> 68.9; T = 1213 43.1, 58.8).
-// The small tiles serve where fewer than a hundred large ones exist (608 x 2912, T = 8000 second: 44.5, 49.0 with
-// large ones; 992 x 3296 70 with large ones, 96).
+//    and with few tokens so do tiles of 64-deep slices (6 slots of 448 x 1280, T = 140 8.1, 9.2, T = 300 8.8, 9.4).  The small tiles
+//    serve where fewer than a hundred large ones exist (608 x 2912, T = 8000 second: 44.5, 49.0 with large ones;
+//    992 x 3296 70 with large ones, 96).
+//  * There are large tiles for the chip many times over, where the matrix products and the power they draw count
+//    and not the bytes alone (128 x 128 tiles -> ring: 768 x 3072, T = 16384 108 -> 94 and 105 -> 80; 32 slots of
+//    1024 x 4096 190 -> 165 and 187 -> 166; 16 of 768 x 2048 80 -> 68 and 75 -> 60).
 int ring_tile(bool first, int R, int N, int T, int per_slot, int tiled) {
     const double tiles = (double)T * N / 65536;            // full 256 x 256 tiles
-    if (R % (tiled == 4 ? 64 : 128) != 0) return tiled == 6 ? 0 : tiles >= 100 ? 10 : 9;
-    if (first) return tiles >= 80 && (per_slot >= 300 || (per_slot >= 120 && per_slot < 184)) ? 10 : 0;
-    return tiles >= 100 || (N >= 1024 && tiles >= 45) ? 10 : 0;
+    if (R % 128 != 0) return tiled == 6 || (first && per_slot < 60 && R % 64 == 0) ? 0 : tiles >= 100 ? 10 : 9;
+    return tiles >= (first ? 300 : 100) ? 10 : 0;
 }
 
 // Tile shapes for the two GEMMs.  A pair fixed at smoe_create (SMOE_FFN_VARIANT="v1,v2", a
 // tuning aid; the indices are those of launch_variant) overrides the built-in choice.
 void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
-    // Thresholds measured on the Switch-base-64 shape (K = 16, 768 x 3072) over T = 48 .. 8192.
-    const int per_slot = T / L->cfg.K;
-    if (per_slot >= 184) { v1 = 8; v2 = 1; }
-    else if (per_slot >= 60) { v1 = 8; v2 = 3; }
-    else if (per_slot >= 28) { v1 = 3; v2 = 4; }
-    else if (per_slot >= 6) { v1 = 4; v2 = 6; }
-    else { v1 = 5; v2 = 6; }             // decode: a few tokens per slot, weight streaming
+    const int d = L->cfg.d_model, f = L->cfg.d_ff, K = L->cfg.K, per_slot = T / K;
+    if (per_slot < 6) {                  // decode: a few tokens per slot, weight streaming
+        v1 = 5;
+        v2 = 6;
+    } else {
+        // The streaming kernel reads a slot's weights once while its tokens fit 32 columns: few tokens on few slots whose
+        // weights are no trifle (us, streaming / best tile: T = 140 4 slots of 768 x 3072 16.0 / 22.0, 16 slots 21.0 / 26.0;
+        // T = 200 16 slots 25.5 / 26.2, 32 slots 37.0 / 31.6; 4 slots of 256 x 768 8.1 / 7.3), or a reduction without
+        // weight prefetch.
+        const bool stream = T <= 200 && K <= 16 && per_slot <= 50 && 2.0 * K * d * f >= 16e6;
+        v1 = d % 128 != 0 ? (per_slot < 28 ? 4 : 3) : pick_tile(true, d, f, T, K);
+        v2 = f % 128 != 0 ? (per_slot < 28 ? 6 : 1) : stream ? 6 : pick_tile(false, f, d, T, K);
+    }
     // the small-batch path of smoe_forward splits the second product's reduction four ways and multiplies 16
     // reduction elements at a time: the separate call does the same, so that both give the same bits
     if (smoe_decode_first_applies(L, T)) {
         v2 = 6;
+        if (v1 == 10) v1 = 8;
     } else {
-        const int d = L->cfg.d_model, f = L->cfg.d_ff;
         const int r1 = ring_tile(true, d, f, T, per_slot, v1), r2 = ring_tile(false, f, d, T, per_slot, v2);
         if (r1 && smoe_ring_applies(true, d, T)) v1 = r1;
         if (r2 && smoe_ring_applies(false, f, T)) v2 = r2;
