@@ -52,7 +52,7 @@ PEAK_HBM_GBS = 8000.0
 PROFILE_FILES = {
     "c3": "profiles/grouped_gemm_bf16_c3_prefill_hbm_counters.txt",
     "c4": "profiles/decode_step_c4_hbm_counters.txt",
-    "c5": "profiles/grouped_gemm_bf16_c5_prefill_hbm_counters.txt",
+    "c5": "profiles/ring_gemm_bf16_c5_prefill_hbm_counters.txt",
 }
 
 
