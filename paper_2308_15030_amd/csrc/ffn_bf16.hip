@@ -855,11 +855,10 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
         v1 = d % 128 != 0 ? (per_slot < 28 ? 4 : 3) : pick_tile(true, d, f, T, K);
         v2 = f % 128 != 0 ? (per_slot < 28 ? 6 : 1) : stream ? 6 : pick_tile(false, f, d, T, K);
     }
-    // the small-batch path of smoe_forward splits the second product's reduction four ways and multiplies 16
-    // reduction elements at a time: the separate call does the same, so that both give the same bits
+    // the small-batch path of smoe_forward splits the second product's reduction four ways: the separate call does the
+    // same, so that both give the same bits (the tiles of the first product all do)
     if (smoe_decode_first_applies(L, T)) {
         v2 = 6;
-        if (v1 == 10) v1 = 8;
     } else {
         const int r1 = ring_tile(true, d, f, T, per_slot, v1), r2 = ring_tile(false, f, d, T, per_slot, v2);
         if (r1 && smoe_ring_applies(true, d, T)) v1 = r1;
