@@ -253,8 +253,9 @@ int smoe_expert_ffn(smoe_layer_t* layer, const void* x_perm, const int32_t* offs
  * empty are streamed for nothing), and the second product picks each token's
  * row from its slot, while one workgroup ranks the tokens and adds the
  * importance sums.  Where the slots that are expected to stay empty have more
- * than 48 MB of first matrices (72 MB beyond 64 experts), the router takes a
- * launch of its own and no weights of empty slots are read.  All the per-token and per-expert outputs of the individual
+ * than 48 MB of first matrices (72 MB beyond 64 experts; up to 16 tokens: 16 MB
+ * and 2 MB per token), the router takes a launch of its own and no weights of
+ * empty slots are read.  All the per-token and per-expert outputs of the individual
  * calls are produced: orig_expert, orig_gate, slot, gate, xnorm [T]; count, gsum,
  * score [E] (accumulate as in smoe_importance); perm, inv_perm [T];
  * offsets [K+1].  residual may be NULL and may alias x; out must not alias x.

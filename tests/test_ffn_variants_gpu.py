@@ -19,9 +19,9 @@ from harness import Case, max_abs_rel, to_dev, to_host, values
 
 pytestmark = pytest.mark.gpu
 
-# indices of launch_variant in csrc/ffn_bf16.hip: (first product, second product).  (10, 10) and
-# (8, 10) run the 256-row tile as the second product: its output turn handles more pieces per
-# thread than fit one group, and the short last group once ran past the tile.
+# indices of launch_variant in csrc/ffn_bf16.hip: (first product, second product).  10 is the ring
+# kernel, and the tiled kernel that stands in for it below reductions of 256; a 256-row tile of the
+# tiled kernel that had this index once ran past its rows as the second product.
 PAIRS = [(1, 1), (3, 3), (4, 4), (5, 5), (6, 6), (8, 8), (10, 1), (10, 8), (8, 3), (5, 6), (4, 6), (10, 10), (8, 10)]
 
 
