@@ -765,17 +765,14 @@ int ring_or_tiled(int v, bool first, int R, int T) {
 }
 
 template <bool FIRST>
-void launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots,
+int launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots,
                     uint16_t* Y, int R, int N, int T, const FuseArgs& fz, hipStream_t s, hipEvent_t e0,
                     hipEvent_t e1) {
     v = ring_or_tiled(v, FIRST, R, T);
-    if (v >= 9) {
-        (void)smoe_launch_ring(v == 9 ? 4 : 8, FIRST, X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die(), s, e0, e1);
-        return;
-    }
+    if (v >= 9) return smoe_launch_ring(v == 9 ? 4 : 8, FIRST, X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die(), s, e0, e1);
     if (R % 64 != 0 && v != 5 && v != 6) {   // d_model / d_ff are multiples of 32 by contract: 32-deep slices always fit
         launch_gemm<1, 4, 4, 32, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);
-        return;
+        return SMOE_OK;
     }
     switch (v) {             //            AF MAXB NW BKT PD OCC     tokens x features per workgroup
         case 1: launch_gemm<1, 4, 4, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  // 128 x 128
@@ -786,6 +783,7 @@ void launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* off
         case 6: launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;   // 32 x 32, reduction split 4 ways
         default: launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;
     }
+    return SMOE_OK;
 }
 
 // Tile shape of one product of a prefill batch, chosen by its predicted time: for every round of one item per compute
@@ -916,8 +914,8 @@ int smoe_launch_ffn_bf16(const smoe_layer* L, const uint16_t* x_perm, const int3
     uint16_t* h = (uint16_t*)L->d_hidden;
     const int32_t* phys = L->cfg.spare_slots > 0 ? L->d_phys : nullptr;   // identity without spare slots
     const FuseArgs none{phys, nullptr, nullptr, nullptr};
-    launch_variant<true>(v1, x_perm, L->slot_w1, offsets, c.K, h, c.d_model, c.d_ff, T, none, s, L->prof_ev[0], L->prof_ev[1]);
-    launch_variant<false>(v2, h, L->slot_w2, offsets, c.K, y_perm, c.d_ff, c.d_model, T, none, s, L->prof_ev[2], L->prof_ev[3]);
+    if (int rc = launch_variant<true>(v1, x_perm, L->slot_w1, offsets, c.K, h, c.d_model, c.d_ff, T, none, s, L->prof_ev[0], L->prof_ev[1])) return rc;
+    if (int rc = launch_variant<false>(v2, h, L->slot_w2, offsets, c.K, y_perm, c.d_ff, c.d_model, T, none, s, L->prof_ev[2], L->prof_ev[3])) return rc;
     return smoe_check_hip(hipGetLastError(), "smoe_expert_ffn launch");
 }
 
@@ -937,7 +935,7 @@ int smoe_launch_ffn_bf16_fused(const smoe_layer* L, const uint16_t* x, const int
     uint16_t* h = (uint16_t*)L->d_hidden;
     const int32_t* phys = L->cfg.spare_slots > 0 ? L->d_phys : nullptr;   // identity without spare slots
     const FuseArgs gather{phys, perm, nullptr, nullptr}, scatter{phys, perm, gate, residual};
-    launch_variant<true>(v1, x, L->slot_w1, offsets, c.K, h, c.d_model, c.d_ff, T, gather, s, L->prof_ev[0], L->prof_ev[1]);
-    launch_variant<false>(v2, h, L->slot_w2, offsets, c.K, out, c.d_ff, c.d_model, T, scatter, s, L->prof_ev[2], L->prof_ev[3]);
+    if (int rc = launch_variant<true>(v1, x, L->slot_w1, offsets, c.K, h, c.d_model, c.d_ff, T, gather, s, L->prof_ev[0], L->prof_ev[1])) return rc;
+    if (int rc = launch_variant<false>(v2, h, L->slot_w2, offsets, c.K, out, c.d_ff, c.d_model, T, scatter, s, L->prof_ev[2], L->prof_ev[3])) return rc;
     return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");
 }
