@@ -161,8 +161,8 @@ __device__ __forceinline__ void panel_tile(const float* const (&wp)[NC], const f
 }
 
 // FIRST: row-major x in, ReLU, hidden activations out; else hidden activations in, row-major y out.
-// NC: 16-feature blocks of an item.  WAVES: 8, one part of the reduction each, or 4, which take two parts each
-// and add them.
+// NC: 16-feature blocks of an item.  WAVES: 8, one part of the reduction each, or 4, which take two parts each.
+// Either way the eight parts meet in LDS and are added in order: a row's bits do not depend on the batch around it.
 template <bool FIRST, int NC, int WAVES>
 __device__ __forceinline__ void panel_items(const float* __restrict__ X, const float* __restrict__ W, const int32_t* __restrict__ offsets,
                                             const int32_t* __restrict__ phys, int nslots, int T, float* __restrict__ Y, int R, int N,
@@ -186,7 +186,6 @@ __device__ __forceinline__ void panel_items(const float* __restrict__ X, const f
     auto run = [&](auto nbc) {
         constexpr int NB = decltype(nbc)::value;
         const float* xq[NB];
-        f32x4 sum[NC][NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) xq[b] = xp[b];
 #pragma unroll 1
@@ -201,12 +200,8 @@ __device__ __forceinline__ void panel_items(const float* __restrict__ X, const f
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) sum[c][b] = i ? sum[c][b] + acc[c][b] : acc[c][b];
+                for (int b = 0; b < NB; ++b) red[wave * PARTS + i][c * 2 + b][lane] = acc[c][b];
         }
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) red[wave][c * 2 + b][lane] = sum[c][b];
     };
     if (two) run(std::integral_constant<int, 2>{});
     else run(std::integral_constant<int, 1>{});
@@ -220,7 +215,7 @@ __device__ __forceinline__ void panel_items(const float* __restrict__ X, const f
         if ((b == 0 || two) && r < rows && f < N) {
             f32x4 v = red[0][q][lane];
 #pragma unroll
-            for (int w = 1; w < WAVES; ++w) v += red[w][q][lane];
+            for (int w = 1; w < PK_WAVES; ++w) v += red[w][q][lane];
             if (FIRST) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
