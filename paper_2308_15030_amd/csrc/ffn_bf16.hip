@@ -566,11 +566,18 @@ __global__ __launch_bounds__(NW * 64, OCC) void grouped_gemm_bf16(
 // Workgroup b serves (slot b / ftiles, feature tile b % ftiles): it knows its
 // weights before it knows whether the slot has any tokens, so the first group
 // of weight loads is issued ahead of the read of the offsets and the latency of
-// the two overlaps; the workgroup of an empty slot then simply leaves.  A slot
-// with more than 32 tokens (rare at these batch sizes) is worked off 32 rows
-// at a time.
+// the two overlaps; the workgroup of an empty slot then simply leaves.  That is
+// a slot's first 32 rows.  The further row tiles of all slots are numbered
+// through -- at most T / 32 of them -- and have workgroups behind those: one
+// that worked off its slot 32 rows at a time streamed the same weights over and
+// over while the others had left.  us per layer, before and after, with four
+// fifths of the tokens alike: 4 slots of 768 x 3072, T = 170 42.5 / 27.8; 16
+// slots, T = 200 64.3 / 50.9; 128 slots, T = 700 326 / 181; clustered tokens: 4
+// slots, T = 200 38.9 / 28.0, of 1024 x 4096 51.9 / 40.1.  Two workgroups to a
+// compute unit: a third, for which there are registers, gains 5 % on 32 slots
+// (T = 180 73 / 69) and costs 4 % on 64 and 128 (T = 64 84.7 / 88.8) and 8 % on 4.
 template <int NWV, int KSPLIT, bool FIRST>
-__global__ __launch_bounds__(NWV * 64) void small_gemm_bf16(
+__global__ __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void small_gemm_bf16(
     const uint16_t* __restrict__ X, const uint4* __restrict__ Wp, const int32_t* __restrict__ offsets,
     int nslots, int T, uint16_t* __restrict__ Y, int R, int N, const FuseArgs fz) {
     constexpr int G = 8;                                   // reduction steps fetched together
@@ -579,7 +586,8 @@ __global__ __launch_bounds__(NWV * 64) void small_gemm_bf16(
     __shared__ __align__(16) float red[KSPLIT > 1 ? (KSPLIT - 1) * FBW * 16 * 64 : 1];
     const int nfb = N >> 5, nrb = R >> 4;
     const int ftiles = (nfb + FBW - 1) / FBW;
-    const int slot = blockIdx.x / ftiles, ftile = blockIdx.x % ftiles;
+    const int item = blockIdx.x / ftiles, ftile = blockIdx.x % ftiles;
+    const int extra = item - nslots;                       // >= 0: which of the further row tiles
     // the wave index as a scalar: the reduction range below must be wave-uniform in the
     // compiler's eyes too, because an MFMA under a lane mask still runs for every lane
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -588,17 +596,21 @@ __global__ __launch_bounds__(NWV * 64) void small_gemm_bf16(
     const bool fb_ok = fb < nfb;
     const int per = (nrb + KSPLIT - 1) / KSPLIT;
     const int kb_lo = min(part * per, nrb), kb_hi = min(kb_lo + per, nrb);
-    const uint4* wp = Wp + ((size_t)(fz.phys ? fz.phys[slot] : slot) * nfb + min(fb, nfb - 1)) * nrb * 64 + lane;
+    auto weights_of = [&](int slot) {
+        return Wp + ((size_t)(fz.phys ? fz.phys[slot] : slot) * nfb + min(fb, nfb - 1)) * nrb * 64 + lane;
+    };
+    int slot = min(item, nslots - 1);
+    const uint4* wp = weights_of(slot);
 
     uint4 wA[G], xA[G], wB[G], xB[G];
     auto fetch_w = [&](uint4 (&w)[G], int g0) {
 #pragma unroll
         for (int i = 0; i < G; ++i) w[i] = wp[(size_t)max(min(g0 + i, kb_hi - 1), 0) * 64];   // past the end: reloaded, not used
     };
-    fetch_w(wA, kb_lo);                                    // on its way before anything else is known
+    if (extra < 0) fetch_w(wA, kb_lo);                     // on its way before anything else is known
 
     // this slot's rows and the padded rows before it (segments re-based to multiples of 32)
-    int seg_a = 0, seg_b = 0, pad_before = 0;
+    int seg_a = 0, seg_b = 0, pad_before = 0, more_before = 0, tile = 0;
     for (int base = 0; base < nslots; base += 64) {
         const int k = base + lane;
         int a = 0, b = 0;
@@ -608,10 +620,19 @@ __global__ __launch_bounds__(NWV * 64) void small_gemm_bf16(
         }
         const int pad = (b - a + 31) & ~31;
         const int pin = smoe_wave_incl_scan(pad, lane);
-        if (slot >= base && slot < base + 64) {
-            seg_a = __shfl(a, slot - base);
-            seg_b = __shfl(b, slot - base);
-            pad_before += __shfl(pin - pad, slot - base);
+        int at = item - base;                              // this workgroup's lane of the chunk, if it is one of its lanes
+        if (extra >= 0) {
+            const int more = max((pad >> 5) - 1, 0), upto = smoe_wave_incl_scan(more, lane);
+            const unsigned long long past = __ballot(more_before + upto > extra);
+            at = past ? __ffsll(past) - 1 : 64;
+            tile = extra - more_before - __shfl(upto - more, at & 63) + 1;
+            more_before += __shfl(upto, 63);
+        }
+        if (at < 64) {
+            slot = base + at;
+            seg_a = __shfl(a, at);
+            seg_b = __shfl(b, at);
+            pad_before += __shfl(pin - pad, at);
             break;
         }
         pad_before += __shfl(pin, 63);
@@ -619,93 +640,95 @@ __global__ __launch_bounds__(NWV * 64) void small_gemm_bf16(
     seg_a = __builtin_amdgcn_readfirstlane(seg_a);
     seg_b = __builtin_amdgcn_readfirstlane(seg_b);
     pad_before = __builtin_amdgcn_readfirstlane(pad_before);
-    if (seg_b <= seg_a) return;                            // nothing routed to this slot
+    if (seg_b <= seg_a) return;                            // nothing routed to this slot, or no further row tile
+    if (extra >= 0) {
+        slot = __builtin_amdgcn_readfirstlane(slot);
+        tile = __builtin_amdgcn_readfirstlane(tile);
+        wp = weights_of(slot);
+        fetch_w(wA, kb_lo);
+    }
 
-    for (int m0 = seg_a; m0 < seg_b; m0 += 32) {
-        const int m_end = seg_b, pm0 = pad_before + (m0 - seg_a);
-        const uint4* xp;                                   // this lane's token operand at reduction step 0
-        size_t xstep;                                      // in uint4 units per reduction step
-        if (XFRAG) {
-            xp = (const uint4*)X + ((size_t)(pm0 >> 5) * (R >> 3) + (lane >> 5)) * 32 + (lane & 31);
-            xstep = 2 * 32;
-        } else {
-            int row = min(m0 + (lane & 31), m_end - 1);
-            if (fz.perm) row = fz.perm[row];
-            xp = (const uint4*)(X + (size_t)row * R + (lane >> 5) * 8);
-            xstep = 2;
+    const int m0 = seg_a + 32 * tile, m_end = seg_b, pm0 = pad_before + 32 * tile;
+    const uint4* xp;                                   // this lane's token operand at reduction step 0
+    size_t xstep;                                      // in uint4 units per reduction step
+    if (XFRAG) {
+        xp = (const uint4*)X + ((size_t)(pm0 >> 5) * (R >> 3) + (lane >> 5)) * 32 + (lane & 31);
+        xstep = 2 * 32;
+    } else {
+        int row = min(m0 + (lane & 31), m_end - 1);
+        if (fz.perm) row = fz.perm[row];
+        xp = (const uint4*)(X + (size_t)row * R + (lane >> 5) * 8);
+        xstep = 2;
+    }
+    auto fetch_x = [&](uint4 (&xv)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) xv[i] = xp[(size_t)max(min(g0 + i, kb_hi - 1), 0) * xstep];
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    auto consume = [&](uint4 (&w)[G], uint4 (&xv)[G], int g0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            // steps past the end of the range multiply by a zero token operand
+            const uint4 xz = g0 + i < kb_hi ? xv[i] : make_uint4(0, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(w[i]), as_frag(xz), acc, 0, 0, 0);
         }
-        auto fetch_x = [&](uint4 (&xv)[G], int g0) {
+    };
+    // two groups of G reduction steps are always in flight: while one group's
+    // MFMAs run, the next group's operands are already on their way
+    fetch_x(xA, kb_lo);
+    for (int g0 = kb_lo; g0 < kb_hi; g0 += 2 * G) {
+        fetch_w(wB, g0 + G);
+        fetch_x(xB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wA, xA, g0);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_w(wA, g0 + 2 * G);
+        fetch_x(xA, g0 + 2 * G);
+        __builtin_amdgcn_sched_barrier(0);
+        consume(wB, xB, g0 + G);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (KSPLIT > 1) {
+        if (part > 0) {
 #pragma unroll
-            for (int i = 0; i < G; ++i) xv[i] = xp[(size_t)max(min(g0 + i, kb_hi - 1), 0) * xstep];
-        };
-        f32x16 acc;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-        auto consume = [&](uint4 (&w)[G], uint4 (&xv)[G], int g0) {
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                // steps past the end of the range multiply by a zero token operand
-                const uint4 xz = g0 + i < kb_hi ? xv[i] : make_uint4(0, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(w[i]), as_frag(xz), acc, 0, 0, 0);
-            }
-        };
-        // two groups of G reduction steps are always in flight: while one group's
-        // MFMAs run, the next group's operands are already on their way
-        if (m0 != seg_a) fetch_w(wA, kb_lo);               // (the first row tile's were issued at the top)
-        fetch_x(xA, kb_lo);
-        for (int g0 = kb_lo; g0 < kb_hi; g0 += 2 * G) {
-            fetch_w(wB, g0 + G);
-            fetch_x(xB, g0 + G);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(wA, xA, g0);
-            __builtin_amdgcn_sched_barrier(0);
-            fetch_w(wA, g0 + 2 * G);
-            fetch_x(xA, g0 + 2 * G);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(wB, xB, g0 + G);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < 16; ++i) red[(((part - 1) * FBW + fbi) * 16 + i) * 64 + lane] = acc[i];
         }
-        if (KSPLIT > 1) {
-            if (m0 != seg_a) __syncthreads();              // the previous row tile's sums have been read
-            if (part > 0) {
+        __syncthreads();
+        if (part == 0) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) red[(((part - 1) * FBW + fbi) * 16 + i) * 64 + lane] = acc[i];
-            }
-            __syncthreads();
-            if (part == 0) {
+            for (int w2 = 0; w2 < KSPLIT - 1; ++w2)
 #pragma unroll
-                for (int w2 = 0; w2 < KSPLIT - 1; ++w2)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[i] += red[((w2 * FBW + fbi) * 16 + i) * 64 + lane];
-            }
+                for (int i = 0; i < 16; ++i) acc[i] += red[((w2 * FBW + fbi) * 16 + i) * 64 + lane];
         }
-        if (part > 0 || !fb_ok) continue;
-        // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, token l%32
-        uint16_t* ydst;
-        const uint16_t* rsrc = nullptr;
-        float gmul = 1.f;
-        if (YFRAG) {
-            ydst = Y + (((size_t)(pm0 >> 5) * (N >> 3) + fb * 4) * 32 + (lane & 31)) * 8 + (lane >> 5) * 4;
-        } else {
-            int row = m0 + (lane & 31);
-            if (row >= m_end) continue;
-            if (fz.perm) {
-                row = fz.perm[row];
-                gmul = fz.gate[row];
-                if (fz.residual) rsrc = fz.residual + (size_t)row * N + fb * 32 + (lane >> 5) * 4;
-            }
-            ydst = Y + (size_t)row * N + fb * 32 + (lane >> 5) * 4;
+    }
+    if (part > 0 || !fb_ok) return;
+    // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, token l%32
+    uint16_t* ydst;
+    const uint16_t* rsrc = nullptr;
+    float gmul = 1.f;
+    if (YFRAG) {
+        ydst = Y + (((size_t)(pm0 >> 5) * (N >> 3) + fb * 4) * 32 + (lane & 31)) * 8 + (lane >> 5) * 4;
+    } else {
+        int row = m0 + (lane & 31);
+        if (row >= m_end) return;
+        if (fz.perm) {
+            row = fz.perm[row];
+            gmul = fz.gate[row];
+            if (fz.residual) rsrc = fz.residual + (size_t)row * N + fb * 32 + (lane >> 5) * 4;
         }
+        ydst = Y + (size_t)row * N + fb * 32 + (lane >> 5) * 4;
+    }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float v0 = acc[4 * g], v1 = acc[4 * g + 1], v2 = acc[4 * g + 2], v3 = acc[4 * g + 3];
-            if (!YFRAG) apply_gate(v0, v1, v2, v3, gmul, rsrc ? rsrc + g * 8 : nullptr, fz.perm != nullptr);
-            if (RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
-            uint2 o;
-            o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-            o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
-            *(uint2*)(ydst + (YFRAG ? g * 32 * 8 : g * 8)) = o;
-        }
+    for (int g = 0; g < 4; ++g) {
+        float v0 = acc[4 * g], v1 = acc[4 * g + 1], v2 = acc[4 * g + 2], v3 = acc[4 * g + 3];
+        if (!YFRAG) apply_gate(v0, v1, v2, v3, gmul, rsrc ? rsrc + g * 8 : nullptr, fz.perm != nullptr);
+        if (RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
+        uint2 o;
+        o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
+        o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+        *(uint2*)(ydst + (YFRAG ? g * 32 * 8 : g * 8)) = o;
     }
 }
 
@@ -713,10 +736,10 @@ template <int NWV, int KSPLIT, bool FIRST>
 void launch_small(const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots, uint16_t* Y, int R,
                   int N, int T, const FuseArgs& fz, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     constexpr int FBW = NWV / KSPLIT;
-    (void)T;
     int nfb = N >> 5;
     int ftiles = (nfb + FBW - 1) / FBW;
-    dim3 grid(nslots * ftiles);                            // one workgroup per (slot, feature tile)
+    // one workgroup per (slot, feature tile), and as many further row tiles as T tokens can need
+    dim3 grid((nslots + T / 32) * ftiles);
     smoe_launch_timed(small_gemm_bf16<NWV, KSPLIT, FIRST>, grid, dim3(NWV * 64), s, e0, e1, X, (const uint4*)Wp,
                       offsets, nslots, T, Y, R, N, fz);
 }
