@@ -868,11 +868,16 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
         v1 = 5;
         v2 = 6;
     } else {
-        // The streaming kernel reads a slot's weights once while its tokens fit 32 columns: few tokens on few slots whose
-        // weights are no trifle (us, streaming / best tile: T = 140 4 slots of 768 x 3072 16.0 / 22.0, 16 slots 21.0 / 26.0;
-        // T = 200 16 slots 25.5 / 26.2, 32 slots 37.0 / 31.6; 4 slots of 256 x 768 8.1 / 7.3), or a reduction without
-        // weight prefetch.
-        const bool stream = T <= 200 && K <= 16 && per_slot <= 50 && 2.0 * K * d * f >= 16e6;
+        // The second product streams while its workgroups, one per 32 features and 32 rows of a slot, are little more than
+        // the chip holds at once (two per compute unit): each then has a quarter of a reduction per wave in front of it,
+        // where a tile has all of it.  Measured on 270 batches of 2 to 100 slots, T = 129 .. 2000, clustered and even tokens,
+        // us per layer, streaming / best tile: up to 600 workgroups 20 .. 0 % ahead (4 slots of 768 x 3072, T = 200 28 / 35; 6,
+        // T = 320 37 / 45; 16 of 512 x 4096, T = 426 55 / 60), up to 780 8 .. 0 % ahead with less than 28 tokens per slot (18
+        // slots of 768 x 3072, T = 374 56 / 59) and even with more, beyond that behind (32 slots, T = 236 67 / 60).  Not for
+        // short reductions, whose end the split lengthens (32 slots of 256 x 512, T = 260 23.5 / 22.4), and not for T = 640 and
+        // more, where the rows of the largest slots stream too often (one slot of 768 x 3072, T = 800 39.7 / 37.8).
+        const int groups = (K + T / 32) * (d >> 5);
+        const bool stream = T <= 512 && f >= 768 && (groups <= 600 || (groups <= 780 && per_slot < 28));
         v1 = d % 128 != 0 ? (per_slot < 28 ? 4 : 3) : pick_tile(true, d, f, T, K);
         v2 = f % 128 != 0 ? (per_slot < 28 ? 6 : 1) : stream ? 6 : pick_tile(false, f, d, T, K);
     }

@@ -1,0 +1,28 @@
+"""Which kernels the separate FFN call and a prefill batch take, at the lines of the rules in pick_variants.  (No GPU: the
+choice is made from the sizes.)"""
+import pytest
+
+from paper_2308_15030_amd import binding as b
+
+
+def kernels(K, d, f, T, fused=False):
+    h = b.smoe_create(max(K, 2), K, d, f, T, b.SMOE_BF16)
+    try:
+        return b.smoe_describe_ffn(h, T, fused).split(" | ")
+    finally:
+        b.smoe_destroy(h)
+
+
+@pytest.mark.parametrize("K,d,f,T,streams", [
+    # few slots, whatever their weights and however many tokens a slot has
+    (6, 512, 2048, 132, True), (4, 768, 3072, 200, True), (2, 768, 3072, 140, True), (1, 768, 3072, 400, True),
+    # up to 600 workgroups (d_model = 768: 25 row tiles of 24 feature blocks)
+    (18, 768, 3072, 223, True), (19, 768, 3072, 223, True), (10, 768, 3072, 480, True), (11, 768, 3072, 480, False),
+    # up to 780 with less than 28 tokens per slot
+    (18, 768, 3072, 374, True), (26, 768, 3072, 223, True), (27, 768, 3072, 223, False), (32, 768, 3072, 236, False),
+    # short reductions and many tokens
+    (8, 256, 768, 140, True), (8, 256, 640, 140, False), (2, 512, 2048, 512, True), (2, 512, 2048, 513, False),
+    # up to five tokens per slot always
+    (100, 512, 2048, 590, True)])
+def test_second_product_streams(K, d, f, T, streams):
+    assert kernels(K, d, f, T)[1].startswith("small_gemm_bf16<4, 4") == streams
