@@ -848,15 +848,21 @@ int pick_tile(bool first, int R, int N, int T, int K) {
 //  * The reduction is no multiple of 128: the tiled kernel then has no weight prefetch.  us, tiled -> ring: 16 slots of
 //    992 x 3296, T = 800 33.0 -> 29.8 and 77.0 -> 42.6, T = 8000 107 -> 72 and 134 -> 70; 11 of 416 x 1696, T = 800 12.5 -> 10.7
 //    and 31.6 -> 18.0.  Where the streaming kernel splits a second product (v = 6) it stays ahead (T = 200: 15.8, 17.8),
-//    and with few tokens so do tiles of 64-deep slices (6 slots of 448 x 1280, T = 140 8.1, 9.2, T = 300 8.8, 9.4).  The small tiles
+//    and with few tokens so do tiles of 64-deep slices (6 slots of 448 x 1280, T = 140 8.1, 9.2, T = 300 8.8, 9.4).  Under 6
+//    tokens per slot the first product's streaming kernel stays where rows are long and slots at most 64 (us per layer, streaming
+//    / ring: 24 slots of 992 x 3296, T = 100 84 / 89, 48 T = 120 .. 264 2 .. 3 % ahead, 16 of 1184 x 4736 5 %; but 48 of 544 x
+//    2176, T = 168 71 / 69, 128 of 928 x 3712, T = 192 1 .. 5 % behind).  The small tiles
 //    serve where fewer than a hundred large ones exist (608 x 2912, T = 8000 second: 44.5, 49.0 with large ones;
 //    992 x 3296 70 with large ones, 96).
 //  * There are large tiles for the chip many times over, where the matrix products and the power they draw count
 //    and not the bytes alone (128 x 128 tiles -> ring: 768 x 3072, T = 16384 108 -> 94 and 105 -> 80; 32 slots of
 //    1024 x 4096 190 -> 165 and 187 -> 166; 16 of 768 x 2048 80 -> 68 and 75 -> 60).
-int ring_tile(bool first, int R, int N, int T, int per_slot, int tiled) {
+int ring_tile(bool first, int R, int N, int T, int K, int tiled) {
     const double tiles = (double)T * N / 65536;            // full 256 x 256 tiles
-    if (R % 128 != 0) return tiled == 6 || (first && per_slot < 60 && R % 64 == 0) ? 0 : tiles >= 100 ? 10 : 9;
+    if (R % 128 != 0) {
+        if (tiled == 6 || (tiled == 5 && R >= 900 && K <= 64) || (first && T / K < 60 && R % 64 == 0)) return 0;
+        return tiles >= 100 ? 10 : 9;
+    }
     return tiles >= (first ? 300 : 100) ? 10 : 0;
 }
 
@@ -886,7 +892,7 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
     if (smoe_decode_first_applies(L, T)) {
         v2 = 6;
     } else {
-        const int r1 = ring_tile(true, d, f, T, per_slot, v1), r2 = ring_tile(false, f, d, T, per_slot, v2);
+        const int r1 = ring_tile(true, d, f, T, K, v1), r2 = ring_tile(false, f, d, T, K, v2);
         if (r1 && smoe_ring_applies(true, d, T)) v1 = r1;
         if (r2 && smoe_ring_applies(false, f, T)) v2 = r2;
     }

@@ -26,3 +26,11 @@ def kernels(K, d, f, T, fused=False):
     (100, 512, 2048, 590, True)])
 def test_second_product_streams(K, d, f, T, streams):
     assert kernels(K, d, f, T)[1].startswith("small_gemm_bf16<4, 4") == streams
+
+
+@pytest.mark.parametrize("K,d,f,T,streams", [
+    # d_model no multiple of 64, fewer than six tokens per slot
+    (24, 992, 3296, 100, True), (64, 992, 3296, 380, True), (65, 992, 3296, 380, False), (24, 864, 3456, 130, False),
+    (32, 416, 1696, 150, False), (24, 992, 3296, 144, False)])
+def test_first_product_streams(K, d, f, T, streams):
+    assert kernels(K, d, f, T)[0].startswith("small_gemm_bf16<4, 1" if streams else "ring_gemm_bf16")
