@@ -565,12 +565,16 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
     }
 }
 
-// NB = 1: at most 32 tokens, 2: more.
+// NB = 1: at most 32 tokens, 2: more.  Two workgroups to a compute unit and no third, for which there are registers:
+// their weights are on their way before they know their tokens, and with three to a unit more of them pull at once on the
+// units that get three (us per layer, three / two: 18 slots of 1024 x 4096, T = 33 64.4 / 60.2, T = 20 59.3 / 54.6; 32 of 768 x 3072,
+// T = 32 47.5 / 44.5; 16 of 512 x 3072, T = 128, four fifths of the tokens alike 44.7 / 40.9; 16 of 768 x 3072 alike).  Where the
+// router runs first and few slots are served the third gains (64 slots of 768 x 3072, T = 32 56.5 / 58.2).
 template <int NB>
-__global__ __launch_bounds__(256, 2) void decode_second_kernel(const second_args a) { decode_second_body<(NB > 1), false, false>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_second_kernel(const second_args a) { decode_second_body<(NB > 1), false, false>(a); }
 
 template <int NB>
-__global__ __launch_bounds__(256, 2) void decode_second_stream_kernel(const second_args a) { decode_second_body<(NB > 1), true, false>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_second_stream_kernel(const second_args a) { decode_second_body<(NB > 1), true, false>(a); }
 
 template <int NB, bool STREAM>
 __global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<(NB > 1), STREAM, true>(a); }
