@@ -711,15 +711,23 @@ bool sparse(const smoe_config& c, int T) {
 
 // Layout of the hidden activations between the two launches.  A wave of the second one reads 32 bytes of each of its
 // tokens per step.  Token by token the steps of a token share lines, and only the slot's own tokens are touched: better
-// where slots hold few of the batch's tokens (us per layer, [feature / 8][token] / [token][feature]: 16 slots of
-// 768 x 3072, T = 32 31.4 / 30.0, T = 64 37.1 / 34.6; eight T = 32 19.6 / 18.4; four of 1024 x 4096, T = 13 20.2 / 19.5).  Unit by
-// unit neighbouring tokens share a line: better where slots hold most of them (two slots of 768 x 3072, T = 32 13.5 /
-// 15.2, T = 64 15.1 / 17.3), and for rows of up to 4 KB (20 slots of 512 x 2048, T = 48 24.5 / 25.3; four of 768 x 2048,
-// T = 48 17.0 / 18.0; six of 416 x 1696 alike).
-hidden_strides hidden_layout(const smoe_config& c, int T) {
-    const int units = c.d_ff >> 3, pitch = (T + 31) & ~31;
-    if (c.K >= 4 && c.d_ff > 2048) return hidden_strides{units * T, units, 1};
-    return hidden_strides{units * pitch, 1, pitch};
+// where slots hold few of the batch's tokens.  Unit by unit neighbouring tokens share a line: better where slots hold most
+// of them, and for rows of up to 4 KB.  What the extra requests of a slot with many tokens cost shows beside weights that
+// come from the cache, and little beside weights from memory.  us per layer, [feature / 8][token] / [token][feature],
+// clustered tokens:
+//   from memory, d_ff > 2048   K = 4 768 x 3072 T = 32 17.0 / 16.1, T = 64 19.5 / 19.2; 6 T = 32 19.6 / 19.1; 16 T = 32 31.4 / 30.0,
+//                              T = 64 37.1 / 34.6; 6 of 512 x 3072 T = 64 21.5 / 20.8; 5 of 1024 x 4096 T = 32 24.4 / 22.8
+//   from the cache             K = 4 512 x 3072 T = 48 13.7 / 14.8, T = 64 14.6 / 15.7; 4 of 768 x 3072 T = 64 16.8 / 17.8; 5 of 640 x
+//                              2560 T = 48 14.9 / 16.3; 6 of 256 x 3072 T = 48 14.0 / 15.0; but 8 of 768 x 3072 T = 32 17.6 / 17.0,
+//                              10 T = 100 28.1 / 26.6; 8 of 512 x 2560 T = 64 18.1 / 17.1
+//   fewer slots                two of 1024 x 4096 T = 32 16.4 / 18.3; three of 768 x 3072 T = 48 18.6 / 20.0
+//   d_ff <= 2048               20 of 512 x 2048 T = 48 24.5 / 25.3; four of 768 x 2048 T = 48 17.0 / 18.0
+// With four fifths of the tokens on one slot the second form is up to 10 % behind from 8 slots on as well.
+bool hidden_by_token(const smoe_config& c, bool stream) { return c.d_ff > 2048 && c.K >= (stream ? 4 : 8); }
+
+hidden_strides hidden_layout(const smoe_layer* L, int T) {
+    const int units = L->cfg.d_ff >> 3, pitch = (T + 31) & ~31;
+    return L->hidden_by_token ? hidden_strides{units * T, units, 1} : hidden_strides{units * pitch, 1, pitch};
 }
 
 template <int NEB, int NBF>
@@ -734,9 +742,9 @@ int launch_first(const smoe_layer* L, const smoe_route_args& ra, bool stream, hi
     if (int rc = raised[stream].ensure((const void*)kern, lds, LDS_LIMIT)) return rc;
     if (e0 && e1)
         hipExtLaunchKernelGGL(kern, grid, dim3(512), lds, s, e0, e1, 0, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden,
-                              hidden_layout(c, ra.T), c.d_ff, phys, fbw);
+                              hidden_layout(L, ra.T), c.d_ff, phys, fbw);
     else
-        hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden, hidden_layout(c, ra.T),
+        hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, ra, (const uint4*)L->slot_w1, (uint16_t*)L->d_hidden, hidden_layout(L, ra.T),
                            c.d_ff, phys, fbw);
     return smoe_check_hip(hipGetLastError(), "smoe_forward: decode launch");
 }
@@ -761,10 +769,10 @@ int launch_first_served(const smoe_layer* L, const smoe_route_args& ra, bool str
     if (int rc = raised[stream].ensure((const void*)kern, lds, LDS_LIMIT)) return rc;
     if (e0 && e1)
         hipExtLaunchKernelGGL(kern, grid, dim3(512), lds, s, e0, e1, 0, (const uint16_t*)ra.x, (const uint4*)L->slot_w1, ra.T,
-                              (uint16_t*)L->d_hidden, hidden_layout(c, ra.T), c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
+                              (uint16_t*)L->d_hidden, hidden_layout(L, ra.T), c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
     else
         hipLaunchKernelGGL(kern, grid, dim3(512), lds, s, (const uint16_t*)ra.x, (const uint4*)L->slot_w1, ra.T, (uint16_t*)L->d_hidden,
-                           hidden_layout(c, ra.T), c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
+                           hidden_layout(L, ra.T), c.d_model, c.d_ff, phys, (const int32_t*)ra.slot, fbw);
     return smoe_check_hip(hipGetLastError(), "smoe_forward: first product launch");
 }
 
@@ -820,6 +828,7 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
     const smoe_route_args ra{x, (const uint4*)L->d_router_split, L->router_w, L->d_expert_to_slot, T, c.d_model, c.E, c.gate_mode,
                              orig_expert, orig_gate, slot, gate, xnorm, nullptr, c.K};
     const bool stream = smoe_weights_outgrow_cache(L);
+    L->hidden_by_token = hidden_by_token(c, stream);
     if (sparse(c, T) && T <= FEW_T) {
         switch (router_instance(c.E)) {
             case 1: return launch_few<1>(L, ra, stream, s, e0, e1);
@@ -845,7 +854,7 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
 int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_of, const float* gate,
                                       const uint16_t* residual, int T, uint16_t* out, hipStream_t s) {
     const smoe_config& c = L->cfg;
-    const second_args a{(const uint16_t*)L->d_hidden, hidden_layout(c, T), (const uint4*)L->slot_w2, slot_of, T, c.E, c.K, c.d_ff, c.d_model,
+    const second_args a{(const uint16_t*)L->d_hidden, hidden_layout(L, T), (const uint4*)L->slot_w2, slot_of, T, c.E, c.K, c.d_ff, c.d_model,
                         c.spare_slots > 0 ? L->d_phys : nullptr, gate, residual, out, L->tail};
     const bool stream = smoe_weights_outgrow_cache(L);
     if (sparse(c, T) && T <= FEW_T) {

@@ -34,6 +34,7 @@ struct smoe_step_tail {
 struct smoe_layer {
     smoe_config cfg;
     mutable smoe_step_tail tail{};           // left by a small batch's first launch for its second
+    mutable bool hidden_by_token = false;    // ... with the layout in which it leaves the hidden activations
     bool bound = false;
     int slots_set = 0;                       // number of slots that hold an expert
     std::vector<int32_t> slot_to_expert;     // host copies of the maps
