@@ -224,16 +224,11 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
     // matrix pipe behind it.
     // Loads past the last slice are clamped to it (fetched again, never used),
     // so the loop body has no conditional loads.
-    // With more than 4 token blocks the operand reads are pipelined in two
-    // half-steps of the block range, which halves the operand registers.
-    constexpr int TD = ((PD & 1) && AF * NBF < 16) ? 2 : 1;   // the largest tile keeps one set only
-    constexpr int NG = NBF > 4 ? 2 : 1;                   // operand groups per reduction step
-    constexpr int GB = (NBF + NG - 1) / NG;               // token blocks per group
-    constexpr int NSTEP = KS * NG;
+    constexpr int TD = PD & 1 ? 2 : 1;
     static_assert(KS % 2 == 0, "the operand double buffer assumes an even number of steps per slice");
     uint4 tregA[CPT], tregB[CPT];                       // token register sets 0 and 1
     uint4 wbuf[PD + 1][KS][AF];
-    bf16x8 xf[2][GB];
+    bf16x8 xf[2][NBF];
 #pragma unroll
     for (int i = 0; i < CPT; ++i) tregA[i] = *(const uint4*)tsrc[i];
 #pragma unroll
@@ -287,7 +282,7 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
         }
     }
 #pragma unroll
-    for (int b = 0; b < GB; ++b) xf[0][b] = as_frag(*(const uint4*)&xs[xoff + b * XB]);
+    for (int b = 0; b < NBF; ++b) xf[0][b] = as_frag(*(const uint4*)&xs[xoff + b * XB]);
 
     int st = 0;                                           // LDS stage of the current slice
     // nchunks is a multiple of PD+1 (the launcher picks PD so; PD is 0, 1 or 3),
@@ -318,25 +313,19 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
         }
         __builtin_amdgcn_sched_barrier(0);                // keep the prefetches ahead of the math
 #pragma unroll
-        for (int t = 0; t < NSTEP; ++t) {
-            const int ks = t / NG, g = t % NG;
-            if (t == NSTEP / 2) __syncthreads();          // stage (c+1)%3 is complete from here on
-            {   // operands of step t+1: the next group, the next reduction step, or the next slice
-                const int t1 = t + 1;
-                const int ks1 = (t1 % NSTEP) / NG, g1 = t1 % NG;
-                const uint16_t* src = (t1 == NSTEP ? tile1 : tile) + ks1 * XK;
+        for (int ks = 0; ks < KS; ++ks) {
+            if (ks == KS / 2) __syncthreads();            // stage (c+1)%3 is complete from here on
+            {   // operands of the next reduction step, or of the next slice's first
+                const uint16_t* src = (ks + 1 == KS ? tile1 : tile) + (ks + 1) % KS * XK;
 #pragma unroll
-                for (int b = 0; b < GB; ++b)
-                    if (g1 * GB + b < NBF) xf[t1 & 1][b] = as_frag(*(const uint4*)&src[(g1 * GB + b) * XB]);
+                for (int b = 0; b < NBF; ++b) xf[(ks + 1) & 1][b] = as_frag(*(const uint4*)&src[b * XB]);
             }
             __builtin_amdgcn_sched_barrier(0);            // next step's operands are on their way
 #pragma unroll
-            for (int b = 0; b < GB; ++b)
+            for (int b = 0; b < NBF; ++b)
 #pragma unroll
                 for (int a = 0; a < AF; ++a)
-                    if (g * GB + b < NBF)
-                        acc[a][g * GB + b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            as_frag(wbuf[u][ks][a]), xf[t & 1][b], acc[a][g * GB + b], 0, 0, 0);
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(wbuf[u][ks][a]), xf[ks & 1][b], acc[a][b], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
         st = st1;
@@ -436,52 +425,45 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
         __syncthreads();
         const bool fused = fz.perm != nullptr, has_res = fused && fz.residual != nullptr;
         const int col0 = ftile * F;
-        constexpr int CH = NP < 8 ? NP : 8;               // pieces handled together (bounds the registers)
+        int prow[NP], pcol[NP];
+        uint4 rs[NP];
 #pragma unroll
-        for (int i0 = 0; i0 < NP; i0 += CH) {
-            int prow[CH], pcol[CH];
-            uint4 rs[CH];
-#pragma unroll
-            for (int j = 0; j < CH; ++j) {                // residual pieces not fetched earlier are asked for first
-                // the last group is short when NP is not a multiple of CH: a piece past NP would belong
-                // to a row below the tile, whose entry of the row table is stale
-                if (i0 + j >= NP) { prow[j] = -1; pcol[j] = 0; rs[j] = make_uint4(0, 0, 0, 0); continue; }
-                const int idx = tid + (i0 + j) * THREADS, r = idx / CPR8, c = idx % CPR8;
-                pcol[j] = col0 + c * 8;
-                prow[j] = pcol[j] < N ? orow[r] : -1;
-                if constexpr (EARLY_RES) {
-                    rs[j] = res[i0 + j];
-                } else {
-                    rs[j] = make_uint4(0, 0, 0, 0);
-                    if (has_res && prow[j] >= 0) rs[j] = *(const uint4*)(fz.residual + (size_t)prow[j] * N + pcol[j]);
-                }
+        for (int j = 0; j < NP; ++j) {                    // residual pieces not fetched earlier are asked for first
+            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8;
+            pcol[j] = col0 + c * 8;
+            prow[j] = pcol[j] < N ? orow[r] : -1;
+            if constexpr (EARLY_RES) {
+                rs[j] = res[j];
+            } else {
+                rs[j] = make_uint4(0, 0, 0, 0);
+                if (has_res && prow[j] >= 0) rs[j] = *(const uint4*)(fz.residual + (size_t)prow[j] * N + pcol[j]);
             }
+        }
 #pragma unroll
-            for (int j = 0; j < CH; ++j) {
-                if (prow[j] < 0) continue;
-                const int idx = tid + (i0 + j) * THREADS, r = idx / CPR8, c = idx % CPR8;
-                const uint2 lo = *(const uint2*)&xs[r * LDO + c * 8], hi = *(const uint2*)&xs[r * LDO + c * 8 + 4];
-                uint4 o = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                if (fused) {
-                    const float g = ogate[r];
-                    uint32_t yw[4] = {o.x, o.y, o.z, o.w}, rw[4] = {rs[j].x, rs[j].y, rs[j].z, rs[j].w};
+        for (int j = 0; j < NP; ++j) {
+            if (prow[j] < 0) continue;
+            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8;
+            const uint2 lo = *(const uint2*)&xs[r * LDO + c * 8], hi = *(const uint2*)&xs[r * LDO + c * 8 + 4];
+            uint4 o = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            if (fused) {
+                const float g = ogate[r];
+                uint32_t yw[4] = {o.x, o.y, o.z, o.w}, rw[4] = {rs[j].x, rs[j].y, rs[j].z, rs[j].w};
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float y0 = __uint_as_float(yw[q] << 16), y1 = __uint_as_float(yw[q] & 0xFFFF0000u);
-                        float o0, o1;
-                        if (has_res) {
-                            o0 = fmaf(g, y0, __uint_as_float(rw[q] << 16));
-                            o1 = fmaf(g, y1, __uint_as_float(rw[q] & 0xFFFF0000u));
-                        } else {
-                            o0 = g * y0;
-                            o1 = g * y1;
-                        }
-                        yw[q] = (uint32_t)smoe_f32_to_bf16(o0) | ((uint32_t)smoe_f32_to_bf16(o1) << 16);
+                for (int q = 0; q < 4; ++q) {
+                    const float y0 = __uint_as_float(yw[q] << 16), y1 = __uint_as_float(yw[q] & 0xFFFF0000u);
+                    float o0, o1;
+                    if (has_res) {
+                        o0 = fmaf(g, y0, __uint_as_float(rw[q] << 16));
+                        o1 = fmaf(g, y1, __uint_as_float(rw[q] & 0xFFFF0000u));
+                    } else {
+                        o0 = g * y0;
+                        o1 = g * y1;
                     }
-                    o = make_uint4(yw[0], yw[1], yw[2], yw[3]);
+                    yw[q] = (uint32_t)smoe_f32_to_bf16(o0) | ((uint32_t)smoe_f32_to_bf16(o1) << 16);
                 }
-                *(uint4*)(Y + (size_t)prow[j] * N + pcol[j]) = o;
+                o = make_uint4(yw[0], yw[1], yw[2], yw[3]);
             }
+            *(uint4*)(Y + (size_t)prow[j] * N + pcol[j]) = o;
         }
         __syncthreads();                                  // the next tile's prologue reuses the ring
     }
@@ -750,8 +732,10 @@ int cus_per_die() {
     if (n == 0) {
         int dev = 0, cus = 0;
         (void)hipGetDevice(&dev);
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < XCDS)
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < XCDS) {
+            (void)hipGetLastError();
             cus = 256;
+        }
         n = cus / XCDS;
     }
     return n;
@@ -825,9 +809,10 @@ int pick_tile(bool first, int R, int N, int T, int K) {
     // unit only, at the rate of cold lines: 16 slots of 1024 x 4096, T = 777 39.5, 31.0 with 128 features), and a count
     // that is nearer to the truth
     const bool thin = first && T / K < 60;
+    const double cus = XCDS * cus_per_die();
     auto rounds = [&](int rows, int features) {
         const double x = (double)T / K / rows, tiles = K * (x + ends + (1 - ends) * std::exp(-2 * x));
-        return std::max(1.0, std::ceil(tiles * ((N + features - 1) / features) / 256 - (thin ? 0.06 : 0.03)));
+        return std::max(1.0, std::ceil(tiles * ((N + features - 1) / features) / cus - (thin ? 0.06 : 0.03)));
     };
     int best = 1;
     double least = 1e30;
