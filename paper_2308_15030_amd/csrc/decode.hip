@@ -445,9 +445,11 @@ struct second_args {
     smoe_step_tail tail;
 };
 
-// SPARSE: no weights are asked for before the slot ids are there (an instance of its own: with a branch around
-// the early loads the wait for the ids becomes a wait for everything, 0.8 us per layer).
-template <bool WIDE, bool STREAM, bool SPARSE>
+// EARLY: the first weights are asked for before the slot ids are there (an instance of its own: with a branch around
+// the early loads the wait for the ids becomes a wait for everything, 0.8 us per layer).  Not behind a router launch of
+// its own, where most slots are empty, and not with WIDE, where half of the workgroups and more have no token: early
+// loads for the first 32 columns only gave nothing (1 to 20 slots, T = 33 .. 128: -0.3 .. 0.4 us).
+template <bool WIDE, bool STREAM, bool EARLY>
 __device__ __forceinline__ void decode_second_body(const second_args& a) {
     constexpr int KSPLIT = 4, G = 8;                       // G: reduction steps fetched together
     __shared__ __align__(16) float red[(KSPLIT - 1) * 16 * 64];
@@ -474,17 +476,16 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
     };
     // A wave's loads complete in order: the slot ids are asked for first, so that waiting for them
     // does not wait for the weights, and the weights' first group right after, before anything is known.
-    // (Past the first 32 columns most workgroups have no token: they ask for the ids only.)
     const int id0 = a.slot[min(lane, a.T - 1)], id1 = WIDE ? a.slot[min(lane + 64, a.T - 1)] : 0;
     __builtin_amdgcn_sched_barrier(0);
     uint4 wA[G], wB[G];
-    if (!SPARSE && !WIDE) fetch_w(wA, kb_lo);
+    if (EARLY) fetch_w(wA, kb_lo);
     __builtin_amdgcn_sched_barrier(0);
     const bool own0 = lane < a.T && id0 == slot, own1 = WIDE && lane + 64 < a.T && id1 == slot;
     const unsigned long long m0 = __ballot(own0), m1 = WIDE ? __ballot(own1) : 0ull;
     const int n0 = __popcll(m0), n = n0 + __popcll(m1);
     if (n <= c0) return;                                   // nothing routed to this slot, or no token left (uniform over the workgroup)
-    if (SPARSE || WIDE) fetch_w(wA, kb_lo);
+    if (!EARLY) fetch_w(wA, kb_lo);
     const unsigned long long below = (1ull << lane) - 1ull;
     if (own0) s_tok[part][__popcll(m0 & below)] = lane;
     if (own1) s_tok[part][n0 + __popcll(m1 & below)] = lane + 64;
@@ -571,13 +572,14 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
 // T = 32 47.5 / 44.5; 16 of 512 x 3072, T = 128, four fifths of the tokens alike 44.7 / 40.9; 16 of 768 x 3072 alike).  Where the
 // router runs first and few slots are served the third gains (64 slots of 768 x 3072, T = 32 56.5 / 58.2).
 template <int NB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_second_kernel(const second_args a) { decode_second_body<(NB > 1), false, false>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_second_kernel(const second_args a) { decode_second_body<(NB > 1), false, NB == 1>(a); }
 
 template <int NB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_second_stream_kernel(const second_args a) { decode_second_body<(NB > 1), true, false>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_second_stream_kernel(const second_args a) { decode_second_body<(NB > 1), true, NB == 1>(a); }
 
-template <int NB, bool STREAM>
-__global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<(NB > 1), STREAM, true>(a); }
+// At most 32 tokens, few of the slots served.
+template <bool STREAM>
+__global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<false, STREAM, false>(a); }
 
 // Few tokens: workgroup (served slot, 16 features, or 8 of them while that leaves compute units idle: the lanes of
 // the other 8 then read the same weights again).  4 waves split the reduction as above, each with 24 loads in flight.
@@ -868,9 +870,7 @@ int smoe_launch_ffn_bf16_dense_second(const smoe_layer* L, const int32_t* slot_o
     const dim3 grid((T + 31) / 32 * c.K * (c.d_model >> 5) + 1);
     auto kern = T <= 32 ? (stream ? decode_second_stream_kernel<1> : decode_second_kernel<1>)
                         : (stream ? decode_second_stream_kernel<2> : decode_second_kernel<2>);
-    if (sparse(c, T))
-        kern = T <= 32 ? (stream ? dense_second_kernel<1, true> : dense_second_kernel<1, false>)
-                       : (stream ? dense_second_kernel<2, true> : dense_second_kernel<2, false>);
+    if (sparse(c, T) && T <= 32) kern = stream ? dense_second_kernel<true> : dense_second_kernel<false>;
     smoe_launch_timed(kern, grid, dim3(256), s, L->prof_ev[2], L->prof_ev[3], a);
     L->tail = smoe_step_tail{};                            // the caller's pointers are not kept
     return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");
@@ -882,7 +882,8 @@ std::string smoe_describe_decode(const smoe_layer* L, int T, bool first) {
     if (sparse(L->cfg, T) && T <= FEW_T) {
         return (first ? "dense_first_kernel_served<" + std::to_string(router_instance(L->cfg.E)) + ", " : std::string("dense_second_kernel_served<")) + tf;
     }
-    if (sparse(L->cfg, T)) return std::string(first ? "dense_first_kernel<" : "dense_second_kernel<") + (T <= 32 ? "1, " : !first || T <= 64 ? "2, " : "4, ") + tf;
+    if (sparse(L->cfg, T) && first) return std::string("dense_first_kernel<") + (T <= 32 ? "1, " : T <= 64 ? "2, " : "4, ") + tf;
+    if (sparse(L->cfg, T) && T <= 32) return "dense_second_kernel<" + tf;
     if (!first) return "decode_second" + st + "_kernel<" + (T <= 32 ? "1>" : "2>");
     return "decode_first" + st + "_kernel<" + std::to_string(router_instance(L->cfg.E)) + ", " + (T <= 32 ? "1>" : T <= 64 ? "2>" : "4>");
 }
