@@ -16,6 +16,7 @@ import pytest
 import torch
 
 from paper_2308_15030_amd import binding as b
+from test_streaming_tiles_gpu import MANY, test_row_tiles as check
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +65,11 @@ def test_ring_products(variant, d, f, extra, spare):
     assert torch.equal(L.forward_fused(x.view(torch.int16), T, accumulate=0, residual=x.view(torch.int16)), out)
     assert not torch.isnan(out.view(torch.bfloat16).float()).any()
     L.close()
+
+
+# more slots than a wave has lanes: the counts of row tiles and the slot tables go on from one chunk of 64 slots to the next
+@pytest.mark.parametrize("variant", ["9,9", "10,10"])
+@pytest.mark.parametrize("d,f", [(256, 288), (288, 544)])
+@pytest.mark.parametrize("lens", [MANY, [0] * 63 + [40, 700], [300] + [0] * 200 + [33], [5] * 256], ids=["many", "64th", "last", "all"])
+def test_many_slots(variant, d, f, lens):
+    check(variant, d, f, lens, "ring_gemm_bf16")
