@@ -567,10 +567,10 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
 }
 
 // NB = 1: at most 32 tokens, 2: more.  Two workgroups to a compute unit and no third, for which there are registers:
-// their weights are on their way before they know their tokens, and with three to a unit more of them pull at once on the
-// units that get three (us per layer, three / two: 18 slots of 1024 x 4096, T = 33 64.4 / 60.2, T = 20 59.3 / 54.6; 32 of 768 x 3072,
-// T = 32 47.5 / 44.5; 16 of 512 x 3072, T = 128, four fifths of the tokens alike 44.7 / 40.9; 16 of 768 x 3072 alike).  Where the
-// router runs first and few slots are served the third gains (64 slots of 768 x 3072, T = 32 56.5 / 58.2).
+// the units that get three are the last to finish (us per layer, three / two: 18 slots of 1024 x 4096, T = 33 64.4 / 60.2, T = 20
+// 59.3 / 54.6; 16 of 512 x 3072, T = 128, four fifths of the tokens alike 44.7 / 40.9; 16 of 768 x 3072 alike; behind a router launch
+// of its own 32 slots of 768 x 3072, T = 24 44.9 / 42.2, 64 of 512 x 2048, T = 32 34.7 / 32.5, 32 of 1024 x 4096, T = 20 63.2 / 58.4,
+// but 64 of 768 x 3072, T = 32 56.3 / 58.2; 13 shapes, T = 17 .. 32: two 4 % ahead in the mean).
 template <int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_second_kernel(const second_args a) { decode_second_body<(NB > 1), false, NB == 1>(a); }
 
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // At most 32 tokens, few of the slots served.
 template <bool STREAM>
-__global__ __launch_bounds__(256, 2) void dense_second_kernel(const second_args a) { decode_second_body<false, STREAM, false>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void dense_second_kernel(const second_args a) { decode_second_body<false, STREAM, false>(a); }
 
 // Few tokens: workgroup (served slot, 16 features, or 8 of them while that leaves compute units idle: the lanes of
 // the other 8 then read the same weights again).  4 waves split the reduction as above, each with 24 loads in flight.
@@ -705,6 +705,9 @@ int first_fbw(const smoe_config& c, double slots) {
 //   768 x 3072, E = 32    K = 8 T = 1 16.3 / 14.1 us (33 MB), T = 6 16.7 / 17.7 us (17 MB); E = 8 K = 4 T = 1 13.7 / 14.0 us (14 MB)
 //   1024 x 4096, E = 64   K = 16 T = 16 45.0 / 42.0 us (48 MB); E = 128 K = 16 T = 16 51.0 / 51.7 us (48 MB)
 //   512 x 2048, E = 64    K = 20 T = 6 18.4 / 16.5 us (31 MB), T = 13 20.0 / 21.9 us (22 MB)
+// These repeat their tokens.  With 64 batches in turn, whose experts do not stay in the cache, both columns hold: 768 x 3072,
+// E = 64 K = 16 T = 1 22.2 / 14.7 us, T = 8 26.7 / 24.0, T = 16 28.6 / 32.1; E = 32 K = 8 T = 1 15.8 / 14.1, T = 4 16.4 / 17.0; 128
+// slots T = 5 116 / 20; 1024 x 4096, E = 64 K = 16 T = 4 38.0 / 22.0; 512 x 2048, K = 20 T = 6 18.5 / 16.7.
 bool sparse(const smoe_config& c, int T) {
     const double unused = (c.K - served_slots(c, T)) * 2.0 * c.d_model * c.d_ff;
     if (T <= FEW_T) return unused > 16e6 + 2e6 * T;
