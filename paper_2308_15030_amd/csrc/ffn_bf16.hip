@@ -863,7 +863,7 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
         // the chip holds at once (two per compute unit): each then has a quarter of a reduction per wave in front of it,
         // where a tile has all of it.  Measured on 270 batches of 2 to 100 slots, T = 129 .. 2000, clustered and even tokens,
         // us per layer, streaming / best tile: up to 600 workgroups 20 .. 0 % ahead (4 slots of 768 x 3072, T = 200 28 / 35; 6,
-        // T = 320 37 / 45; 16 of 512 x 4096, T = 426 55 / 60), up to 780 8 .. 0 % ahead with less than 28 tokens per slot (18
+        // T = 320 37 / 45; 16 of 512 x 4096, T = 426 53 / 60), up to 780 8 .. 0 % ahead with less than 28 tokens per slot (18
         // slots of 768 x 3072, T = 374 56 / 59) and even with more, beyond that behind (32 slots, T = 236 67 / 60).  Not for
         // short reductions, whose end the split lengthens (32 slots of 256 x 512, T = 260 23.5 / 22.4), and not for T = 640 and
         // more, where the rows of the largest slots stream too often (one slot of 768 x 3072, T = 800 39.7 / 37.8).

@@ -19,9 +19,11 @@
 // 21 us, so the feature range is narrowed until the items fill the chip.
 //
 // Both products, four slots of 768 x 3072 (LDS tiles of 32 x 64 with vector FMAs before): T = 512
-// 280 -> 68 us (71 TFLOP/s), T = 32 23 us, T = 4 16 us (75 MB of weights: 4.7 TB/s).  What bounds T = 512 now: an item of
-// the first product takes 295 KB through its compute unit (8.4 us at the 35 GB/s of a mix of cached and missing lines) for
-// 5.1 us of products.  Items of 64 tokens halve that per product and gave nothing (T = 512 35 us, T = 1024 67 and 54 us).
+// 280 -> 68 us (71 TFLOP/s; 40.0 + 34.4 in a kernel trace), T = 32 23 us, T = 4 16 us (75 MB of weights: 4.7 TB/s).  At
+// T = 512 no unit is at its limit (trace and counters): the matrix cores are busy for 16.3 us of each launch, the L1 sees 0.30
+// and 0.18 accesses per cycle (a token load of the first product is one per lane, 16 rows lying apart), 77 and 63 % of the L2
+// requests hit, and a wave waits for its next instruction two thirds of the time, with two waves to a SIMD.  Items of
+// 64 tokens halve the bytes per product and gave nothing (first product T = 512 35 us, both T = 1024 67 and 54 us).
 
 #include <algorithm>
 #include <cstdio>

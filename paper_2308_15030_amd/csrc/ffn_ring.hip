@@ -5,7 +5,7 @@
 //
 // What bounds these products on this chip, and what the kernel does about it:
 //  * Power.  At the Switch-large prefill shape (16384 tokens, 32 slots of 1024 x 4096) random data pulls the clock
-//    from 2.4 to 1.3 GHz, so energy per operation is time.  v_mfma_f32_16x16x32 does the same work as
+//    from 2.4 to 2.14 (first product) and 2.23 GHz.  v_mfma_f32_16x16x32 does the same work as
 //    v_mfma_f32_32x32x16 at 12 % more (2008 against 1785 TFLOP/s from registers, 1707 against 1552 with the operand
 //    reads), and a wave tile of 64 features x 128 tokens reads 0.75 KB of LDS per 32768 operations where one
 //    feature block x 256 tokens reads 1.13.
@@ -14,8 +14,9 @@
 //    issue of its stores, no prologue (256 x 256 tiles: 7 of 35 us before).  Any multiple of 32 is as good a
 //    reduction length as another.
 //  * Balance.  Tile heights are chosen on the device from the segment lengths, and a slot's rows are cut evenly.
-// Both products at that shape: 355 -> 315 us; 8000 tokens, 16 slots of 992 x 3296: 241 -> 142 us.
-// What is left is the chip's memory path: the loads alone take 125 and 105 us of the two products' 150 and 150.
+// Both products at that shape, from kernel traces: 168 + 188 -> 157 + 168 us; 8000 tokens, 16 slots of 992 x 3296: 241 ->
+// 142 us.  What is left: of launches of 160 and 167 us the loads alone take 143 and 158, the products with their LDS reads
+// 133 and 134 (both at 2.4 GHz), and a workgroup is there for 136 and 140 us in the mean, the last one 148 and 169.
 //
 // Workgroup = 2 * NWF waves; tile = (64 * NWF features) x (at most 64 * NWF tokens), in blocks of 32.  Wave w loads
 // feature block w and token block w of every slice; it multiplies the feature blocks 2 * (w % NWF) and the next with
