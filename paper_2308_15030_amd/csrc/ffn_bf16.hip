@@ -861,14 +861,17 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
     } else {
         // The second product streams while its workgroups, one per 32 features and 32 rows of a slot, are little more than
         // the chip holds at once (two per compute unit): each then has a quarter of a reduction per wave in front of it,
-        // where a tile has all of it.  Measured on 270 batches of 2 to 100 slots, T = 129 .. 2000, clustered and even tokens,
-        // us per layer, streaming / best tile: up to 600 workgroups 20 .. 0 % ahead (4 slots of 768 x 3072, T = 200 28 / 35; 6,
-        // T = 320 37 / 45; 16 of 512 x 4096, T = 426 53 / 60), up to 780 8 .. 0 % ahead with less than 28 tokens per slot (18
-        // slots of 768 x 3072, T = 374 56 / 59) and even with more, beyond that behind (32 slots, T = 236 67 / 60).  Not for
-        // short reductions, whose end the split lengthens (32 slots of 256 x 512, T = 260 23.5 / 22.4), and not for T = 640 and
-        // more, where the rows of the largest slots stream too often (one slot of 768 x 3072, T = 800 39.7 / 37.8).
+        // where a tile has all of it.  Measured on 340 batches of 2 to 100 slots, T = 129 .. 2000, clustered and even tokens,
+        // us per layer, streaming / best tile.  700 workgroups: 25 .. 0 % ahead below (4 slots of 768 x 3072, T = 200 28 / 35; 6,
+        // T = 320 37 / 45; 4 of 2048 x 8192, T = 200 90 / 106), 3 % behind above (18 of 768 x 3072, T = 668 69 / 67).  Under 28
+        // tokens per slot, where most of a tile is empty, 780: 24 slots of 768 x 2048, T = 248 57.0 / 57.3, T = 400 54.9 / 53.4; 26 of 768 x
+        // 3072, T = 263 71 / 69.  A long reduction makes the rounds of the tiles long, 850: 16 slots of 1024 x 4096, T = 300 73 / 76; 12
+        // of 1280 x 5120, T = 300 88 / 93; 20 of 768 x 3072, T = 500 58.3 / 62.6 (even), 22 T = 480 66.7 / 66.1; but not with so few
+        // tokens that the tiles are one round anyway (16 of 1280 x 5120, T = 160 104 / 101).
+        // Not for short reductions, whose end the split lengthens (32 slots of 256 x 512, T = 260 23.5 / 22.4), and not for T = 640
+        // and more, where the rows of the largest slots stream too often (one slot of 768 x 3072, T = 800 39.7 / 37.8).
         const int groups = (K + T / 32) * (d >> 5);
-        const bool stream = T <= 512 && f >= 768 && (groups <= 600 || (groups <= 780 && per_slot < 28));
+        const bool stream = T <= 512 && f >= 768 && groups <= (per_slot >= 28 ? 700 : per_slot >= 14 && f >= 3072 ? 850 : 780);
         v1 = d % 128 != 0 ? (per_slot < 28 ? 4 : 3) : pick_tile(true, d, f, T, K);
         v2 = f % 128 != 0 ? (per_slot < 28 ? 6 : 1) : stream ? 6 : pick_tile(false, f, d, T, K);
     }

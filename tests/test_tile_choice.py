@@ -16,10 +16,11 @@ def kernels(K, d, f, T, fused=False):
 @pytest.mark.parametrize("K,d,f,T,streams", [
     # few slots, whatever their weights and however many tokens a slot has
     (6, 512, 2048, 132, True), (4, 768, 3072, 200, True), (2, 768, 3072, 140, True), (1, 768, 3072, 400, True),
-    # up to 600 workgroups (d_model = 768: 25 row tiles of 24 feature blocks)
-    (18, 768, 3072, 223, True), (19, 768, 3072, 223, True), (10, 768, 3072, 480, True), (11, 768, 3072, 480, False),
-    # up to 780 with less than 28 tokens per slot
-    (18, 768, 3072, 374, True), (26, 768, 3072, 223, True), (27, 768, 3072, 223, False), (32, 768, 3072, 236, False),
+    # d_model = 768, 24 workgroups per row tile: up to 700 from 28 tokens per slot on, below 780, or 850 with
+    # long reductions and 14 tokens per slot
+    (14, 768, 3072, 480, True), (15, 768, 3072, 480, False), (16, 768, 3072, 448, False), (17, 768, 3072, 448, True),
+    (20, 768, 3072, 480, True), (21, 768, 3072, 480, False), (18, 768, 2048, 448, True), (19, 768, 2048, 448, False), (26, 768, 3072, 223, True), (27, 768, 3072, 223, False),
+    (32, 768, 3072, 236, False),
     # short reductions and many tokens
     (8, 256, 768, 140, True), (8, 256, 640, 140, False), (2, 512, 2048, 512, True), (2, 512, 2048, 513, False),
     # up to five tokens per slot always
