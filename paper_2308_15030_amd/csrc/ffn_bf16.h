@@ -1,4 +1,4 @@
-// Declarations shared by the grouped bf16 products (ffn_bf16.hip, ffn_ring.hip).
+// Declarations shared by the grouped bf16 products (ffn_bf16.hip, ffn_ring.hip, ffn_split.hip).
 #pragma once
 
 #include "smoe_internal.h"
@@ -22,3 +22,7 @@ bool smoe_ring_applies(bool first, int R, int T);
 int smoe_launch_ring(int blocks, bool first, const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots,
                      uint16_t* Y, int R, int N, int T, const FuseArgs& fz, int cus_per_die, hipStream_t s, hipEvent_t e0,
                      hipEvent_t e1);
+
+// ffn_split.hip: second product, reduction split over the waves, tiles of up to 128 x 128
+int smoe_launch_split(const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots, uint16_t* Y, int R, int N, int T,
+                      const FuseArgs& fz, int cus_per_die, hipStream_t s, hipEvent_t e0, hipEvent_t e1);

@@ -762,11 +762,13 @@ void launch_gemm(const uint16_t* X, const void* Wp, const int32_t* offsets, int 
 
 // The tile shapes launch_variant knows; every one of them is chosen somewhere by pick_variants.
 constexpr bool is_variant(int v) {
-    return v == 1 || v == 3 || v == 4 || v == 5 || v == 6 || v == 8 || v == 9 || v == 10;
+    return v == 1 || v == 3 || v == 4 || v == 5 || v == 6 || v == 8 || v == 9 || v == 10 || v == 11;
 }
 
-// What stands in where the ring kernel (9, 10) does not apply.
+// What stands in where the ring kernel (9, 10) does not apply; the splitting kernel (11) is the second product's and takes the
+// place of the tiles of 64 and 32 rows there.
 int ring_or_tiled(int v, bool first, int R, int T) {
+    if (v == 11 || v == 3 || v == 4) return first ? (v == 11 ? 1 : v) : 11;
     if (v < 9 || smoe_ring_applies(first, R, T)) return v;
     return v == 9 ? 1 : 8;
 }
@@ -776,6 +778,7 @@ int launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* offs
                     uint16_t* Y, int R, int N, int T, const FuseArgs& fz, hipStream_t s, hipEvent_t e0,
                     hipEvent_t e1) {
     v = ring_or_tiled(v, FIRST, R, T);
+    if (v == 11) return smoe_launch_split(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die(), s, e0, e1);
     if (v >= 9) return smoe_launch_ring(v == 9 ? 4 : 8, FIRST, X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die(), s, e0, e1);
     if (R % 64 != 0 && v != 5 && v != 6) {   // d_model / d_ff are multiples of 32 by contract: 32-deep slices always fit
         launch_gemm<1, 4, 4, 32, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);
@@ -783,8 +786,8 @@ int launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* offs
     }
     switch (v) {             //            AF MAXB NW BKT PD OCC     tokens x features per workgroup
         case 1: launch_gemm<1, 4, 4, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  // 128 x 128
-        case 3: launch_gemm<1, 2, 4, 64, 1, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  64 x 128
-        case 4: launch_gemm<1, 1, 4, 64, 3, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  32 x 128
+        case 3: if constexpr (FIRST) launch_gemm<1, 2, 4, 64, 1, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  64 x 128
+        case 4: if constexpr (FIRST) launch_gemm<1, 1, 4, 64, 3, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  32 x 128
         case 8: launch_gemm<1, 4, 8, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  // 128 x 256, 8 waves
         case 5: launch_small<4, 1, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;   // 32 x 128, streaming
         case 6: launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;   // 32 x 32, reduction split 4 ways
@@ -851,6 +854,24 @@ int ring_tile(bool first, int R, int N, int T, int K, int tiled) {
     return tiles >= (first ? 300 : 100) ? 10 : 0;
 }
 
+// Where the second product splits its reduction (ffn_split.hip) instead of taking the tile `tiled`.  Kernel times of 146 batches (13
+// shapes, T = 132 .. 8192), split / what was chosen before:
+//  * In the place of the tiles of 32 and 64 rows always: 0.52 .. 1.03, 0.87 in the mean (4 slots of 768 x 3072, T = 520 12.7 / 17.5; 16
+//    slots, T = 1213 26.7 / 30.1; 64 slots, T = 2000 68.8 / 69.6; the one loser 5 of 256 x 768, T = 6000 11.0 / 9.2).
+//  * In the place of 128 x 128 tiles while its own leave a fifth of the compute units to slots that are cut unevenly: up to an expected
+//    204 of 4 x 4 blocks (16 slots of 768 x 3072, T = 3100, 200: 33.5 / 37.0; 4 slots, T = 3100 27.4 / 32.2; 16 of 512 x 2048, T =
+//    4096, 163: 23.2 / 25.3; 4 of 768 x 3072, T = 4096, 205: 33 / 33 .. 35 from memory, 26.3 / 26.2 from the cache; 16, T = 4096,
+//    245: 38.3 / 37.7; 8 of 768 x 2048, T = 4096, 218: 26.9 / 25.4).  Slots of less than a tile's rows take smaller tiles,
+//    whose number that says little about (32 of 1024 x 4096, T = 520 64 / 78, T = 800 63 / 69; 32 of 768 x 3072, T = 2000 43 / 47).
+//  * Where the reduction is no multiple of 128, and the other choice the ring kernel, up to 300 (10 of 992 x 3296, T = 800 25.9 / 41.8,
+//    T = 4096, 300: 57.6 / 58.3, T = 6000, 419: 67 / 64).
+bool splits(int R, int N, int T, int K, int tiled) {
+    if (tiled == 3 || tiled == 4) return true;
+    const double x = (double)T / K / 128, tiles = K * (x + 0.55 + 0.45 * std::exp(-2 * x)) * ((N + 127) / 128);
+    if (R % 128 != 0) return tiled == 1 && tiles <= 300;
+    return tiled == 1 && (tiles <= 0.8 * XCDS * cus_per_die() || T / K < 128);
+}
+
 // Tile shapes for the two GEMMs.  A pair fixed at smoe_create (SMOE_FFN_VARIANT="v1,v2", a
 // tuning aid; the indices are those of launch_variant) overrides the built-in choice.
 void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
@@ -880,7 +901,8 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
     if (smoe_decode_first_applies(L, T)) {
         v2 = 6;
     } else {
-        const int r1 = ring_tile(true, d, f, T, K, v1), r2 = ring_tile(false, f, d, T, K, v2);
+        if (splits(f, d, T, K, v2)) v2 = 11;
+        const int r1 = ring_tile(true, d, f, T, K, v1), r2 = v2 == 11 ? 0 : ring_tile(false, f, d, T, K, v2);
         if (r1 && smoe_ring_applies(true, d, T)) v1 = r1;
         if (r2 && smoe_ring_applies(false, f, T)) v2 = r2;
     }
@@ -908,6 +930,7 @@ int smoe_describe_ffn_bf16(const smoe_layer* L, int T, int fused, char* out, siz
         if (fused && smoe_decode_first_applies(L, T) && v[1] == 6) name = smoe_describe_decode(L, T, first);
         else if (v[i] == 5) name = std::string("small_gemm_bf16<4, 1, ") + (first ? "true>" : "false>");
         else if (v[i] == 6) name = std::string("small_gemm_bf16<4, 4, ") + (first ? "true>" : "false>");
+        else if (v[i] == 11) name = "split_gemm_bf16";
         else if (v[i] >= 9) name = std::string("ring_gemm_bf16<") + (v[i] == 9 ? "2, " : "4, ") + (first ? "true>" : "false>");
         else if (R % 64 != 0) shape = "1, 4, 4, 32, ";
         else if (v[i] == 1) shape = "1, 4, 4, 64, ";

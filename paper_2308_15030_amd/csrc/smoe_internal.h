@@ -223,6 +223,36 @@ __device__ __forceinline__ uint16_t smoe_f32_to_bf16(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// Two values narrowed by the conversion instruction (the same rounding) and packed, the first in the lower half.
+__device__ __forceinline__ uint32_t smoe_pack_bf16(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {a, b};
+    union { bf16x2 b; uint32_t u; } c;
+    c.b = __builtin_convertvector(v, bf16x2);
+    return c.u;
+}
+
+// Combine on 8 consecutive outputs of one token that are rounded to bf16 already: out = gate * y (+ residual) in fp32 with
+// one final rounding, as smoe_apply_gate.
+__device__ __forceinline__ uint4 smoe_gate_unit(uint4 y, float g, uint4 r, bool has_res) {
+    uint32_t yw[4] = {y.x, y.y, y.z, y.w};
+    const uint32_t rw[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float o0 = __uint_as_float(yw[q] << 16), o1 = __uint_as_float(yw[q] & 0xFFFF0000u);
+        if (has_res) {
+            o0 = fmaf(g, o0, __uint_as_float(rw[q] << 16));
+            o1 = fmaf(g, o1, __uint_as_float(rw[q] & 0xFFFF0000u));
+        } else {
+            o0 *= g;
+            o1 *= g;
+        }
+        yw[q] = smoe_pack_bf16(o0, o1);
+    }
+    return make_uint4(yw[0], yw[1], yw[2], yw[3]);
+}
+
 // Combine on 4 consecutive outputs of one token.  The product is first rounded to bf16 exactly as the
 // separate calls store y_perm, so both give the same bits; then out = gate * y (+ residual) in fp32
 // with one final rounding.

@@ -30,12 +30,14 @@ __device__ __forceinline__ float smoe_row_sum(float v) {
     return v + smoe_row_ror<1>(v);
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave.
-__device__ __forceinline__ int smoe_wave_incl_scan(int v, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(v, d);
-        if (lane >= d) v += o;
-    }
+// Inclusive prefix sum over the 64 lanes of a wave, all of them active: shifts within the rows of 16 lanes, then the rows'
+// totals, six vector additions without a trip through the LDS crossbar.
+__device__ __forceinline__ int smoe_wave_incl_scan(int v, int) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // the last lane of rows 0 and 2 to the rows behind them
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // lane 31 to the upper half
     return v;
 }
