@@ -13,6 +13,12 @@
 //    side runs on into the next tile while this one is multiplied and stored: a tile costs its reduction and the
 //    issue of its stores, no prologue (256 x 256 tiles: 7 of 35 us before).  Any multiple of 32 is as good a
 //    reduction length as another.
+//  * Control.  The loop has no branch that is taken in ordinary steps: a wave without a block of its own loads one
+//    lane's 16 bytes, so every slice has four loads to count.  With a branch for each of these the same loop without loads,
+//    products and LDS reads took 40 and 55 us of launches of 168 and 177.
+//  * Stores.  Without them the first product takes 134 of 156 us.  They stay on their way through the next tile's first
+//    two steps, and the h of large tiles passes the L2 by (the next product reads it on other dies): second product
+//    169 -> 164 us.  That of small ones stays: 11 slots of 416 x 1696, T = 1213, 31.8 us a layer, 33.3 past the L2.
 //  * Balance.  Tile heights are chosen on the device from the segment lengths, and a slot's rows are cut evenly.
 // Both products at that shape, from kernel traces: 168 + 188 -> 157 + 168 us; 8000 tokens, 16 slots of 992 x 3296: 241 ->
 // 142 us.  What is left: of launches of 160 and 167 us the loads alone take 143 and 158, the products with their LDS reads
@@ -72,13 +78,17 @@ __device__ __forceinline__ bf16x8 lds_frag(uint32_t off) { return *(const bf16x8
 __device__ __forceinline__ uint32_t lds_addr(uint32_t off) {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(ring_lds + off);
 }
-__device__ __forceinline__ void load_1k(const char* base, uint32_t lane_off, uint32_t off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 ::"s"(lds_addr(off)), "v"(lane_off), "s"(base) : "memory");
+// A wave without a block of its own loads one lane's 16 bytes (of another wave's block, to a place that nobody reads): the loop
+// then has no branch for it, and every slice the same number of loads to count.
+__device__ __forceinline__ void load_1k(const char* base, uint32_t lo, uint32_t hi, uint32_t off, uint64_t lanes) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %1, %3\n\ts_add_u32 m0, %0, 0x400\n\t"
+                 "s_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, -1"
+                 ::"s"(lds_addr(off)), "v"(lo), "v"(hi), "s"(base), "s"(lanes) : "memory", "scc");
 }
-__device__ __forceinline__ void load_2k(const char* base, uint32_t lane16, uint32_t off) {   // the offset moves both sides
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024"
-                 ::"s"(lds_addr(off)), "v"(lane16), "s"(base) : "memory");
+__device__ __forceinline__ void load_2k(const char* base, uint32_t lane16, uint32_t off, uint64_t lanes) {   // the offset moves both sides
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+                 "s_mov_b64 exec, -1"
+                 ::"s"(lds_addr(off)), "v"(lane16), "s"(base), "s"(lanes) : "memory");
 }
 __device__ __forceinline__ void load_words(const void* src, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr(off)), "v"(src) : "memory");
@@ -108,7 +118,7 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
     int T, uint16_t* __restrict__ Y, int R, int N, const FuseArgs fz) {
     using S = RingShape<NWF, FIRST>;
     constexpr int MAXB = S::NB, STAGE = S::STAGE;
-    static_assert(ST == 4 && MAXB <= 8, "wait_next counts two slices ahead; tiles_of has 8 entries");
+    static_assert(ST == 4 && MAXB <= 8, "wait_slice counts two slices ahead; tiles_of has 8 entries");
     const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
     const int wf = wave % NWF, wt = wave / NWF;
     const int nfb = N >> 5, ftiles = (nfb + MAXB - 1) / MAXB, nsub = R >> 5;
@@ -213,16 +223,15 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
     }
 
     // load side: runs ST - 1 slices ahead of the products, across tiles
-    int lg = 0, lc = 0, lpar = 0;
-    bool lw = false, lt = false;
-    int last = 0;                                          // loads of the last issue
+    int lc = 0, lpar = 0;                                  // slice of the tile; half of the tables
+    uint32_t lst = 0;                                      // stage of the ring
+    uint64_t lw = 1, lt = 1;                               // lanes that load weights and tokens
     const char *wsrc = nullptr, *tsrc = nullptr;           // scalar bases
     uint32_t to0 = 0, to1 = 0;                             // row-major tokens: this lane's two rows
     const uint32_t lane16 = lane * 16;
     auto load_tile = [&](const Tile& t, int p) {
-        lw = wave < t.width;
-        lt = wave < t.nb;
-        lc = 0;
+        lw = wave < t.width ? ~0ull : 1;
+        lt = wave < t.nb ? ~0ull : 1;
         wsrc = (const char*)Wp + ((size_t)t.phys * nfb + t.fb0 + min(wave, t.width - 1)) * (R >> 4) * 1024;
         if (FIRST) {
             tsrc = (const char*)X;
@@ -238,43 +247,47 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
                 load_words(fz.gate + s_row[p * MAXB * 32 + tid], S::GATES + (p * MAXB * 32 + wave * 64) * 4);
         }
     };
-    auto issue_w = [&]() {
-        if (lw) load_2k(wsrc, lane16, (uint32_t)(lg & (ST - 1)) * STAGE + wave * BLK);
-    };
+    auto issue_w = [&]() { load_2k(wsrc, lane16, lst + wave * BLK, lw); };
     auto issue_t = [&]() {
-        if (lt) {
-            const uint32_t st = (uint32_t)(lg & (ST - 1)) * STAGE + (wave + MAXB) * BLK;
-            if (FIRST) { load_1k(tsrc, to0, st); load_1k(tsrc, to1, st + 1024); }
-            else load_2k(tsrc, lane16, st);
-        }
+        const uint32_t st = lst + (wave + MAXB) * BLK;
+        if (FIRST) load_1k(tsrc, to0, to1, st, lt);
+        else load_2k(tsrc, lane16, st, lt);
         wsrc += 2048;
         tsrc += FIRST ? 64 : 2048;
-        last = (lw ? 2 : 0) + (lt ? 2 : 0);
-        ++lg;
-        if (++lc == nsub) {
-            lpar ^= 1;
-            lw = lt = false;
+        lst = (lst + STAGE) & (ST * STAGE - 1);
+        if (__builtin_expect(++lc == nsub, 0)) {
             lc = 0;
-            if (nxt.nb > 0) load_tile(nxt, lpar);
+            lpar ^= 1;
+            if (nxt.nb > 0) {
+                load_tile(nxt, lpar);
+            } else {                                       // no tile left: the start of this one again, for one lane
+                wsrc -= (size_t)nsub * 2048;
+                tsrc -= (size_t)nsub * (FIRST ? 64 : 2048);
+                lw = lt = 1;
+            }
         }
-    };
-    // the slice after this one has landed: nothing but the loads of the last issue is outstanding
-    auto wait_next = [&]() {
-        if (last == 4) wait_vm<4>();
-        else if (last == 2) wait_vm<2>();
-        else wait_vm<0>();
     };
 
     load_tile(cur, 0);
     nxt.nb = 0;
 #pragma unroll 1
     for (int i = 0; i < ST - 1; ++i) { issue_w(); issue_t(); }
-    if (last == 4) wait_vm<8>();                           // the first slice
-    else if (last == 2) wait_vm<4>();
-    else wait_vm<0>();
+    wait_vm<8>();                                          // the first slice
     __builtin_amdgcn_s_barrier();
 
-    int g = 0;                                             // slices multiplied so far
+    uint32_t cst = 0;                                      // stage that is multiplied
+    int pend = 0;                                          // stores of this wave at the end of the tile before
+    // The next slice has landed: nothing but the four loads of the slice behind it is outstanding.  In a tile's first two
+    // steps the last tile's stores, too, are younger than what is waited for, and stay on their way.
+    auto wait_slice = [&](int c) {
+        if (__builtin_expect(c < 2, 0)) {
+            if (pend >= 16) wait_vm<20>();
+            else if (pend >= 8) wait_vm<12>();
+            else wait_vm<4>();
+        } else {
+            wait_vm<4>();
+        }
+    };
     auto run = [&](auto nbc) {
         constexpr int NB = decltype(nbc)::value;           // token blocks of this wave: wt, wt + 2, ...
         constexpr int NBA = NB ? NB : 1;
@@ -309,30 +322,28 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
         };
         constexpr int P = 4 * NB;
         if (NB) {
-            const uint32_t st = (uint32_t)(g & (ST - 1)) * STAGE;
-            read_a(fa[0], st);
-            read_b(f0, st, 0);
+            read_a(fa[0], cst);
+            read_b(f0, cst, 0);
         }
         auto step = [&](bf16x8 (&fa)[4], bf16x8 (&fn)[4], int c) {
             if (NB) {
-                read_b(f1, (uint32_t)(g & (ST - 1)) * STAGE, 1);
+                read_b(f1, cst, 1);
                 __builtin_amdgcn_sched_barrier(0);
                 mul(fa, f0, 0, 0, P);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            wait_next();
+            wait_slice(c);
             __builtin_amdgcn_s_barrier();
-            ++g;
+            cst = (cst + STAGE) & (ST * STAGE - 1);
             if (NB) {
-                const uint32_t st = (uint32_t)(g & (ST - 1)) * STAGE;
-                read_a(fn, st);
-                read_b(f0, st, 0);
+                read_a(fn, cst);
+                read_b(f0, cst, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 mul(fa, f1, 1, 0, P / 4);
                 __builtin_amdgcn_sched_barrier(0);
             }
             // every wave is in this tile now, so nobody reads the rows of the one before any more
-            if (c == 0 && nxt.nb > 0 && gather && wave * 64 < MAXB * 32)
+            if (__builtin_expect(c == 0, 0) && nxt.nb > 0 && gather && wave * 64 < MAXB * 32)
                 load_words(fz.perm + min(nxt.m0 + tid, nxt.m_end - 1), S::ROWS + ((par ^ 1) * MAXB * 32 + wave * 64) * 4);
             issue_w();
             if (NB) {
@@ -355,29 +366,34 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
             // accumulator register i of lane l: feature 4*(l/16) + i, token l%16.  Swapping rows of 16 lanes
             // between the two halves of a feature block gives every lane 8 consecutive features of its token.
             const int unit = ((lane >> 4) & 1) * 2 + (lane >> 5);
+            uint4 rs[2][2 * NB];
+            int row[2 * NB];
+            float gate[2 * NB];
+            pend = 0;
+            if (!FIRST) {                                  // every piece of the residual is asked for before the first store
+#pragma unroll
+                for (int b = 0; b < 2 * NB; ++b) {
+                    const int r = ((b >> 1) * 2 + wt) * 32 + (b & 1) * 16 + (lane & 15);
+                    row[b] = cur.m0 + r;
+                    gate[b] = 1.f;
+                    if (gather) {                          // past the segment's end: its last row, not stored
+                        row[b] = s_row[par * MAXB * 32 + r];
+                        gate[b] = s_gate[par * MAXB * 32 + r];
+                    }
+                }
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2 * NB; ++b) {
+                        rs[a][b] = make_uint4(0, 0, 0, 0);
+                        if (gather && fz.residual)
+                            rs[a][b] = *(const uint4*)(fz.residual + (size_t)row[b] * N + (cur.fb0 + min(wf * 2 + a, cur.width - 1)) * 32 + unit * 8);
+                    }
+            }
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
                 if (wf * 2 + a >= cur.width) continue;
                 const int fbk = cur.fb0 + wf * 2 + a;
-                uint4 rs[2 * NB];
-                int row[2 * NB];
-                float gate[2 * NB];
-                if (!FIRST) {
-#pragma unroll
-                    for (int b = 0; b < 2 * NB; ++b) {
-                        const int r = ((b >> 1) * 2 + wt) * 32 + (b & 1) * 16 + (lane & 15);
-                        row[b] = cur.m0 + r;
-                        gate[b] = 1.f;
-                        if (row[b] >= cur.m_end) row[b] = -1;
-                        else if (gather) {
-                            row[b] = s_row[par * MAXB * 32 + r];
-                            gate[b] = s_gate[par * MAXB * 32 + r];
-                        }
-                        rs[b] = make_uint4(0, 0, 0, 0);
-                        if (gather && fz.residual && row[b] >= 0)
-                            rs[b] = *(const uint4*)(fz.residual + (size_t)row[b] * N + fbk * 32 + unit * 8);
-                    }
-                }
 #pragma unroll
                 for (int b = 0; b < 2 * NB; ++b) {
                     uint32_t w[4];
@@ -385,37 +401,27 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
                     for (int q = 0; q < 4; ++q) {          // w[0], w[1]: lower half of the block; w[2], w[3]: upper
                         float v0 = acc[2 * a + (q >> 1)][b][2 * (q & 1)], v1 = acc[2 * a + (q >> 1)][b][2 * (q & 1) + 1];
                         if (FIRST) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
-                        w[q] = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
+                        w[q] = smoe_pack_bf16(v0, v1);
                     }
                     const auto s0 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);
                     const auto s1 = __builtin_amdgcn_permlane16_swap(w[1], w[3], false, false);
                     uint4 o = make_uint4(s0[0], s1[0], s0[1], s1[1]);
                     if (FIRST) {
                         const size_t u = ((size_t)(cur.pb0 + (b >> 1) * 2 + wt) * (N >> 3) + fbk * 4 + unit) * 32 + (b & 1) * 16 + (lane & 15);
-                        *(uint4*)(Y + u * 8) = o;
+                        if (NWF == 4) smoe_store_stream((uint4*)(Y + u * 8), o);
+                        else *(uint4*)(Y + u * 8) = o;
+                        ++pend;
                     } else {
-                        if (row[b] < 0) continue;
-                        if (gather) {
-                            uint32_t yw[4] = {o.x, o.y, o.z, o.w}, rw[4] = {rs[b].x, rs[b].y, rs[b].z, rs[b].w};
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const float y0 = __uint_as_float(yw[q] << 16), y1 = __uint_as_float(yw[q] & 0xFFFF0000u);
-                                float o0, o1;
-                                if (fz.residual) {
-                                    o0 = fmaf(gate[b], y0, __uint_as_float(rw[q] << 16));
-                                    o1 = fmaf(gate[b], y1, __uint_as_float(rw[q] & 0xFFFF0000u));
-                                } else {
-                                    o0 = gate[b] * y0;
-                                    o1 = gate[b] * y1;
-                                }
-                                yw[q] = (uint32_t)smoe_f32_to_bf16(o0) | ((uint32_t)smoe_f32_to_bf16(o1) << 16);
-                            }
-                            o = make_uint4(yw[0], yw[1], yw[2], yw[3]);
-                        }
-                        *(uint4*)(Y + (size_t)row[b] * N + fbk * 32 + unit * 8) = o;
+                        const int r0 = cur.m0 + ((b >> 1) * 2 + wt) * 32 + (b & 1) * 16;
+                        if (r0 >= cur.m_end) continue;     // uniform; else one store, of the lanes whose row is there
+                        if (gather) o = smoe_gate_unit(o, gate[b], rs[a][b], fz.residual != nullptr);
+                        if (r0 + (lane & 15) < cur.m_end) *(uint4*)(Y + (size_t)row[b] * N + fbk * 32 + unit * 8) = o;
+                        ++pend;
                     }
                 }
             }
+        } else {
+            pend = 0;
         }
     };
     while (true) {
@@ -434,6 +440,7 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
         cur = nxt;
         par ^= 1;
     }
+    wait_vm<0>();                                          // no load is on its way into LDS that is given back
 }
 
 template <int NWF, bool FIRST>
