@@ -149,8 +149,8 @@ __device__ __forceinline__ void dense_first_all(const uint16_t* __restrict__ x, 
             const float v0 = fmaxf(acc[b][4 * g], 0.f), v1 = fmaxf(acc[b][4 * g + 1], 0.f), v2 = fmaxf(acc[b][4 * g + 2], 0.f),
                         v3 = fmaxf(acc[b][4 * g + 3], 0.f);
             uint2 o;
-            o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-            o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+            o.x = smoe_pack_bf16(v0, v1);
+            o.y = smoe_pack_bf16(v2, v3);
             *(uint2*)(ydst + (size_t)g * hs.unit * 8) = o;
         }
     }
@@ -347,8 +347,8 @@ __global__ __launch_bounds__(256, 2) void dense_first_kernel_served(const smoe_r
     const int tok = lane & 15;
     if (tok >= a.T) return;
     uint2 o;
-    o.x = (uint32_t)smoe_f32_to_bf16(fmaxf(acc[0], 0.f)) | ((uint32_t)smoe_f32_to_bf16(fmaxf(acc[1], 0.f)) << 16);
-    o.y = (uint32_t)smoe_f32_to_bf16(fmaxf(acc[2], 0.f)) | ((uint32_t)smoe_f32_to_bf16(fmaxf(acc[3], 0.f)) << 16);
+    o.x = smoe_pack_bf16(fmaxf(acc[0], 0.f), fmaxf(acc[1], 0.f));
+    o.y = smoe_pack_bf16(fmaxf(acc[2], 0.f), fmaxf(acc[3], 0.f));
     *(uint2*)(h + ((size_t)slot * a.T + tok) * d_ff + hb * 16 + 4 * (lane >> 4)) = o;
 }
 
@@ -560,8 +560,8 @@ __device__ __forceinline__ void decode_second_body(const second_args& a) {
         float v0 = acc[4 * g], v1 = acc[4 * g + 1], v2 = acc[4 * g + 2], v3 = acc[4 * g + 3];
         smoe_apply_gate(v0, v1, v2, v3, gmul, rres[g], a.residual != nullptr);
         uint2 o;
-        o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-        o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+        o.x = smoe_pack_bf16(v0, v1);
+        o.y = smoe_pack_bf16(v2, v3);
         *(uint2*)(ydst + g * 8) = o;
     }
 }
@@ -659,8 +659,8 @@ __global__ __launch_bounds__(256, 2) void dense_second_kernel_served(const secon
     float v0 = acc[0], v1 = acc[1], v2 = acc[2], v3 = acc[3];
     smoe_apply_gate(v0, v1, v2, v3, gmul, rres, a.residual != nullptr);
     uint2 o;
-    o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-    o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+    o.x = smoe_pack_bf16(v0, v1);
+    o.y = smoe_pack_bf16(v2, v3);
     *(uint2*)(a.out + (size_t)tok * a.N + f) = o;
 }
 

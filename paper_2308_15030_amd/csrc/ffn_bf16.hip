@@ -355,8 +355,8 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
                           v3 = acc[a][b][4 * g + 3];
                     if (RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
                     uint2 o;
-                    o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-                    o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+                    o.x = smoe_pack_bf16(v0, v1);
+                    o.y = smoe_pack_bf16(v2, v3);
                     *(uint2*)(ydst + g * 32 * 8) = o;
                 }
             }
@@ -393,8 +393,8 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
                     apply_gate_v(v0, v1, v2, v3, gmul, rr[b][g], has_res, fused);
                     if (RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
                     uint2 o;
-                    o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-                    o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+                    o.x = smoe_pack_bf16(v0, v1);
+                    o.y = smoe_pack_bf16(v2, v3);
                     *(uint2*)(ydst + g * 8) = o;
                 }
             }
@@ -418,8 +418,8 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
                           v3 = acc[a][b][4 * g + 3];
                     if (RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
                     uint2 o;
-                    o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-                    o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+                    o.x = smoe_pack_bf16(v0, v1);
+                    o.y = smoe_pack_bf16(v2, v3);
                     *(uint2*)&xs[(b * 32 + (lane & 31)) * LDO + (wave * AF + a) * 32 + g * 8 + (lane >> 5) * 4] = o;
                 }
         __syncthreads();
@@ -459,7 +459,7 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
                         o0 = g * y0;
                         o1 = g * y1;
                     }
-                    yw[q] = (uint32_t)smoe_f32_to_bf16(o0) | ((uint32_t)smoe_f32_to_bf16(o1) << 16);
+                    yw[q] = smoe_pack_bf16(o0, o1);
                 }
                 o = make_uint4(yw[0], yw[1], yw[2], yw[3]);
             }
@@ -708,8 +708,8 @@ __global__ __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2, 2))
         if (!YFRAG) apply_gate(v0, v1, v2, v3, gmul, rsrc ? rsrc + g * 8 : nullptr, fz.perm != nullptr);
         if (RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
         uint2 o;
-        o.x = (uint32_t)smoe_f32_to_bf16(v0) | ((uint32_t)smoe_f32_to_bf16(v1) << 16);
-        o.y = (uint32_t)smoe_f32_to_bf16(v2) | ((uint32_t)smoe_f32_to_bf16(v3) << 16);
+        o.x = smoe_pack_bf16(v0, v1);
+        o.y = smoe_pack_bf16(v2, v3);
         *(uint2*)(ydst + (YFRAG ? g * 32 * 8 : g * 8)) = o;
     }
 }

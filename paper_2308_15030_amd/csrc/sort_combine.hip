@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
                 lo *= g;
                 hi *= g;
             }
-            ow[i] = (uint32_t)smoe_f32_to_bf16(lo) | ((uint32_t)smoe_f32_to_bf16(hi) << 16);
+            ow[i] = smoe_pack_bf16(lo, hi);
         }
     } else {
 #pragma unroll
