@@ -139,7 +139,8 @@ __device__ __forceinline__ void apply_gate(float& v0, float& v1, float& v2, floa
 //   BKT   reduction slice per LDS stage    PD    weight prefetch distance in slices
 //   XFRAG token operand X is in fragment order (else row-major [T, R])
 //   YFRAG output Y is written in fragment order (else row-major [T, N])
-template <int AF, int NBF, int NW, int BKT, int PD, bool XFRAG, bool YFRAG, bool RELU, bool EARLY>
+//   PAST  fragment-order output goes past the caches
+template <int AF, int NBF, int NW, int BKT, int PD, bool XFRAG, bool YFRAG, bool RELU, bool EARLY, bool PAST>
 __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const uint4* __restrict__ Wp,
                                          uint16_t* __restrict__ Y, int R, int N, int slot, int m0,
                                          int m_end, int pm0, int ftile, uint16_t* xs, int stage_elems,
@@ -341,6 +342,8 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
     __syncthreads();                                      // the next tile's first write may hit any stage
 
     // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, token l%32
+    // h goes past the caches where tiles are low, whose batches are bound by the weight stream that it would displace (16 slots
+    // of 768 x 3072, two layers: T = 777 118.6 -> 115.4 us); with tiles of 128 rows T = 4096, six layers, took 507 -> 510 us.
     if constexpr (YFRAG) {   // unit [(pm0/32 + b)][(fb0+a)*4 + g][lane%32], 8 bytes at half (lane/32)
 #pragma unroll
         for (int a = 0; a < AF; ++a) {
@@ -357,7 +360,8 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
                     uint2 o;
                     o.x = smoe_pack_bf16(v0, v1);
                     o.y = smoe_pack_bf16(v2, v3);
-                    *(uint2*)(ydst + g * 32 * 8) = o;
+                    if (PAST) smoe_store_stream((uint2*)(ydst + g * 32 * 8), o);
+                    else *(uint2*)(ydst + g * 32 * 8) = o;
                 }
             }
         }
@@ -476,7 +480,7 @@ struct TileSwitch {
                                               uint16_t* xs, int* orow, float* ogate, const FuseArgs fz) {
         constexpr int stage = MAXB * 32 * (BKT + KPAD);
         if (nbf == NBF)
-            run_tile<AF, NBF, NW, BKT, PD, XFRAG, YFRAG, RELU, EARLY>(X, Wp, Y, R, N, slot, m0, m_end, pm0, ftile, xs,
+            run_tile<AF, NBF, NW, BKT, PD, XFRAG, YFRAG, RELU, EARLY, (MAXB <= 2)>(X, Wp, Y, R, N, slot, m0, m_end, pm0, ftile, xs,
                                                                stage, orow, ogate, fz);
         else if constexpr (NBF > 1)
             TileSwitch<AF, NBF - 1, MAXB, NW, BKT, PD, XFRAG, YFRAG, RELU, EARLY>::go(nbf, X, Wp, Y, R, N, slot, m0,

@@ -212,7 +212,11 @@ __device__ __forceinline__ uint4 smoe_load_stream(const uint4* p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// 16-byte store of data that this launch does not read, on its way past the caches likewise.
+// Stores of data that this launch does not read, on their way past the caches likewise.
+__device__ __forceinline__ void smoe_store_stream(uint2* p, uint2 v) {
+    typedef unsigned int smoe_u32x2 __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store(smoe_u32x2{v.x, v.y}, (smoe_u32x2*)p);
+}
 __device__ __forceinline__ void smoe_store_stream(uint4* p, uint4 v) {
     typedef unsigned int smoe_u32x4 __attribute__((ext_vector_type(4)));
     __builtin_nontemporal_store(smoe_u32x4{v.x, v.y, v.z, v.w}, (smoe_u32x4*)p);
