@@ -59,7 +59,6 @@ struct SlotMap {
     int pad[MAX_SLOTS];                   // 32-row blocks before slot k (segments are re-based to blocks)
     int a[MAX_SLOTS], b[MAX_SLOTS];       // clamped segment bounds
     int phys[MAX_SLOTS];                  // where the slot's weights are
-    int tiles_of[8];                      // row tiles if they were at most i + 1 blocks high
 };
 
 struct Tile {
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
     int T, uint16_t* __restrict__ Y, int R, int N, const FuseArgs fz) {
     using S = RingShape<NWF, FIRST>;
     constexpr int MAXB = S::NB, STAGE = S::STAGE;
-    static_assert(ST == 4 && MAXB <= 8, "wait_slice counts two slices ahead; tiles_of has 8 entries");
+    static_assert(ST == 4 && MAXB <= 8, "wait_slice counts two slices ahead");
     const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
     const int wf = wave % NWF, wt = wave / NWF;
     const int nfb = N >> 5, ftiles = (nfb + MAXB - 1) / MAXB, nsub = R >> 5;
@@ -126,28 +125,31 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
     const int* s_row = (const int*)(ring_lds + S::ROWS);
     const float* s_gate = (const float*)(ring_lds + S::GATES);
 
-    // tile height: wave w counts the row tiles of at most w + 1 blocks, all take the best
-    {
-        const int h = wave + 1;
-        int n = 0;
-        for (int base = 0; base < nslots; base += 64) {
-            const int k = base + lane;
-            int len = 0;
-            if (k < nslots) {
-                const int a = min(max(offsets[k], 0), T);
-                len = max(min(max(offsets[k + 1], 0), T) - a, 0);
-            }
-            n += (((len + 31) >> 5) + h - 1) / h;
+    struct Seg { int a, b; };
+    auto segment = [&](int k) {
+        Seg g{0, 0};
+        if (k < nslots) {
+            g.a = min(max(offsets[k], 0), T);              // clamps guard misuse
+            g.b = max(min(max(offsets[k + 1], 0), T), g.a);
         }
+        return g;
+    };
+    auto place = [&](int k) { return k < nslots && fz.phys ? fz.phys[k] : k; };
+    const Seg seg0 = segment(lane);
+    const int phys0 = place(lane);
+    // tile height: the row tiles of at most 1, 2, .. blocks are counted, all take the best
+    int tiles_of[MAXB] = {};
+    for (int base = 0; base < nslots; base += 64) {
+        const Seg g = base ? segment(base + lane) : seg0;
+        const int nb = (g.b - g.a + 31) >> 5;
 #pragma unroll
-        for (int d = 32; d; d >>= 1) n += __shfl_xor(n, d);
-        if (lane == 0) map.tiles_of[h - 1] = n;
+        for (int h = 1; h <= MAXB; ++h) tiles_of[h - 1] += __builtin_amdgcn_readlane(smoe_wave_incl_scan((nb + h - 1) / h, lane), 63);
     }
-    __syncthreads();
     const int nwg = gridDim.x / XCDS;
     int H = MAXB, best = 0x7fffffff;
+#pragma unroll
     for (int h = MAXB; h >= 1; --h) {
-        const int per_die = (uni(map.tiles_of[h - 1]) * ftiles + XCDS - 1) / XCDS;
+        const int per_die = (tiles_of[h - 1] * ftiles + XCDS - 1) / XCDS;
         const int cost = (per_die + nwg - 1) / nwg * (TILE_COST0 + h);
         if (cost < best) { best = cost; H = h; }
     }
@@ -155,22 +157,18 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
         int tiles_before = 0, pad_before = 0;
         for (int base = 0; base < nslots; base += 64) {
             const int k = base + lane;
-            int a = 0, b = 0;
-            if (k < nslots) {
-                a = min(max(offsets[k], 0), T);
-                b = max(min(max(offsets[k + 1], 0), T), a);
-            }
-            const int pad = (b - a + 31) >> 5, tiles = (pad + H - 1) / H;
+            const Seg g = base ? segment(k) : seg0;
+            const int pad = (g.b - g.a + 31) >> 5, tiles = (pad + H - 1) / H;
             const int tin = smoe_wave_incl_scan(tiles, lane), pin = smoe_wave_incl_scan(pad, lane);
             if (k < nslots) {
                 map.first[k] = tiles_before + tin - tiles;
                 map.pad[k] = pad_before + pin - pad;
-                map.a[k] = a;
-                map.b[k] = b;
-                map.phys[k] = fz.phys ? fz.phys[k] : k;
+                map.a[k] = g.a;
+                map.b[k] = g.b;
+                map.phys[k] = base ? place(k) : phys0;
             }
-            tiles_before += __shfl(tin, 63);
-            pad_before += __shfl(pin, 63);
+            tiles_before += __builtin_amdgcn_readlane(tin, 63);
+            pad_before += __builtin_amdgcn_readlane(pin, 63);
         }
         if (lane == 0) map.first[nslots] = tiles_before;
     }
@@ -213,15 +211,6 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
     Tile cur = tile_at(j), nxt = cur;
     const bool gather = fz.perm != nullptr;
     int par = 0;                                           // which half of the tables the current tile has
-    if (gather) {
-        if (tid < MAXB * 32) {
-            const int row = fz.perm[min(cur.m0 + tid, cur.m_end - 1)];
-            ((int*)(ring_lds + S::ROWS))[tid] = row;
-            if (!FIRST) ((float*)(ring_lds + S::GATES))[tid] = fz.gate[row];
-        }
-        __syncthreads();
-    }
-
     // load side: runs ST - 1 slices ahead of the products, across tiles
     int lc = 0, lpar = 0;                                  // slice of the tile; half of the tables
     uint32_t lst = 0;                                      // stage of the ring
@@ -229,10 +218,16 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
     const char *wsrc = nullptr, *tsrc = nullptr;           // scalar bases
     uint32_t to0 = 0, to1 = 0;                             // row-major tokens: this lane's two rows
     const uint32_t lane16 = lane * 16;
-    auto load_tile = [&](const Tile& t, int p) {
+    auto weights_of = [&](const Tile& t) {
         lw = wave < t.width ? ~0ull : 1;
-        lt = wave < t.nb ? ~0ull : 1;
         wsrc = (const char*)Wp + ((size_t)t.phys * nfb + t.fb0 + min(wave, t.width - 1)) * (R >> 4) * 1024;
+    };
+    auto ask_rows = [&](const Tile& t, int p) {            // the rows of a tile's tokens, into half p of the table
+        if (gather && wave * 64 < MAXB * 32)
+            load_words(fz.perm + min(t.m0 + tid, t.m_end - 1), S::ROWS + (p * MAXB * 32 + wave * 64) * 4);
+    };
+    auto tokens_of = [&](const Tile& t, int p) {           // the rows are there
+        lt = wave < t.nb ? ~0ull : 1;
         if (FIRST) {
             tsrc = (const char*)X;
             const int r0 = min(wave, t.nb - 1) * 32 + (lane >> 2);
@@ -243,23 +238,30 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
             to1 = (uint32_t)g1 * (uint32_t)(R * 2) + u;
         } else {
             tsrc = (const char*)X + (size_t)(t.pb0 + min(wave, t.nb - 1)) * (R >> 3) * 512;
-            if (gather && p != par && tid < MAXB * 32)     // the rows' gates, for this tile's last step
+            if (gather && tid < MAXB * 32)                 // the rows' gates, for this tile's last step
                 load_words(fz.gate + s_row[p * MAXB * 32 + tid], S::GATES + (p * MAXB * 32 + wave * 64) * 4);
         }
     };
-    auto issue_w = [&]() { load_2k(wsrc, lane16, lst + wave * BLK, lw); };
-    auto issue_t = [&]() {
+    auto load_w = [&]() {
+        load_2k(wsrc, lane16, lst + wave * BLK, lw);
+        wsrc += 2048;
+    };
+    auto load_t = [&]() {
         const uint32_t st = lst + (wave + MAXB) * BLK;
         if (FIRST) load_1k(tsrc, to0, to1, st, lt);
         else load_2k(tsrc, lane16, st, lt);
-        wsrc += 2048;
         tsrc += FIRST ? 64 : 2048;
-        lst = (lst + STAGE) & (ST * STAGE - 1);
+    };
+    auto next_stage = [&]() { lst = (lst + STAGE) & (ST * STAGE - 1); };
+    auto issue_t = [&]() {
+        load_t();
+        next_stage();
         if (__builtin_expect(++lc == nsub, 0)) {
             lc = 0;
             lpar ^= 1;
             if (nxt.nb > 0) {
-                load_tile(nxt, lpar);
+                weights_of(nxt);
+                tokens_of(nxt, lpar);
             } else {                                       // no tile left: the start of this one again, for one lane
                 wsrc -= (size_t)nsub * 2048;
                 tsrc -= (size_t)nsub * (FIRST ? 64 : 2048);
@@ -268,21 +270,33 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
         }
     };
 
-    load_tile(cur, 0);
+    // The first slices: weights on their way while the rows of the tokens are looked up.
     nxt.nb = 0;
+    ask_rows(cur, 0);
+    weights_of(cur);
 #pragma unroll 1
-    for (int i = 0; i < ST - 1; ++i) { issue_w(); issue_t(); }
-    wait_vm<8>();                                          // the first slice
+    for (int i = 0; i < ST - 1; ++i) { load_w(); next_stage(); }
+    wait_vm<2 * (ST - 1)>();                               // the rows
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    lst = 0;
+    tokens_of(cur, 0);
+#pragma unroll 1
+    for (int i = 0; i < ST - 1; ++i) { load_t(); next_stage(); }
+    lc = ST - 1;
+    wait_vm<4>();                                          // the first slice
     __builtin_amdgcn_s_barrier();
 
     uint32_t cst = 0;                                      // stage that is multiplied
-    int pend = 0;                                          // stores of this wave at the end of the tile before
+    int pend = -1;                                         // stores of this wave at the end of the tile before; -1: no such tile, the
+                                                           // first slices' weights were asked for before their tokens
     // The next slice has landed: nothing but the four loads of the slice behind it is outstanding.  In a tile's first two
     // steps the last tile's stores, too, are younger than what is waited for, and stay on their way.
     auto wait_slice = [&](int c) {
         if (__builtin_expect(c < 2, 0)) {
             if (pend >= 16) wait_vm<20>();
             else if (pend >= 8) wait_vm<12>();
+            else if (pend < 0 && c == 0) wait_vm<2>();
             else wait_vm<4>();
         } else {
             wait_vm<4>();
@@ -343,9 +357,8 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
                 __builtin_amdgcn_sched_barrier(0);
             }
             // every wave is in this tile now, so nobody reads the rows of the one before any more
-            if (__builtin_expect(c == 0, 0) && nxt.nb > 0 && gather && wave * 64 < MAXB * 32)
-                load_words(fz.perm + min(nxt.m0 + tid, nxt.m_end - 1), S::ROWS + ((par ^ 1) * MAXB * 32 + wave * 64) * 4);
-            issue_w();
+            if (__builtin_expect(c == 0, 0) && nxt.nb > 0) ask_rows(nxt, par ^ 1);
+            load_w();
             if (NB) {
                 __builtin_amdgcn_sched_barrier(0);
                 mul(fa, f1, 1, P / 4, P / 2);
