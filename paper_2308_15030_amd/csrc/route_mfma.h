@@ -248,8 +248,10 @@ __device__ __forceinline__ void smoe_route_mfma_body(const int block, const smoe
     using S = smoe_route_shape<NEB, TB>;
     constexpr int NS = S::NS, NEBH = S::NEBH, RT = SMOE_RT, NTOK = S::NTOK;
     constexpr int KC = SMOE_ROUTE_KC;
-    // reduction steps whose weights are fetched together; two such groups are in flight
-    constexpr int G = NEBH == 1 ? 4 : NEBH == 2 ? 3 : 2;
+    // Reduction steps whose weights are fetched together; two such groups are in flight.  More of them only queue at the
+    // compute unit's memory path: groups of 4 and 3 took 0.3 .. 1.2 us more a layer (16384 tokens, 128 experts, four layers 1384
+    // and 1376 us), two groups of 6 asked for before the tokens are staged 1.4 us more (T = 777, 64 experts).
+    constexpr int G = NEBH == 1 ? 3 : 2;
     uint16_t* xs = (uint16_t*)smem;                        // [NTOK][ldx] columns of x
 
     // wave index as a scalar: loop bounds that guard MFMAs must be wave-uniform for the
