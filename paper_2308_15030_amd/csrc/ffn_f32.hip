@@ -111,9 +111,12 @@ constexpr int PK_WAVES = 8;
 
 // One wave's share of NC blocks of 16 features times NB blocks of 16 tokens: n steps of 16 reduction elements.  Lane l
 // holds unit l / 16 of a step: of feature l % 16 of every 16-feature block, of token l % 16 of a block.
-template <int NB, int NC>
+// CUT: two parts of the reduction in one stream of loads, the second part's operands on their way while the first is
+// multiplied; cut(acc) takes the sums of the first part, cut_at steps (us, five calls: four slots of 768 x 3072, T = 512 89.7 ->
+// 88.6, T = 1024 141.5 -> 139.2; two of 300 x 1200, T = 1024 53.3 -> 51.2).
+template <int NB, int NC, bool CUT, typename F>
 __device__ __forceinline__ void panel_tile(const float* const (&wp)[NC], const float* const (&xp)[NB], int wstep, int xstep, int u0,
-                                           int n, int units, f32x4 (&acc)[NC][NB]) {
+                                           int n, int units, f32x4 (&acc)[NC][NB], int cut_at, F&& cut) {
     constexpr int G = NC == 4 ? (NB == 1 ? 3 : 2) : 4;     // steps fetched together; two such groups are in flight
     const int sub = (threadIdx.x & 63) >> 4;
     f32x4 wA[G][NC], wB[G][NC], xA[G][NB], xB[G][NB];
@@ -128,6 +131,7 @@ __device__ __forceinline__ void panel_tile(const float* const (&wp)[NC], const f
         }
     };
     auto step = [&](f32x4 (&w)[NC], f32x4 (&x)[NB], int i) {
+        if (CUT && i == cut_at) cut(acc);                  // uniform
         const bool in = u0 + i * 4 + sub < units;          // the reduction may end in the middle of a step
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -190,20 +194,31 @@ __device__ __forceinline__ void panel_items(const float* __restrict__ X, const f
         const float* xq[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) xq[b] = xp[b];
-#pragma unroll 1
-        for (int i = 0; i < PARTS; ++i) {
-            const int lo = min((wave * PARTS + i) * per, steps), n = min(lo + per, steps) - lo;
-            f32x4 acc[NC][NB];
+        const int lo = min(wave * PARTS * per, steps), n = min(lo + PARTS * per, steps) - lo;
+        f32x4 acc[NC][NB];
+        auto clear = [&](f32x4 (&acc)[NC][NB]) {
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int c = 0; c < NC; ++c) acc[c][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (n > 0) panel_tile<NB, NC>(wp, xq, nw * 4, xstep, lo * 4, n, units, acc);
+        };
+        auto put = [&](f32x4 (&acc)[NC][NB], int part) {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) red[wave * PARTS + i][c * 2 + b][lane] = acc[c][b];
+                for (int b = 0; b < NB; ++b) red[wave * PARTS + part][c * 2 + b][lane] = acc[c][b];
+        };
+        clear(acc);
+        if (n > 0)
+            panel_tile<NB, NC, (PARTS > 1)>(wp, xq, nw * 4, xstep, lo * 4, n, units, acc, per, [&](f32x4 (&acc)[NC][NB]) {
+                put(acc, 0);
+                clear(acc);
+            });
+        if (PARTS > 1 && n <= per) {                       // the second part is empty
+            put(acc, 0);
+            clear(acc);
         }
+        put(acc, PARTS - 1);
     };
     if (two) run(std::integral_constant<int, 2>{});
     else run(std::integral_constant<int, 1>{});
