@@ -83,8 +83,10 @@ __device__ __forceinline__ void run_tile(const TileArgs& t) {
         for (int p = 0; p < W * H; ++p)
             acc[p / H][p % H] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(v[p / H]), frag(v[W + p % H]), acc[p / H][p % H], 0, 0, 0);
     };
-    if constexpr (NL >= 7) {                               // one set of four steps, each refilled behind its products
-        constexpr int D = 4;
+    if constexpr (NL >= 7 || NL == 2) {                    // one set of steps, each refilled behind its products
+        // One block either way needs many steps in flight, and two sets of twelve did not fit the half of the register file that
+        // products read from: 96 copies, three operands of every round through scratch, all loads waited for.
+        constexpr int D = NL == 2 ? 12 : 4;
         u32x4 buf[D][NL];
 #pragma unroll
         for (int i = 0; i < D; ++i) load(buf[i], i);
@@ -104,7 +106,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& t) {
             if (s0 + i < t.n) mul(buf[i]);                 // uniform
     } else {                                               // two sets in turn: with few products the compiler moves the loads in
         // front of them and copies the registers
-        constexpr int D = NL >= 5 ? 4 : NL == 4 ? 6 : NL == 3 ? 8 : 12;
+        constexpr int D = NL >= 5 ? 4 : NL == 4 ? 6 : 8;
         u32x4 A[D][NL], B[D][NL];
 #pragma unroll
         for (int i = 0; i < D; ++i) load(A[i], i);
@@ -124,8 +126,9 @@ __device__ __forceinline__ void run_tile(const TileArgs& t) {
             for (int i = 0; i < D; ++i) mul(B[i]);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (t.n - s0 > D)                                  // uniform
 #pragma unroll
-        for (int i = 0; i < D; ++i) load(B[i], s0 + D + i);
+            for (int i = 0; i < D; ++i) load(B[i], s0 + D + i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < D; ++i)
@@ -274,6 +277,8 @@ __global__ __launch_bounds__(256, 1) void split_gemm_bf16(const uint16_t* __rest
         t.lo = min(part * per, nrb);
         t.n = min(t.lo + per, nrb) - t.lo;
         t.lo = t.n > 0 ? t.lo : 0;
+        asm volatile("" : "+s"(t.n), "+s"(t.lo));          // known per item only: else every shape's first addresses are computed in
+        // front of the items' loop, and 43 scalars kept in vector registers (2 now)
         t.m0 = a + 32 * b0;
         t.rows = min(32 * h, b - t.m0);
         t.col0 = f0 * 32;
