@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "ffn_bf16.h"
+#include "split_price.h"
 #include "wave_ops.h"
 
 namespace {
@@ -231,13 +232,11 @@ __global__ __launch_bounds__(256, 1) void split_gemm_bf16(const uint16_t* __rest
     const int mine = (lane & 3) == 0 ? tl[0] : (lane & 3) == 1 ? tl[1] : (lane & 3) == 2 ? tl[2] : tl[3];
     const int cft = (nfb + cw - 1) / cw;
     const int rounds = ((mine * cft + XCDS - 1) / XCDS + nwg - 1) / nwg;
-    // Fitted to 150 batches (13 shapes from 5 slots of 256 x 768 to 64 of 768 x 3072, T = 132 .. 8192; 4 % off at the median), in
-    // 2.2 ns: a step's blocks and products, and the meeting of the parts.
-    const int cost = rounds * (per * (15 * (cw + ch) + 4 * cw * ch) + 157 * cw * ch);
-    int best = cost * 16 + (lane & 15);
+    const float price = smoe_split_price((float)rounds, (float)per, cw, ch);
+    float best = price;
 #pragma unroll
-    for (int d = 8; d; d >>= 1) best = min(best, __shfl_xor(best, d));
-    const int id = uni(best) & 15, W = (id >> 2) + 1, H = (id & 3) + 1;
+    for (int d = 8; d; d >>= 1) best = fminf(best, __shfl_xor(best, d));
+    const int id = __ffsll((long long)__ballot(price == best)) - 1, W = (id >> 2) + 1, H = (id & 3) + 1;
     const int ftiles = (nfb + W - 1) / W;
     const int G = (H == 1 ? tl[0] : H == 2 ? tl[1] : H == 3 ? tl[2] : tl[3]) * ftiles;
     const int die = blockIdx.x % XCDS;
