@@ -116,11 +116,14 @@ static void note_slot_load(smoe_layer* L) {
     if (L->slot_device == dev) L->slot_traffic_seen += one;
 }
 
-bool smoe_weights_outgrow_cache(const smoe_layer* L) {
-    constexpr uint64_t kCacheable = 192ull << 20;          // three quarters of the 256 MB Infinity Cache
+uint64_t smoe_slot_traffic(const smoe_layer* L) {
     const int dev = L->slot_device;                        // -1: not bound yet
     const uint64_t since = dev < 0 ? 0 : g_slot_traffic[dev].load(std::memory_order_relaxed) - L->slot_traffic_seen;
-    return since + layer_slot_bytes(L->cfg) > kCacheable;
+    return since + layer_slot_bytes(L->cfg);
+}
+
+bool smoe_weights_outgrow_cache(const smoe_layer* L) {
+    return smoe_slot_traffic(L) > 192ull << 20;            // three quarters of the 256 MB Infinity Cache
 }
 
 int smoe_refresh_maps(smoe_layer* L) {

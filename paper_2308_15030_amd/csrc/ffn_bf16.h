@@ -15,6 +15,7 @@ struct FuseArgs {
     const int32_t* perm;
     const float* gate;
     const uint16_t* residual;
+    bool past;                // first product: hidden activations are stored past the caches (kernels that know how to)
 };
 
 // ffn_ring.hip: tiles of at most `blocks` x 32 tokens and `blocks` x 32 features, blocks = 4 or 8

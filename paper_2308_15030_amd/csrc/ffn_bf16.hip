@@ -139,7 +139,7 @@ __device__ __forceinline__ void apply_gate(float& v0, float& v1, float& v2, floa
 //   BKT   reduction slice per LDS stage    PD    weight prefetch distance in slices
 //   XFRAG token operand X is in fragment order (else row-major [T, R])
 //   YFRAG output Y is written in fragment order (else row-major [T, N])
-//   PAST  fragment-order output goes past the caches
+//   PAST  fragment-order output goes past the caches if fz.past
 template <int AF, int NBF, int NW, int BKT, int PD, bool XFRAG, bool YFRAG, bool RELU, bool EARLY, bool PAST>
 __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const uint4* __restrict__ Wp,
                                          uint16_t* __restrict__ Y, int R, int N, int slot, int m0,
@@ -342,8 +342,6 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
     __syncthreads();                                      // the next tile's first write may hit any stage
 
     // accumulator register i of lane l: feature 8*(i/4) + 4*(l/32) + i%4, token l%32
-    // h goes past the caches where tiles are low, whose batches are bound by the weight stream that it would displace (16 slots
-    // of 768 x 3072, two layers: T = 777 118.6 -> 115.4 us); with tiles of 128 rows T = 4096, six layers, took 507 -> 510 us.
     if constexpr (YFRAG) {   // unit [(pm0/32 + b)][(fb0+a)*4 + g][lane%32], 8 bytes at half (lane/32)
 #pragma unroll
         for (int a = 0; a < AF; ++a) {
@@ -360,7 +358,7 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
                     uint2 o;
                     o.x = smoe_pack_bf16(v0, v1);
                     o.y = smoe_pack_bf16(v2, v3);
-                    if (PAST) smoe_store_stream((uint2*)(ydst + g * 32 * 8), o);
+                    if (PAST && fz.past) smoe_store_stream((uint2*)(ydst + g * 32 * 8), o);
                     else *(uint2*)(ydst + g * 32 * 8) = o;
                 }
             }
@@ -916,6 +914,25 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
     }
 }
 
+// Whether the first product (tile v1) stores the hidden activations past the caches.  Whole passes, past / plain in the mean, over 32
+// shapes (4 MB to 2.1 GB of slots a layer), T = 130 .. 16384, one layer alone and up to six in turn; "all" are the slots that pass
+// through memory from one pass of a layer to the next:
+//  * Low tiles (3, 4): where weights come from memory, 100 MB or more of them a layer, whose stream h would displace: 0.965 .. 0.995 at
+//    every such shape (16 slots of 768 x 3072, four layers, T = 777 56.4 -> 53.9 us a layer).  From the cache, one layer, 1.000 ..
+//    1.02; six layers of 2 slots 1.05, of 8 of 768 x 2048 1.015.
+//  * 256 x 256 tiles (10): 0.96 where a layer's slots are far more than the cache, which h would leave before it is read (0.94 at 64 slots
+//    of 768 x 3072, 0.97 at 32 of 1024 x 4096; but 1.03 at 32 of 768 x 3072).  With less, large second products: 0.99 while all
+//    slots stay in the cache, 1.01 where they do not.  Second products in smaller tiles read h more often: 1.02 .. 1.04, but
+//    0.98 where all slots would stay in the cache beside each other and not beside h.
+// Tiles of 128 rows store plainly.
+bool h_past_caches(const smoe_layer* L, int v1, int v2) {
+    const double own = 4.0 * L->cfg.K * L->cfg.d_model * L->cfg.d_ff * 1e-6, all = smoe_slot_traffic(L) * 1e-6;
+    if (v1 == 3 || v1 == 4) return own >= 100 && smoe_weights_outgrow_cache(L);
+    if (v1 != 10) return false;
+    const bool large = v2 == 1 || v2 == 8 || v2 == 10;
+    return own >= 400 || (all <= 240 && (large || (own < 100 && all >= 100)));
+}
+
 }  // namespace
 
 // Names of the two kernel instances the FFN of a T-token batch runs, as a profiler prints them
@@ -962,8 +979,8 @@ int smoe_launch_ffn_bf16(const smoe_layer* L, const uint16_t* x_perm, const int3
     pick_variants(L, T, v1, v2);
     uint16_t* h = (uint16_t*)L->d_hidden;
     const int32_t* phys = L->cfg.spare_slots > 0 ? L->d_phys : nullptr;   // identity without spare slots
-    const FuseArgs none{phys, nullptr, nullptr, nullptr};
-    if (int rc = launch_variant<true>(v1, x_perm, L->slot_w1, offsets, c.K, h, c.d_model, c.d_ff, T, none, s, L->prof_ev[0], L->prof_ev[1])) return rc;
+    const FuseArgs none{phys, nullptr, nullptr, nullptr, false}, first{phys, nullptr, nullptr, nullptr, h_past_caches(L, v1, v2)};
+    if (int rc = launch_variant<true>(v1, x_perm, L->slot_w1, offsets, c.K, h, c.d_model, c.d_ff, T, first, s, L->prof_ev[0], L->prof_ev[1])) return rc;
     if (int rc = launch_variant<false>(v2, h, L->slot_w2, offsets, c.K, y_perm, c.d_ff, c.d_model, T, none, s, L->prof_ev[2], L->prof_ev[3])) return rc;
     return smoe_check_hip(hipGetLastError(), "smoe_expert_ffn launch");
 }
@@ -983,7 +1000,7 @@ int smoe_launch_ffn_bf16_fused(const smoe_layer* L, const uint16_t* x, const int
     pick_variants(L, T, v1, v2);
     uint16_t* h = (uint16_t*)L->d_hidden;
     const int32_t* phys = L->cfg.spare_slots > 0 ? L->d_phys : nullptr;   // identity without spare slots
-    const FuseArgs gather{phys, perm, nullptr, nullptr}, scatter{phys, perm, gate, residual};
+    const FuseArgs gather{phys, perm, nullptr, nullptr, h_past_caches(L, v1, v2)}, scatter{phys, perm, gate, residual, false};
     if (int rc = launch_variant<true>(v1, x, L->slot_w1, offsets, c.K, h, c.d_model, c.d_ff, T, gather, s, L->prof_ev[0], L->prof_ev[1])) return rc;
     if (int rc = launch_variant<false>(v2, h, L->slot_w2, offsets, c.K, out, c.d_ff, c.d_model, T, scatter, s, L->prof_ev[2], L->prof_ev[3])) return rc;
     return smoe_check_hip(hipGetLastError(), "smoe_forward: FFN launch");

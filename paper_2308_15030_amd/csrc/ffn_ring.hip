@@ -17,8 +17,8 @@
 //    lane's 16 bytes, so every slice has four loads to count.  With a branch for each of these the same loop without loads,
 //    products and LDS reads took 40 and 55 us of launches of 168 and 177.
 //  * Stores.  Without them the first product takes 134 of 156 us.  They stay on their way through the next tile's first
-//    two steps, and the h of large tiles passes the L2 by (the next product reads it on other dies): second product
-//    169 -> 164 us.  That of small ones stays: 11 slots of 416 x 1696, T = 1213, 31.8 us a layer, 33.3 past the L2.
+//    two steps, and the h of large tiles passes the caches by where that pays (h_past_caches in ffn_bf16.hip; here the second
+//    product 169 -> 164 us).
 //  * Balance.  Tile heights are chosen on the device from the segment lengths, and a slot's rows are cut evenly.
 // Both products at that shape, from kernel traces: 168 + 188 -> 157 + 168 us; 8000 tokens, 16 slots of 992 x 3296: 241 ->
 // 142 us.  What is left: of launches of 160 and 167 us the loads alone take 143 and 158, the products with their LDS reads
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
                     uint4 o = make_uint4(s0[0], s1[0], s0[1], s1[1]);
                     if (FIRST) {
                         const size_t u = ((size_t)(cur.pb0 + (b >> 1) * 2 + wt) * (N >> 3) + fbk * 4 + unit) * 32 + (b & 1) * 16 + (lane & 15);
-                        if (NWF == 4) smoe_store_stream((uint4*)(Y + u * 8), o);
+                        if (NWF == 4 && fz.past) smoe_store_stream((uint4*)(Y + u * 8), o);
                         else *(uint4*)(Y + u * 8) = o;
                         ++pend;
                     } else {

@@ -133,9 +133,10 @@ int smoe_launch_decode_first(const smoe_layer* L, const void* x, int T, int32_t*
                              int32_t* slot, float* gate, float* xnorm, int32_t* count, float* gsum, float* score,
                              int accumulate, int32_t* perm, int32_t* inv_perm, int32_t* offsets, hipStream_t s,
                              hipEvent_t e0, hipEvent_t e1);
-// True when the layer's expert slots (both matrices, spare slots included) and the slots of the other
-// layers on its GPU that were loaded or passed over since its own last pass are more than the 256 MB
-// Infinity Cache can hold: its weights come from HBM then, and the small batch's kernels mark their loads
+// Bytes of the layer's expert slots (both matrices, spare slots included) and of the slots of the other layers on its GPU
+// that were loaded or passed over since its own last pass.
+uint64_t smoe_slot_traffic(const smoe_layer* L);
+// True when those are more than the 256 MB Infinity Cache can hold: its weights come from HBM then, and the small batch's kernels mark their loads
 // non-temporal.  Measured with 16 slots of 768 x 3072: one layer stepped alone (151 MB, stays cached from
 // step to step) is 15 % slower with such loads, six layers in turn (906 MB) are 7 % faster.  A captured
 // graph keeps the choice of its capture; the results are the same bits either way.
