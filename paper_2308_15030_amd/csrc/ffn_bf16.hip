@@ -121,16 +121,9 @@ __device__ __forceinline__ bf16x8 as_frag(uint4 v) {
     return c.b;
 }
 
-__device__ __forceinline__ void apply_gate_v(float& v0, float& v1, float& v2, float& v3, float g, uint2 r,
-                                             bool has_res, bool fused) {
-    if (fused) smoe_apply_gate(v0, v1, v2, v3, g, r, has_res);
-}
-
 __device__ __forceinline__ void apply_gate(float& v0, float& v1, float& v2, float& v3, float g,
                                            const uint16_t* res, bool fused) {
-    uint2 r = make_uint2(0, 0);
-    if (fused && res) r = *(const uint2*)res;
-    apply_gate_v(v0, v1, v2, v3, g, r, res != nullptr, fused);
+    if (fused) smoe_apply_gate(v0, v1, v2, v3, g, res ? *(const uint2*)res : make_uint2(0, 0), res != nullptr);
 }
 
 // One workgroup tile with NBF live token blocks.  Everything is compile-time
@@ -140,7 +133,7 @@ __device__ __forceinline__ void apply_gate(float& v0, float& v1, float& v2, floa
 //   XFRAG token operand X is in fragment order (else row-major [T, R])
 //   YFRAG output Y is written in fragment order (else row-major [T, N])
 //   PAST  fragment-order output goes past the caches if fz.past
-template <int AF, int NBF, int NW, int BKT, int PD, bool XFRAG, bool YFRAG, bool RELU, bool EARLY, bool PAST>
+template <int AF, int NBF, int NW, int BKT, int PD, bool XFRAG, bool YFRAG, bool RELU, bool PAST>
 __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const uint4* __restrict__ Wp,
                                          uint16_t* __restrict__ Y, int R, int N, int slot, int m0,
                                          int m_end, int pm0, int ftile, uint16_t* xs, int stage_elems,
@@ -254,26 +247,13 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
     }
     __syncthreads();
     // Row-major output, single-call path: the residual rows come from far away by now (two
-    // weight streams have passed through the caches since x was read), so small tiles ask for
-    // their pieces here and carry them through the reduction in registers.
+    // weight streams have passed through the caches since x was read), so their pieces are asked for
+    // here and carried through the reduction in registers.
     constexpr int OF = NW * AF * 32;                      // features of the workgroup tile
     constexpr int OCPR = OF / 8;                          // 16-byte pieces per output row
     constexpr int ONP = YFRAG ? 1 : 32 * NBF * OCPR / THREADS;   // pieces per thread (2 * NBF * AF)
-    constexpr bool EARLY_RES = !YFRAG && EARLY;           // the launcher knows the register budget
-    // small tiles store straight from the accumulator layout: this lane's rows and gates, taken
-    // from the tables now (the next tile refills the tables while slower waves are still storing)
-    constexpr int NDIRECT = (!YFRAG && NBF <= 2 && !EARLY) ? NBF : 1;
-    int drow[NDIRECT];
-    float dgate[NDIRECT];
-    if constexpr (!YFRAG && NBF <= 2 && !EARLY) {
-#pragma unroll
-        for (int b = 0; b < NBF; ++b) {
-            drow[b] = orow[b * 32 + (lane & 31)];
-            dgate[b] = ogate[b * 32 + (lane & 31)];
-        }
-    }
-    uint4 res[EARLY_RES ? ONP : 1];
-    if (EARLY_RES && fz.perm && fz.residual) {
+    uint4 res[ONP];
+    if (!YFRAG && fz.perm && fz.residual) {
 #pragma unroll
         for (int i = 0; i < ONP; ++i) {
             const int idx = tid + i * THREADS, r = idx / OCPR, c = idx % OCPR;
@@ -363,44 +343,6 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
                 }
             }
         }
-    } else if constexpr (NBF <= 2 && !EARLY) {
-        // Row-major output of a small tile of the small-tile kernels, straight from the accumulator layout (a lane holds 4
-        // consecutive features of one token): the two extra barriers of the LDS turn below cost
-        // more than the scattered 8-byte stores of at most two token blocks.
-        const bool fused = fz.perm != nullptr, has_res = fused && fz.residual != nullptr;
-#pragma unroll
-        for (int a = 0; a < AF; ++a) {
-            if (fb0 + a >= nfb) continue;
-            const int col = (fb0 + a) * 32 + (lane >> 5) * 4;
-            int dst[NBF];
-            uint2 rr[NBF][4];
-#pragma unroll
-            for (int b = 0; b < NBF; ++b) {       // every residual piece of this feature block is asked for first
-                dst[b] = drow[b];
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    rr[b][g] = make_uint2(0, 0);
-                    if (has_res && dst[b] >= 0) rr[b][g] = *(const uint2*)(fz.residual + (size_t)dst[b] * N + col + g * 8);
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < NBF; ++b) {
-                if (dst[b] < 0) continue;
-                const float gmul = dgate[b];
-                uint16_t* ydst = Y + (size_t)dst[b] * N + col;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float v0 = acc[a][b][4 * g], v1 = acc[a][b][4 * g + 1], v2 = acc[a][b][4 * g + 2],
-                          v3 = acc[a][b][4 * g + 3];
-                    apply_gate_v(v0, v1, v2, v3, gmul, rr[b][g], has_res, fused);
-                    if (RELU) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f); }
-                    uint2 o;
-                    o.x = smoe_pack_bf16(v0, v1);
-                    o.y = smoe_pack_bf16(v2, v3);
-                    *(uint2*)(ydst + g * 8) = o;
-                }
-            }
-        }
     } else {
         // Row-major output.  In the accumulator layout a store instruction would touch 32 rows
         // with 8 bytes each; the tile is turned through LDS instead (the ring is idle now), so
@@ -427,61 +369,31 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
         __syncthreads();
         const bool fused = fz.perm != nullptr, has_res = fused && fz.residual != nullptr;
         const int col0 = ftile * F;
-        int prow[NP], pcol[NP];
-        uint4 rs[NP];
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {                    // residual pieces not fetched earlier are asked for first
-            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8;
-            pcol[j] = col0 + c * 8;
-            prow[j] = pcol[j] < N ? orow[r] : -1;
-            if constexpr (EARLY_RES) {
-                rs[j] = res[j];
-            } else {
-                rs[j] = make_uint4(0, 0, 0, 0);
-                if (has_res && prow[j] >= 0) rs[j] = *(const uint4*)(fz.residual + (size_t)prow[j] * N + pcol[j]);
-            }
-        }
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
-            if (prow[j] < 0) continue;
-            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8;
+            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8, col = col0 + c * 8;
+            const int row = col < N ? orow[r] : -1;
+            if (row < 0) continue;
             const uint2 lo = *(const uint2*)&xs[r * LDO + c * 8], hi = *(const uint2*)&xs[r * LDO + c * 8 + 4];
             uint4 o = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            if (fused) {
-                const float g = ogate[r];
-                uint32_t yw[4] = {o.x, o.y, o.z, o.w}, rw[4] = {rs[j].x, rs[j].y, rs[j].z, rs[j].w};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float y0 = __uint_as_float(yw[q] << 16), y1 = __uint_as_float(yw[q] & 0xFFFF0000u);
-                    float o0, o1;
-                    if (has_res) {
-                        o0 = fmaf(g, y0, __uint_as_float(rw[q] << 16));
-                        o1 = fmaf(g, y1, __uint_as_float(rw[q] & 0xFFFF0000u));
-                    } else {
-                        o0 = g * y0;
-                        o1 = g * y1;
-                    }
-                    yw[q] = smoe_pack_bf16(o0, o1);
-                }
-                o = make_uint4(yw[0], yw[1], yw[2], yw[3]);
-            }
-            *(uint4*)(Y + (size_t)prow[j] * N + pcol[j]) = o;
+            if (fused) o = smoe_gate_unit(o, ogate[r], res[j], has_res);
+            *(uint4*)(Y + (size_t)row * N + col) = o;
         }
         __syncthreads();                                  // the next tile's prologue reuses the ring
     }
 }
 
-template <int AF, int NBF, int MAXB, int NW, int BKT, int PD, bool XFRAG, bool YFRAG, bool RELU, bool EARLY>
+template <int AF, int NBF, int MAXB, int NW, int BKT, int PD, bool XFRAG, bool YFRAG, bool RELU>
 struct TileSwitch {
     static __device__ __forceinline__ void go(int nbf, const uint16_t* X, const uint4* Wp, uint16_t* Y, int R,
                                               int N, int slot, int m0, int m_end, int pm0, int ftile,
                                               uint16_t* xs, int* orow, float* ogate, const FuseArgs fz) {
         constexpr int stage = MAXB * 32 * (BKT + KPAD);
         if (nbf == NBF)
-            run_tile<AF, NBF, NW, BKT, PD, XFRAG, YFRAG, RELU, EARLY, (MAXB <= 2)>(X, Wp, Y, R, N, slot, m0, m_end, pm0, ftile, xs,
+            run_tile<AF, NBF, NW, BKT, PD, XFRAG, YFRAG, RELU, (MAXB <= 2)>(X, Wp, Y, R, N, slot, m0, m_end, pm0, ftile, xs,
                                                                stage, orow, ogate, fz);
         else if constexpr (NBF > 1)
-            TileSwitch<AF, NBF - 1, MAXB, NW, BKT, PD, XFRAG, YFRAG, RELU, EARLY>::go(nbf, X, Wp, Y, R, N, slot, m0,
+            TileSwitch<AF, NBF - 1, MAXB, NW, BKT, PD, XFRAG, YFRAG, RELU>::go(nbf, X, Wp, Y, R, N, slot, m0,
                                                                               m_end, pm0, ftile, xs, orow, ogate, fz);
     }
 };
@@ -530,7 +442,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void grouped_gemm_bf16(
         }
         if (fz.phys) slot = __builtin_amdgcn_readfirstlane(fz.phys[slot]);   // from here on: where the weights live
         const int nbf = min(MAXB, (m_end - m0 + 31) >> 5);    // token blocks that hold real rows
-        TileSwitch<AF, MAXB, MAXB, NW, BKT, PD, !FIRST, FIRST, FIRST, !FIRST && AF * MAXB <= 4 && OCC <= 2>::go(nbf, X, Wp, Y, R, N, slot, m0, m_end,
+        TileSwitch<AF, MAXB, MAXB, NW, BKT, PD, !FIRST, FIRST, FIRST>::go(nbf, X, Wp, Y, R, N, slot, m0, m_end,
                                                                          pm0, ftile, xs, s_orow, s_ogate, fz);
     }
 }
