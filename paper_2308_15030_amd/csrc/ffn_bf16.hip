@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "ffn_bf16.h"
+#include "split_price.h"
 #include "wave_ops.h"
 
 namespace {
@@ -710,80 +711,92 @@ int launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* offs
     return SMOE_OK;
 }
 
-// Tile shape of one product of a prefill batch, chosen by its predicted time: for every round of one item per compute
+// Tile shape of the first product of a prefill batch, chosen by its predicted time: for every round of one item per compute
 // unit the bytes of an item's weights and rows at the rate at which that tile takes them in.  A slot with x tiles' worth
 // of tokens in the mean has about x + 1/2 tiles, and one where x is small.  The rates were fitted to 180 batches (13
 // shapes from 4 slots of 256 x 768 to 32 of 1024 x 4096, T = 140 .. 6000, weights from HBM, every tile measured on each): the
-// pick is 1.3 % (first product) and 0.5 % (second) slower than the best tile of each batch in the mean, where thresholds
-// on the tokens per slot alone were 10 and 13 % slower.  us, those thresholds / this choice, second product: 8 slots of
-// 768 x 3072, T = 1000 27.0 / 23.0, T = 2000 33.4 / 27.1; 16 slots, T = 2500 43.7 / 35.9; 16 of 1024 x 4096, T = 2000 60.4 /
-// 48.7; first: 4 slots of 768 x 3072, T = 600 17.4 / 13.1; 16 of 768 x 2048, T = 4096 35.4 / 27.3.
-int pick_tile(bool first, int R, int N, int T, int K) {
-    struct Rate { int v, rows, features; double first_gbs, second_gbs; };
-    static constexpr Rate rates[] = {{4, 32, 128, 47.4, 71.6}, {3, 64, 128, 56.7, 67.3}, {1, 128, 128, 61.1, 60.0}, {8, 128, 256, 48.4, 47.2}};
-    const double ends = first ? 0.5 : 0.55;
-    // slots of less than two blocks of rows: no wide tiles for the first product (each weight would pass through one compute
+// pick is 1.3 % slower than the best tile of each batch in the mean, where thresholds on the tokens per slot alone were 10 %
+// slower.  us, those thresholds / this choice: 4 slots of 768 x 3072, T = 600 17.4 / 13.1; 16 of 768 x 2048, T = 4096 35.4 / 27.3.
+int pick_first(int R, int N, int T, int K) {
+    struct Rate { int v, rows, features; double gbs; };
+    static constexpr Rate rates[] = {{4, 32, 128, 47.4}, {3, 64, 128, 56.7}, {1, 128, 128, 61.1}, {8, 128, 256, 48.4}};
+    // slots of less than two blocks of rows: no wide tiles (each weight would pass through one compute
     // unit only, at the rate of cold lines: 16 slots of 1024 x 4096, T = 777 39.5, 31.0 with 128 features), and a count
     // that is nearer to the truth
-    const bool thin = first && T / K < 60;
+    const bool thin = T / K < 60;
     const double cus = XCDS * cus_per_die();
     auto rounds = [&](int rows, int features) {
-        const double x = (double)T / K / rows, tiles = K * (x + ends + (1 - ends) * std::exp(-2 * x));
+        const double x = (double)T / K / rows, tiles = K * (x + 0.5 + 0.5 * std::exp(-2 * x));
         return std::max(1.0, std::ceil(tiles * ((N + features - 1) / features) / cus - (thin ? 0.06 : 0.03)));
     };
     int best = 1;
     double least = 1e30;
     for (const Rate& r : rates) {
         if (thin && r.features > 128) continue;
-        const double us = rounds(r.rows, r.features) * (r.rows + r.features) * 2e-3 * R / (first ? r.first_gbs : r.second_gbs);
+        const double us = rounds(r.rows, r.features) * (r.rows + r.features) * 2e-3 * R / r.gbs;
         if (us < least) { least = us; best = r.v; }
     }
-    if (!thin && smoe_ring_applies(first, R, T))
+    if (!thin && smoe_ring_applies(true, R, T))
         for (int h = 1; h <= 8; ++h) {                     // the ring kernel chooses the height of its tiles
-            const double us = (first ? -0.6 : 1.6) + rounds(32 * h, 256) * (256 + 32 * h) * 2e-3 * R / (first ? 38.4 : 42.0);
+            const double us = -0.6 + rounds(32 * h, 256) * (256 + 32 * h) * 2e-3 * R / 38.4;
             if (us < least) { least = us; best = 10; }
         }
     return best;
 }
 
-// Where the ring kernel takes a product in any case: 9 (at most 128 x 128) or 10 (at most 256 x 256), else 0.
-//  * The reduction is no multiple of 128: the tiled kernel then has no weight prefetch.  us, tiled -> ring: 16 slots of
-//    992 x 3296, T = 800 33.0 -> 29.8 and 77.0 -> 42.6, T = 8000 107 -> 72 and 134 -> 70; 11 of 416 x 1696, T = 800 12.5 -> 10.7
-//    and 31.6 -> 18.0.  Where the streaming kernel splits a second product (v = 6) it stays ahead (T = 200: 15.8, 17.8),
-//    and with few tokens so do tiles of 64-deep slices (6 slots of 448 x 1280, T = 140 8.1, 9.2, T = 300 8.8, 9.4).  Under 6
-//    tokens per slot the first product's streaming kernel stays where rows are long and slots at most 64 (us per layer, streaming
-//    / ring: 24 slots of 992 x 3296, T = 100 84 / 89, 48 T = 120 .. 264 2 .. 3 % ahead, 16 of 1184 x 4736 5 %; but 48 of 544 x
-//    2176, T = 168 71 / 69, 128 of 928 x 3712, T = 192 1 .. 5 % behind).  The small tiles
-//    serve where fewer than a hundred large ones exist (608 x 2912, T = 8000 second: 44.5, 49.0 with large ones;
-//    992 x 3296 70 with large ones, 96).
-//  * There are large tiles for the chip many times over, where the matrix products and the power they draw count
-//    and not the bytes alone (128 x 128 tiles -> ring: 768 x 3072, T = 16384 108 -> 94 and 105 -> 80; 32 slots of
-//    1024 x 4096 190 -> 165 and 187 -> 166; 16 of 768 x 2048 80 -> 68 and 75 -> 60).
-int ring_tile(bool first, int R, int N, int T, int K, int tiled) {
-    const double tiles = (double)T * N / 65536;            // full 256 x 256 tiles
-    if (R % 128 != 0) {
-        if (tiled == 6 || (tiled == 5 && R >= 900 && K <= 64) || (first && T / K < 60 && R % 64 == 0)) return 0;
-        return tiles >= 100 ? 10 : 9;
+// Kernel of the second product of a prefill batch, by predicted time likewise: tiled, ring, or splitting by the price that the kernel
+// itself uses, with the expected number of tiles in the place of the counted.  Fitted to whole passes of 3720 batches, each of them with
+// every kernel in turn (32 shapes from 2 slots of 768 x 3072 to 128 of 1024 x 4096, T = 130 .. 16384, clustered and even tokens,
+// one layer alone and up to six): the pick takes 0.6 % more than the best of each batch in the mean, 3.8 % at the 95th percentile.
+// us a layer with weights from memory, clustered tokens, splitting / 128 x 128 / 128 x 256 / large ring: 16 slots of 768 x 3072, T = 3000
+// 78.0 / 80.1 / 92.1 / 93.6, T = 4000 86.5 / 84.9 / 97.6 / 97.8, T = 5500 105.4 / 105.3 / 103.5 / 108.4; 24 of 768 x 2048, T = 4500 87.3 / 90.5
+// / 86.9 / 88.3; 128 of 1024 x 4096, T = 3000 411 / 402 / 398 / 398, T = 16384 615 / 596 / 584 / 560.
+// Where the reduction is no multiple of 128 the tiled kernel has no weight prefetch, and the ring kernel stands for it (16 slots of 992
+// x 3296, T = 800 77.0 and 42.6): its small tiles, two workgroups of them to a compute unit, while fewer than a hundred large ones
+// exist (608 x 2912, T = 8000 44.5, 49.0 with large ones; 992 x 3296 70 with large ones, 96).
+int pick_second(int R, int N, int T, int K) {
+    struct Rate { int v, low, high, features, per_cu; double ends, slack, fixed, gbs; };   // heights in blocks of 32 rows
+    static constexpr Rate rates[] = {{1, 4, 4, 128, 1, 0.48, 0, 2.3, 71.4}, {8, 4, 4, 256, 1, 0.48, 0, -1.0, 64.8},
+                                     {9, 1, 4, 128, 2, 0.87, 0.19, 2.4, 39.7}, {10, 1, 8, 256, 1, 0.21, 0.23, 0.6, 55.6}};
+    const double cus = XCDS * cus_per_die();
+    auto rounds = [&](int h, int features, double n, double ends, double slack) {
+        const double x = (double)T / K / (32 * h), tiles = K * (x + ends + (1 - ends) * std::exp(-2 * x));
+        return std::max(1.0, std::ceil(tiles * ((N + features - 1) / features) / n - slack));
+    };
+    int best = 11;
+    double least = 1e30;
+    for (int w = 1; w <= 4; ++w)
+        for (int h = 1; h <= 4; ++h)
+            least = std::min(least, 2.2e-3 * smoe_split_price((float)rounds(h, 32 * w, cus, 0.57, 0.02), (float)((R + 63) / 64), w, h));
+    const bool ring = smoe_ring_applies(false, R, T), whole = R % 128 == 0, many = (double)T * N / 65536 >= 100;
+    for (const Rate& r : rates) {
+        if (r.v == 1 || r.v == 8 ? ring && !whole : !ring || (r.v == 9 ? whole || many : !whole && !many)) continue;
+        for (int h = r.low; h <= r.high; ++h) {
+            const double us = r.fixed + rounds(h, r.features, cus * r.per_cu, r.ends, r.slack) * (r.features + 32 * h) * 2e-3 * R / r.gbs;
+            if (us < least) { least = us; best = r.v; }
+        }
     }
-    return tiles >= (first ? 300 : 100) ? 10 : 0;
+    return best;
 }
 
-// Where the second product splits its reduction (ffn_split.hip) instead of taking the tile `tiled`.  Kernel times of 146 batches (13
-// shapes, T = 132 .. 8192), split / what was chosen before:
-//  * In the place of the tiles of 32 and 64 rows always: 0.52 .. 1.03, 0.87 in the mean (4 slots of 768 x 3072, T = 520 12.7 / 17.5; 16
-//    slots, T = 1213 26.7 / 30.1; 64 slots, T = 2000 68.8 / 69.6; the one loser 5 of 256 x 768, T = 6000 11.0 / 9.2).
-//  * In the place of 128 x 128 tiles while its own leave a fifth of the compute units to slots that are cut unevenly: up to an expected
-//    204 of 4 x 4 blocks (16 slots of 768 x 3072, T = 3100, 200: 33.5 / 37.0; 4 slots, T = 3100 27.4 / 32.2; 16 of 512 x 2048, T =
-//    4096, 163: 23.2 / 25.3; 4 of 768 x 3072, T = 4096, 205: 33 / 33 .. 35 from memory, 26.3 / 26.2 from the cache; 16, T = 4096,
-//    245: 38.3 / 37.7; 8 of 768 x 2048, T = 4096, 218: 26.9 / 25.4).  Slots of less than a tile's rows take smaller tiles,
-//    whose number that says little about (32 of 1024 x 4096, T = 520 64 / 78, T = 800 63 / 69; 32 of 768 x 3072, T = 2000 43 / 47).
-//  * Where the reduction is no multiple of 128, and the other choice the ring kernel, up to 300 (10 of 992 x 3296, T = 800 25.9 / 41.8,
-//    T = 4096, 300: 57.6 / 58.3, T = 6000, 419: 67 / 64).
-bool splits(int R, int N, int T, int K, int tiled) {
-    if (tiled == 3 || tiled == 4) return true;
-    const double x = (double)T / K / 128, tiles = K * (x + 0.55 + 0.45 * std::exp(-2 * x)) * ((N + 127) / 128);
-    if (R % 128 != 0) return tiled == 1 && tiles <= 300;
-    return tiled == 1 && (tiles <= 0.8 * XCDS * cus_per_die() || T / K < 128);
+// Where the ring kernel takes the first product in any case: 9 (at most 128 x 128) or 10 (at most 256 x 256), else 0.
+//  * The reduction is no multiple of 128: the tiled kernel then has no weight prefetch.  us, tiled -> ring: 16 slots of
+//    992 x 3296, T = 800 33.0 -> 29.8, T = 8000 107 -> 72; 11 of 416 x 1696, T = 800 12.5 -> 10.7.  With few tokens tiles of 64-deep
+//    slices stay ahead (6 slots of 448 x 1280, T = 140 8.1, 9.2, T = 300 8.8, 9.4).  Under 6
+//    tokens per slot the streaming kernel stays where rows are long and slots at most 64 (us per layer, streaming
+//    / ring: 24 slots of 992 x 3296, T = 100 84 / 89, 48 T = 120 .. 264 2 .. 3 % ahead, 16 of 1184 x 4736 5 %; but 48 of 544 x
+//    2176, T = 168 71 / 69, 128 of 928 x 3712, T = 192 1 .. 5 % behind).  The small tiles
+//    serve where fewer than a hundred large ones exist.
+//  * There are large tiles for the chip many times over, where the matrix products and the power they draw count
+//    and not the bytes alone (128 x 128 tiles -> ring: 768 x 3072, T = 16384 108 -> 94; 32 slots of
+//    1024 x 4096 190 -> 165; 16 of 768 x 2048 80 -> 68).
+int ring_first(int R, int N, int T, int K, int tiled) {
+    const double tiles = (double)T * N / 65536;            // full 256 x 256 tiles
+    if (R % 128 != 0) {
+        if ((tiled == 5 && R >= 900 && K <= 64) || (T / K < 60 && R % 64 == 0)) return 0;
+        return tiles >= 100 ? 10 : 9;
+    }
+    return tiles >= 300 ? 10 : 0;
 }
 
 // Tile shapes for the two GEMMs.  A pair fixed at smoe_create (SMOE_FFN_VARIANT="v1,v2", a
@@ -797,7 +810,8 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
         // The second product streams while its workgroups, one per 32 features and 32 rows of a slot, are little more than
         // the chip holds at once (two per compute unit): each then has a quarter of a reduction per wave in front of it,
         // where a tile has all of it.  Measured on 340 batches of 2 to 100 slots, T = 129 .. 2000, clustered and even tokens,
-        // us per layer, streaming / best tile.  700 workgroups: 25 .. 0 % ahead below (4 slots of 768 x 3072, T = 200 28 / 35; 6,
+        // us per layer, streaming / best tile of the tiled kernel (the splitting kernel, which came later, is ahead of both on many of
+        // them: 8 slots of 1024 x 4096, T = 400 55.5 / 47.9; not yet part of this line).  700 workgroups: 25 .. 0 % ahead below (4 slots of 768 x 3072, T = 200 28 / 35; 6,
         // T = 320 37 / 45; 4 of 2048 x 8192, T = 200 90 / 106), 3 % behind above (18 of 768 x 3072, T = 668 69 / 67).  Under 28
         // tokens per slot, where most of a tile is empty, 780: 24 slots of 768 x 2048, T = 248 57.0 / 57.3, T = 400 54.9 / 53.4; 26 of 768 x
         // 3072, T = 263 71 / 69.  A long reduction makes the rounds of the tiles long, 850: 16 slots of 1024 x 4096, T = 300 73 / 76; 12
@@ -807,18 +821,19 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
         // and more, where the rows of the largest slots stream too often (one slot of 768 x 3072, T = 800 39.7 / 37.8).
         const int groups = (K + T / 32) * (d >> 5);
         const bool stream = T <= 512 && f >= 768 && groups <= (per_slot >= 28 ? 700 : per_slot >= 14 && f >= 3072 ? 850 : 780);
-        v1 = d % 128 != 0 ? (per_slot < 28 ? 4 : 3) : pick_tile(true, d, f, T, K);
-        v2 = f % 128 != 0 ? (per_slot < 28 ? 6 : 1) : stream ? 6 : pick_tile(false, f, d, T, K);
+        v1 = d % 128 != 0 ? (per_slot < 28 ? 4 : 3) : pick_first(d, f, T, K);
+        v2 = (f % 128 != 0 ? per_slot < 28 : stream) ? 6 : pick_second(f, d, T, K);
     }
     // the small-batch path of smoe_forward splits the second product's reduction four ways: the separate call does the
     // same, so that both give the same bits (the tiles of the first product all do)
     if (smoe_decode_first_applies(L, T)) {
         v2 = 6;
     } else {
-        if (splits(f, d, T, K, v2)) v2 = 11;
-        const int r1 = ring_tile(true, d, f, T, K, v1), r2 = v2 == 11 ? 0 : ring_tile(false, f, d, T, K, v2);
+        const int r1 = ring_first(d, f, T, K, v1);
         if (r1 && smoe_ring_applies(true, d, T)) v1 = r1;
-        if (r2 && smoe_ring_applies(false, f, T)) v2 = r2;
+        // The second product does not stream beside a hundred large tiles: rows of thousands of outputs, short reductions (128 slots of 9216 x 256, T = 760
+        // 590 us a layer streaming, 345 through the ring)
+        if (v2 == 6 && f % 128 == 0 && (double)T * d / 65536 >= 100 && smoe_ring_applies(false, f, T)) v2 = 10;
     }
     if (is_variant(L->ffn_variant[0]) && is_variant(L->ffn_variant[1])) {
         v1 = L->ffn_variant[0];

@@ -14,18 +14,22 @@ from test_streaming_tiles_gpu import MANY
 from test_tile_choice import kernels
 
 
-@pytest.mark.parametrize("K,d,f,T,split", [
-    # instead of tiles of 32 and 64 rows; instead of 128 x 128 tiles while its own leave a fifth of the chip free
-    (4, 768, 3072, 520, True), (16, 768, 3072, 777, True), (4, 768, 3072, 4000, True), (16, 768, 3072, 3100, True), (4, 768, 3072, 4096, False),
-    (16, 768, 3072, 4096, False), (8, 768, 2048, 4096, False), (4, 768, 3072, 6000, False),
+@pytest.mark.parametrize("K,d,f,T,kernel", [
+    # small tiles, and larger ones while its own leave a fifth of the chip free
+    (4, 768, 3072, 520, "split"), (16, 768, 3072, 777, "split"), (4, 768, 3072, 3750, "split"), (16, 768, 3072, 3100, "split"), (4, 768, 3072, 4096, "tiled"),
+    (16, 768, 3072, 4096, "tiled"), (8, 768, 2048, 4096, "tiled"), (4, 768, 3072, 6000, "tiled"),
     # slots of less than a tile's rows
-    (32, 1024, 4096, 800, True), (32, 768, 3072, 2000, True),
-    # no multiple of 128
-    (11, 416, 1696, 1213, True), (10, 992, 3296, 4000, True), (10, 992, 3296, 6000, False),
-    # what streams stays so
-    (4, 768, 3072, 200, False), (16, 768, 3072, 60, False)])
-def test_choice(K, d, f, T, split):
-    assert (kernels(K, d, f, T)[1] == "split_gemm_bf16") == split
+    (32, 1024, 4096, 800, "split"), (32, 768, 3072, 2000, "split"),
+    # no multiple of 128; too short for the ring kernel
+    (11, 416, 1696, 1213, "split"), (10, 992, 3296, 3100, "split"), (10, 992, 3296, 4000, "ring<2"), (10, 992, 3296, 6000, "ring<2"),
+    (4, 64, 160, 1000, "split"), (4, 64, 160, 1000000, "tiled"),
+    # large tiles for the chip many times over, whatever the rows of a slot
+    (16, 768, 3072, 12000, "ring<4"), (128, 1024, 4096, 6000, "ring<4"), (128, 1024, 4096, 16000, "ring<4"), (16, 608, 2400, 12000, "ring<4"),
+    # what streams stays so, but for wide rows
+    (4, 768, 3072, 200, "streaming"), (16, 768, 3072, 60, "streaming"), (128, 9216, 256, 700, "streaming"), (128, 9216, 256, 760, "ring<4")])
+def test_choice(K, d, f, T, kernel):
+    name = {"split": "split_gemm_bf16", "tiled": "grouped_gemm_bf16<", "streaming": "small_gemm_bf16<4, 4"}.get(kernel, kernel.replace("ring", "ring_gemm_bf16"))
+    assert kernels(K, d, f, T)[1].startswith(name)
 
 
 @pytest.mark.gpu
