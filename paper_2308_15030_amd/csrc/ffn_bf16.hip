@@ -675,16 +675,18 @@ void launch_gemm(const uint16_t* X, const void* Wp, const int32_t* offsets, int 
                           (const uint4*)Wp, offsets, nslots, T, Y, R, N, fz);
 }
 
-// The tile shapes launch_variant knows; every one of them is chosen somewhere by pick_variants.
+// The kernels launch_variant knows; every one of them is chosen somewhere by pick_variants.
 constexpr bool is_variant(int v) {
     return v == 1 || v == 3 || v == 4 || v == 5 || v == 6 || v == 8 || v == 9 || v == 10 || v == 11;
 }
 
-// What stands in where the ring kernel (9, 10) does not apply; the splitting kernel (11) is the second product's and takes the
-// place of the tiles of 64 and 32 rows there.
-int ring_or_tiled(int v, bool first, int R, int T) {
-    if (v == 11 || v == 3 || v == 4) return first ? (v == 11 ? 1 : v) : 11;
-    if (v < 9 || smoe_ring_applies(first, R, T)) return v;
+// What stands in where a kernel does not serve a product, as only a pair forced by hand can ask: the tiles of 64 and 32 rows (3, 4)
+// are the first product's and the splitting kernel (11) the second's, which has it in their place; the ring kernel (9, 10) does not
+// apply everywhere.
+int standing_in(int v, bool first, int R, int T) {
+    if (first && v == 11) return 1;
+    if (!first && (v == 3 || v == 4)) return 11;
+    if (v < 9 || v == 11 || smoe_ring_applies(first, R, T)) return v;
     return v == 9 ? 1 : 8;
 }
 
@@ -692,21 +694,24 @@ template <bool FIRST>
 int launch_variant(int v, const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots,
                     uint16_t* Y, int R, int N, int T, const FuseArgs& fz, hipStream_t s, hipEvent_t e0,
                     hipEvent_t e1) {
-    v = ring_or_tiled(v, FIRST, R, T);
+    v = standing_in(v, FIRST, R, T);
     if (v == 11) return smoe_launch_split(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die(), s, e0, e1);
     if (v >= 9) return smoe_launch_ring(v == 9 ? 4 : 8, FIRST, X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die(), s, e0, e1);
     if (R % 64 != 0 && v != 5 && v != 6) {   // d_model / d_ff are multiples of 32 by contract: 32-deep slices always fit
         launch_gemm<1, 4, 4, 32, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);
         return SMOE_OK;
     }
-    switch (v) {             //            AF MAXB NW BKT PD OCC     tokens x features per workgroup
-        case 1: launch_gemm<1, 4, 4, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  // 128 x 128
-        case 3: if constexpr (FIRST) launch_gemm<1, 2, 4, 64, 1, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  64 x 128
-        case 4: if constexpr (FIRST) launch_gemm<1, 1, 4, 64, 3, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  //  32 x 128
-        case 8: launch_gemm<1, 4, 8, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;  // 128 x 256, 8 waves
-        case 5: launch_small<4, 1, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;   // 32 x 128, streaming
-        case 6: launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;   // 32 x 32, reduction split 4 ways
-        default: launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1); break;
+    // tokens x features of a workgroup  AF MAXB NW BKT PD OCC
+    if (v == 1) launch_gemm<1, 4, 4, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);        // 128 x 128
+    else if (v == 8) launch_gemm<1, 4, 8, 64, 1, 2, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);   // 128 x 256, 8 waves
+    else if (v == 5) launch_small<4, 1, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);               // 32 x 128, streaming
+    else if (v == 6) launch_small<4, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);               // 32 x 32, reduction split 4 ways
+    else if constexpr (FIRST) {
+        if (v == 3) launch_gemm<1, 2, 4, 64, 1, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);    //  64 x 128
+        else if (v == 4) launch_gemm<1, 1, 4, 64, 3, 4, FIRST>(X, Wp, offsets, nslots, Y, R, N, T, fz, s, e0, e1);   //  32 x 128
+        else return smoe_fail(SMOE_EINVAL, "expert FFN: no first product %d", v);
+    } else {
+        return smoe_fail(SMOE_EINVAL, "expert FFN: no second product %d", v);
     }
     return SMOE_OK;
 }
@@ -872,7 +877,7 @@ int smoe_describe_ffn_bf16(const smoe_layer* L, int T, int fused, char* out, siz
     for (int i = 0; i < 2; ++i) {
         const bool first = i == 0;
         const int R = first ? L->cfg.d_model : L->cfg.d_ff;
-        v[i] = ring_or_tiled(v[i], first, R, T);
+        v[i] = standing_in(v[i], first, R, T);
         const char* shape = nullptr;                       // AF, MAXB, NW, BKT, PD, OCC of launch_variant
         std::string name;
         if (fused && smoe_decode_first_applies(L, T) && v[1] == 6) name = smoe_describe_decode(L, T, first);

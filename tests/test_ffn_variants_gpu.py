@@ -14,15 +14,32 @@ import pytest
 import torch
 
 import oracle
+from paper_2308_15030_amd import binding as b
 from paper_2308_15030_amd import workloads as wl
 from harness import Case, max_abs_rel, to_dev, to_host, values
 
 pytestmark = pytest.mark.gpu
 
-# indices of launch_variant in csrc/ffn_bf16.hip: (first product, second product).  10 is the ring
+# indices of launch_variant in csrc/ffn_bf16.hip: (first product, second product).  3 and 4 are tiles of the first product;
+# forced on the second they mean 11, the splitting kernel that serves in their place.  10 is the ring
 # kernel, and the tiled kernel that stands in for it below reductions of 256; a 256-row tile of the
 # tiled kernel that had this index once ran past its rows as the second product.
-PAIRS = [(1, 1), (3, 3), (4, 4), (5, 5), (6, 6), (8, 8), (10, 1), (10, 8), (8, 3), (5, 6), (4, 6), (10, 10), (8, 10)]
+PAIRS = [(1, 1), (3, 3), (4, 4), (5, 5), (6, 6), (8, 8), (10, 1), (10, 8), (8, 3), (5, 6), (4, 6), (10, 10), (8, 10), (1, 11), (3, 11), (4, 11),
+         (8, 11), (9, 11), (10, 11), (9, 9)]
+
+
+def kernel(v, first, R):
+    """Name of the kernel that index v runs on a product with reduction R."""
+    v = 11 if not first and v in (3, 4) else 8 if v == 10 and R < 256 else 1 if v == 9 and R < 256 else v
+    if v == 11:
+        return "split_gemm_bf16"
+    if v in (5, 6):
+        return f"small_gemm_bf16<4, {1 if v == 5 else 4},"
+    if v in (9, 10):
+        return f"ring_gemm_bf16<{2 if v == 9 else 4},"
+    if R % 64:
+        return "grouped_gemm_bf16<1, 4, 4, 32,"
+    return "grouped_gemm_bf16<1, " + {1: "4, 4,", 3: "2, 4,", 4: "1, 4,", 8: "4, 8,"}[v]
 
 
 @pytest.mark.parametrize("v1,v2", PAIRS)
@@ -37,6 +54,8 @@ def test_tile_variant(v1, v2, d_model, d_ff):
     finally:
         del os.environ["SMOE_FFN_VARIANT"]
     L = c.L
+    names = b.smoe_describe_ffn(L.handle, c.T, False).split(" | ")
+    assert names[0].startswith(kernel(v1, True, d_model)) and names[1].startswith(kernel(v2, False, d_ff)), names
     r = oracle.layer_forward(c.x, c.Wr, *c.slot_weights_host(), c.e2s)
     assert min(np.diff(r["offsets"])) > 0 and max(np.diff(r["offsets"])) > 256   # several row tiles and a ragged tail
     L.x_perm.copy_(to_dev(r["x_perm"])); L.offsets.copy_(to_dev(r["offsets"]))
