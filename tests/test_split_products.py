@@ -1,6 +1,7 @@
 """The second product with its reduction split over the waves of a workgroup (split_gemm_bf16): the rule that chooses it, and
-the kernel where it can go wrong -- every tile shape of 1 to 4 blocks either way, narrow last tiles, reductions too short for
-four parts or with parts of unequal length, empty slots, more slots than a wave has lanes, several tiles per workgroup.
+the kernel where it can go wrong -- narrow last tiles, reductions too short for four parts or with parts of unequal length, empty
+slots, more slots than a wave has lanes, several tiles per workgroup (small shapes), and every tile shape of 1 to 4 blocks either
+way in long reductions, whose loops go round (`executed` below repeats the kernel's choice and says which run).
 
 Forced through SMOE_FFN_VARIANT (11; read at smoe_create).  Reference and tolerance as in test_ring_gpu.py."""
 import os
@@ -32,12 +33,50 @@ def test_choice(K, d, f, T, kernel):
     assert kernels(K, d, f, T)[1].startswith(name)
 
 
+def executed(lens, N, R, per_die=32):
+    """Tile shapes (feature, token blocks) that the kernel runs on these segments, and the one that it picks."""
+    nfb, per = N // 32, -(-(R // 16) // 4)
+    items = (sum(lens) // 32 + len(lens)) * nfb
+    nwg = max(min(-(-items // 8), per_die), 1)
+    blocks = [-(-n // 32) for n in lens]
+    def price(w, h):
+        tiles = sum(-(-b // h) for b in blocks) * -(-nfb // w)
+        return -(-(-(-tiles // 8)) // nwg) * (per * (15 * (w + h) + 4 * w * h) + 157 * w * h)
+    W, H = min(((w, h) for w in range(1, 5) for h in range(1, 5)), key=lambda s: price(*s))
+    cut = lambda n, most: {n // -(-n // most) + (i < n % -(-n // most)) for i in range(-(-n // most))}
+    return (W, H), {(w, h) for b in blocks if b for w in cut(nfb, W) for h in cut(b, H)}
+
+
+# (segments, d_model, d_ff): each is the pick of one shape, evenly or unevenly cut, with parts of 24 steps and more
+LONG = [([1], 768, 3072), ([97, 128, 129, 300], 384, 3072), ([97, 128, 129, 300], 768, 3072), ([120] * 48, 160, 1696), ([412, 88], 992, 1632),
+        ([1500, 40, 700], 384, 3072), ([1500, 40, 700], 512, 2048), ([1500, 40, 700], 768, 3072), ([97, 128, 129, 300], 992, 3296),
+        ([1300, 700, 33, 1950], 384, 3072), ([190] * 16, 768, 3072), ([1000] * 4, 768, 3072), ([858, 142], 992, 1632), ([1300, 700, 33, 1950], 992, 3296),
+        ([190] * 16, 992, 3296), ([900, 100, 640, 31, 0, 333, 517, 64, 1200, 215], 768, 3072)]
+SHAPES = [(w, h) for w in range(1, 5) for h in range(1, 5)]
+
+
+def test_every_shape_is_run():
+    assert [executed(*c)[0] for c in LONG] == SHAPES
+    assert {s for c in LONG for s in executed(*c)[1]} == set(SHAPES)
+    assert any(len(executed(*c)[1]) > 2 for c in LONG)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,d,f", LONG, ids=[f"{w}x{h}" for w, h in SHAPES])
+def test_long_reductions(lens, d, f):
+    check(lens, d, f)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("lens", [[1], [0, 31, 0, 33, 64, 0], [97, 128, 129, 300], [1500, 40, 700], MANY, [5] * 200],
                          ids=["one", "empty", "edges", "large", "many", "thin"])
 # (d_model, d_ff): 1 to 5 and 25 feature blocks; reductions of 2, 6, 10, 18 and 106 steps of 16
 @pytest.mark.parametrize("d,f", [(32, 32), (64, 96), (96, 160), (160, 288), (128, 1696), (800, 288)])
 def test_split_products(d, f, lens):
+    check(lens, d, f)
+
+
+def check(lens, d, f):
     K, T, dev = len(lens), sum(lens), "cuda:0"
     g = torch.Generator(device=dev)
     g.manual_seed(d + f + T)
