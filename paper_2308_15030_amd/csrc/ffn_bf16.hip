@@ -83,7 +83,7 @@ __device__ __forceinline__ void build_item_map(ItemMap& m, const int32_t* __rest
                 tiles = (b - a + bt - 1) / bt;
                 pad = (b - a + 31) & ~31;
             }
-            const int tin = smoe_wave_incl_scan(tiles, lane), pin = smoe_wave_incl_scan(pad, lane);
+            const int tin = smoe_wave_incl_scan(tiles), pin = smoe_wave_incl_scan(pad);
             if (k < nslots) {
                 m.first[k] = tiles_before + tin - tiles;
                 m.pad[k] = pad_before + pin - pad;
@@ -516,10 +516,10 @@ __global__ __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(2, 2))
             b = max(min(max(offsets[k + 1], 0), T), a);
         }
         const int pad = (b - a + 31) & ~31;
-        const int pin = smoe_wave_incl_scan(pad, lane);
+        const int pin = smoe_wave_incl_scan(pad);
         int at = item - base;                              // this workgroup's lane of the chunk, if it is one of its lanes
         if (extra >= 0) {
-            const int more = max((pad >> 5) - 1, 0), upto = smoe_wave_incl_scan(more, lane);
+            const int more = max((pad >> 5) - 1, 0), upto = smoe_wave_incl_scan(more);
             const unsigned long long past = __ballot(more_before + upto > extra);
             at = past ? __ffsll(past) - 1 : 64;
             tile = extra - more_before - __shfl(upto - more, at & 63) + 1;

@@ -54,7 +54,7 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, i
             b = max(min(max(offsets[k + 1], 0), T), a);
         }
         const int tiles = (b - a + bt - 1) / bt, pad = (b - a + 31) & ~31;
-        const int incl = before + smoe_wave_incl_scan(tiles, lane), pincl = pad_before + smoe_wave_incl_scan(pad, lane);
+        const int incl = before + smoe_wave_incl_scan(tiles), pincl = pad_before + smoe_wave_incl_scan(pad);
         const unsigned long long past = __ballot(incl > mt);
         if (past) {
             const int who = __ffsll((long long)past) - 1;
@@ -82,7 +82,7 @@ __device__ __forceinline__ int count_tiles(const int32_t* __restrict__ offsets, 
             a = min(max(offsets[k], 0), T);
             b = max(min(max(offsets[k + 1], 0), T), a);
         }
-        total += __builtin_amdgcn_readlane(smoe_wave_incl_scan((b - a + bt - 1) / bt, lane), 63);
+        total += __builtin_amdgcn_readlane(smoe_wave_incl_scan((b - a + bt - 1) / bt), 63);
     }
     return total;
 }

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
         const Seg g = base ? segment(base + lane) : seg0;
         const int nb = (g.b - g.a + 31) >> 5;
 #pragma unroll
-        for (int h = 1; h <= MAXB; ++h) tiles_of[h - 1] += __builtin_amdgcn_readlane(smoe_wave_incl_scan((nb + h - 1) / h, lane), 63);
+        for (int h = 1; h <= MAXB; ++h) tiles_of[h - 1] += __builtin_amdgcn_readlane(smoe_wave_incl_scan((nb + h - 1) / h), 63);
     }
     const int nwg = gridDim.x / XCDS;
     int H = MAXB, best = 0x7fffffff;
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
             const int k = base + lane;
             const Seg g = base ? segment(k) : seg0;
             const int pad = (g.b - g.a + 31) >> 5, tiles = (pad + H - 1) / H;
-            const int tin = smoe_wave_incl_scan(tiles, lane), pin = smoe_wave_incl_scan(pad, lane);
+            const int tin = smoe_wave_incl_scan(tiles), pin = smoe_wave_incl_scan(pad);
             if (k < nslots) {
                 map.first[k] = tiles_before + tin - tiles;
                 map.pad[k] = pad_before + pin - pad;

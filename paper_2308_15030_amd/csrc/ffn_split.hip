@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256, 1) void split_gemm_bf16(const uint16_t* __rest
             s.b = max(min(max(offsets[base + lane + 1], 0), T), s.a);
         }
         const int nb = (s.b - s.a + 31) >> 5;
-        s.pad = before + smoe_wave_incl_scan(nb, lane) - nb;
+        s.pad = before + smoe_wave_incl_scan(nb) - nb;
         return s;
     };
     const Lane first = slots(0, 0);
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(256, 1) void split_gemm_bf16(const uint16_t* __rest
         const Lane s = base ? slots(base, 0) : first;
         const int nb = (s.b - s.a + 31) >> 5;
 #pragma unroll
-        for (int h = 1; h <= MAXH; ++h) tl[h - 1] += __builtin_amdgcn_readlane(smoe_wave_incl_scan((nb + h - 1) / h, lane), 63);
+        for (int h = 1; h <= MAXH; ++h) tl[h - 1] += __builtin_amdgcn_readlane(smoe_wave_incl_scan((nb + h - 1) / h), 63);
     }
     const int cw = ((lane >> 2) & 3) + 1, ch = (lane & 3) + 1;
     const int mine = (lane & 3) == 0 ? tl[0] : (lane & 3) == 1 ? tl[1] : (lane & 3) == 2 ? tl[2] : tl[3];
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256, 1) void split_gemm_bf16(const uint16_t* __rest
         for (int base = 0; base < nslots; base += 64) {
             const Lane s = base ? slots(base, pad_before) : first;
             const int nb = (s.b - s.a + 31) >> 5, mt = (nb + H - 1) / H;
-            const int tin = before + smoe_wave_incl_scan(mt, lane);
+            const int tin = before + smoe_wave_incl_scan(mt);
             const unsigned long long past = __ballot(tin * ftiles > g);
             if (past) {
                 const int who = __ffsll((long long)past) - 1;

@@ -306,7 +306,7 @@ __global__ __launch_bounds__(SB) void rank_importance_kernel(
         int run = 0;
         for (int base = 0; base < K; base += 64) {
             const int k = base + lane, tot = k < K ? s_total[k] : 0;
-            const int incl = run + smoe_wave_incl_scan(tot, lane);
+            const int incl = run + smoe_wave_incl_scan(tot);
             if (k < K) {
                 if (blk == 0) offsets[k] = incl - tot;
                 s_base[k] += incl - tot;
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restri
             if (k < K)
 #pragma unroll
                 for (int w = 0; w < 4; ++w) { n += s_total[w][k]; b += s_before[w][k]; }
-            const int incl = run + smoe_wave_incl_scan(n, lane);
+            const int incl = run + smoe_wave_incl_scan(n);
             if (k < K) {
                 s_before[0][k] = incl - n + b;             // first position of the block's tokens of slot k
                 if (blockIdx.x == 0) offsets[k] = incl - n;

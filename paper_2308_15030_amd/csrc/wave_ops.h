@@ -32,7 +32,7 @@ __device__ __forceinline__ float smoe_row_sum(float v) {
 
 // Inclusive prefix sum over the 64 lanes of a wave, all of them active: shifts within the rows of 16 lanes, then the rows'
 // totals, six vector additions without a trip through the LDS crossbar.
-__device__ __forceinline__ int smoe_wave_incl_scan(int v, int) {
+__device__ __forceinline__ int smoe_wave_incl_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
