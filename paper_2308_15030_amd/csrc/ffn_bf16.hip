@@ -816,9 +816,9 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
         // the chip holds at once (two per compute unit): each then has a quarter of a reduction per wave in front of it,
         // where a tile has all of it.  Measured on 340 batches of 2 to 100 slots, T = 129 .. 2000, clustered and even tokens,
         // us per layer, streaming / best tile of the tiled kernel (the splitting kernel, which came later, is ahead of both on many of
-        // them: 8 slots of 1024 x 4096, T = 400 55.5 / 47.9; not yet part of this line).  700 workgroups: 25 .. 0 % ahead below (4 slots of 768 x 3072, T = 200 28 / 35; 6,
-        // T = 320 37 / 45; 4 of 2048 x 8192, T = 200 90 / 106), 3 % behind above (18 of 768 x 3072, T = 668 69 / 67).  Under 28
-        // tokens per slot, where most of a tile is empty, 780: 24 slots of 768 x 2048, T = 248 57.0 / 57.3, T = 400 54.9 / 53.4; 26 of 768 x
+        // them, 8 slots of 1024 x 4096, T = 400 55.5 / 47.9, and not yet part of this line).  700 workgroups: 25 .. 0 % ahead below (4
+        // slots of 768 x 3072, T = 200 28 / 35; 6, T = 320 37 / 45; 4 of 2048 x 8192, T = 200 90 / 106), 3 % behind above (18 of 768 x 3072,
+        // T = 668 69 / 67).  Under 28 tokens per slot, where most of a tile is empty, 780: 24 slots of 768 x 2048, T = 248 57.0 / 57.3, T = 400 54.9 / 53.4; 26 of 768 x
         // 3072, T = 263 71 / 69.  A long reduction makes the rounds of the tiles long, 850: 16 slots of 1024 x 4096, T = 300 73 / 76; 12
         // of 1280 x 5120, T = 300 88 / 93; 20 of 768 x 3072, T = 500 58.3 / 62.6 (even), 22 T = 480 66.7 / 66.1; but not with so few
         // tokens that the tiles are one round anyway (16 of 1280 x 5120, T = 160 104 / 101).
@@ -836,8 +836,8 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
     } else {
         const int r1 = ring_first(d, f, T, K, v1);
         if (r1 && smoe_ring_applies(true, d, T)) v1 = r1;
-        // The second product does not stream beside a hundred large tiles: rows of thousands of outputs, short reductions (128 slots of 9216 x 256, T = 760
-        // 590 us a layer streaming, 345 through the ring)
+        // The second product does not stream beside a hundred large tiles: rows of thousands of outputs, short reductions (128 slots of
+        // 9216 x 256, T = 760 590 us a layer streaming, 345 through the ring)
         if (v2 == 6 && f % 128 == 0 && (double)T * d / 65536 >= 100 && smoe_ring_applies(false, f, T)) v2 = 10;
     }
     if (is_variant(L->ffn_variant[0]) && is_variant(L->ffn_variant[1])) {

@@ -1,7 +1,8 @@
 // Grouped bf16 products of prefill batches, both operands staged through a ring in LDS:
 // Y[T, N] = act(X[T, R] . B_k[R, N]) for the rows of slot k, with the operand layouts, the rounding and the
-// fusions of ffn_bf16.hip.  Used where there are tiles for the whole chip, and wherever the reduction is no
-// multiple of 128 (see ring_tile in ffn_bf16.hip for the rule and what it measured).
+// fusions of ffn_bf16.hip.  Used where there are large tiles for the chip many times over, and where the reduction is no
+// multiple of 128: for every first product but with few tokens, for second products from where the splitting kernel no longer
+// fills the chip better (ring_first and pick_second in ffn_bf16.hip have the rules and what they measured).
 //
 // What bounds these products on this chip, and what the kernel does about it:
 //  * Power.  At the Switch-large prefill shape (16384 tokens, 32 slots of 1024 x 4096) random data pulls the clock
@@ -21,8 +22,8 @@
 //    product 169 -> 164 us).
 //  * Balance.  Tile heights are chosen on the device from the segment lengths, and a slot's rows are cut evenly.
 // Both products at that shape, from kernel traces: 168 + 188 -> 157 + 168 us; 8000 tokens, 16 slots of 992 x 3296: 241 ->
-// 142 us.  What is left: of launches of 160 and 167 us the loads alone take 143 and 158, the products with their LDS reads
-// 133 and 134 (both at 2.4 GHz), and a workgroup is there for 136 and 140 us in the mean, the last one 148 and 169.
+// 142 us.  What is left: launches of 156 and 164 us take 112 and 123 without their loads, 134 and 160 without the stores of h (traces of
+// copies without the part): the loads bind.  The matrix cores are busy 0.47 and 0.46 of the time.
 //
 // Workgroup = 2 * NWF waves; tile = (64 * NWF features) x (at most 64 * NWF tokens), in blocks of 32.  Wave w loads
 // feature block w and token block w of every slice; it multiplies the feature blocks 2 * (w % NWF) and the next with

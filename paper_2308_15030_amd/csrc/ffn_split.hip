@@ -10,12 +10,13 @@
 // unit, where a tile of the tiled kernel has 48).  The parts meet in LDS at the end and are added in order.
 // The tile shape, up to 4 x 4 blocks, is chosen on the device from the segment lengths: every lane prices one shape.
 //
-// us, tiled or ring kernel before / now (kernel times, weights from memory): 16 slots of 768 x 3072 (first d_model, then
-// d_ff), T = 800 27.3 / 23.8, T = 1213 30.1 / 26.7, T = 3100 37.0 / 33.5; 4 slots, T = 520 17.5 / 12.7, T = 3100 32.2 / 27.4;
-// 11 of 416 x 1696, T = 1213 18.1 / 10.3; 10 of 992 x 3296, T = 800 41.8 / 25.9; 32 of 1024 x 4096, T = 520 78 / 64.  Of the 23 us
-// at 16 slots, T = 777: 1.3 until the shape is chosen, 1 more until the operands are asked for, 17 in the loop (the weights, 75 MB, at
-// 4.5 TB/s; without loads 3), 1.5 for the meeting and the stores.  With 4 x 4 tiles (4 slots, T = 4096, 26.4 us) the loop takes 18
-// us, 13 of them products and 14 loads by themselves, and the end 4.
+// us a layer, whole passes, weights from memory, clustered tokens, with tiled or ring kernel / with this one: 16 slots of 768 x 3072 (first
+// d_model, then d_ff), T = 777 61.0 / 55.2, T = 3000 81.1 / 77.3; 4 slots, T = 600 39.3 / 32.7, T = 3000 70.8 / 63.0; 11 of
+// 416 x 1696, T = 1213 40.3 / 31.2; 10 of 992 x 3296, T = 777 79.0 / 63.7; 32 of 1024 x 4096, T = 600 144 / 129; 64 of 768 x
+// 3072, T = 2000 154 / 150.  The launch of 16 slots, T = 777, takes 23.1 us, without its products 22.9, without its loads 10.5,
+// without either 7.3 (until the shape is chosen and the operands have come, the meeting and the stores): the loads bind it, 90 MB
+// at 3.7 TB/s.  With 4 x 4 tiles (4 slots, T = 4096) 33.4, 29.7, 25.4 and 14.1: one wave per SIMD does not overlap products
+// and loads wholly.
 
 #include <algorithm>
 #include <type_traits>
