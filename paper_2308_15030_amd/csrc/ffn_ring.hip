@@ -404,36 +404,41 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
                             rs[a][b] = *(const uint4*)(fz.residual + (size_t)row[b] * N + (cur.fb0 + min(wf * 2 + a, cur.width - 1)) * 32 + unit * 8);
                     }
             }
+            // h past the caches, or plainly: one branch a tile (one a store took 1 to 3 % of the first product)
+            auto put = [&](auto past) {
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                if (wf * 2 + a >= cur.width) continue;
-                const int fbk = cur.fb0 + wf * 2 + a;
+                for (int a = 0; a < 2; ++a) {
+                    if (wf * 2 + a >= cur.width) continue;
+                    const int fbk = cur.fb0 + wf * 2 + a;
 #pragma unroll
-                for (int b = 0; b < 2 * NB; ++b) {
-                    uint32_t w[4];
+                    for (int b = 0; b < 2 * NB; ++b) {
+                        uint32_t w[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {          // w[0], w[1]: lower half of the block; w[2], w[3]: upper
-                        float v0 = acc[2 * a + (q >> 1)][b][2 * (q & 1)], v1 = acc[2 * a + (q >> 1)][b][2 * (q & 1) + 1];
-                        if (FIRST) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
-                        w[q] = smoe_pack_bf16(v0, v1);
-                    }
-                    const auto s0 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);
-                    const auto s1 = __builtin_amdgcn_permlane16_swap(w[1], w[3], false, false);
-                    uint4 o = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-                    if (FIRST) {
-                        const size_t u = ((size_t)(cur.pb0 + (b >> 1) * 2 + wt) * (N >> 3) + fbk * 4 + unit) * 32 + (b & 1) * 16 + (lane & 15);
-                        if (NWF == 4 && fz.past) smoe_store_stream((uint4*)(Y + u * 8), o);
-                        else *(uint4*)(Y + u * 8) = o;
-                        ++pend;
-                    } else {
-                        const int r0 = cur.m0 + ((b >> 1) * 2 + wt) * 32 + (b & 1) * 16;
-                        if (r0 >= cur.m_end) continue;     // uniform; else one store, of the lanes whose row is there
-                        if (gather) o = smoe_gate_unit(o, gate[b], rs[a][b], fz.residual != nullptr);
-                        if (r0 + (lane & 15) < cur.m_end) *(uint4*)(Y + (size_t)row[b] * N + fbk * 32 + unit * 8) = o;
-                        ++pend;
+                        for (int q = 0; q < 4; ++q) {      // w[0], w[1]: lower half of the block; w[2], w[3]: upper
+                            float v0 = acc[2 * a + (q >> 1)][b][2 * (q & 1)], v1 = acc[2 * a + (q >> 1)][b][2 * (q & 1) + 1];
+                            if (FIRST) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
+                            w[q] = smoe_pack_bf16(v0, v1);
+                        }
+                        const auto s0 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);
+                        const auto s1 = __builtin_amdgcn_permlane16_swap(w[1], w[3], false, false);
+                        uint4 o = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+                        if (FIRST) {
+                            const size_t u = ((size_t)(cur.pb0 + (b >> 1) * 2 + wt) * (N >> 3) + fbk * 4 + unit) * 32 + (b & 1) * 16 + (lane & 15);
+                            if (past) smoe_store_stream((uint4*)(Y + u * 8), o);
+                            else *(uint4*)(Y + u * 8) = o;
+                            ++pend;
+                        } else {
+                            const int r0 = cur.m0 + ((b >> 1) * 2 + wt) * 32 + (b & 1) * 16;
+                            if (r0 >= cur.m_end) continue; // uniform; else one store, of the lanes whose row is there
+                            if (gather) o = smoe_gate_unit(o, gate[b], rs[a][b], fz.residual != nullptr);
+                            if (r0 + (lane & 15) < cur.m_end) *(uint4*)(Y + (size_t)row[b] * N + fbk * 32 + unit * 8) = o;
+                            ++pend;
+                        }
                     }
                 }
-            }
+            };
+            if (FIRST && NWF == 4 && fz.past) put(std::true_type{});
+            else put(std::false_type{});
         } else {
             pend = 0;
         }
