@@ -854,7 +854,8 @@ void pick_variants(const smoe_layer* L, int T, int& v1, int& v2) {
 //    1.02; six layers of 2 slots 1.05, of 8 of 768 x 2048 1.015.
 //  * 256 x 256 tiles (10): 0.96 where a layer's slots are far more than the cache, which h would leave before it is read (0.94 at 64 slots
 //    of 768 x 3072, 0.97 at 32 of 1024 x 4096; but 1.03 at 32 of 768 x 3072).  With less, large second products: 0.99 while all
-//    slots stay in the cache, 1.01 where they do not.  Second products in smaller tiles read h more often: 1.02 .. 1.04, but
+//    slots stay in the cache; where they do not, 1.00 under 100 MB (in the separate calls 0.97: eight layers of 4 slots of 768 x 3072,
+//    T = 4096 83.5 / 80.8) and 1.01 above.  Second products in smaller tiles read h more often: 1.02 .. 1.04, but
 //    0.98 where all slots would stay in the cache beside each other and not beside h.
 // Tiles of 128 rows store plainly.
 bool h_past_caches(const smoe_layer* L, int v1, int v2) {
@@ -862,7 +863,7 @@ bool h_past_caches(const smoe_layer* L, int v1, int v2) {
     if (v1 == 3 || v1 == 4) return own >= 100 && smoe_weights_outgrow_cache(L);
     if (v1 != 10) return false;
     const bool large = v2 == 1 || v2 == 8 || v2 == 10;
-    return own >= 400 || (all <= 240 && (large || (own < 100 && all >= 100)));
+    return own >= 400 || (large ? own < 100 || all <= 240 : own < 100 && all >= 100 && all <= 240);
 }
 
 }  // namespace
