@@ -370,15 +370,21 @@ __device__ __forceinline__ void run_tile(const uint16_t* __restrict__ X, const u
         __syncthreads();
         const bool fused = fz.perm != nullptr, has_res = fused && fz.residual != nullptr;
         const int col0 = ftile * F;
+        int prow[NP], pcol[NP];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {                    // every row first: one trip to LDS for all of them
+            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8;
+            pcol[j] = col0 + c * 8;
+            prow[j] = pcol[j] < N ? orow[r] : -1;
+        }
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
-            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8, col = col0 + c * 8;
-            const int row = col < N ? orow[r] : -1;
-            if (row < 0) continue;
+            if (prow[j] < 0) continue;
+            const int idx = tid + j * THREADS, r = idx / CPR8, c = idx % CPR8;
             const uint2 lo = *(const uint2*)&xs[r * LDO + c * 8], hi = *(const uint2*)&xs[r * LDO + c * 8 + 4];
             uint4 o = make_uint4(lo.x, lo.y, hi.x, hi.y);
             if (fused) o = smoe_gate_unit(o, ogate[r], res[j], has_res);
-            *(uint4*)(Y + (size_t)row * N + col) = o;
+            *(uint4*)(Y + (size_t)prow[j] * N + pcol[j]) = o;
         }
         __syncthreads();                                  // the next tile's prologue reuses the ring
     }
@@ -885,6 +891,7 @@ int smoe_describe_ffn_bf16(const smoe_layer* L, int T, int fused, char* out, siz
         else if (v[i] == 5) name = std::string("small_gemm_bf16<4, 1, ") + (first ? "true>" : "false>");
         else if (v[i] == 6) name = std::string("small_gemm_bf16<4, 4, ") + (first ? "true>" : "false>");
         else if (v[i] == 11) name = "split_gemm_bf16";
+        else if (v[i] == 10 && first && !h_past_caches(L, 10, v[1])) name = "ring_gemm_bf16_kept";
         else if (v[i] >= 9) name = std::string("ring_gemm_bf16<") + (v[i] == 9 ? "2, " : "4, ") + (first ? "true>" : "false>");
         else if (R % 64 != 0) shape = "1, 4, 4, 32, ";
         else if (v[i] == 1) shape = "1, 4, 4, 64, ";

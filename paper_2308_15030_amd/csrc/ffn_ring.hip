@@ -112,8 +112,9 @@ struct RingShape {
 // fragment-order h out.  Otherwise the d_ff -> d_model product: h in, row-major rows out (scattered through perm with
 // gate and residual in the single-call path).  Items are numbered, dealt to the dies and walked as in
 // grouped_gemm_bf16.
-template <int NWF, bool FIRST>
-__global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
+// PAST: hidden activations are stored past the caches.
+template <int NWF, bool FIRST, bool PAST>
+__device__ __forceinline__ void ring_body(
     const uint16_t* __restrict__ X, const uint4* __restrict__ Wp, const int32_t* __restrict__ offsets, int nslots,
     int T, uint16_t* __restrict__ Y, int R, int N, const FuseArgs fz) {
     using S = RingShape<NWF, FIRST>;
@@ -404,41 +405,36 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
                             rs[a][b] = *(const uint4*)(fz.residual + (size_t)row[b] * N + (cur.fb0 + min(wf * 2 + a, cur.width - 1)) * 32 + unit * 8);
                     }
             }
-            // h past the caches, or plainly: one branch a tile (one a store took 1 to 3 % of the first product)
-            auto put = [&](auto past) {
 #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    if (wf * 2 + a >= cur.width) continue;
-                    const int fbk = cur.fb0 + wf * 2 + a;
+            for (int a = 0; a < 2; ++a) {
+                if (wf * 2 + a >= cur.width) continue;
+                const int fbk = cur.fb0 + wf * 2 + a;
 #pragma unroll
-                    for (int b = 0; b < 2 * NB; ++b) {
-                        uint32_t w[4];
+                for (int b = 0; b < 2 * NB; ++b) {
+                    uint32_t w[4];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {      // w[0], w[1]: lower half of the block; w[2], w[3]: upper
-                            float v0 = acc[2 * a + (q >> 1)][b][2 * (q & 1)], v1 = acc[2 * a + (q >> 1)][b][2 * (q & 1) + 1];
-                            if (FIRST) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
-                            w[q] = smoe_pack_bf16(v0, v1);
-                        }
-                        const auto s0 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);
-                        const auto s1 = __builtin_amdgcn_permlane16_swap(w[1], w[3], false, false);
-                        uint4 o = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-                        if (FIRST) {
-                            const size_t u = ((size_t)(cur.pb0 + (b >> 1) * 2 + wt) * (N >> 3) + fbk * 4 + unit) * 32 + (b & 1) * 16 + (lane & 15);
-                            if (past) smoe_store_stream((uint4*)(Y + u * 8), o);
-                            else *(uint4*)(Y + u * 8) = o;
-                            ++pend;
-                        } else {
-                            const int r0 = cur.m0 + ((b >> 1) * 2 + wt) * 32 + (b & 1) * 16;
-                            if (r0 >= cur.m_end) continue; // uniform; else one store, of the lanes whose row is there
-                            if (gather) o = smoe_gate_unit(o, gate[b], rs[a][b], fz.residual != nullptr);
-                            if (r0 + (lane & 15) < cur.m_end) *(uint4*)(Y + (size_t)row[b] * N + fbk * 32 + unit * 8) = o;
-                            ++pend;
-                        }
+                    for (int q = 0; q < 4; ++q) {          // w[0], w[1]: lower half of the block; w[2], w[3]: upper
+                        float v0 = acc[2 * a + (q >> 1)][b][2 * (q & 1)], v1 = acc[2 * a + (q >> 1)][b][2 * (q & 1) + 1];
+                        if (FIRST) { v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f); }
+                        w[q] = smoe_pack_bf16(v0, v1);
+                    }
+                    const auto s0 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);
+                    const auto s1 = __builtin_amdgcn_permlane16_swap(w[1], w[3], false, false);
+                    uint4 o = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+                    if (FIRST) {
+                        const size_t u = ((size_t)(cur.pb0 + (b >> 1) * 2 + wt) * (N >> 3) + fbk * 4 + unit) * 32 + (b & 1) * 16 + (lane & 15);
+                        if (PAST) smoe_store_stream((uint4*)(Y + u * 8), o);
+                        else *(uint4*)(Y + u * 8) = o;
+                        ++pend;
+                    } else {
+                        const int r0 = cur.m0 + ((b >> 1) * 2 + wt) * 32 + (b & 1) * 16;
+                        if (r0 >= cur.m_end) continue;     // uniform; else one store, of the lanes whose row is there
+                        if (gather) o = smoe_gate_unit(o, gate[b], rs[a][b], fz.residual != nullptr);
+                        if (r0 + (lane & 15) < cur.m_end) *(uint4*)(Y + (size_t)row[b] * N + fbk * 32 + unit * 8) = o;
+                        ++pend;
                     }
                 }
-            };
-            if (FIRST && NWF == 4 && fz.past) put(std::true_type{});
-            else put(std::false_type{});
+            }
         } else {
             pend = 0;
         }
@@ -462,11 +458,26 @@ __global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
     wait_vm<0>();                                          // no load is on its way into LDS that is given back
 }
 
+// Large tiles store h past the caches; ring_gemm_bf16_kept is the instance for h that is better kept.  An instance of its own: one kernel
+// with a branch at the end of a tile took 0.6 us more of 25 (4096 tokens, 4 slots of 768 x 3072), with one a store 1 to 3 %.
 template <int NWF, bool FIRST>
+__global__ __launch_bounds__(NWF * 128, 2) void ring_gemm_bf16(
+    const uint16_t* __restrict__ X, const uint4* __restrict__ Wp, const int32_t* __restrict__ offsets, int nslots,
+    int T, uint16_t* __restrict__ Y, int R, int N, const FuseArgs fz) {
+    ring_body<NWF, FIRST, FIRST && NWF == 4>(X, Wp, offsets, nslots, T, Y, R, N, fz);
+}
+__global__ __launch_bounds__(4 * 128, 2) void ring_gemm_bf16_kept(
+    const uint16_t* __restrict__ X, const uint4* __restrict__ Wp, const int32_t* __restrict__ offsets, int nslots,
+    int T, uint16_t* __restrict__ Y, int R, int N, const FuseArgs fz) {
+    ring_body<4, true, false>(X, Wp, offsets, nslots, T, Y, R, N, fz);
+}
+
+template <int NWF, bool FIRST, bool KEPT = false>
 int launch(const uint16_t* X, const void* Wp, const int32_t* offsets, int nslots, uint16_t* Y, int R, int N, int T,
            const FuseArgs& fz, int cus_per_die, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     using S = RingShape<NWF, FIRST>;
     auto kern = ring_gemm_bf16<NWF, FIRST>;
+    if constexpr (KEPT) kern = ring_gemm_bf16_kept;
     static smoe_lds_raised raised;
     if (int rc = raised.ensure((const void*)kern, S::LDS, (int)S::LDS)) return rc;
     const int ftiles = ((N >> 5) + S::NB - 1) / S::NB;
@@ -490,8 +501,9 @@ int smoe_launch_ring(int blocks, bool first, const uint16_t* X, const void* Wp, 
                      uint16_t* Y, int R, int N, int T, const FuseArgs& fz, int cus_per_die, hipStream_t s, hipEvent_t e0,
                      hipEvent_t e1) {
     if (blocks == 8)
-        return first ? launch<4, true>(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die, s, e0, e1)
-                     : launch<4, false>(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die, s, e0, e1);
+        return !first    ? launch<4, false>(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die, s, e0, e1)
+               : fz.past ? launch<4, true>(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die, s, e0, e1)
+                         : launch<4, true, true>(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die, s, e0, e1);
     return first ? launch<2, true>(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die, s, e0, e1)
                  : launch<2, false>(X, Wp, offsets, nslots, Y, R, N, T, fz, cus_per_die, s, e0, e1);
 }

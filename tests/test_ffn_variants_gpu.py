@@ -36,7 +36,7 @@ def kernel(v, first, R):
     if v in (5, 6):
         return f"small_gemm_bf16<4, {1 if v == 5 else 4},"
     if v in (9, 10):
-        return f"ring_gemm_bf16<{2 if v == 9 else 4},"
+        return "ring_gemm_bf16" if first and v == 10 else f"ring_gemm_bf16<{2 if v == 9 else 4},"   # or the instance that keeps h
     if R % 64:
         return "grouped_gemm_bf16<1, 4, 4, 32,"
     return "grouped_gemm_bf16<1, " + {1: "4, 4,", 3: "2, 4,", 4: "1, 4,", 8: "4, 8,"}[v]

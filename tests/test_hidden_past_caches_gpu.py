@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
     # 101 MB of slots beside 201 MB of others: tiles of 32 and 64 rows
     (32, 512, 1536, 300, "grouped_gemm_bf16<1, 1", (16, 1024, 3072)), (32, 512, 1536, 1000, "grouped_gemm_bf16<1, 2", (16, 1024, 3072)),
     # 25 MB beside 134 MB: 256 x 256 tiles, several to a workgroup, ragged ends
-    (16, 256, 1536, 8001, "ring_gemm_bf16<4", (16, 1024, 2048)), (5, 320, 2048, 6000, "ring_gemm_bf16<4", (16, 1024, 2048))])
+    (16, 256, 1536, 8001, "ring_gemm_bf16_kept", (16, 1024, 2048)), (5, 320, 2048, 6000, "ring_gemm_bf16_kept", (16, 1024, 2048))])
 def test_same_bits(K, d, f, T, kernel, other):
     g = torch.Generator(device="cuda:0")
     g.manual_seed(K + d + f + T)
@@ -27,6 +27,7 @@ def test_same_bits(K, d, f, T, kernel, other):
     assert not torch.isnan(want.view(torch.bfloat16).float()).any()
     for call in (L.forward_fused, L.forward):
         o.forward_fused(y, 1, accumulate=0)
+        assert b.smoe_describe_ffn(L.handle, T).startswith(kernel.replace("_kept", "<4, true>"))
         L.out.fill_(0)
         assert torch.equal(call(x, T, accumulate=0, residual=x), want)
     L.close()
